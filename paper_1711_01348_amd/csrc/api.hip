@@ -40,6 +40,7 @@ int tad_eval_forward(const tad_plan *plan, const void *const *args_dev, void *f_
         if (!args_dev[plan->root[p]]) return TAD_EINVAL;
     if (plan->ws_bytes && (!ws_dev || ws_bytes < plan->ws_bytes)) return TAD_ENOMEM;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (plan->prod.on && ws_bytes >= plan->ws_full) return product_forward(*plan, args_dev, f_dev, ws_dev, s);
     switch (plan->fwd_family) {
     case TAD_FAMILY_GENERIC: return generic_forward(*plan, args_dev, f_dev, ws_dev, s);
     case TAD_FAMILY_WORKED: return worked_forward(*plan, args_dev, f_dev, s);
@@ -66,6 +67,16 @@ int tad_eval_backward(const tad_plan *plan, const void *const *args_dev, const v
     bool any_wanted = false;
     for (size_t p = 0; p < plan->args.size(); ++p) any_wanted |= dx_dev[p] != nullptr;
     if (!any_wanted) return TAD_OK;
+    void *rest[kMaxArgs];   // the gradients the dense products leave to the family
+    if (plan->prod.on && ws_bytes >= plan->ws_full) {
+        for (size_t p = 0; p < plan->args.size(); ++p) rest[p] = dx_dev[p];
+        const int rc = product_backward(*plan, args_dev, df_dev, rest, ws_dev, s);
+        if (rc) return rc;
+        dx_dev = rest;
+        any_wanted = false;
+        for (size_t p = 0; p < plan->args.size(); ++p) any_wanted |= rest[p] != nullptr;
+        if (!any_wanted) return TAD_OK;
+    }
     // a specialised family owns all gradients of its expression; anything left is generic
     int fam = TAD_FAMILY_GENERIC;
     for (size_t p = 0; p < plan->args.size(); ++p)

@@ -367,7 +367,7 @@ static int build_graph(const tad_plan &pl, int arg, tad_derived &d) {
     d.root = pl.root;
     d.count = pl.arg_count[(size_t)arg];
     const size_t es = pl.dtype == TAD_F64 ? 8 : 4;
-    size_t ws = 0, sub = 0;
+    size_t ws = 0, sub = 0, sub_least = 0;
     auto seed_for = [&](int which) -> int {        // which: kSrcSeedG or -3 - p
         for (const auto &s : d.seeds)
             if (s.seed == which) return TAD_OK;
@@ -384,7 +384,8 @@ static int build_graph(const tad_plan &pl, int arg, tad_derived &d) {
         for (int q = 0; q < n - 1; ++q) node.src.push_back(q);
         node.out_offset = ws;
         ws += align256((size_t)pl.f_count * es);
-        sub = std::max(sub, node.plan->ws_bytes);
+        sub = std::max(sub, node.plan->ws_full);
+        sub_least = std::max(sub_least, node.plan->ws_bytes);
         d.seeds.push_back(std::move(node));
         node.plan = nullptr;
         return TAD_OK;
@@ -412,7 +413,8 @@ static int build_graph(const tad_plan &pl, int arg, tad_derived &d) {
             rc = node_plan(e, a, n, pl.dtype, node);
             if (rc) return rc;
             node.src.assign(src, src + n);
-            sub = std::max(sub, node.plan->ws_bytes);
+            sub = std::max(sub, node.plan->ws_full);
+            sub_least = std::max(sub_least, node.plan->ws_bytes);
             d.parts.push_back(std::move(node));
             node.plan = nullptr;
         }
@@ -421,6 +423,7 @@ static int build_graph(const tad_plan &pl, int arg, tad_derived &d) {
     if (d.parts.size() > 1) ws += align256((size_t)d.count * es);
     d.sub_offset = ws;
     d.ws_bytes = ws + sub;
+    d.ws_least = ws + sub_least;
     return TAD_OK;
 }
 

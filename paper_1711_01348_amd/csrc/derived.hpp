@@ -28,6 +28,7 @@ struct tad_derived {
     size_t tmp_offset = 0;                 // a second tensor of the gradient's size (results of the later parts)
     size_t sub_offset = 0;                 // workspace of the expressions' own kernels (shared: they run one after another)
     size_t ws_bytes = 0;
+    size_t ws_least = 0;                   // without the dense products of the expressions (a smaller workspace is refused)
     ~tad_derived() {
         for (auto &n : seeds) tad_plan_free(n.plan);
         for (auto &n : parts) tad_plan_free(n.plan);

@@ -22,7 +22,7 @@ extern "C" int tad_eval_derived(const tad_derived *d, const void *const *args_de
     if (!d || !args_dev || !df_dev || !dx_dev) return TAD_EINVAL;
     for (int q = 0; q < d->n_original; ++q)
         if (!args_dev[d->root[(size_t)q]]) return TAD_EINVAL;
-    if (d->ws_bytes && (!ws_dev || ws_bytes < d->ws_bytes)) return TAD_ENOMEM;
+    if (d->ws_least && (!ws_dev || ws_bytes < d->ws_least)) return TAD_ENOMEM;
     char *ws = static_cast<char *>(ws_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
     auto source = [&](int src) -> const void * {

@@ -6,6 +6,7 @@
 
 #include "plan.hpp"
 #include "launch_geom.h"
+#include "product_match.hpp"
 
 namespace tad {
 
@@ -337,8 +338,17 @@ static void select_specialised(tad_plan &plan) {
     if (match_contraction(plan)) return;
 }
 
+static void reserve_partial_sums(tad_plan &plan);
+
 void select_families(tad_plan &plan) {
     select_specialised(plan);
+    reserve_partial_sums(plan);
+    match_product(plan);
+    plan.prod.ws_offset = align256(plan.ws_bytes);
+    plan.ws_full = plan.prod.on && plan.prod.ws_bytes ? plan.prod.ws_offset + plan.prod.ws_bytes : plan.ws_bytes;
+}
+
+static void reserve_partial_sums(tad_plan &plan) {
     // the fallback kernels share the elements of a gradient with few elements and long sums among several blocks:
     // room for their partial sums behind whatever the family keeps in the workspace
     bool fallback = true;

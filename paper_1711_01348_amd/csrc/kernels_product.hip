@@ -1,0 +1,276 @@
+// Dense products with 64-bit accumulation on the matrix cores (v_mfma_f64_16x16x4_f64): the sums of product.hpp and
+// their gradients, in either precision and for any extents and strides.  The general kernels add the terms of such a
+// sum in 64 bits, so these do: a 32-bit operand is widened when it is staged, its products are then exact, and the
+// result is rounded once.
+//
+// C[r][c] = sum_q A(r, q) B(q, c).  A workgroup of four wavefronts computes one square tile of the output.  The operands go
+// through registers into LDS, [row][q] with an odd row length (conflict-free for the stores, along q or along the rows,
+// and for the fragment loads); the loads of a stage are issued before the matrix instructions of the stage before it.
+// Everything that depends on the tile's place is settled before the loop: a row beyond the edge repeats the last row (its
+// results are not stored), so that the loads are unconditional, from a uniform base plus a constant 32-bit offset per thread,
+// and only the last stage looks at the end of the sum, where it stages zeros.
+// A 16 x 16 x 4 instruction occupies its matrix core for 64 cycles: the matrix cores bound these kernels (78.6 TFLOP/s), two
+// operand fragments per instruction are cheap, and what counts is enough wavefronts to cover the barriers.  Hence one set of
+// tiles in LDS and three workgroups per compute unit rather than two sets and two workgroups (2001 x 2002 x 2003, 32-bit
+// operands: 311 us against 333 us; two workgroups with 64-bit operands, which need the registers), and small tiles:
+//   edge 64  a wavefront owns 32 x 32 results; 32 values of q per stage
+//   edge 32  every wavefront computes the whole tile over a quarter of each stage's 64 values of q, and the four sums are added
+//            in a fixed order at the end: four times as many workgroups for small results (512 x 1024 x 768: 21 us against
+//            36 us), and a chain of additions a quarter as long
+// Operands of 64 bits: the rounding of the sum is all there is, so it is kept as small as that of the general kernels, which
+// share a sum among 64 lanes: a wavefront adds up 16 products at a time and adds those to two totals in turn (1000 x 1203 x 777:
+// relative error 2e-16, against 5e-16 in one chain).
+//
+// MFMA operand layout: A operand lane l = A[l % 16][l / 16], B operand lane l = B[l / 16][l % 16], result register i of
+// lane l = D[4 i + l / 16][l % 16].
+#include <hip/hip_runtime.h>
+
+#include "launch.h"
+#include "product.hpp"
+#include "profile.h"
+
+namespace tad {
+
+typedef double double4p __attribute__((ext_vector_type(4)));
+
+struct ProductArgs {
+    const void *a, *b;
+    void *c;           // the result, or (pieces > 1) the partial sums [piece][r][c] in 64 bits
+    int R, C, Q;
+    int ar, aq, bq, bc;
+    int gr, gc;        // tiles along r and c
+    int chunk;         // values of q per piece
+    int wide;          // store 64-bit results
+};
+
+// Neighbouring workgroups go to different dies: each die gets a contiguous range of tiles, walked in groups of eight
+// tile rows, so that workgroups that run together share operand tiles in their L2.
+__device__ __forceinline__ void product_tile(int gr, int gc, int &tr, int &tc) {
+    const int total = gr * gc;
+    int lid = blockIdx.x;
+    const int per = total >> 3;
+    if (lid < (per << 3)) lid = (lid & 7) * per + (lid >> 3);
+    const int group = 8 * gc;
+    const int g0 = (lid / group) * 8;
+    const int rows = min(8, gr - g0);
+    const int in = lid - (lid / group) * group;
+    tr = g0 + in % rows;
+    tc = in / rows;
+}
+
+template <typename TA, typename TB, int EDGE>
+__global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) void k_product(const ProductArgs P) {
+    constexpr bool SHARE = EDGE == 32;              // the wavefronts share the tile's sum; else each owns a quarter of the tile
+    constexpr int KT = SHARE ? 64 : 32;             // values of q per stage
+    constexpr int KW = SHARE ? 16 : 32;             // ... of one wavefront
+    constexpr int LDK = KT + 1;                     // row length in LDS
+    constexpr int WT = 2;                           // 16 x 16 results of a wavefront, per direction
+    constexpr int PER = EDGE * KT / 256;            // elements of each operand a thread stages
+    constexpr bool BLOCKED = sizeof(TA) == 8 && sizeof(TB) == 8;   // sums of 16 products added to a total
+    constexpr int TILES = EDGE * LDK * (int)(sizeof(TA) + sizeof(TB)), SUMS = SHARE ? 4 * EDGE * EDGE * 8 : 0;
+    __shared__ __attribute__((aligned(16))) char lds[TILES > SUMS ? TILES : SUMS];
+    // the wider operand first: both regions then start on a multiple of their element
+    constexpr bool A_FIRST = sizeof(TA) >= sizeof(TB);
+    TA *const As = reinterpret_cast<TA *>(lds + (A_FIRST ? 0 : EDGE * LDK * (int)sizeof(TB)));
+    TB *const Bs = reinterpret_cast<TB *>(lds + (A_FIRST ? EDGE * LDK * (int)sizeof(TA) : 0));
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int tr, tc;
+    product_tile(P.gr, P.gc, tr, tc);
+    const int r0 = tr * EDGE, c0 = tc * EDGE;
+    const int q_begin = blockIdx.y * P.chunk, q_end = min(P.Q, q_begin + P.chunk);
+    // staging: neighbouring threads along q or along the rows, whichever is contiguous in memory
+    const bool a_q = P.aq <= P.ar, b_q = P.bq <= P.bc;   // uniform
+    const int a_row = a_q ? tid / KT : tid % EDGE, a_k = a_q ? tid % KT : tid / EDGE;
+    const int b_row = b_q ? tid / KT : tid % EDGE, b_k = b_q ? tid % KT : tid / EDGE;
+    const int a_dr = a_q ? 256 / KT : 0, a_dk = a_q ? 0 : 256 / EDGE;   // from one element of a thread to the next
+    const int b_dr = b_q ? 256 / KT : 0, b_dk = b_q ? 0 : 256 / EDGE;
+    unsigned ao[PER], bo[PER];   // byte offsets within a stage
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        ao[p] = (unsigned)(min(a_row + p * a_dr, P.R - 1 - r0) * P.ar + (a_k + p * a_dk) * P.aq) * (unsigned)sizeof(TA);
+        bo[p] = (unsigned)(min(b_row + p * b_dr, P.C - 1 - c0) * P.bc + (b_k + p * b_dk) * P.bq) * (unsigned)sizeof(TB);
+    }
+    const char *pa = reinterpret_cast<const char *>(static_cast<const TA *>(P.a) + (size_t)r0 * P.ar + (size_t)q_begin * P.aq);
+    const char *pb = reinterpret_cast<const char *>(static_cast<const TB *>(P.b) + (size_t)c0 * P.bc + (size_t)q_begin * P.bq);
+    TA va[PER];
+    TB vb[PER];
+    auto load = [&](int q0) {
+        if (q0 + KT <= q_end) {   // the same for the whole workgroup
+#pragma unroll
+            for (int p = 0; p < PER; ++p) va[p] = *reinterpret_cast<const TA *>(pa + ao[p]);
+#pragma unroll
+            for (int p = 0; p < PER; ++p) vb[p] = *reinterpret_cast<const TB *>(pb + bo[p]);
+        } else {                  // the last stage: beyond the end of the sum the last value is read and a zero staged
+#pragma unroll
+            for (int p = 0; p < PER; ++p) {
+                const int over = max(q0 + a_k + p * a_dk - (q_end - 1), 0);
+                const TA v = *reinterpret_cast<const TA *>(pa + (ao[p] - (unsigned)(over * P.aq) * (unsigned)sizeof(TA)));
+                va[p] = over ? TA(0) : v;
+            }
+#pragma unroll
+            for (int p = 0; p < PER; ++p) {
+                const int over = max(q0 + b_k + p * b_dk - (q_end - 1), 0);
+                const TB v = *reinterpret_cast<const TB *>(pb + (bo[p] - (unsigned)(over * P.bq) * (unsigned)sizeof(TB)));
+                vb[p] = over ? TB(0) : v;
+            }
+        }
+        pa += (size_t)KT * P.aq * sizeof(TA);
+        pb += (size_t)KT * P.bq * sizeof(TB);
+    };
+    const int as = a_row * LDK + a_k, as_inc = a_dr * LDK + a_dk, bs = b_row * LDK + b_k, bs_inc = b_dr * LDK + b_dk;
+    auto stage = [&]() {
+#pragma unroll
+        for (int p = 0; p < PER; ++p) As[as + p * as_inc] = va[p];
+#pragma unroll
+        for (int p = 0; p < PER; ++p) Bs[bs + p * bs_inc] = vb[p];
+    };
+    const double4p zero = {0., 0., 0., 0.};
+    double4p acc[WT][WT], even[WT][WT], odd[WT][WT];   // even, odd: totals of every other stage (64-bit operands)
+#pragma unroll
+    for (int x = 0; x < WT; ++x)
+#pragma unroll
+        for (int y = 0; y < WT; ++y) acc[x][y] = even[x][y] = odd[x][y] = zero;
+    const int wr = SHARE ? 0 : (wave >> 1) * (EDGE / 2), wc = SHARE ? 0 : (wave & 1) * (EDGE / 2);
+    const int fk = (SHARE ? wave * KW : 0) + (lane >> 4);
+    const int fa = (wr + (lane & 15)) * LDK + fk, fb = (wc + (lane & 15)) * LDK + fk;
+    load(q_begin);
+    stage();
+    __syncthreads();
+    auto step = [&](int q0, double4p (&total)[WT][WT]) {
+        const bool more = q0 + KT < q_end;   // the same for the whole workgroup
+        if (more) load(q0 + KT);
+#pragma unroll
+        for (int ks = 0; ks < KW / 4; ++ks) {
+            double a[WT], b[WT];
+#pragma unroll
+            for (int x = 0; x < WT; ++x) {
+                a[x] = (double)As[fa + x * 16 * LDK + ks * 4];
+                b[x] = (double)Bs[fb + x * 16 * LDK + ks * 4];
+            }
+#pragma unroll
+            for (int x = 0; x < WT; ++x)
+#pragma unroll
+                for (int y = 0; y < WT; ++y)
+                    acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[y], BLOCKED && ks % 4 == 0 ? zero : acc[x][y], 0, 0, 0);
+            if (BLOCKED && ks % 4 == 3) {
+#pragma unroll
+                for (int x = 0; x < WT; ++x)
+#pragma unroll
+                    for (int y = 0; y < WT; ++y) total[x][y] += acc[x][y];
+            }
+        }
+        __syncthreads();
+        if (more) {
+            stage();
+            __syncthreads();
+        }
+    };
+    for (int q0 = q_begin; q0 < q_end; q0 += 2 * KT) {
+        step(q0, even);
+        if (q0 + KT < q_end) step(q0 + KT, odd);
+    }
+    if constexpr (BLOCKED) {
+#pragma unroll
+        for (int x = 0; x < WT; ++x)
+#pragma unroll
+            for (int y = 0; y < WT; ++y) acc[x][y] = even[x][y] + odd[x][y];
+    }
+    char *out = static_cast<char *>(P.c) + (size_t)blockIdx.y * (gridDim.y > 1 ? (size_t)P.R * P.C * sizeof(double) : 0);
+    auto store = [&](int r, int c, double v) {
+        if (r >= P.R || c >= P.C) return;
+        const size_t at = (size_t)r * P.C + c;
+        if (P.wide) reinterpret_cast<double *>(out)[at] = v;
+        else reinterpret_cast<float *>(out)[at] = (float)v;
+    };
+    if constexpr (!SHARE) {
+#pragma unroll
+        for (int x = 0; x < WT; ++x)
+#pragma unroll
+            for (int y = 0; y < WT; ++y)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    store(r0 + wr + x * 16 + 4 * i + (lane >> 4), c0 + wc + y * 16 + (lane & 15), acc[x][y][i]);
+    } else {
+        // the wavefronts' sums of the tile, added in ascending order (behind the last barrier of the loop the tiles are free)
+        double *const sums = reinterpret_cast<double *>(lds);
+#pragma unroll
+        for (int x = 0; x < WT; ++x)
+#pragma unroll
+            for (int y = 0; y < WT; ++y)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    sums[wave * EDGE * EDGE + (x * 16 + 4 * i + (lane >> 4)) * EDGE + y * 16 + (lane & 15)] = acc[x][y][i];
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < EDGE * EDGE / 256; ++p) {
+            const int at = tid + 256 * p;
+            const double v = (sums[at] + sums[EDGE * EDGE + at]) + (sums[2 * EDGE * EDGE + at] + sums[3 * EDGE * EDGE + at]);
+            store(r0 + at / EDGE, c0 + at % EDGE, v);
+        }
+    }
+}
+
+// c[i] = the pieces' partial sums of element i, added in ascending order
+template <typename T>
+__global__ __launch_bounds__(256) void k_product_reduce(const double *__restrict__ part, T *__restrict__ c, long long n, int pieces) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    double s = part[i];
+    for (int p = 1; p < pieces; ++p) s += part[(long long)p * n + i];
+    c[i] = (T)s;
+}
+
+template <typename TA, typename TB>
+static int launch_product(const ProductDesc &d, const void *a, const void *b, void *c, bool wide, void *ws, hipStream_t s) {
+    ProductArgs P;
+    P.a = a; P.b = b;
+    P.c = d.pieces > 1 ? ws : c;
+    P.R = d.R; P.C = d.C; P.Q = d.Q;
+    P.ar = (int)d.ar; P.aq = (int)d.aq; P.bq = (int)d.bq; P.bc = (int)d.bc;
+    P.gr = (d.R + d.tile - 1) / d.tile; P.gc = (d.C + d.tile - 1) / d.tile;
+    P.chunk = d.pieces > 1 ? d.chunk : d.Q;
+    P.wide = wide || d.pieces > 1;
+    const dim3 grid((unsigned)(P.gr * P.gc), (unsigned)d.pieces), block(256);
+    if constexpr (sizeof(TA) == 4 || sizeof(TB) == 4) {
+        if (d.tile == 64) {
+            TAD_LAUNCH("k_product", (k_product<TA, TB, 64>), grid, block, 0, s, P);
+            return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;   // pieces only with the small tile
+        }
+    }
+    TAD_LAUNCH("k_product", (k_product<TA, TB, 32>), grid, block, 0, s, P);
+    if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
+    if (d.pieces > 1) {
+        const long long n = (long long)d.R * d.C;
+        const dim3 rgrid((unsigned)((n + 255) / 256));
+        if (wide) TAD_LAUNCH("k_product_reduce", (k_product_reduce<double>), rgrid, block, 0, s, (const double *)ws, (double *)c, n, d.pieces);
+        else TAD_LAUNCH("k_product_reduce", (k_product_reduce<float>), rgrid, block, 0, s, (const double *)ws, (float *)c, n, d.pieces);
+        if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
+    }
+    return TAD_OK;
+}
+
+static int product(bool f64, const ProductDesc &d, const void *a, const void *b, void *c, void *ws, hipStream_t s) {
+    return f64 ? launch_product<double, double>(d, a, b, c, true, ws, s) : launch_product<float, float>(d, a, b, c, false, ws, s);
+}
+
+int product_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s) {
+    const ProductPlan &pp = pl.prod;
+    return product(pl.dtype == TAD_F64, pp.forward, args[pp.side[0].operand], args[pp.side[1].operand], f,
+                   static_cast<char *>(ws) + pp.ws_offset, s);
+}
+
+int product_backward(const tad_plan &pl, const void *const *args, const void *df, void **dx, void *ws, hipStream_t s) {
+    const ProductPlan &pp = pl.prod;
+    for (int q = 0; q < 2; ++q) {
+        const ProductSide &sd = pp.side[q];
+        if (!sd.grad || !dx[sd.operand]) continue;
+        const void *other = args[pp.side[1 - q].operand];
+        const int rc = product(pl.dtype == TAD_F64, sd.desc, sd.k_major ? other : df, sd.k_major ? df : other, dx[sd.operand],
+                               static_cast<char *>(ws) + pp.ws_offset, s);   // the products share the partial sums' place in turn
+        if (rc) return rc;
+        dx[sd.operand] = nullptr;
+    }
+    return TAD_OK;
+}
+
+}  // namespace tad

@@ -33,6 +33,11 @@ int contract_forward(const tad_plan &pl, const void *const *args, void *f, void 
 int contract_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws,
                       hipStream_t s);
 
+// Sums of products as dense products.  product_backward writes the gradients it is responsible for and clears their
+// entries of dx; the rest is left to the family's kernels.
+int product_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
+int product_backward(const tad_plan &pl, const void *const *args, const void *df, void **dx, void *ws, hipStream_t s);
+
 int program_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
 int program_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws,
                      hipStream_t s);

@@ -648,7 +648,7 @@ int tad_plan_derive(const tad_expr *expr, const tad_arg *args, int n_args, tad_d
 
 void tad_plan_free(tad_plan *plan) { delete plan; }
 
-size_t tad_plan_workspace_bytes(const tad_plan *plan) { return plan ? plan->ws_bytes : 0; }
+size_t tad_plan_workspace_bytes(const tad_plan *plan) { return plan ? plan->ws_full : 0; }
 
 int tad_plan_forward_family(const tad_plan *plan) { return plan ? plan->fwd_family : TAD_EINVAL; }
 

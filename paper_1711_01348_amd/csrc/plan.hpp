@@ -7,6 +7,7 @@
 #include "../../include/tad.h"
 #include "fm.hpp"
 #include "plan_dev.h"
+#include "product.hpp"
 #include "program.hpp"
 #include "snf.hpp"
 
@@ -70,7 +71,9 @@ struct tad_plan {
     tad::FastParams fast;
     tad::ProgramBody prog;                     // TAD_BODY_PROGRAM only
     std::vector<tad::TermList> term_list;      // one entry if the terms of every gradient element are listed (small expressions)
-    size_t ws_bytes = 0;
+    tad::ProductPlan prod;                     // products that separate over the function indices (on: some run as dense products)
+    size_t ws_bytes = 0;                       // workspace of the family's kernels
+    size_t ws_full = 0;                        // ... and of the dense products; a smaller workspace runs without those
     size_t split_ws_offset = 0;                // fallback kernels: where the partial sums of shared elements start
 };
 

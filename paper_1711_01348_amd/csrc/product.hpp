@@ -1,0 +1,50 @@
+// Sums of products that separate over the function indices,
+//
+//     s_mn = sum_k A(m, k) B(k, n),
+//
+// where m stands for the leading function indices, n for the trailing ones and k for the summation indices: what an
+// expression with a product inside the sum is when one factor ignores n and the other one m.  The sum and its two
+// derived gradients  dA(m, k) = sum_n g_mn B(k, n)  and  dB(k, n) = sum_m A(m, k) g_mn  are dense products then.
+#pragma once
+#include <cstddef>
+#include <cstdint>
+
+struct tad_plan;
+
+namespace tad {
+
+// One dense product C[r][c] = sum_q A(r, q) B(q, c) with 64-bit accumulation.  A(r, q) = a[r * ar + q * aq],
+// B(q, c) = b[q * bq + c * bc] (element strides of any order), C row-major.
+struct ProductDesc {
+    int R = 0, C = 0, Q = 0;
+    int64_t ar = 0, aq = 0, bq = 0, bc = 0;
+    int tile = 0;      // output tile edge, 32 or 64
+    int pieces = 1;    // pieces of q computed by separate workgroups (few output tiles, long sum)
+    int chunk = 0;     // values of q per piece (pieces > 1)
+};
+
+// One factor of the product.
+struct ProductSide {
+    int operand = -1;          // the tensor that is the factor
+    int64_t sm = 0, sk = 0;    // element strides along m (first factor) or n (second one) and along k
+    bool grad = false;         // its gradient is a dense product that fills the tensor in its own memory order
+    bool k_major = false;      // ... whose rows run over k
+    ProductDesc desc;          // ... this one
+};
+
+struct ProductPlan {
+    bool on = false;
+    int64_t M = 0, N = 0, K = 0;
+    ProductDesc forward;
+    ProductSide side[2];
+    size_t ws_offset = 0, ws_bytes = 0;   // partial sums of shared tiles, behind the workspace of the other kernels
+};
+
+// Tile and pieces for a product of these extents.
+void product_shape(ProductDesc &d, bool f64);
+// Bytes of partial sums a product needs (0: none).
+size_t product_partial_bytes(const ProductDesc &d);
+// Does the expression separate, and which of its products run as dense products (plan.prod)?
+void match_product(tad_plan &plan);
+
+}  // namespace tad

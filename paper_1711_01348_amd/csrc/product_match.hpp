@@ -1,0 +1,120 @@
+// Recognition of sums of products that separate over the function indices (product.hpp).  Host only; included by
+// families.cpp.
+#pragma once
+#include <algorithm>
+
+#include "plan.hpp"
+#include "product.hpp"
+
+namespace tad {
+
+// Extents from which the dense products are used, and the least number of terms of the whole sum: below that the
+// general kernels take a few microseconds as well.
+constexpr int64_t kProductExtent = 16, kProductSum = 8;
+
+void product_shape(ProductDesc &d, bool f64) {
+    auto tiles = [&](int t) { return (long long)((d.R + t - 1) / t) * ((d.C + t - 1) / t); };
+    d.pieces = 1;
+    d.chunk = d.Q;
+    // Tile edge 64 from three workgroups per compute unit on (2001 x 2002 x 2003: 311 us against 348 us with edge 32; with one
+    // workgroup per compute unit it is the slower one, 1000 x 1203 x 777: 72 us against 60 us).  64-bit operands always take
+    // edge 32, whose sums are shared by the wavefronts and therefore rounded less.
+    d.tile = !f64 && tiles(64) >= 768 ? 64 : 32;
+    if (d.tile == 32 && tiles(32) < 256 && d.Q >= 512) {
+        const long long want = std::min<long long>((512 + tiles(32) - 1) / tiles(32), d.Q / 256);
+        d.chunk = (int)(((d.Q + want - 1) / want + 63) / 64 * 64);
+        d.pieces = (d.Q + d.chunk - 1) / d.chunk;
+    }
+}
+
+size_t product_partial_bytes(const ProductDesc &d) {
+    return d.pieces > 1 ? align256((size_t)d.pieces * (size_t)d.R * (size_t)d.C * sizeof(double)) : 0;
+}
+
+// Offset of one tensor along a group of extended indices as a single stride: the group's indices, the last one
+// fastest, count through 0 .. n - 1 and the offset is stride * that number.  False if it is not linear in it.
+static bool group_stride(const int64_t *off, const int64_t *extent, int count, int64_t &stride) {
+    stride = 0;
+    int64_t inner = 1;     // values of the indices behind the current one
+    bool first = true;
+    for (int d = count - 1; d >= 0; --d) {
+        if (extent[d] == 1) continue;
+        if (first) stride = off[d];
+        else if (off[d] != stride * inner) return false;
+        first = false;
+        inner *= extent[d];
+    }
+    return stride >= 0;
+}
+
+// The kernels address the elements of a stage (up to 128 rows, up to 64 values of q) with 32-bit byte offsets from
+// a 64-bit base.
+static bool tile_addressable(const ProductDesc &d) {
+    const int64_t limit = (int64_t)1 << 21;
+    return d.ar < limit && d.aq < limit && d.bq < limit && d.bc < limit;
+}
+
+void match_product(tad_plan &pl) {
+    ProductPlan &pp = pl.prod;
+    pp = ProductPlan{};
+    const tad_expr &e = pl.expr;
+    if (pl.flags & TAD_PLAN_GENERIC_ONLY) return;
+    if (pl.has_alias || e.n_constraints > 0 || e.n_sum < 1 || e.n_f < 2) return;
+    if (e.body != TAD_BODY_MUL || pl.fwd_family != TAD_FAMILY_GENERIC) return;
+    for (int s = 0; s < e.n_sum; ++s)
+        if (e.sum_lo[s] != 0) return;
+    // every function index belongs to one factor: the leading ones to one of them, the trailing ones to the other
+    auto moves = [&](int p, int d) { return pl.fwd.off[p][d] != 0; };
+    int lead = 0;    // function indices of m
+    const int first = moves(0, 0) ? 0 : 1;
+    while (lead < e.n_f && moves(first, lead) && !moves(1 - first, lead)) ++lead;
+    if (lead == 0 || lead == e.n_f) return;
+    for (int d = lead; d < e.n_f; ++d)
+        if (moves(first, d) || !moves(1 - first, d)) return;
+    int64_t extent[TAD_MAX_EXT];
+    int64_t M = 1, N = 1, K = 1;
+    for (int d = 0; d < pl.n_ext; ++d) {
+        extent[d] = pl.hi[d] - pl.lo[d] + 1;
+        (d < lead ? M : d < e.n_f ? N : K) *= extent[d];
+    }
+    if (M < kProductExtent || N < kProductExtent || K < kProductSum || K >= ((int64_t)1 << 30)) return;
+    pp.M = M; pp.N = N; pp.K = K;
+    const bool f64 = pl.dtype == TAD_F64;
+    for (int q = 0; q < 2; ++q) {
+        ProductSide &s = pp.side[q];
+        s.operand = q == 0 ? first : 1 - first;
+        const int64_t *off = pl.fwd.off[s.operand];
+        const int at = q == 0 ? 0 : lead, count = q == 0 ? lead : e.n_f - lead;
+        if (!group_stride(off + at, extent + at, count, s.sm)) return;
+        if (!group_stride(off + e.n_f, extent + e.n_f, e.n_sum, s.sk)) return;
+    }
+    const ProductSide &A = pp.side[0], &B = pp.side[1];
+    ProductDesc &f = pp.forward;
+    f.R = (int)M; f.C = (int)N; f.Q = (int)K;
+    f.ar = A.sm; f.aq = A.sk; f.bq = B.sk; f.bc = B.sm;
+    if (!tile_addressable(f)) return;
+    product_shape(f, f64);
+    size_t ws = product_partial_bytes(f);
+    for (int q = 0; q < 2; ++q) {
+        ProductSide &s = pp.side[q];
+        const ProductSide &o = pp.side[1 - q];
+        const int64_t X = q == 0 ? M : N, Y = q == 0 ? N : M;   // extents of the factor's own and of the other function index
+        const int64_t gx = q == 0 ? N : 1, gy = q == 0 ? 1 : N;  // strides of the gradient of the sum along them
+        // the products fill the tensor only if its elements and the pairs (m, k) or (n, k) are the same thing
+        const bool rows = s.sm == K && s.sk == 1, cols = s.sm == 1 && s.sk == X;
+        if (!pl.ap[s.operand].derived || pl.arg_count[s.operand] != X * K || !(rows || cols)) continue;
+        s.k_major = !rows;
+        ProductDesc &d = s.desc;
+        d.Q = (int)Y;
+        if (rows) { d.R = (int)X; d.C = (int)K; d.ar = gx; d.aq = gy; d.bq = o.sm; d.bc = o.sk; }   // sum_y g(x, y) O(k, y)
+        else { d.R = (int)K; d.C = (int)X; d.ar = o.sk; d.aq = o.sm; d.bq = gy; d.bc = gx; }        // sum_y O(k, y) g(x, y)
+        if (!tile_addressable(d)) continue;
+        product_shape(d, f64);
+        s.grad = true;
+        ws = std::max(ws, product_partial_bytes(d));
+    }
+    pp.ws_bytes = ws;
+    pp.on = true;
+}
+
+}  // namespace tad

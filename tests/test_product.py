@@ -1,0 +1,106 @@
+"""Sums of products that separate over the function indices: run as dense products with 64-bit accumulation."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1711_01348_amd import check
+from paper_1711_01348_amd import workloads as wl
+from paper_1711_01348_amd.workloads import ArgSpec, ExprSpec
+
+
+def grouped_expr(dtype):
+    """f_abn = sum_kl x_abkl y_kln: two indices in every group."""
+    a, b, n, k, l = 5, 7, 36, 3, 9
+    unit = lambda *d: [[1 if c == q else 0 for c in range(5)] for q in d]
+    return ExprSpec("mul", (a, b, n), [(0, k - 1), (0, l - 1)],
+                    [ArgSpec("x", (a, b, k, l), unit(0, 1, 3, 4)), ArgSpec("y", (k, l, n), unit(3, 4, 2))], dtype)
+
+
+def window_expr(dtype):
+    """f_in = sum_k x_{2i+k} y_kn: an overlapping view of x; only the gradient of y is a dense product."""
+    return ExprSpec("mul", (70, 33), [(0, 20)],
+                    [ArgSpec("x", (160,), [[2, 0, 1]]), ArgSpec("y", (21, 33), [[0, 0, 1], [0, 1, 0]])], dtype)
+
+
+def slack_expr(dtype):
+    """y is larger than what is read of it: its gradient has zeros no product would write."""
+    return ExprSpec("mul", (40, 37), [(0, 29)],
+                    [ArgSpec("x", (40, 30), [[1, 0, 0], [0, 0, 1]]), ArgSpec("y", (33, 40), [[0, 0, 1], [0, 1, 0]])], dtype)
+
+
+CASES = [(f"{I}x{J}x{K}_{dt}{'_xt' * xt}{'_yt' * yt}{'_swap' * sw}",
+          lambda I=I, J=J, K=K, dt=dt, xt=xt, yt=yt, sw=sw: wl.matmul_expr(I, J, K, dt, xt, yt, sw))
+         for I, J, K, xt, yt, sw in
+         [(16, 16, 8, 0, 0, 0), (16, 17, 64, 0, 0, 1), (31, 33, 65, 0, 1, 0), (33, 65, 129, 1, 0, 0), (64, 97, 63, 1, 1, 1),
+          (40, 23, 1100, 0, 0, 0), (130, 35, 513, 1, 1, 0), (257, 46, 70, 0, 1, 1)]
+         for dt in ("f32", "f64")]
+CASES += [(f"{make.__name__}_{dt}", lambda make=make, dt=dt: make(dt)) for make in (grouped_expr, window_expr, slack_expr)
+          for dt in ("f32", "f64")]
+
+
+def _run(plan, w, ws_bytes=None):
+    """Forward and backward through the C entry points with a workspace of ws_bytes (default: what the plan asks for)."""
+    import torch
+    from paper_1711_01348_amd import binding as B
+    args = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in w.arg_list()]
+    df = torch.from_numpy(w.df).cuda()
+    f = torch.full_like(df, float("nan"))
+    grads = [torch.full_like(a, float("nan")) for a in args]
+    ws = torch.empty(max(plan.workspace_bytes, 1), dtype=torch.uint8, device="cuda")
+    n = plan.workspace_bytes if ws_bytes is None else ws_bytes
+    ptrs = (ctypes.c_void_p * len(args))(*[t.data_ptr() for t in args])
+    outs = (ctypes.c_void_p * len(args))(*[t.data_ptr() for t in grads])
+    wp = ws.data_ptr() if n else None
+    assert B.lib.tad_eval_forward(plan._h, ptrs, f.data_ptr(), wp, n, None) == 0
+    assert B.lib.tad_eval_backward(plan._h, ptrs, f.data_ptr(), df.data_ptr(), outs, wp, n, None) == 0
+    torch.cuda.synchronize()
+    return f.cpu().numpy(), [g.cpu().numpy() for g in grads]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,make", CASES, ids=[c[0] for c in CASES])
+def test_products_of_any_extents_and_orders(name, make):
+    """Against the oracle; and with the workspace the general kernels need, which leaves the products out."""
+    from paper_1711_01348_amd import binding as B
+    expr = make()
+    w = wl.random_inputs(expr, 77)
+    plan, general = B.Plan(expr), B.Plan(expr, generic_only=True)
+    f_ref, g_ref = oracle.forward(expr, w.arg_list()), oracle.backward(expr, w.arg_list(), w.df)
+    for ws_bytes in (None, general.workspace_bytes):
+        f, grads = _run(plan, w, ws_bytes)
+        assert check.within(f, f_ref, expr.dtype), (name, ws_bytes, check.errors(f, f_ref))
+        for g, r in zip(grads, g_ref):
+            assert check.within(g, r, expr.dtype), (name, ws_bytes, check.errors(g, r))
+            assert np.all(g[r == 0] == 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_infinities_stay_in_their_rows_and_columns(dtype):
+    """Edge tiles repeat rows and pad the sum: an infinity or a NaN in the last row, column or term reaches the results it
+    belongs to and no others."""
+    from paper_1711_01348_amd import binding as B
+    I, J, K = 37, 41, 67
+    expr = wl.matmul_expr(I, J, K, dtype)
+    w = wl.random_inputs(expr, 5)
+    x, y = w.arg_list()
+    x[I - 1, K - 1] = np.inf
+    y[K - 1, J - 1] = np.nan
+    f, (dx, dy) = _run(B.Plan(expr), w)
+    x64, y64, d64 = x.astype(np.float64), y.astype(np.float64), w.df.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        want = [(x64[:, :, None] * y64[None]).sum(1), (d64[:, None, :] * y64[None]).sum(2), (x64[:, :, None] * d64[:, None, :]).sum(0)]
+    for got, ref in zip((f, dx, dy), want):
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+        ok = np.isfinite(ref)
+        assert check.within(np.where(ok, got, 0), np.where(ok, ref, 0), dtype)
+
+
+def test_families_and_workspace_are_those_of_the_general_kernels():
+    from paper_1711_01348_amd import binding as B
+    e = wl.matmul_expr(100, 90, 70, "f64")
+    assert B.Plan(e).forward_family == "generic" and B.Plan(e, generic_only=True).forward_family == "generic"
+    e = wl.matmul_expr(40, 23, 5000, "f64")             # few tiles, long sum: partial sums
+    assert B.Plan(e).workspace_bytes > B.Plan(e, generic_only=True).workspace_bytes
