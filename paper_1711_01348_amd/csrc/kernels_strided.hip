@@ -195,7 +195,8 @@ struct LoadSeed {       // t = df (1 - f^2), the factor every term of both gradi
 // Floats [first, first + count) of a tensor of `limit` floats -> lds[mis + k] for element first + k, copied by the NT
 // threads tid = 0 .. NT-1, where mis
 // (returned) is the distance of the first element from the 16-byte boundary below it.  Vectors that lie inside the
-// tensor are loaded whole, four per thread in flight; the at most two vectors that stick out, element by element.
+// tensor are loaded whole, four per thread in flight; the at most two vectors that lie across its ends, element by element;
+// what lies behind the tensor is not written.
 template <int NT, class OP>
 __device__ __forceinline__ int slice_to_lds(const float *__restrict__ base, int first, int count, int limit, float *lds,
                                             int tid, OP op) {
@@ -217,11 +218,12 @@ TAD_NOUNROLL
         for (int h = 0; h < 4; ++h)
             if (inside[h]) *reinterpret_cast<float4s *>(lds + 4 * (v0 + h * NT)) = val[h];
     }
-    // the first and the last vector may reach beyond the tensor: their elements one by one (zeros outside)
+    // the vector that reaches beyond the tensor's start and the one across its end (not the last one of the slice if the slice
+    // goes on behind the tensor): their elements one by one (zeros outside)
     if (tid < 8) {
-        const int v = tid < 4 ? 0 : nvec - 1, c = tid & 3;
+        const int v = tid < 4 ? 0 : (limit - start) >> 2, c = tid & 3;
         const int at = start + 4 * v;
-        if (at < 0 || at > limit - 4) lds[4 * v + c] = (at + c >= 0 && at + c < limit) ? op.one(at + c) : 0.f;
+        if (v < nvec && (at < 0 || at > limit - 4)) lds[4 * v + c] = (at + c >= 0 && at + c < limit) ? op.one(at + c) : 0.f;
     }
     return mis;
 }
