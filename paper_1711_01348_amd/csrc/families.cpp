@@ -7,6 +7,7 @@
 #include "plan.hpp"
 #include "launch_geom.h"
 #include "product_match.hpp"
+#include "separable_match.hpp"
 
 namespace tad {
 
@@ -346,6 +347,8 @@ void select_families(tad_plan &plan) {
     match_product(plan);
     plan.prod.ws_offset = align256(plan.ws_bytes);
     plan.ws_full = plan.prod.on && plan.prod.ws_bytes ? plan.prod.ws_offset + plan.prod.ws_bytes : plan.ws_bytes;
+    match_separable(plan);
+    if (plan.sep.on) plan.ws_full = std::max(plan.ws_bytes, plan.sep.ws_bytes);   // one or the other
 }
 
 static void reserve_partial_sums(tad_plan &plan) {

@@ -249,8 +249,15 @@ static int launch_product(const ProductDesc &d, const void *a, const void *b, vo
     return TAD_OK;
 }
 
+int product_run(const ProductDesc &d, const void *a, bool a64, const void *b, bool b64, void *c, bool c64, void *ws, hipStream_t s) {
+    if (a64 && b64) return launch_product<double, double>(d, a, b, c, c64, ws, s);
+    if (a64) return launch_product<double, float>(d, a, b, c, c64, ws, s);
+    if (b64) return launch_product<float, double>(d, a, b, c, c64, ws, s);
+    return launch_product<float, float>(d, a, b, c, c64, ws, s);
+}
+
 static int product(bool f64, const ProductDesc &d, const void *a, const void *b, void *c, void *ws, hipStream_t s) {
-    return f64 ? launch_product<double, double>(d, a, b, c, true, ws, s) : launch_product<float, float>(d, a, b, c, false, ws, s);
+    return product_run(d, a, f64, b, f64, c, f64, ws, s);
 }
 
 int product_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s) {

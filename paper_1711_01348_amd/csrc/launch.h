@@ -38,6 +38,13 @@ int contract_backward(const tad_plan &pl, const void *const *args, const void *d
 int product_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
 int product_backward(const tad_plan &pl, const void *const *args, const void *df, void **dx, void *ws, hipStream_t s);
 
+// one product; a64, b64, c64: 64-bit elements; ws: partial sums of shared tiles
+int product_run(const ProductDesc &d, const void *a, bool a64, const void *b, bool b64, void *c, bool c64, void *ws, hipStream_t s);
+
+// sums of products of two functions (separable.hpp)
+int separable_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
+int separable_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws, hipStream_t s);
+
 int program_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
 int program_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws,
                      hipStream_t s);

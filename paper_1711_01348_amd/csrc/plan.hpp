@@ -9,6 +9,7 @@
 #include "plan_dev.h"
 #include "product.hpp"
 #include "program.hpp"
+#include "separable.hpp"
 #include "snf.hpp"
 
 namespace tad {
@@ -72,6 +73,7 @@ struct tad_plan {
     tad::ProgramBody prog;                     // TAD_BODY_PROGRAM only
     std::vector<tad::TermList> term_list;      // one entry if the terms of every gradient element are listed (small expressions)
     tad::ProductPlan prod;                     // products that separate over the function indices (on: some run as dense products)
+    tad::SepPlan sep;                          // sums of products of two functions (on: the whole expression runs on dense products)
     size_t ws_bytes = 0;                       // workspace of the family's kernels
     size_t ws_full = 0;                        // ... and of the dense products; a smaller workspace runs without those
     size_t split_ws_offset = 0;                // fallback kernels: where the partial sums of shared elements start

@@ -80,21 +80,24 @@ struct GatherShape {
     int layout;
     int splits;
 };
+// Is f contiguous along the elements of the gradient (last index of beta), and far from it along z_0?
+inline bool contiguous_along_elements(const GatherPlan &P) {
+    if (P.kappa < 1 || P.rank < 1) return false;
+    int64_t along_elements = 0;
+    for (int r = 0; r < P.R; ++r) {
+        const int64_t num = P.offY[kSlotF][r] * (int64_t)P.U[r][P.rank - 1];
+        if (num % P.diag[r] != 0) return false;
+        along_elements += num / P.diag[r];
+    }
+    const int64_t along_z = P.offZ[kSlotF][0];
+    return along_elements >= -1 && along_elements <= 1 && (along_z <= -16 || along_z >= 16);
+}
 inline GatherShape gather_shape(const GatherPlan &P, long long n_elements, double terms_total) {
     GatherShape g{kLayoutThreads, 1};
     if (!use_cooperative_gather(n_elements, terms_total)) return g;
     g.layout = kLayoutBlocks;
     g.splits = cooperative_splits(n_elements, terms_total);
-    if (P.kappa < 1 || P.rank < 1) return g;
-    // offset of f between neighbouring elements (last index of beta) and between neighbouring values of z_0
-    int64_t along_elements = 0;
-    for (int r = 0; r < P.R; ++r) {
-        const int64_t num = P.offY[kSlotF][r] * (int64_t)P.U[r][P.rank - 1];
-        if (num % P.diag[r] != 0) return g;
-        along_elements += num / P.diag[r];
-    }
-    const int64_t along_z = P.offZ[kSlotF][0];
-    if ((along_elements < -1 || along_elements > 1) || (along_z > -16 && along_z < 16)) return g;
+    if (!contiguous_along_elements(P)) return g;
     g.layout = kLayoutLanes;
     const long long blocks = (n_elements + 255) / 256;
     const long long want = (2048 + blocks - 1) / blocks;                                  // about 2048 blocks in all
@@ -102,6 +105,33 @@ inline GatherShape gather_shape(const GatherPlan &P, long long n_elements, doubl
     long long sp = want < most ? want : most;
     if (sp > 256) sp = 256;
     g.splits = sp < 1 ? 1 : (int)sp;
+    return g;
+}
+
+// Plain sums of a tensor's elements through a plan (the last pass of the gradients of separable.hpp): who adds up an element.
+//   thread   a thread each (short sums);
+//   wave     a wavefront each, its lanes take the terms in turn;
+//   block    a workgroup each (sums of thousands of terms for few elements), possibly several;
+//   columns  32 neighbouring elements per workgroup of 1024 threads, 32 threads each, where the tensor is contiguous along
+//            the elements: a wavefront reads two rows of 32 neighbours.
+// A sum shared by workgroups (splits > 1: too few of them otherwise) goes through fp64 partial sums.
+enum SumLayout { kSumThread = 0, kSumWave = 1, kSumBlock = 2, kSumColumns = 3 };
+inline GatherShape sum_shape(const GatherPlan &P, long long n_elements, double terms_total) {
+    GatherShape g{kSumThread, 1};
+    const double each = terms_total / (double)(n_elements > 0 ? n_elements : 1);
+    if (each < 16.0) return g;   // walking the plan costs as much as a few dozen loads
+    if (contiguous_along_elements(P)) {
+        g.layout = kSumColumns;
+        const long long blocks = (n_elements + 31) / 32;
+        const long long want = (512 + blocks - 1) / blocks, most = (long long)(each / 1024.0);
+        const long long sp = want < most ? want : most;
+        g.splits = sp < 1 ? 1 : sp > 256 ? 256 : (int)sp;
+        return g;
+    }
+    g.layout = kSumWave;
+    if (each < 2048.0 || n_elements >= 4096) return g;
+    g.layout = kSumBlock;
+    g.splits = cooperative_splits(n_elements, terms_total);
     return g;
 }
 

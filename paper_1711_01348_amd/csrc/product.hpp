@@ -40,6 +40,16 @@ struct ProductPlan {
     size_t ws_offset = 0, ws_bytes = 0;   // partial sums of shared tiles, behind the workspace of the other kernels
 };
 
+// Extents from which the dense products are used, and the least number of terms of the whole sum: below that the
+// general kernels take a few microseconds as well.
+constexpr int64_t kProductExtent = 16, kProductSum = 8;
+
+// Offset of one tensor along a group of extended indices as a single stride: the group's indices, the last one
+// fastest, count through 0 .. n - 1 and the offset is stride * that number.  False if it is not linear in it.
+bool product_group_stride(const int64_t *off, const int64_t *extent, int count, int64_t &stride);
+// The kernels address the elements of a stage (up to 128 rows, up to 64 values of q) with 32-bit byte offsets from
+// a 64-bit base.
+bool product_addressable(const ProductDesc &d);
 // Tile and pieces for a product of these extents.
 void product_shape(ProductDesc &d, bool f64);
 // Bytes of partial sums a product needs (0: none).

@@ -8,10 +8,6 @@
 
 namespace tad {
 
-// Extents from which the dense products are used, and the least number of terms of the whole sum: below that the
-// general kernels take a few microseconds as well.
-constexpr int64_t kProductExtent = 16, kProductSum = 8;
-
 void product_shape(ProductDesc &d, bool f64) {
     auto tiles = [&](int t) { return (long long)((d.R + t - 1) / t) * ((d.C + t - 1) / t); };
     d.pieces = 1;
@@ -31,9 +27,7 @@ size_t product_partial_bytes(const ProductDesc &d) {
     return d.pieces > 1 ? align256((size_t)d.pieces * (size_t)d.R * (size_t)d.C * sizeof(double)) : 0;
 }
 
-// Offset of one tensor along a group of extended indices as a single stride: the group's indices, the last one
-// fastest, count through 0 .. n - 1 and the offset is stride * that number.  False if it is not linear in it.
-static bool group_stride(const int64_t *off, const int64_t *extent, int count, int64_t &stride) {
+bool product_group_stride(const int64_t *off, const int64_t *extent, int count, int64_t &stride) {
     stride = 0;
     int64_t inner = 1;     // values of the indices behind the current one
     bool first = true;
@@ -47,9 +41,7 @@ static bool group_stride(const int64_t *off, const int64_t *extent, int count, i
     return stride >= 0;
 }
 
-// The kernels address the elements of a stage (up to 128 rows, up to 64 values of q) with 32-bit byte offsets from
-// a 64-bit base.
-static bool tile_addressable(const ProductDesc &d) {
+bool product_addressable(const ProductDesc &d) {
     const int64_t limit = (int64_t)1 << 21;
     return d.ar < limit && d.aq < limit && d.bq < limit && d.bc < limit;
 }
@@ -85,14 +77,14 @@ void match_product(tad_plan &pl) {
         s.operand = q == 0 ? first : 1 - first;
         const int64_t *off = pl.fwd.off[s.operand];
         const int at = q == 0 ? 0 : lead, count = q == 0 ? lead : e.n_f - lead;
-        if (!group_stride(off + at, extent + at, count, s.sm)) return;
-        if (!group_stride(off + e.n_f, extent + e.n_f, e.n_sum, s.sk)) return;
+        if (!product_group_stride(off + at, extent + at, count, s.sm)) return;
+        if (!product_group_stride(off + e.n_f, extent + e.n_f, e.n_sum, s.sk)) return;
     }
     const ProductSide &A = pp.side[0], &B = pp.side[1];
     ProductDesc &f = pp.forward;
     f.R = (int)M; f.C = (int)N; f.Q = (int)K;
     f.ar = A.sm; f.aq = A.sk; f.bq = B.sk; f.bc = B.sm;
-    if (!tile_addressable(f)) return;
+    if (!product_addressable(f)) return;
     product_shape(f, f64);
     size_t ws = product_partial_bytes(f);
     for (int q = 0; q < 2; ++q) {
@@ -108,7 +100,7 @@ void match_product(tad_plan &pl) {
         d.Q = (int)Y;
         if (rows) { d.R = (int)X; d.C = (int)K; d.ar = gx; d.aq = gy; d.bq = o.sm; d.bc = o.sk; }   // sum_y g(x, y) O(k, y)
         else { d.R = (int)K; d.C = (int)X; d.ar = o.sk; d.aq = o.sm; d.bq = gy; d.bc = gx; }        // sum_y O(k, y) g(x, y)
-        if (!tile_addressable(d)) continue;
+        if (!product_addressable(d)) continue;
         product_shape(d, f64);
         s.grad = true;
         ws = std::max(ws, product_partial_bytes(d));

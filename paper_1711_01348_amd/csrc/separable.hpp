@@ -1,0 +1,60 @@
+// Sums whose terms are products of two functions,
+//
+//     f_mn = outer( s_mn, operands at (m, n) ),   s_mn = sum_k A(m, k) B(k, n),
+//
+// where m stands for the leading function indices, n for the trailing ones and k for the summation indices, and A and B
+// are what the factors of the inner function that ignore n and m multiply to.  A and B are evaluated once per pair of
+// indices instead of once per term, the sum is a dense product, and so are the derivatives of the factors,
+//
+//     dA(m, k) = sum_n g_mn B(k, n),   dB(k, n) = sum_m A(m, k) g_mn,   g = df * d outer / d s;
+//
+// the gradient of an operand of A is the gather of an expression over (m, k) without a sum of its own:
+// dx_beta = sum over the pairs (m, k) that read x_beta of dA(m, k) * (dA / dx)(operands at (m, k)).
+#pragma once
+#include <cstddef>
+#include <cstdint>
+#include <memory>
+#include <vector>
+
+#include "product.hpp"
+#include "program.hpp"
+
+struct tad_plan;
+
+namespace tad {
+
+struct SepSide {
+    int operand = -1;            // the tensor that is the factor; -1: a function of operands, evaluated into the workspace
+    bool fills = false;          // ... whose elements are exactly the pairs of indices: its gradient is the product itself
+    int64_t X = 0;               // values of the side's function index
+    int64_t sm = 0, sk = 0;      // element strides of the factor along the function index and along k
+    bool k_major = false;        // rows of the factor's derivative run over k
+    ProductDesc grad;            // the factor's derivative
+    // the factor as an expression over its pairs of indices, in the order of its derivative's elements; null if the tensor
+    // is the factor and its gradient is the product (or not wanted)
+    std::shared_ptr<tad_plan> sub;
+    std::vector<int> operands;   // operand of sub -> operand of the expression
+    size_t value_offset = 0;     // workspace: the evaluated factor, in 64 bits
+};
+
+struct SepPlan {
+    bool on = false;
+    int64_t M = 0, N = 0, K = 0;
+    ProductDesc forward;
+    SepSide side[2];
+    ProgramBody prog;            // outer function and its derivatives
+    bool identity = false;       // the outer function is the sum
+    bool term_is_g[TAD_MAX_ARGS] = {};   // d outer / d operand and d outer / d sum are the same program
+    // workspace
+    size_t s_offset = 0;         // sums
+    size_t g_offset = 0;         // g = df * d outer / d s
+    size_t h_offset = 0;         // 64-bit terms of a gradient that several pairs of indices add to
+    size_t d_offset = 0;         // derivative of a factor, in 64 bits
+    size_t part_offset = 0;      // partial sums of the products and of the gathers
+    size_t ws_bytes = 0;
+};
+
+// Does the inner function separate, and is the sum large enough for the dense form (plan.sep)?
+void match_separable(tad_plan &plan);
+
+}  // namespace tad

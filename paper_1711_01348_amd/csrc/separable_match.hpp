@@ -1,0 +1,281 @@
+// Recognition of sums of products of two functions (separable.hpp).  Host only; included by families.cpp.
+#pragma once
+#include <algorithm>
+#include <cstring>
+
+#include "plan.hpp"
+#include "separable.hpp"
+
+namespace tad {
+
+namespace {
+
+struct Factor {
+    int node;
+    bool inverse;
+    uint32_t reads;   // operands
+};
+
+uint32_t operands_of(const Graph &g, const std::vector<int> &alias, int node) {
+    const int t = alias[node];
+    const Node &nd = g.nodes[t];
+    if (nd.op == P_ARG) return 1u << nd.k;
+    uint32_t m = 0;
+    if (nd.a >= 0) m |= operands_of(g, alias, nd.a);
+    if (nd.b >= 0) m |= operands_of(g, alias, nd.b);
+    return m;
+}
+
+// The factors of a node: inputs of its products, quotients and negations.  False: more than a program can hold.
+bool collect_factors(Graph &g, const std::vector<int> &alias, int node, bool inverse, std::vector<Factor> &out) {
+    const int t = alias[node];
+    const Node nd = g.nodes[t];
+    if (out.size() > 16) return false;
+    switch (nd.op) {
+    case P_MUL: return collect_factors(g, alias, nd.a, inverse, out) && collect_factors(g, alias, nd.b, inverse, out);
+    case P_DIV: return collect_factors(g, alias, nd.a, inverse, out) && collect_factors(g, alias, nd.b, !inverse, out);
+    case P_NEG:
+        if (!collect_factors(g, alias, nd.a, inverse, out)) return false;
+        out.push_back(Factor{-1, false, 0});   // a sign
+        return true;
+    default: out.push_back(Factor{t, inverse, operands_of(g, alias, t)}); return true;
+    }
+}
+
+// One expression from the factors of a side: (product of the numerators) / (product of the denominators).
+int side_expression(Graph &g, const std::vector<Factor> &factors) {
+    int num = -1, den = -1;
+    bool negative = false;
+    for (const Factor &f : factors) {
+        if (f.node < 0) { negative = !negative; continue; }
+        int &to = f.inverse ? den : num;
+        to = to < 0 ? f.node : g.add(P_MUL, to, f.node);
+    }
+    if (num < 0) num = g.constant(1.0);
+    const int q = den < 0 ? num : g.add(P_DIV, num, den);
+    return negative ? g.add(P_NEG, q) : q;
+}
+
+bool same_program(const DevProg &x, const DevProg &y) {
+    if (x.n != y.n || x.result != y.result) return false;
+    for (int i = 0; i < x.n; ++i)
+        if (x.op[i] != y.op[i] || x.a[i] != y.a[i] || x.b[i] != y.b[i] || x.k[i] != y.k[i]) return false;
+    for (int c = 0; c < kMaxProgConst; ++c)
+        if (x.cst[c] != y.cst[c]) return false;
+    return true;
+}
+
+}  // namespace
+
+void match_separable(tad_plan &pl) {
+    SepPlan &sp = pl.sep;
+    sp = SepPlan{};
+    const tad_expr &e = pl.expr;
+    if (pl.flags & (TAD_PLAN_GENERIC_ONLY | TAD_PLAN_KEEP_PROGRAM)) return;
+    if (pl.has_alias || e.n_constraints > 0 || e.n_sum < 1 || e.n_f < 2) return;
+    const bool program = e.body == TAD_BODY_PROGRAM && pl.fwd_family == TAD_FAMILY_PROGRAM;
+    if (!program && !(e.body == TAD_BODY_TANH_DOT && pl.fwd_family == TAD_FAMILY_GENERIC)) return;
+    for (int s = 0; s < e.n_sum; ++s)
+        if (e.sum_lo[s] != 0) return;
+    const int n_ops = (int)pl.args.size();
+
+    // ---- factors ---------------------------------------------------------------------------------------------------
+    tad_expr text = e;
+    if (!program) {
+        std::vector<tad_op> in, out;
+        if (!builtin_body_programs(e.body, in, out)) return;
+        text.n_operands = n_ops;
+        text.n_inner = (int)in.size();
+        text.n_outer = (int)out.size();
+        std::copy(in.begin(), in.end(), text.inner);
+        std::copy(out.begin(), out.end(), text.outer);
+        uint32_t wanted = 0;
+        for (int p = 0; p < n_ops; ++p) wanted |= pl.args[p].needs_grad ? 1u << p : 0u;
+        if (build_program_body(text, sp.prog, 0, wanted)) return;
+    } else {
+        sp.prog = pl.prog;
+    }
+    Graph g;
+    const int root = parse_postfix(text.inner, text.n_inner, false, n_ops, g);
+    if (root < 0) return;
+    const std::vector<int> alias = simplify(g);
+    std::vector<Factor> factors;
+    if (!collect_factors(g, alias, root, false, factors)) return;
+
+    // ---- function indices of the two sides ------------------------------------------------------------------------
+    int64_t extent[TAD_MAX_EXT];
+    for (int d = 0; d < pl.n_ext; ++d) extent[d] = pl.hi[d] - pl.lo[d] + 1;
+    auto moves = [&](uint32_t reads, int d) {
+        for (int p = 0; p < n_ops; ++p) {
+            if (!((reads >> p) & 1u) || extent[d] == 1) continue;
+            for (int r = 0; r < pl.args[p].rank; ++r)
+                if (pl.args[p].index[r][d] != 0) return true;
+        }
+        return false;
+    };
+    std::vector<Factor> of[2];
+    int lead = 0;
+    for (int split = 1; split < e.n_f && !lead; ++split) {
+        bool good = true;
+        of[0].clear();
+        of[1].clear();
+        bool own[2] = {false, false};
+        for (const Factor &f : factors) {
+            bool in[2] = {false, false};
+            for (int d = 0; d < e.n_f; ++d)
+                if (moves(f.reads, d)) in[d < split ? 0 : 1] = true;
+            good = good && !(in[0] && in[1]);
+            own[0] = own[0] || in[0];
+            own[1] = own[1] || in[1];
+            of[in[1] ? 1 : 0].push_back(f);
+        }
+        if (good && own[0] && own[1]) lead = split;
+    }
+    if (!lead) return;
+    int64_t M = 1, N = 1, K = 1;
+    for (int d = 0; d < pl.n_ext; ++d) (d < lead ? M : d < e.n_f ? N : K) *= extent[d];
+    if (M < kProductExtent || N < kProductExtent || K < kProductSum || K >= ((int64_t)1 << 30)) return;
+    // Factors are evaluated in 64 bits: of 32-bit operands nothing overflows there that did not in 32 bits, in whatever order
+    // the factors are multiplied.  With 64-bit operands the order of the operations has to stay as written: one product
+    // of two functions.
+    if (pl.dtype == TAD_F64 && (of[0].size() != 1 || of[1].size() != 1 || of[0][0].inverse || of[1][0].inverse)) return;
+    sp.M = M; sp.N = N; sp.K = K;
+
+    // ---- the sides ------------------------------------------------------------------------------------------------
+    for (int q = 0; q < 2; ++q) {
+        SepSide &s = sp.side[q];
+        const int at = q == 0 ? 0 : lead, count = q == 0 ? lead : e.n_f - lead;
+        s.X = q == 0 ? M : N;
+        if (count + e.n_sum > TAD_MAX_EXT) return;
+        const int node = side_expression(g, of[q]);
+        const std::vector<int> simple = simplify(g);
+        uint32_t reads = 0, wanted = 0;
+        for (const Factor &f : of[q]) reads |= f.reads;
+        for (int p = 0; p < n_ops; ++p)
+            if (((reads >> p) & 1u) && pl.args[p].needs_grad) wanted |= 1u << p;
+        const Node &top = g.nodes[simple[node]];
+        int64_t sm = 0, sk = 0;
+        if (top.op == P_ARG && product_group_stride(pl.fwd.off[top.k] + at, extent + at, count, sm) &&
+            product_group_stride(pl.fwd.off[top.k] + e.n_f, extent + e.n_f, e.n_sum, sk)) {
+            s.operand = top.k;
+            const bool rows = sm == K && sk == 1, cols = sm == 1 && sk == s.X;
+            s.fills = (rows || cols) && pl.arg_count[top.k] == s.X * K;
+            s.k_major = !rows && cols;
+        }
+        if (s.operand < 0 || (!s.fills && wanted)) {
+            // the order of the pairs: along the faster index of the first operand that moves along both
+            if (s.operand < 0)
+                for (int p = 0; p < n_ops; ++p) {
+                    const int64_t *off = pl.fwd.off[p];
+                    if (!((reads >> p) & 1u) || off[at + count - 1] == 0 || off[pl.n_ext - 1] == 0) continue;
+                    const int64_t x = off[at + count - 1] < 0 ? -off[at + count - 1] : off[at + count - 1];
+                    const int64_t k = off[pl.n_ext - 1] < 0 ? -off[pl.n_ext - 1] : off[pl.n_ext - 1];
+                    s.k_major = x < k;
+                    break;
+                }
+            tad_expr se;
+            tad_arg sa[TAD_MAX_ARGS];
+            std::memset(&se, 0, sizeof se);
+            std::memset(sa, 0, sizeof sa);
+            se.body = TAD_BODY_PROGRAM;
+            int dims[TAD_MAX_EXT], n = 0;
+            if (s.k_major)
+                for (int k = 0; k < e.n_sum; ++k) dims[n++] = e.n_f + k;
+            for (int d = 0; d < count; ++d) dims[n++] = at + d;
+            if (!s.k_major)
+                for (int k = 0; k < e.n_sum; ++k) dims[n++] = e.n_f + k;
+            se.n_f = n;
+            for (int d = 0; d < n; ++d) se.f_shape[d] = extent[dims[d]];
+            std::vector<tad_op> ops;
+            if (!emit_postfix(g, simple, node, ops, TAD_MAX_PROGRAM)) return;
+            int index[TAD_MAX_ARGS];
+            for (int p = 0; p < n_ops; ++p) {
+                if (!((reads >> p) & 1u)) continue;
+                index[p] = (int)s.operands.size();
+                tad_arg &a = sa[index[p]];
+                s.operands.push_back(p);
+                a.rank = pl.args[p].rank;
+                a.needs_grad = pl.args[p].needs_grad;
+                for (int r = 0; r < a.rank; ++r) {
+                    a.shape[r] = pl.args[p].shape[r];
+                    for (int d = 0; d < n; ++d) a.index[r][d] = pl.args[p].index[r][dims[d]];
+                }
+            }
+            for (size_t i = 0; i < ops.size(); ++i) {
+                se.inner[i] = ops[i];
+                if (ops[i].op == TAD_OP_ARG) se.inner[i].iarg = index[ops[i].iarg];
+            }
+            se.n_inner = (int)ops.size();
+            se.outer[0].op = TAD_OP_SUM;
+            se.n_outer = 1;
+            se.n_operands = (int)s.operands.size();
+            if (se.n_operands < 1) return;
+            tad_plan *sub = nullptr;
+            // KEEP_PROGRAM: the derivatives of the factor are read from its program
+            if (derive_plan(&se, sa, se.n_operands, pl.dtype, TAD_PLAN_KEEP_PROGRAM, &sub)) return;
+            s.sub.reset(sub);
+        }
+        if (s.operand >= 0) {
+            s.sm = sm;
+            s.sk = sk;
+        } else {
+            s.sm = s.k_major ? 1 : K;
+            s.sk = s.k_major ? s.X : 1;
+        }
+    }
+    // ---- products -------------------------------------------------------------------------------------------------
+    const bool f64 = pl.dtype == TAD_F64;
+    const SepSide &A = sp.side[0], &B = sp.side[1];
+    auto wide = [&](const SepSide &s) { return f64 || s.operand < 0; };
+    ProductDesc &f = sp.forward;
+    f.R = (int)M; f.C = (int)N; f.Q = (int)K;
+    f.ar = A.sm; f.aq = A.sk; f.bq = B.sk; f.bc = B.sm;
+    if (!product_addressable(f)) return;
+    product_shape(f, wide(A) && wide(B));
+    size_t part = product_partial_bytes(f), value = 0, derivative = 0, terms = 0;
+    for (int q = 0; q < 2; ++q) {
+        SepSide &s = sp.side[q];
+        const SepSide &o = sp.side[1 - q];
+        const int64_t gx = q == 0 ? N : 1, gy = q == 0 ? 1 : N;   // strides of g along the side's own and the other function index
+        ProductDesc &d = s.grad;
+        d.Q = (int)o.X;
+        if (!s.k_major) { d.R = (int)s.X; d.C = (int)K; d.ar = gx; d.aq = gy; d.bq = o.sm; d.bc = o.sk; }
+        else { d.R = (int)K; d.C = (int)s.X; d.ar = o.sk; d.aq = o.sm; d.bq = gy; d.bc = gx; }
+        if (!product_addressable(d)) return;
+        product_shape(d, f64);
+        part = std::max(part, product_partial_bytes(d));
+        if (s.operand < 0) {
+            s.value_offset = value;
+            value += align256((size_t)(s.X * K) * 8);
+        }
+        if (s.sub) {
+            derivative = std::max(derivative, align256((size_t)(s.X * K) * 8));
+            terms = std::max(terms, align256((size_t)(s.X * K) * 8));
+        }
+    }
+    for (int p = 0; p < n_ops; ++p) sp.term_is_g[p] = same_program(sp.prog.douter_arg[p], sp.prog.douter);
+    sp.identity = sp.prog.outer.n == 1 && sp.prog.outer.op[0] == P_SUM;
+    // partial sums of the gathers
+    auto gathers = [&](const ArgPlan &ap, int64_t count, double pairs) {
+        if (!ap.derived) return;
+        const long long n = gather_launch_count(ap.dev, count);
+        part = std::max(part, split_workspace_bytes(n, sum_shape(ap.dev, n, pairs).splits));
+    };
+    for (const SepSide &s : sp.side)
+        if (s.sub)
+            for (size_t p = 0; p < s.operands.size(); ++p) gathers(s.sub->ap[p], s.sub->arg_count[p], (double)(s.X * K));
+    for (int p = 0; p < n_ops; ++p)
+        if ((sp.prog.outer_mask >> p) & 1u) gathers(pl.ap_outer[p], pl.arg_count[p], (double)pl.f_count);
+    const size_t sums = align256((size_t)pl.f_count * (f64 ? 8 : 4));
+    if (sp.prog.outer_mask) terms = std::max(terms, align256((size_t)pl.f_count * 8));
+    size_t ws = value;
+    sp.s_offset = ws; ws += sums;
+    sp.g_offset = ws; ws += sums;
+    sp.h_offset = ws; ws += terms;
+    sp.d_offset = ws; ws += derivative;
+    sp.part_offset = ws; ws += part;
+    sp.ws_bytes = ws;
+    sp.on = true;
+}
+
+}  // namespace tad

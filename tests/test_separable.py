@@ -1,0 +1,158 @@
+"""Sums whose terms are products of two functions: run as dense products with 64-bit accumulation."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1711_01348_amd import check
+from paper_1711_01348_amd import workloads as wl
+from paper_1711_01348_amd.workloads import ArgSpec, ExprSpec
+
+A0, A1, A2, A3 = (("arg", p) for p in range(4))
+X, Y = [[1, 0, 0], [0, 0, 1]], [[0, 0, 1], [0, 1, 0]]
+
+
+def program(f_shape, sums, args, dtype, inner, outer):
+    return ExprSpec("program", f_shape, sums, args, dtype, inner, outer)
+
+
+def tanh_dot(I, J, K, dtype, xt=False, yt=False):
+    e = wl.matmul_expr(I, J, K, dtype, xt, yt)
+    return ExprSpec("tanh_dot", e.f_shape, e.sums, e.args, dtype)
+
+
+def weighted(dtype):
+    """sum_k x_ik w_k / (1 + y_kj^2), negated: a factor of k alone, a quotient across the sides, and a sign."""
+    I, J, K = 40, 53, 31
+    return program((I, J), [(0, K - 1)], [ArgSpec("x", (I, K), X), ArgSpec("y", (K, J), Y), ArgSpec("w", (K,), [[0, 0, 1]])], dtype,
+                   [A0, A2, ("mul",), ("const", 1.0), A1, ("powi", 2), ("add",), ("div",), ("neg",)], [("sum",), ("sin",)])
+
+
+def both_sides(dtype):
+    """w_k inside a factor of either side: its gradient is a sum of two."""
+    I, J, K = 65, 33, 17
+    return program((I, J), [(0, K - 1)], [ArgSpec("x", (K, I), [[0, 0, 1], [1, 0, 0]]), ArgSpec("y", (J, K), [[0, 1, 0], [0, 0, 1]]),
+                                          ArgSpec("w", (K,), [[0, 0, 1]])], dtype,
+                   [A0, A2, ("add",), ("exp",), A1, A2, ("mul",), ("cos",), ("mul",)], [("sum",)])
+
+
+def grouped(dtype):
+    """Two indices in every group; the sum is scaled by a tensor over all function indices and shifted by one over some."""
+    a, b, n, k, l = 5, 7, 36, 3, 9
+    unit = lambda *d: [[1 if c == q else 0 for c in range(5)] for q in d]
+    return program((a, b, n), [(0, k - 1), (0, l - 1)],
+                   [ArgSpec("x", (a, b, k, l), unit(0, 1, 3, 4)), ArgSpec("y", (n, l, k), unit(2, 4, 3)),
+                    ArgSpec("c", (a, b, n), unit(0, 1, 2)), ArgSpec("v", (b,), unit(1))], dtype,
+                   [A0, A1, ("sin",), ("mul",)], [A2, ("sum",), ("mul",), A3, ("add",), ("tanh",)])
+
+
+def diagonal(dtype):
+    """x_iik: the gradient is zero off the diagonal; y is larger than what is read of it."""
+    I, J, K = 40, 37, 30
+    return program((I, J), [(0, K - 1)], [ArgSpec("x", (I, I, K), [[1, 0, 0], [1, 0, 0], [0, 0, 1]]), ArgSpec("y", (33, 40), Y)], dtype,
+                   [A0, ("exp",), A1, ("mul",)], [("sum",)])
+
+
+def windows(dtype):
+    """x_{2i+k}: an overlapping view as a plain factor, and y_{j+k} inside a function."""
+    I, J, K = 70, 33, 21
+    return program((I, J), [(0, K - 1)], [ArgSpec("x", (160,), [[2, 0, 1]]), ArgSpec("y", (J + K - 1,), [[0, 1, 1]])], dtype,
+                   [A0, A1, ("exp",), ("mul",)], [("sum",), ("powi", 2)])
+
+
+def inside_and_outside(dtype):
+    """x_i is a factor of the sum and read by the outer function too."""
+    I, J, K = 50, 49, 16
+    return program((I, J), [(0, K - 1)], [ArgSpec("x", (I,), [[1, 0, 0]]), ArgSpec("y", (J, K), [[0, 1, 0], [0, 0, 1]])], dtype,
+                   [A0, ("exp",), A1, ("mul",)], [A0, ("sum",), ("mul",)])
+
+
+def tall(dtype):
+    """Few functions of many terms behind a bias: long column sums."""
+    return wl.dense_layer_expr(9000, 33, 16, dtype)
+
+
+CASES = [(f"{make.__name__}_{dt}", lambda make=make, dt=dt: make(dt))
+         for make in (weighted, both_sides, grouped, diagonal, windows, inside_and_outside, tall) for dt in ("f32", "f64")]
+CASES += [(f"dense_{I}x{J}x{K}_{dt}", lambda I=I, J=J, K=K, dt=dt: wl.dense_layer_expr(I, J, K, dt))
+          for I, J, K in [(16, 16, 8), (33, 65, 129), (64, 16, 1100), (257, 46, 70)] for dt in ("f32", "f64")]
+CASES += [(f"tanh_dot_{'xt' * xt}{'yt' * yt}_{dt}", lambda xt=xt, yt=yt, dt=dt: tanh_dot(45, 33, 67, dt, xt, yt))
+          for xt in (0, 1) for yt in (0, 1) for dt in ("f32", "f64")]
+CASES += [(f"softplus_{I}x{J}x{K}", lambda I=I, J=J, K=K: wl.softplus_ratio_expr(I, J, K, "f32"))
+          for I, J, K in [(16, 17, 8), (70, 65, 33), (300, 129, 8)]]
+
+
+def run(plan, w, ws_bytes=None, skew=0):
+    """Forward and backward through the C entry points with ws_bytes of workspace, `skew` bytes off its alignment."""
+    import torch
+    from paper_1711_01348_amd import binding as B
+    args = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in w.arg_list()]
+    df = torch.from_numpy(w.df).cuda()
+    f = torch.full_like(df, float("nan"))
+    grads = [torch.full_like(a, float("nan")) for a in args]
+    n = plan.workspace_bytes if ws_bytes is None else ws_bytes
+    ws = torch.full((n + 16,), 255, dtype=torch.uint8, device="cuda")       # NaNs: nothing is read before it is written
+    ptrs = (ctypes.c_void_p * len(args))(*[t.data_ptr() for t in args])
+    outs = (ctypes.c_void_p * len(args))(*[t.data_ptr() for t in grads])
+    wp = ws.data_ptr() + skew
+    assert B.lib.tad_eval_forward(plan._h, ptrs, f.data_ptr(), wp, n, None) == 0
+    assert B.lib.tad_eval_backward(plan._h, ptrs, f.data_ptr(), df.data_ptr(), outs, wp, n, None) == 0
+    torch.cuda.synchronize()
+    return f.cpu().numpy(), [g.cpu().numpy() for g in grads]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,make", CASES, ids=[c[0] for c in CASES])
+def test_dense_form_of_separable_sums(name, make):
+    """Against the oracle, and the term-by-term kernels (what a workspace of their size runs) give the same."""
+    from paper_1711_01348_amd import binding as B
+    expr = make()
+    w = wl.random_inputs(expr, 99)
+    plan, general = B.Plan(expr), B.Plan(expr, generic_only=True)
+    f_ref, g_ref = oracle.forward(expr, w.arg_list()), oracle.backward(expr, w.arg_list(), w.df)
+    for ws_bytes in (None, general.workspace_bytes):
+        f, grads = run(plan, w, ws_bytes)
+        assert check.within(f, f_ref, expr.dtype), (name, ws_bytes, check.errors(f, f_ref))
+        for a, g, r in zip(expr.args, grads, g_ref):
+            assert check.within(g, r, expr.dtype), (name, a.name, ws_bytes, check.errors(g, r))
+            assert np.all(g[r == 0] == 0)
+
+
+@pytest.mark.gpu
+def test_a_workspace_off_its_alignment_runs_the_term_by_term_kernels():
+    from paper_1711_01348_amd import binding as B
+    expr = wl.dense_layer_expr(48, 40, 36, "f32")
+    w = wl.random_inputs(expr, 3)
+    f, grads = run(B.Plan(expr), w, skew=4)
+    assert check.within(f, oracle.forward(expr, w.arg_list()), "f32")
+    for g, r in zip(grads, oracle.backward(expr, w.arg_list(), w.df)):
+        assert check.within(g, r, "f32")
+
+
+@pytest.mark.gpu
+def test_factors_are_not_limited_by_the_range_of_32_bits():
+    """x_ik y_kj z_ik with x z beyond the largest 32-bit number while x y, and every term, is far from it."""
+    from paper_1711_01348_amd import binding as B
+    I, J, K = 48, 40, 36
+    expr = program((I, J), [(0, K - 1)], [ArgSpec("x", (I, K), X), ArgSpec("y", (K, J), Y), ArgSpec("z", (I, K), X)], "f32",
+                   [A0, A1, ("mul",), A2, ("mul",)], [("sum",)])
+    w = wl.random_inputs(expr, 4, 0.5, 1.0)
+    for name, scale in (("x", 1e26), ("y", 1e-36), ("z", 1e14)):
+        w.inputs[name] = (w.inputs[name] * np.float32(scale)).astype(np.float32)
+    w.df *= np.float32(1e-5)     # the gradient of y, about x z df, is representable
+    f, grads = run(B.Plan(expr), w)
+    assert check.within(f, oracle.forward(expr, w.arg_list()), "f32")
+    for g, r in zip(grads, oracle.backward(expr, w.arg_list(), w.df)):
+        assert check.within(g, r, "f32")
+
+
+def test_workspace_and_family():
+    """The family is reported unchanged; the dense form asks for more workspace only where it is taken."""
+    from paper_1711_01348_amd import binding as B
+    for expr, more in [(wl.dense_layer_expr(64, 64, 64, "f32"), True), (wl.dense_layer_expr(15, 64, 64, "f32"), False),
+                       (wl.softplus_ratio_expr(64, 64, 64, "f32"), True), (wl.softplus_ratio_expr(64, 64, 64, "f64"), False),
+                       (wl.gated_gauss_expr(64, 64, 64, "f32"), False)]:
+        plan, general = B.Plan(expr), B.Plan(expr, generic_only=True)
+        assert plan.forward_family == general.forward_family == "program"
+        assert (plan.workspace_bytes > general.workspace_bytes) == more
