@@ -103,9 +103,9 @@ static bool all_derived(const tad_plan &pl) {
 }
 
 // f_ij = exp(-sum_k((a_ik + b_jk)^2 c_ii + d_{i+k}^3)), extended index (i, j, k)
-static bool match_worked(tad_plan &pl) {
+static bool worked_structure(tad_plan &pl) {
     const tad_expr &e = pl.expr;
-    if (e.body != TAD_BODY_WORKED || pl.dtype != TAD_F32 || e.n_f != 2 || e.n_sum != 1) return false;
+    if (e.body != TAD_BODY_WORKED || e.n_f != 2 || e.n_sum != 1) return false;
     if (e.sum_lo[0] != 0 || !all_derived(pl)) return false;
     const int64_t I = e.f_shape[0], J = e.f_shape[1], K = e.sum_hi[0] + 1;
     const tad_arg &a = pl.args[0], &b = pl.args[1], &c = pl.args[2], &d = pl.args[3];
@@ -113,7 +113,6 @@ static bool match_worked(tad_plan &pl) {
     if (!index_is(b, 3, {{0, 1, 0}, {0, 0, 1}}) || b.shape[0] != J || b.shape[1] != K) return false;
     if (!index_is(c, 3, {{1, 0, 0}, {1, 0, 0}})) return false;
     if (!index_is(d, 3, {{1, 0, 1}})) return false;
-    if (J % 4 != 0) return false;   // rows of f must start 16-byte aligned for the vector loads and stores
     // plan of d: one kernel coordinate must be the collapsed j, the other the clipped window moving i
     const ArgPlan &pd = pl.ap[3];
     if (pd.smith.R != 1 || pd.K.cols != 2 || pd.VR(1, 0) != 0) return false;
@@ -130,6 +129,13 @@ static bool match_worked(tad_plan &pl) {
     pl.fast.dd_level = lvl_w;
     pl.fast.dd_iy = (int)pd.VR(0, 0);
     pl.fast.dd_iz = (int)pd.K(0, lvl_w);
+    return true;
+}
+
+static bool match_worked(tad_plan &pl) {
+    if (pl.dtype != TAD_F32 || !worked_structure(pl)) return false;
+    const int64_t I = pl.fast.I, J = pl.fast.J, K = pl.fast.K;
+    if (J % 4 != 0) return false;   // rows of f must start 16-byte aligned for the vector loads and stores
     if (K <= kWorkedMaxK) {
         pl.fwd_family = TAD_FAMILY_WORKED;
         for (auto &ap : pl.ap) ap.family = TAD_FAMILY_WORKED;
@@ -348,7 +354,15 @@ void select_families(tad_plan &plan) {
     plan.prod.ws_offset = align256(plan.ws_bytes);
     plan.ws_full = plan.prod.on && plan.prod.ws_bytes ? plan.prod.ws_offset + plan.prod.ws_bytes : plan.ws_bytes;
     match_separable(plan);
-    if (plan.sep.on) plan.ws_full = std::max(plan.ws_bytes, plan.sep.ws_bytes);   // one or the other
+}
+
+// The worked expression in a form the fused 32-bit kernels do not take; the family stays the general one.
+void select_worked_wide(tad_plan &plan) {
+    if ((plan.flags & TAD_PLAN_GENERIC_ONLY) || plan.has_alias || plan.expr.n_constraints > 0) return;
+    if (plan.fwd_family != TAD_FAMILY_GENERIC || !plan.term_list.empty()) return;
+    if (!worked_structure(plan) || plan.fast.K > kWideMaxK) return;
+    plan.worked_wide = true;
+    plan.ws_full = std::max(plan.ws_bytes, worked_wide_geom(plan.fast.I, plan.fast.J, plan.fast.K).ws_bytes);
 }
 
 static void reserve_partial_sums(tad_plan &plan) {

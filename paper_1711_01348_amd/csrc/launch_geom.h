@@ -19,6 +19,29 @@ inline size_t worked_workspace_bytes(int64_t I, int64_t J, int64_t K) {
     return align256(n_jt * I * (K + 2) * 4) + align256(n_it * (K + 1) * J * 4);
 }
 
+// The worked expression with 64-bit sums (kernels_worked_wide.hip).
+constexpr int kWideMaxK = 16, kWideMaxRows = 128;
+// columns of a lane: as many as their sums and factors fit in registers
+constexpr int wide_lane_columns(int K) { return K <= 7 ? 4 : 2; }
+struct WideGeom {
+    int tile_rows;       // rows of a tile, a multiple of 8
+    int n_jt, n_it;      // tiles along the columns and the rows
+    size_t col_offset, ws_bytes;   // row sums [n_jt][K + 2][I], then column sums [n_it][K][J]
+};
+inline WideGeom worked_wide_geom(int64_t I, int64_t J, int64_t K) {
+    WideGeom g;
+    const int64_t tj = 64 * wide_lane_columns((int)K);
+    g.n_jt = (int)((J + tj - 1) / tj);
+    // about two workgroups per compute unit; fewer rows per tile mean more column sums in memory
+    int64_t rows = (I * g.n_jt + 511) / 512;
+    rows = (rows + 7) / 8 * 8;
+    g.tile_rows = (int)(rows > kWideMaxRows ? kWideMaxRows : rows);
+    g.n_it = (int)((I + g.tile_rows - 1) / g.tile_rows);
+    g.col_offset = align256((size_t)g.n_jt * (size_t)I * (size_t)(K + 2) * 8);
+    g.ws_bytes = g.col_offset + align256((size_t)g.n_it * (size_t)K * (size_t)J * 8);
+    return g;
+}
+
 // long summed index (MFMA family): number of chunks the collapsed contraction index is split in (4 leaves the
 // chip under-filled: 133 / 117 us per contraction instead of 98 / 94)
 constexpr int kMfmaSplit = 8;

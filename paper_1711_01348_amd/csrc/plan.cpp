@@ -520,6 +520,7 @@ int derive_plan(const tad_expr *expr, const tad_arg *args, int n_args, tad_dtype
     }
     select_families(*pl);
     list_terms(*pl);
+    select_worked_wide(*pl);
     guard.p = nullptr;
     *out = pl;
     return TAD_OK;

@@ -1,0 +1,77 @@
+"""The worked expression with rows of any length, in either precision, on the kernels with 64-bit sums."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1711_01348_amd import check
+from paper_1711_01348_amd import workloads as wl
+from test_separable import run
+
+# one row, one column, tiles of 256 and 128 columns and their neighbours, tiles of rows with and without a last odd row, the
+# widest sum of each column count, the largest of all
+SIZES = [(3, 1, 8), (1, 403, 3), (2, 255, 16), (9, 257, 7), (17, 127, 8), (33, 129, 9), (130, 65, 1), (1031, 1025, 5),
+         (301, 2047, 7), (259, 514, 16), (1100, 70, 12)]
+
+
+def workload(I, J, K, dtype, seed=6):
+    w = wl.random_inputs(wl.worked_expr(I, J, K, dtype, d_len=I + K + 2), seed)
+    w.inputs["c"] = (np.abs(w.inputs["c"]) / K).astype(w.inputs["c"].dtype)
+    return w
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("I,J,K", SIZES)
+def test_rows_of_any_length(I, J, K, dtype):
+    """Against the oracle; a workspace of the general kernels' size runs those and gives the same."""
+    from paper_1711_01348_amd import binding as B
+    w = workload(I, J, K, dtype)
+    plan, general = B.Plan(w.expr), B.Plan(w.expr, generic_only=True)
+    f_ref, g_ref = oracle.forward(w.expr, w.arg_list()), oracle.backward(w.expr, w.arg_list(), w.df)
+    for ws_bytes in {plan.workspace_bytes, general.workspace_bytes}:
+        f, grads = run(plan, w, ws_bytes)
+        assert check.within(f, f_ref, dtype), (ws_bytes, check.errors(f, f_ref))
+        for a, g, r in zip(w.expr.args, grads, g_ref):
+            assert check.within(g, r, dtype), (a.name, ws_bytes, check.errors(g, r))
+            assert np.all(g[r == 0] == 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_infinities_in_a_row_beside_columns_beyond_the_edge(dtype):
+    """An infinite a_ik with c_ii < 0 makes f infinite: the sums stay what the general kernels give, and columns that only
+    fill up a tile add nothing to them."""
+    from paper_1711_01348_amd import binding as B
+    w = workload(21, 301, 4, dtype)
+    w.inputs["a"][5, 2] = np.inf
+    w.inputs["c"][5, 5] = -0.25
+    w.df[5] = np.abs(w.df[5])
+    plan = B.Plan(w.expr)
+    f, grads = run(plan, w)
+    f_gen, g_gen = run(plan, w, B.Plan(w.expr, generic_only=True).workspace_bytes)
+    for x, y in zip([f] + grads, [f_gen] + g_gen):
+        assert np.array_equal(np.isnan(x), np.isnan(y)) and np.array_equal(np.isinf(x), np.isinf(y))
+        ok = np.isfinite(y)
+        assert check.within(np.where(ok, x, 0), np.where(ok, y, 0), dtype)
+
+
+@pytest.mark.gpu
+def test_gradients_that_are_not_wanted_are_left_alone():
+    import torch
+    from paper_1711_01348_amd import binding as B
+    w = workload(65, 131, 3, "f32")
+    plan = B.Plan(w.expr)
+    args = [torch.from_numpy(a).cuda() for a in w.arg_list()]
+    f, df = plan.forward(args), torch.from_numpy(w.df).cuda()
+    every = plan.backward(args, f, df)
+    for p in range(4):
+        out = plan.backward(args, f, df, out=[torch.empty_like(a) if q == p else None for q, a in enumerate(args)],
+                            wanted=[q == p for q in range(4)])
+        assert torch.equal(out[p], every[p])
+
+
+def test_family_is_that_of_the_general_kernels():
+    from paper_1711_01348_amd import binding as B
+    for I, J, K, dtype in [(40, 41, 5, "f32"), (40, 40, 5, "f64"), (40, 41, 17, "f32")]:
+        assert B.Plan(wl.worked_expr(I, J, K, dtype)).forward_family == "generic"
+    assert B.Plan(wl.worked_expr(40, 40, 5, "f32")).forward_family == "worked"
