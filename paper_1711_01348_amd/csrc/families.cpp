@@ -354,6 +354,7 @@ void select_families(tad_plan &plan) {
     plan.prod.ws_offset = align256(plan.ws_bytes);
     plan.ws_full = plan.prod.on && plan.prod.ws_bytes ? plan.prod.ws_offset + plan.prod.ws_bytes : plan.ws_bytes;
     match_separable(plan);
+    if (plan.sep.on) plan.ws_full = std::max(plan.ws_bytes, plan.sep.ws_bytes);   // one or the other
 }
 
 // The worked expression in a form the fused 32-bit kernels do not take; the family stays the general one.

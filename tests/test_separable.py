@@ -92,13 +92,15 @@ def run(plan, w, ws_bytes=None, skew=0):
     f = torch.full_like(df, float("nan"))
     grads = [torch.full_like(a, float("nan")) for a in args]
     n = plan.workspace_bytes if ws_bytes is None else ws_bytes
-    ws = torch.full((n + 16,), 255, dtype=torch.uint8, device="cuda")       # NaNs: nothing is read before it is written
+    behind = 1 << 20
+    ws = torch.full((n + 16 + behind,), 255, dtype=torch.uint8, device="cuda")   # NaNs: nothing is read before it is written
     ptrs = (ctypes.c_void_p * len(args))(*[t.data_ptr() for t in args])
     outs = (ctypes.c_void_p * len(args))(*[t.data_ptr() for t in grads])
     wp = ws.data_ptr() + skew
     assert B.lib.tad_eval_forward(plan._h, ptrs, f.data_ptr(), wp, n, None) == 0
     assert B.lib.tad_eval_backward(plan._h, ptrs, f.data_ptr(), df.data_ptr(), outs, wp, n, None) == 0
     torch.cuda.synchronize()
+    assert bool((ws[n + skew:] == 255).all()), "written beyond the workspace"
     return f.cpu().numpy(), [g.cpu().numpy() for g in grads]
 
 
