@@ -124,6 +124,25 @@ def _load():
 lib = _load()
 
 
+_torch = None
+_current_stream = None
+
+
+def _import_torch():
+    """torch (imported on the first call that needs it: planning works without) and the function that returns the handle of
+    the current device's current stream.  The latter asks torch's extension module, where this build has the function: a
+    Stream object per call costs as much as launching a kernel."""
+    global _torch, _current_stream
+    import torch
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is not None and device is not None:
+        _current_stream = lambda: raw(device())
+    else:
+        _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+    _torch = torch
+    return torch
+
+
 def strerror(status: int) -> str:
     return lib.tad_strerror(int(status)).decode()
 
@@ -201,6 +220,11 @@ class Plan:
             (PLAN_KEEP_PROGRAM if keep_program else 0) | (0 if term_lists else PLAN_NO_TERM_LISTS)
         _check(lib.tad_plan_derive(ctypes.byref(e), a, len(expr.args), self.dtype, flags,
                                    ctypes.byref(self._h)), "tad_plan_derive")
+        # what every call compares its tensors with, and the type of its pointer arrays
+        self._f_shape = tuple(int(n) for n in expr.f_shape)
+        self._operands = [(None if getattr(q, "same_as", None) is not None else tuple(int(n) for n in q.shape), q.name)
+                          for q in expr.args]
+        self._pointers = ctypes.c_void_p * len(expr.args)
 
     def __del__(self):
         h, self._h = getattr(self, "_h", None), None
@@ -328,28 +352,23 @@ class Plan:
 
     # ---- device evaluation (torch tensors supply memory and stream) -----------------------------
     def _torch_dtype(self):
-        import torch
+        torch = _torch or _import_torch()
         return torch.float64 if self.dtype == F64 else torch.float32
 
-    def _check_tensor(self, t, shape, what):
-        if t.device.type != "cuda" or not t.is_contiguous() or t.dtype != self._torch_dtype() \
-                or tuple(t.shape) != tuple(shape):
-            raise ValueError(f"{what}: need a contiguous {self._torch_dtype()} cuda tensor of shape {tuple(shape)}, "
+    def _pointer(self, t, shape, dtype, what):
+        """Address of a tensor the kernels can work on: dense, of the plan's type, on a GPU, of this shape."""
+        if t.shape != shape or t.dtype is not dtype or not t.is_cuda or not t.is_contiguous():
+            raise ValueError(f"{what}: need a contiguous {dtype} cuda tensor of shape {shape}, "
                              f"got {t.dtype} {tuple(t.shape)} on {t.device}")
+        return t.data_ptr()
 
     def _is_alias(self, p: int) -> bool:
-        return getattr(self.expr.args[p], "same_as", None) is not None
+        return self._operands[p][0] is None
 
-    def _arg_ptrs(self, args):
+    def _arg_ptrs(self, args, dtype):
         """One entry per operand; the entry of an alias operand is not used (it may be None)."""
-        ptrs = []
-        for p, (t, a) in enumerate(zip(args, self.expr.args)):
-            if self._is_alias(p):
-                ptrs.append(None)
-                continue
-            self._check_tensor(t, a.shape, a.name)
-            ptrs.append(t.data_ptr())
-        return (ctypes.c_void_p * len(args))(*ptrs)
+        ptrs = [None if shape is None else self._pointer(t, shape, dtype, name) for t, (shape, name) in zip(args, self._operands)]
+        return (self._pointers if len(args) == len(self._operands) else ctypes.c_void_p * len(args))(*ptrs)
 
     def workspace(self, device="cuda"):
         import torch
@@ -357,39 +376,42 @@ class Plan:
         return torch.empty(max(n, 1), dtype=torch.uint8, device=device)
 
     def forward(self, args, out=None, ws=None):
-        import torch
-        ptrs = self._arg_ptrs(args)
+        torch = _torch or _import_torch()
+        dtype = torch.float64 if self.dtype == F64 else torch.float32
+        ptrs = self._arg_ptrs(args, dtype)
         if out is None:
-            out = torch.empty(tuple(self.expr.f_shape), dtype=self._torch_dtype(), device=args[0].device)
-        self._check_tensor(out, self.expr.f_shape, "f")
+            out = torch.empty(self._f_shape, dtype=dtype, device=args[0].device)
+        f_ptr = self._pointer(out, self._f_shape, dtype, "f")
         ws = self.workspace(args[0].device) if ws is None else ws
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.tad_eval_forward(self._h, ptrs, out.data_ptr(), ws.data_ptr(), ws.numel(),
-                                    ctypes.c_void_p(stream)), "tad_eval_forward")
+        rc = lib.tad_eval_forward(self._h, ptrs, f_ptr, ws.data_ptr(), ws.numel(), _current_stream())
+        if rc:
+            raise TadError(rc, "tad_eval_forward")
         return out
 
     def backward(self, args, f, df, wanted: Optional[Sequence[bool]] = None, out=None, ws=None, static=False):
         """static=True: tad_eval_backward_static (the library's own fixed scratch array instead of a workspace)."""
-        import torch
-        ptrs = self._arg_ptrs(args)
-        self._check_tensor(f, self.expr.f_shape, "f")
-        self._check_tensor(df, self.expr.f_shape, "df")
-        wanted = [True] * len(args) if wanted is None else list(wanted)
-        wanted = [w and not self._is_alias(p) for p, w in enumerate(wanted)]   # an alias has no gradient of its own
+        torch = _torch or _import_torch()
+        dtype = torch.float64 if self.dtype == F64 else torch.float32
+        ptrs = self._arg_ptrs(args, dtype)
+        f_ptr = self._pointer(f, self._f_shape, dtype, "f")
+        df_ptr = self._pointer(df, self._f_shape, dtype, "df")
         if out is None:
+            wanted = [True] * len(args) if wanted is None else list(wanted)
+            wanted = [w and not self._is_alias(p) for p, w in enumerate(wanted)]   # an alias has no gradient of its own
             out = [torch.empty_like(t) if w else None for t, w in zip(args, wanted)]
-        for t, a in zip(out, self.expr.args):
-            if t is not None:
-                self._check_tensor(t, a.shape, "d" + a.name)
-        dptr = (ctypes.c_void_p * len(args))(*[None if t is None else t.data_ptr() for t in out])
-        stream = torch.cuda.current_stream().cuda_stream
+        dptrs = [None if t is None else self._pointer(t, shape or tuple(self.expr.args[p].shape), dtype, "d" + name)
+                 for p, (t, (shape, name)) in enumerate(zip(out, self._operands))]
+        if len(out) == len(self._operands) == len(args):
+            dptr = self._pointers(*dptrs)
+        else:
+            dptr = (ctypes.c_void_p * len(args))(*[None if t is None else t.data_ptr() for t in out])
         if static:
-            _check(lib.tad_eval_backward_static(self._h, ptrs, f.data_ptr(), df.data_ptr(), dptr,
-                                                ctypes.c_void_p(stream)), "tad_eval_backward_static")
+            _check(lib.tad_eval_backward_static(self._h, ptrs, f_ptr, df_ptr, dptr, _current_stream()), "tad_eval_backward_static")
             return out
         ws = self.workspace(args[0].device) if ws is None else ws
-        _check(lib.tad_eval_backward(self._h, ptrs, f.data_ptr(), df.data_ptr(), dptr, ws.data_ptr(),
-                                     ws.numel(), ctypes.c_void_p(stream)), "tad_eval_backward")
+        rc = lib.tad_eval_backward(self._h, ptrs, f_ptr, df_ptr, dptr, ws.data_ptr(), ws.numel(), _current_stream())
+        if rc:
+            raise TadError(rc, "tad_eval_backward")
         return out
 
 
@@ -416,18 +438,19 @@ class DerivedGradient:
         return int(lib.tad_derived_workspace_bytes(self._h))
 
     def evaluate(self, args, df, out=None, ws=None):
-        import torch
+        torch = _torch or _import_torch()
         plan = self.plan
-        ptrs = plan._arg_ptrs(args)
-        plan._check_tensor(df, plan.expr.f_shape, "df")
+        dtype = plan._torch_dtype()
+        ptrs = plan._arg_ptrs(args, dtype)
+        df_ptr = plan._pointer(df, plan._f_shape, dtype, "df")
         if out is None:
             out = torch.empty_like(args[self.arg])
-        plan._check_tensor(out, plan.expr.args[self.arg].shape, "d" + plan.expr.args[self.arg].name)
+        shape, name = plan._operands[self.arg]
+        out_ptr = plan._pointer(out, shape, dtype, "d" + name)
         if ws is None:
             ws = torch.empty(max(self.workspace_bytes, 1), dtype=torch.uint8, device=df.device)
-        stream = torch.cuda.current_stream().cuda_stream
-        _check(lib.tad_eval_derived(self._h, ptrs, df.data_ptr(), out.data_ptr(), ws.data_ptr(), ws.numel(),
-                                    ctypes.c_void_p(stream)), "tad_eval_derived")
+        _check(lib.tad_eval_derived(self._h, ptrs, df_ptr, out_ptr, ws.data_ptr(), ws.numel(), _current_stream()),
+               "tad_eval_derived")
         return out
 
 
