@@ -357,10 +357,15 @@ void select_families(tad_plan &plan) {
     if (plan.sep.on) plan.ws_full = std::max(plan.ws_bytes, plan.sep.ws_bytes);   // one or the other
 }
 
-// The worked expression in a form the fused 32-bit kernels do not take; the family stays the general one.
+// The worked expression on the kernels with 64-bit sums; the reported family stays what it is without them.  They take the
+// forms the fused 32-bit kernels have no code for, and those of fewer than 2^23 elements: the tiles of the 32-bit kernels
+// (256 x 512) are made for a full chip.  Forward and gradients, 32-bit sums against 64-bit sums with one more column: 64 x 64 x 5
+// 45 / 20 us, 1024 x 1024 x 5 44 / 24, 2048 x 2048 x 1 40 / 25, x 8 61 / 42, 4096 x 2048 x 5 58 / 57, 4096 x 4096 x 5 66 / 95 us.
+constexpr int64_t kWideElements = (int64_t)1 << 23;
+
 void select_worked_wide(tad_plan &plan) {
-    if ((plan.flags & TAD_PLAN_GENERIC_ONLY) || plan.has_alias || plan.expr.n_constraints > 0) return;
-    if (plan.fwd_family != TAD_FAMILY_GENERIC || !plan.term_list.empty()) return;
+    if ((plan.flags & TAD_PLAN_GENERIC_ONLY) || plan.has_alias || plan.expr.n_constraints > 0 || !plan.term_list.empty()) return;
+    if (plan.fwd_family != TAD_FAMILY_GENERIC && (plan.fwd_family != TAD_FAMILY_WORKED || plan.f_count >= kWideElements)) return;
     if (!worked_structure(plan) || plan.fast.K > kWideMaxK) return;
     plan.worked_wide = true;
     plan.ws_full = std::max(plan.ws_bytes, worked_wide_geom(plan.fast.I, plan.fast.J, plan.fast.K).ws_bytes);

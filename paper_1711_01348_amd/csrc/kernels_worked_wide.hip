@@ -1,6 +1,7 @@
-// The worked expression of the paper (kernels_worked.hip) for the forms the fused 32-bit kernels do not take: 64-bit
-// tensors, rows of f that start anywhere (J not a multiple of four), K up to 16.  The plan-driven kernels, which evaluate
-// these otherwise, accumulate in 64 bits, so these do; sums are of the terms as they stand, not expanded,
+// The worked expression of the paper (kernels_worked.hip) with 64-bit sums: for the forms the fused 32-bit kernels do not take
+// (64-bit tensors, rows of f that start anywhere, K up to 16) and for tensors that do not fill the chip with the large tiles of
+// those.  The plan-driven kernels, which evaluate the former otherwise, accumulate in 64 bits, so these do; sums are of the terms
+// as they stand, not expanded,
 //
 //     t_ijk = a_ik + b_jk,  q_ij = sum_k t_ijk^2,  g_ij = df_ij f_ij:       f_ij = exp(-(c_ii q_ij + sum_k d_{i+k}^3))
 //     da_ik = -2 c_ii sum_j g_ij t_ijk     db_jk = -2 sum_i c_ii g_ij t_ijk     dc_ii = -sum_j g_ij q_ij

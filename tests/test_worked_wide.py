@@ -70,6 +70,27 @@ def test_gradients_that_are_not_wanted_are_left_alone():
         assert torch.equal(out[p], every[p])
 
 
+def align(n):
+    return (n + 255) // 256 * 256
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("I,J,K", [(64, 64, 5), (300, 1028, 5), (513, 516, 8), (5, 2052, 1)])
+def test_fused_32_bit_kernels_run_in_a_workspace_of_their_size(I, J, K):
+    """Sizes that the 64-bit sums take over otherwise."""
+    from paper_1711_01348_amd import binding as B
+    w = workload(I, J, K, "f32")
+    plan = B.Plan(w.expr)
+    fused = align(-(-J // 512) * I * (K + 2) * 4) + align(-(-I // 256) * (K + 1) * J * 4)
+    f_ref, g_ref = oracle.forward(w.expr, w.arg_list()), oracle.backward(w.expr, w.arg_list(), w.df)
+    assert plan.forward_family == "worked" and fused < plan.workspace_bytes
+    for ws_bytes in (fused, plan.workspace_bytes):
+        f, grads = run(plan, w, ws_bytes)
+        assert check.within(f, f_ref, "f32"), (ws_bytes, check.errors(f, f_ref))
+        for g, r in zip(grads, g_ref):
+            assert check.within(g, r, "f32"), (ws_bytes, check.errors(g, r))
+
+
 def test_family_is_that_of_the_general_kernels():
     from paper_1711_01348_amd import binding as B
     for I, J, K, dtype in [(40, 41, 5, "f32"), (40, 40, 5, "f64"), (40, 41, 17, "f32")]:
