@@ -10,9 +10,10 @@
 // results are not stored), so that the loads are unconditional, from a uniform base plus a constant 32-bit offset per thread,
 // and only the last stage looks at the end of the sum, where it stages zeros.
 // A 16 x 16 x 4 instruction occupies its matrix core for 64 cycles: the matrix cores bound these kernels (78.6 TFLOP/s), two
-// operand fragments per instruction are cheap, and what counts is enough wavefronts to cover the barriers.  Hence one set of
-// tiles in LDS and three workgroups per compute unit rather than two sets and two workgroups (2001 x 2002 x 2003, 32-bit
-// operands: 311 us against 333 us; two workgroups with 64-bit operands, which need the registers), and small tiles:
+// operand fragments per instruction are cheap, and what counts is that the barriers are covered: two sets of tiles in LDS, so
+// that a stage takes one barrier and the stores of the next one go on under its matrix instructions (1000 x 1203 x 777 in 64 bits,
+// forward and gradients: 193 -> 176 us, 32 TFLOP/s; the results of 32 x 32 tiles leave a third of the last round of workgroups
+// idle, and 64 x 64 tiles with 64-bit operands spill: 237 us), and small tiles:
 //   edge 64  a wavefront owns 32 x 32 results; 32 values of q per stage
 //   edge 32  every wavefront computes the whole tile over a quarter of each stage's 64 values of q, and the four sums are added
 //            in a fixed order at the end: four times as many workgroups for small results (512 x 1024 x 768: 21 us against
@@ -25,29 +26,38 @@
 // lane l = D[4 i + l / 16][l % 16].
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+#include <utility>
+
 #include "launch.h"
 #include "product.hpp"
+#include "product_outer.h"
 #include "profile.h"
 
 namespace tad {
 
 typedef double double4p __attribute__((ext_vector_type(4)));
 
-struct ProductArgs {
+struct ProductTask {
     const void *a, *b;
     void *c;           // the result, or (pieces > 1) the partial sums [piece][r][c] in 64 bits
     int R, C, Q;
     int ar, aq, bq, bc;
     int gr, gc;        // tiles along r and c
-    int chunk;         // values of q per piece
+    int pieces, chunk; // pieces of q, values of q per piece
     int wide;          // store 64-bit results
+    int turned;        // store the result [c][r]
 };
-
+// One or two products (the derivatives of the two factors of a sum) in one launch: workgroup b works on the first one for
+// b < first, else on the second one.
+struct ProductArgs {
+    ProductTask task[2];
+    int first;
+};
 // Neighbouring workgroups go to different dies: each die gets a contiguous range of tiles, walked in groups of eight
 // tile rows, so that workgroups that run together share operand tiles in their L2.
-__device__ __forceinline__ void product_tile(int gr, int gc, int &tr, int &tc) {
+__device__ __forceinline__ void product_tile(int lid, int gr, int gc, int &tr, int &tc) {
     const int total = gr * gc;
-    int lid = blockIdx.x;
     const int per = total >> 3;
     if (lid < (per << 3)) lid = (lid & 7) * per + (lid >> 3);
     const int group = 8 * gc;
@@ -58,8 +68,8 @@ __device__ __forceinline__ void product_tile(int gr, int gc, int &tr, int &tc) {
     tc = in / rows;
 }
 
-template <typename TA, typename TB, int EDGE>
-__global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) void k_product(const ProductArgs P) {
+template <typename TA, typename TB, int EDGE, typename TO>
+__device__ __forceinline__ void product_kernel(const ProductArgs &M, const ProductOuter *O) {
     constexpr bool SHARE = EDGE == 32;              // the wavefronts share the tile's sum; else each owns a quarter of the tile
     constexpr int KT = SHARE ? 64 : 32;             // values of q per stage
     constexpr int KW = SHARE ? 16 : 32;             // ... of one wavefront
@@ -67,17 +77,19 @@ __global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) vo
     constexpr int WT = 2;                           // 16 x 16 results of a wavefront, per direction
     constexpr int PER = EDGE * KT / 256;            // elements of each operand a thread stages
     constexpr bool BLOCKED = sizeof(TA) == 8 && sizeof(TB) == 8;   // sums of 16 products added to a total
-    constexpr int TILES = EDGE * LDK * (int)(sizeof(TA) + sizeof(TB)), SUMS = SHARE ? 4 * EDGE * EDGE * 8 : 0;
+    constexpr int TILES = 2 * EDGE * LDK * (int)(sizeof(TA) + sizeof(TB)), SUMS = SHARE ? 4 * EDGE * EDGE * 8 : 0;
     __shared__ __attribute__((aligned(16))) char lds[TILES > SUMS ? TILES : SUMS];
     // the wider operand first: both regions then start on a multiple of their element
     constexpr bool A_FIRST = sizeof(TA) >= sizeof(TB);
-    TA *const As = reinterpret_cast<TA *>(lds + (A_FIRST ? 0 : EDGE * LDK * (int)sizeof(TB)));
-    TB *const Bs = reinterpret_cast<TB *>(lds + (A_FIRST ? EDGE * LDK * (int)sizeof(TA) : 0));
+    TA *const As = reinterpret_cast<TA *>(lds + (A_FIRST ? 0 : 2 * EDGE * LDK * (int)sizeof(TB)));
+    TB *const Bs = reinterpret_cast<TB *>(lds + (A_FIRST ? 2 * EDGE * LDK * (int)sizeof(TA) : 0));
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const ProductTask &P = M.task[(int)blockIdx.x < M.first ? 0 : 1];   // the same for the whole workgroup
+    const int id = (int)blockIdx.x - ((int)blockIdx.x < M.first ? 0 : M.first), tiles = P.gr * P.gc, piece = id / tiles;
     int tr, tc;
-    product_tile(P.gr, P.gc, tr, tc);
+    product_tile(id - piece * tiles, P.gr, P.gc, tr, tc);
     const int r0 = tr * EDGE, c0 = tc * EDGE;
-    const int q_begin = blockIdx.y * P.chunk, q_end = min(P.Q, q_begin + P.chunk);
+    const int q_begin = piece * P.chunk, q_end = min(P.Q, q_begin + P.chunk);
     // staging: neighbouring threads along q or along the rows, whichever is contiguous in memory
     const bool a_q = P.aq <= P.ar, b_q = P.bq <= P.bc;   // uniform
     const int a_row = a_q ? tid / KT : tid % EDGE, a_k = a_q ? tid % KT : tid / EDGE;
@@ -118,11 +130,11 @@ __global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) vo
         pb += (size_t)KT * P.bq * sizeof(TB);
     };
     const int as = a_row * LDK + a_k, as_inc = a_dr * LDK + a_dk, bs = b_row * LDK + b_k, bs_inc = b_dr * LDK + b_dk;
-    auto stage = [&]() {
+    auto stage = [&](int set) {
 #pragma unroll
-        for (int p = 0; p < PER; ++p) As[as + p * as_inc] = va[p];
+        for (int p = 0; p < PER; ++p) As[set * EDGE * LDK + as + p * as_inc] = va[p];
 #pragma unroll
-        for (int p = 0; p < PER; ++p) Bs[bs + p * bs_inc] = vb[p];
+        for (int p = 0; p < PER; ++p) Bs[set * EDGE * LDK + bs + p * bs_inc] = vb[p];
     };
     const double4p zero = {0., 0., 0., 0.};
     double4p acc[WT][WT], even[WT][WT], odd[WT][WT];   // even, odd: totals of every other stage (64-bit operands)
@@ -134,18 +146,22 @@ __global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) vo
     const int fk = (SHARE ? wave * KW : 0) + (lane >> 4);
     const int fa = (wr + (lane & 15)) * LDK + fk, fb = (wc + (lane & 15)) * LDK + fk;
     load(q_begin);
-    stage();
+    stage(0);
+    if (q_begin + KT < q_end) load(q_begin + KT);
     __syncthreads();
-    auto step = [&](int q0, double4p (&total)[WT][WT]) {
-        const bool more = q0 + KT < q_end;   // the same for the whole workgroup
-        if (more) load(q0 + KT);
+    // one stage: what the registers hold of the next one goes into the other set of tiles, the loads of the one behind it are
+    // issued, and the matrix instructions cover both
+    auto step = [&](int q0, int set, double4p (&total)[WT][WT]) {
+        if (q0 + KT < q_end) stage(set ^ 1);   // the same for the whole workgroup
+        if (q0 + 2 * KT < q_end) load(q0 + 2 * KT);
+        const int ab = set * EDGE * LDK + fa, bb = set * EDGE * LDK + fb;
 #pragma unroll
         for (int ks = 0; ks < KW / 4; ++ks) {
             double a[WT], b[WT];
 #pragma unroll
             for (int x = 0; x < WT; ++x) {
-                a[x] = (double)As[fa + x * 16 * LDK + ks * 4];
-                b[x] = (double)Bs[fb + x * 16 * LDK + ks * 4];
+                a[x] = (double)As[ab + x * 16 * LDK + ks * 4];
+                b[x] = (double)Bs[bb + x * 16 * LDK + ks * 4];
             }
 #pragma unroll
             for (int x = 0; x < WT; ++x)
@@ -160,14 +176,10 @@ __global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) vo
             }
         }
         __syncthreads();
-        if (more) {
-            stage();
-            __syncthreads();
-        }
     };
     for (int q0 = q_begin; q0 < q_end; q0 += 2 * KT) {
-        step(q0, even);
-        if (q0 + KT < q_end) step(q0 + KT, odd);
+        step(q0, 0, even);
+        if (q0 + KT < q_end) step(q0 + KT, 1, odd);
     }
     if constexpr (BLOCKED) {
 #pragma unroll
@@ -175,10 +187,10 @@ __global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) vo
 #pragma unroll
             for (int y = 0; y < WT; ++y) acc[x][y] = even[x][y] + odd[x][y];
     }
-    char *out = static_cast<char *>(P.c) + (size_t)blockIdx.y * (gridDim.y > 1 ? (size_t)P.R * P.C * sizeof(double) : 0);
+    char *out = static_cast<char *>(P.c) + (size_t)piece * P.R * P.C * sizeof(double);   // (one piece: 0)
     auto store = [&](int r, int c, double v) {
         if (r >= P.R || c >= P.C) return;
-        const size_t at = (size_t)r * P.C + c;
+        const size_t at = P.turned ? (size_t)c * P.R + r : (size_t)r * P.C + c;
         if (P.wide) reinterpret_cast<double *>(out)[at] = v;
         else reinterpret_cast<float *>(out)[at] = (float)v;
     };
@@ -201,13 +213,58 @@ __global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) vo
                 for (int i = 0; i < 4; ++i)
                     sums[wave * EDGE * EDGE + (x * 16 + 4 * i + (lane >> 4)) * EDGE + y * 16 + (lane & 15)] = acc[x][y][i];
         __syncthreads();
+        // neighbouring threads along the direction that is contiguous in the result
+        auto place = [&](int p, int &r, int &c) {
+            const int n = tid + 256 * p, at = P.turned ? (n % EDGE) * EDGE + n / EDGE : n;
+            r = r0 + at / EDGE;
+            c = c0 + at % EDGE;
+            return (sums[at] + sums[EDGE * EDGE + at]) + (sums[2 * EDGE * EDGE + at] + sums[3 * EDGE * EDGE + at]);
+        };
+        if constexpr (std::is_same<TO, void>::value) {
 #pragma unroll
-        for (int p = 0; p < EDGE * EDGE / 256; ++p) {
-            const int at = tid + 256 * p;
-            const double v = (sums[at] + sums[EDGE * EDGE + at]) + (sums[2 * EDGE * EDGE + at] + sums[3 * EDGE * EDGE + at]);
-            store(r0 + at / EDGE, c0 + at % EDGE, v);
+            for (int p = 0; p < EDGE * EDGE / 256; ++p) {
+                int r, c;
+                const double v = place(p, r, c);
+                store(r, c, v);
+            }
+        } else {
+            // U results per pass of the interpreter: an operation costs more to fetch than to carry out
+            constexpr int U = ProgWidth<TO>::U;
+#pragma unroll 1
+            for (int p0 = 0; p0 < EDGE * EDGE / 256; p0 += U) {
+                TO s[U], w[kMaxArgs][U], o[U];
+                int at[U];
+                bool inside[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    int r, c;
+                    s[u] = (TO)place(p0 + u, r, c);
+                    inside[u] = r < P.R && c < P.C;
+                    at[u] = inside[u] ? r * P.C + c : 0;
+#pragma unroll
+                    for (int q = 0; q < kMaxArgs; ++q)
+                        w[q][u] = O->args.p[q] ? static_cast<const TO *>(O->args.p[q])[inside[u] ? O->off_r[q] * r + O->off_c[q] * c : 0] : TO(0);
+                }
+                prog_eval_block<TO, U, true>(O->prog, w, s, o);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (!inside[u]) continue;
+                    reinterpret_cast<TO *>(out)[at[u]] = O->df ? static_cast<const TO *>(O->df)[at[u]] * o[u] : o[u];
+                    if (O->s_out) static_cast<TO *>(O->s_out)[at[u]] = s[u];
+                }
+            }
         }
     }
+}
+
+template <typename TA, typename TB, int EDGE>
+__global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) void k_product(const ProductArgs M) {
+    product_kernel<TA, TB, EDGE, void>(M, nullptr);
+}
+// sums of type TO that go through a program first
+template <typename TA, typename TB, typename TO>
+__global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) void k_product_outer(const ProductArgs M, const ProductOuter O) {
+    product_kernel<TA, TB, 32, TO>(M, &O);
 }
 
 // c[i] = the pieces' partial sums of element i, added in ascending order
@@ -220,64 +277,116 @@ __global__ __launch_bounds__(256) void k_product_reduce(const double *__restrict
     c[i] = (T)s;
 }
 
-template <typename TA, typename TB>
-static int launch_product(const ProductDesc &d, const void *a, const void *b, void *c, bool wide, void *ws, hipStream_t s) {
-    ProductArgs P;
-    P.a = a; P.b = b;
-    P.c = d.pieces > 1 ? ws : c;
+static ProductTask product_task(const ProductJob &j, void *ws) {
+    const ProductDesc &d = *j.desc;
+    ProductTask P;
+    P.a = j.a; P.b = j.b;
+    P.c = d.pieces > 1 ? ws : j.c;
     P.R = d.R; P.C = d.C; P.Q = d.Q;
     P.ar = (int)d.ar; P.aq = (int)d.aq; P.bq = (int)d.bq; P.bc = (int)d.bc;
     P.gr = (d.R + d.tile - 1) / d.tile; P.gc = (d.C + d.tile - 1) / d.tile;
+    P.pieces = d.pieces;
     P.chunk = d.pieces > 1 ? d.chunk : d.Q;
-    P.wide = wide || d.pieces > 1;
-    const dim3 grid((unsigned)(P.gr * P.gc), (unsigned)d.pieces), block(256);
-    if constexpr (sizeof(TA) == 4 || sizeof(TB) == 4) {
-        if (d.tile == 64) {
-            TAD_LAUNCH("k_product", (k_product<TA, TB, 64>), grid, block, 0, s, P);
-            return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;   // pieces only with the small tile
+    P.wide = j.c64 || d.pieces > 1;
+    P.turned = j.turned;
+    return P;
+}
+
+template <typename TA, typename TB>
+static int launch_product(const ProductArgs &M, int tile, unsigned blocks, const ProductOuter *outer, bool c64, hipStream_t s) {
+    const dim3 grid(blocks), block(256);
+    if (outer) {
+        if (c64) TAD_LAUNCH("k_product_outer", (k_product_outer<TA, TB, double>), grid, block, 0, s, M, *outer);
+        else TAD_LAUNCH("k_product_outer", (k_product_outer<TA, TB, float>), grid, block, 0, s, M, *outer);
+    } else {
+        if constexpr (sizeof(TA) == 4 || sizeof(TB) == 4) {
+            if (tile == 64) {
+                TAD_LAUNCH("k_product", (k_product<TA, TB, 64>), grid, block, 0, s, M);
+                return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
+            }
         }
+        TAD_LAUNCH("k_product", (k_product<TA, TB, 32>), grid, block, 0, s, M);
     }
-    TAD_LAUNCH("k_product", (k_product<TA, TB, 32>), grid, block, 0, s, P);
-    if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    if (d.pieces > 1) {
-        const long long n = (long long)d.R * d.C;
-        const dim3 rgrid((unsigned)((n + 255) / 256));
-        if (wide) TAD_LAUNCH("k_product_reduce", (k_product_reduce<double>), rgrid, block, 0, s, (const double *)ws, (double *)c, n, d.pieces);
-        else TAD_LAUNCH("k_product_reduce", (k_product_reduce<float>), rgrid, block, 0, s, (const double *)ws, (float *)c, n, d.pieces);
-        if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    }
-    return TAD_OK;
+    return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
-int product_run(const ProductDesc &d, const void *a, bool a64, const void *b, bool b64, void *c, bool c64, void *ws, hipStream_t s) {
-    if (a64 && b64) return launch_product<double, double>(d, a, b, c, c64, ws, s);
-    if (a64) return launch_product<double, float>(d, a, b, c, c64, ws, s);
-    if (b64) return launch_product<float, double>(d, a, b, c, c64, ws, s);
-    return launch_product<float, float>(d, a, b, c, c64, ws, s);
+// count (1 or 2) products of the same operand types and tile; two of them only without shared tiles
+static int launch_jobs(const ProductJob *jobs, int count, const ProductOuter *outer, void *ws, hipStream_t s) {
+    ProductArgs M{};
+    unsigned blocks = 0;
+    for (int q = 0; q < count; ++q) {
+        M.task[q] = product_task(jobs[q], ws);
+        blocks += (unsigned)(M.task[q].gr * M.task[q].gc * M.task[q].pieces);
+        if (q == 0) M.first = (int)blocks;
+    }
+    const ProductJob &j = jobs[0];
+    const int tile = j.desc->tile;
+    int rc;
+    if (j.a64 && j.b64) rc = launch_product<double, double>(M, tile, blocks, outer, j.c64, s);
+    else if (j.a64) rc = launch_product<double, float>(M, tile, blocks, outer, j.c64, s);
+    else if (j.b64) rc = launch_product<float, double>(M, tile, blocks, outer, j.c64, s);
+    else rc = launch_product<float, float>(M, tile, blocks, outer, j.c64, s);
+    if (rc || j.desc->pieces == 1) return rc;
+    const long long n = (long long)j.desc->R * j.desc->C;
+    const dim3 rgrid((unsigned)((n + 255) / 256));
+    if (j.c64) TAD_LAUNCH("k_product_reduce", (k_product_reduce<double>), rgrid, dim3(256), 0, s, (const double *)ws, (double *)j.c, n, j.desc->pieces);
+    else TAD_LAUNCH("k_product_reduce", (k_product_reduce<float>), rgrid, dim3(256), 0, s, (const double *)ws, (float *)j.c, n, j.desc->pieces);
+    return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
-static int product(bool f64, const ProductDesc &d, const void *a, const void *b, void *c, void *ws, hipStream_t s) {
-    return product_run(d, a, f64, b, f64, c, f64, ws, s);
+int product_run(const ProductJob &j, void *ws, hipStream_t s) { return launch_jobs(&j, 1, nullptr, ws, s); }
+
+bool product_outer_fits(const ProductDesc &d) { return d.tile == 32 && d.pieces == 1; }
+
+int product_run_outer(const ProductJob &j, const ProductOuter &o, hipStream_t s) { return launch_jobs(&j, 1, &o, nullptr, s); }
+
+// the same product with its operands exchanged: the result's transpose, stored back in place
+static ProductJob turned(const ProductJob &j, ProductDesc &d) {
+    d = *j.desc;
+    std::swap(d.R, d.C);
+    std::swap(d.ar, d.bc);
+    std::swap(d.aq, d.bq);
+    ProductJob t = j;
+    t.desc = &d;
+    std::swap(t.a, t.b);
+    std::swap(t.a64, t.b64);
+    t.turned = !j.turned;
+    return t;
+}
+
+int product_run_two(const ProductJob &x, const ProductJob &y, void *ws, hipStream_t s) {
+    // one launch for both: a launch costs as much as a small product, and two products fill the chip better than one
+    // (operands of mixed widths: one of the two with its operands exchanged)
+    ProductJob jobs[2] = {x, y};
+    ProductDesc d;
+    if (x.a64 != y.a64 && x.a64 == y.b64 && x.b64 == y.a64) jobs[1] = turned(y, d);
+    if (jobs[0].a64 == jobs[1].a64 && jobs[0].b64 == jobs[1].b64 && x.desc->tile == y.desc->tile && x.desc->pieces == 1 && y.desc->pieces == 1)
+        return launch_jobs(jobs, 2, nullptr, ws, s);
+    const int rc = product_run(x, ws, s);
+    return rc ? rc : product_run(y, ws, s);
 }
 
 int product_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s) {
     const ProductPlan &pp = pl.prod;
-    return product(pl.dtype == TAD_F64, pp.forward, args[pp.side[0].operand], args[pp.side[1].operand], f,
-                   static_cast<char *>(ws) + pp.ws_offset, s);
+    const bool f64 = pl.dtype == TAD_F64;
+    const ProductJob j = {&pp.forward, args[pp.side[0].operand], f64, args[pp.side[1].operand], f64, f, f64};
+    return product_run(j, static_cast<char *>(ws) + pp.ws_offset, s);
 }
 
 int product_backward(const tad_plan &pl, const void *const *args, const void *df, void **dx, void *ws, hipStream_t s) {
     const ProductPlan &pp = pl.prod;
+    const bool f64 = pl.dtype == TAD_F64;
+    void *const part = static_cast<char *>(ws) + pp.ws_offset;   // used by the products in turn
+    ProductJob jobs[2];
+    int n = 0;
     for (int q = 0; q < 2; ++q) {
         const ProductSide &sd = pp.side[q];
         if (!sd.grad || !dx[sd.operand]) continue;
         const void *other = args[pp.side[1 - q].operand];
-        const int rc = product(pl.dtype == TAD_F64, sd.desc, sd.k_major ? other : df, sd.k_major ? df : other, dx[sd.operand],
-                               static_cast<char *>(ws) + pp.ws_offset, s);   // the products share the partial sums' place in turn
-        if (rc) return rc;
+        jobs[n++] = {&sd.desc, sd.k_major ? other : df, f64, sd.k_major ? df : other, f64, dx[sd.operand], f64};
         dx[sd.operand] = nullptr;
     }
-    return TAD_OK;
+    return n == 2 ? product_run_two(jobs[0], jobs[1], part, s) : n == 1 ? product_run(jobs[0], part, s) : TAD_OK;
 }
 
 }  // namespace tad

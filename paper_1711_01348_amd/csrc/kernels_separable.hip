@@ -10,60 +10,47 @@
 // interpreted term per thread 9895 us, 1.2 10^9 interpreted terms.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
+#include "element.h"
 #include "gather_loop.h"
 #include "launch.h"
 #include "plan_dev.h"
+#include "product_outer.h"
 #include "prog_eval.h"
 #include "profile.h"
 #include "separable.hpp"
 
 namespace tad {
 
-// Offsets of the operands at element `lin` of an expression without summation indices.
-__device__ __forceinline__ void element_offsets(const ForwardPlan &P, int n_ops, int lin, int64_t *base) {
-    // unrolled to the largest rank and cut short by tests of the uniform rank, so that every field of the plan comes from a
-    // fixed place in the kernel arguments
-    int32_t ext[kMaxExt];
-    int t = lin;
-#pragma unroll
-    for (int d = kMaxExt - 1; d >= 1; --d) {
-        ext[d] = 0;
-        if (d < P.n_f) {
-            const int s = P.f_shape[d], q = t / s;
-            ext[d] = t - q * s;
-            t = q;
-        }
-    }
-    ext[0] = t;
-#pragma unroll
-    for (int p = 0; p < kMaxArgs; ++p) {
-        if (p >= n_ops) continue;
-        int64_t o = P.base0[p];
-#pragma unroll
-        for (int d = 0; d < kMaxExt; ++d)
-            if (d < P.n_f) o += P.off[p][d] * (int64_t)ext[d];
-        base[p] = o;
-    }
-}
-
-// Values of the operands of `mask` at element `lin`, widened; the others are 0.
-template <typename T, typename TV>
-__device__ __forceinline__ void element_values(const ForwardPlan &P, int n_ops, uint32_t mask, const ArgPtrs &A, int lin, TV *v) {
-    int64_t base[kMaxArgs];
-    element_offsets(P, n_ops, lin, base);
-#pragma unroll
-    for (int p = 0; p < kMaxArgs; ++p) v[p] = p < n_ops && ((mask >> p) & 1u) ? (TV)static_cast<const T *>(A.p[p])[base[p]] : TV(0);
-}
-
-// A factor at every pair of indices, evaluated in 64 bits: of 32-bit operands nothing can overflow on the way there.
-template <typename T, int FORM>
-__global__ __launch_bounds__(256) void k_sep_factor(const ForwardPlan P, const DevProg inner, int n_ops, const ArgPtrs A,
-                                                    double *__restrict__ out, int n) {
-    const int lin = blockIdx.x * 256 + threadIdx.x;
-    if (lin >= n) return;
+// Passes over the pairs of indices of a factor, several in one launch (a launch costs as much as such a pass): workgroup b works
+// on the task with first <= b < first of the next one.
+struct PairTask {
+    ForwardPlan plan;      // pairs of indices -> elements of the operands
+    DevProg prog;
+    ArgPtrs args;
+    const double *d;       // null: out = prog, else out = d * prog
+    double *out;           // 64-bit results, or null:
+    void *dx;              // ... results of the operands' type
+    int32_t n_ops, n, first;
+};
+template <int N> struct PairTasks {
+    int32_t count;
+    PairTask task[N];
+};
+// Everything in 64 bits: of 32-bit operands nothing can overflow on the way to a product of factors.
+template <typename T, int FORM, int N>
+__global__ __launch_bounds__(256) void k_sep_pairs(const PairTasks<N> M) {
+    int w = 0;
+    while (w + 1 < M.count && (int)blockIdx.x >= M.task[w + 1].first) ++w;   // the same for the whole workgroup
+    const PairTask &t = M.task[w];
+    const int lin = ((int)blockIdx.x - t.first) * 256 + threadIdx.x;
+    if (lin >= t.n) return;
     double v[kMaxArgs];
-    element_values<T>(P, n_ops, ~0u, A, lin, v);
-    out[lin] = prog_eval<double, FORM>(inner, v, 0.0);
+    element_values<T>(t.plan, t.n_ops, ~0u, t.args, lin, v);
+    const double o = prog_eval<double, FORM>(t.prog, v, 0.0), r = t.d ? t.d[lin] * o : o;
+    if (t.out) t.out[lin] = r;
+    else static_cast<T *>(t.dx)[lin] = (T)r;
 }
 
 // df == nullptr: out = prog(s, operands), else out = df * prog(s, operands); `out` may be `s`.  TO: T, or double for terms
@@ -77,19 +64,6 @@ __global__ __launch_bounds__(256) void k_sep_outer(const ForwardPlan P, const De
     if (mask) element_values<T>(P, n_ops, mask, A, lin, v);
     const T o = prog_eval<T, FORM>(prog, v, s[lin]);
     out[lin] = df ? (TO)df[lin] * (TO)o : (TO)o;
-}
-
-// d * (partial derivative) at every pair of indices: into dx where pair number and element number are the same, else into h.
-template <typename T, int FORM>
-__global__ __launch_bounds__(256) void k_sep_terms(const ForwardPlan P, const DevProg dinner, int n_ops, const ArgPtrs A,
-                                                   const double *__restrict__ d, T *__restrict__ dx, double *__restrict__ h, int n) {
-    const int lin = blockIdx.x * 256 + threadIdx.x;
-    if (lin >= n) return;
-    double v[kMaxArgs];
-    element_values<T>(P, n_ops, ~0u, A, lin, v);
-    const double t = d[lin] * prog_eval<double, FORM>(dinner, v, 0.0);
-    if (dx) dx[lin] = (T)t;
-    else h[lin] = t;
 }
 
 // Sum of h over the pairs that read element `idx` (part of it, shared by parts threads of groups workgroups).
@@ -170,38 +144,65 @@ static ArgPtrs operand_pointers(const SepSide &side, const void *const *args) {
     return A;
 }
 
+// passes over pairs of indices collected for one launch
+template <typename T>
+struct PairPass {
+    PairTasks<6> tasks{};
+    int blocks = 0;
+    bool registers = true;
+    hipStream_t stream;
+    explicit PairPass(hipStream_t s) : stream(s) {}
+    int add(const SepSide &side, const void *const *args, const DevProg &prog, const double *d, double *out, void *dx) {
+        if (tasks.count == 6) {
+            const int rc = run();
+            if (rc) return rc;
+        }
+        const tad_plan &sub = *side.sub;
+        PairTask &t = tasks.task[tasks.count++];
+        t.plan = sub.fwd;
+        t.prog = prog;
+        t.args = operand_pointers(side, args);
+        t.d = d;
+        t.out = out;
+        t.dx = dx;
+        t.n_ops = (int)sub.args.size();
+        t.n = (int)sub.f_count;
+        t.first = blocks;
+        blocks += (t.n + 255) / 256;
+        registers = registers && has_register_form(prog);
+        return TAD_OK;
+    }
+    template <int N> int launch() {
+        PairTasks<N> M;
+        M.count = tasks.count;
+        std::copy(tasks.task, tasks.task + N, M.task);
+        if (registers) TAD_LAUNCH("k_sep_pairs", (k_sep_pairs<T, 1, N>), dim3(blocks), dim3(256), 0, stream, M);
+        else TAD_LAUNCH("k_sep_pairs", (k_sep_pairs<T, 0, N>), dim3(blocks), dim3(256), 0, stream, M);
+        return launched();
+    }
+    int run() {
+        if (tasks.count == 0) return TAD_OK;
+        const int rc = tasks.count <= 2 ? launch<2>() : tasks.count == 3 ? launch<3>() : launch<6>();
+        tasks.count = blocks = 0;
+        registers = true;
+        return rc;
+    }
+};
+
 // the factors that are functions of operands
 template <typename T>
 static int evaluate_factors(const SepPlan &sp, const void *const *args, char *ws, hipStream_t s) {
+    PairPass<T> pass(s);
     for (const SepSide &side : sp.side) {
         if (side.operand >= 0) continue;
-        const tad_plan &sub = *side.sub;
-        const int n = (int)sub.f_count;
-        const ArgPtrs A = operand_pointers(side, args);
-        double *const out = reinterpret_cast<double *>(ws + side.value_offset);
-        const dim3 grid((n + 255) / 256), block(256);
-        if (has_register_form(sub.prog.inner))
-            TAD_LAUNCH("k_sep_factor", (k_sep_factor<T, 1>), grid, block, 0, s, sub.fwd, sub.prog.inner, (int)sub.args.size(), A, out, n);
-        else
-            TAD_LAUNCH("k_sep_factor", (k_sep_factor<T, 0>), grid, block, 0, s, sub.fwd, sub.prog.inner, (int)sub.args.size(), A, out, n);
-        if (launched()) return TAD_EDEVICE;
+        const int rc = pass.add(side, args, side.sub->prog.inner, nullptr, reinterpret_cast<double *>(ws + side.value_offset), nullptr);
+        if (rc) return rc;
     }
-    return TAD_OK;
+    return pass.run();
 }
 
 static const void *factor(const SepSide &side, const void *const *args, const char *ws) {
     return side.operand >= 0 ? args[side.operand] : ws + side.value_offset;
-}
-
-template <typename T>
-static int sums(const tad_plan &pl, const void *const *args, void *out, char *ws, hipStream_t s) {
-    const SepPlan &sp = pl.sep;
-    const int rc = evaluate_factors<T>(sp, args, ws, s);
-    if (rc) return rc;
-    constexpr bool f64 = sizeof(T) == 8;
-    const SepSide &a = sp.side[0], &b = sp.side[1];
-    return product_run(sp.forward, factor(a, args, ws), f64 || a.operand < 0, factor(b, args, ws), f64 || b.operand < 0, out, f64,
-                       ws + sp.part_offset, s);
 }
 
 template <typename T, typename TO>
@@ -217,6 +218,36 @@ static int apply_outer(const tad_plan &pl, const DevProg &prog, const void *cons
         TAD_LAUNCH("k_sep_outer", (k_sep_outer<T, TO, 0>), grid, block, 0, s, pl.fwd, prog, (int)pl.args.size(), pl.sep.prog.outer_mask, A,
                    sum, static_cast<const T *>(df), out, n);
     return launched();
+}
+
+// Sums through `prog` (null: stored as they are) into out; s_out (may be null): where the sums themselves are needed as well.
+// df: see k_sep_outer.
+template <typename T>
+static int sums(const tad_plan &pl, const DevProg *prog, const void *const *args, const void *df, void *out, T *s_out, char *ws, hipStream_t s) {
+    const SepPlan &sp = pl.sep;
+    int rc = evaluate_factors<T>(sp, args, ws, s);
+    if (rc) return rc;
+    constexpr bool f64 = sizeof(T) == 8;
+    const SepSide &a = sp.side[0], &b = sp.side[1];
+    ProductJob j = {&sp.forward, factor(a, args, ws), f64 || a.operand < 0, factor(b, args, ws), f64 || b.operand < 0, out, f64};
+    if (prog && has_register_form(*prog) && sp.outer_linear && product_outer_fits(sp.forward)) {
+        ProductOuter o{};
+        o.prog = *prog;
+        for (size_t q = 0; q < pl.args.size(); ++q) {
+            if (!((sp.prog.outer_mask >> q) & 1u)) continue;
+            o.args.p[q] = args[q];
+            o.off_r[q] = sp.outer_r[q];
+            o.off_c[q] = sp.outer_c[q];
+        }
+        o.df = df;
+        o.s_out = s_out;
+        return product_run_outer(j, o, s);
+    }
+    T *const sum = s_out ? s_out : reinterpret_cast<T *>(ws + sp.s_offset);
+    if (prog) j.c = sum;
+    rc = product_run(j, ws + sp.part_offset, s);
+    if (rc || !prog) return rc;
+    return apply_outer<T, T>(pl, *prog, args, sum, df, static_cast<T *>(out), s);
 }
 
 template <typename TI, typename T>
@@ -255,22 +286,7 @@ static int sum_through_plan(const GatherPlan &g, int64_t count, double pairs, co
 
 template <typename T>
 static int forward_t(const tad_plan &pl, const void *const *args, void *f, char *ws, hipStream_t s) {
-    const SepPlan &sp = pl.sep;
-    T *const sum = sp.identity ? static_cast<T *>(f) : reinterpret_cast<T *>(ws + sp.s_offset);
-    const int rc = sums<T>(pl, args, sum, ws, s);
-    if (rc || sp.identity) return rc;
-    return apply_outer<T, T>(pl, sp.prog.outer, args, sum, nullptr, static_cast<T *>(f), s);
-}
-
-// every pair of indices reads an element of its own, numbered alike
-static bool pairs_are_elements(const tad_plan &sub, int p) {
-    if (sub.arg_count[p] != sub.f_count) return false;
-    int64_t stride = 1;
-    for (int d = sub.expr.n_f - 1; d >= 0; --d) {
-        if (sub.expr.f_shape[d] != 1 && sub.fwd.off[p][d] != stride) return false;
-        stride *= sub.expr.f_shape[d];
-    }
-    return true;
+    return sums<T>(pl, pl.sep.identity ? nullptr : &pl.sep.prog.outer, args, nullptr, f, nullptr, ws, s);
 }
 
 template <typename T>
@@ -279,59 +295,69 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *d
     constexpr bool f64 = sizeof(T) == 8;
     const int n_ops = (int)pl.args.size();
     char *const part = ws + sp.part_offset;
-    T *const sum = reinterpret_cast<T *>(ws + sp.s_offset);
+    T *sum = nullptr;   // the sums themselves: for the terms of operands of the outer function that are not g
+    for (int q = 0; q < n_ops; ++q)
+        if (dx[q] && ((sp.prog.outer_mask >> q) & 1u) && !sp.term_is_g[q]) sum = reinterpret_cast<T *>(ws + sp.s_offset);
     const T *g = static_cast<const T *>(df);
     int rc;
     if (!sp.identity) {
-        rc = sums<T>(pl, args, sum, ws, s);
-        if (rc) return rc;
         T *const gw = reinterpret_cast<T *>(ws + sp.g_offset);
-        rc = apply_outer<T, T>(pl, sp.prog.douter, args, sum, df, gw, s);
-        if (rc) return rc;
+        rc = sums<T>(pl, &sp.prog.douter, args, df, gw, sum, ws, s);
         g = gw;
     } else {
         rc = evaluate_factors<T>(sp, args, ws, s);
-        if (rc) return rc;
     }
-    bool stored[kMaxArgs] = {};
+    if (rc) return rc;
+    // the derivatives of the factors
+    bool stored[kMaxArgs] = {}, wanted[2] = {};
+    ProductJob jobs[2];
+    int n_jobs = 0;
     for (int q = 0; q < 2; ++q) {
         const SepSide &side = sp.side[q], &other = sp.side[1 - q];
-        bool wanted = side.sub == nullptr && side.operand >= 0 && dx[side.operand];
         if (side.sub)
-            for (int p : side.operands) wanted = wanted || dx[p];
-        if (!wanted) continue;
+            for (int p : side.operands) wanted[q] = wanted[q] || dx[p];
+        else
+            wanted[q] = dx[side.operand] != nullptr;
+        if (!wanted[q]) continue;
         const void *o = factor(other, args, ws);
-        const bool o64 = f64 || other.operand < 0;
-        double *const d = reinterpret_cast<double *>(ws + sp.d_offset);
-        void *const to = side.sub ? d : dx[side.operand];
-        rc = side.k_major ? product_run(side.grad, o, o64, g, f64, to, f64 || side.sub, part, s)
-                          : product_run(side.grad, g, f64, o, o64, to, f64 || side.sub, part, s);
-        if (rc) return rc;
-        if (!side.sub) {
-            stored[side.operand] = true;
-            continue;
-        }
-        const tad_plan &sub = *side.sub;
-        const int n = (int)sub.f_count;
-        const ArgPtrs A = operand_pointers(side, args);
+        const bool o64 = f64 || other.operand < 0, wide = f64 || side.sub;
+        void *const to = side.sub ? ws + side.d_offset : dx[side.operand];
+        if (side.k_major) jobs[n_jobs++] = {&side.grad, o, o64, g, f64, to, wide};
+        else jobs[n_jobs++] = {&side.grad, g, f64, o, o64, to, wide};
+        if (!side.sub) stored[side.operand] = true;
+    }
+    rc = n_jobs == 2 ? product_run_two(jobs[0], jobs[1], part, s) : n_jobs == 1 ? product_run(jobs[0], part, s) : TAD_OK;
+    if (rc) return rc;
+    // derivative of the factor * derivative by its operand, at every pair of indices ...
+    PairPass<T> pass(s);
+    bool direct[2][kMaxArgs] = {};
+    for (int q = 0; q < 2; ++q) {
+        const SepSide &side = sp.side[q];
+        if (!wanted[q] || !side.sub || side.operand >= 0) continue;
         for (int p = 0; p < (int)side.operands.size(); ++p) {
             const int op = side.operands[p];
             if (!dx[op]) continue;
-            const double *h = d;
-            if (side.operand < 0) {
-                const DevProg &prog = sub.prog.dinner[p];
-                T *const direct = !stored[op] && pairs_are_elements(sub, p) ? static_cast<T *>(dx[op]) : nullptr;
-                double *const terms = reinterpret_cast<double *>(ws + sp.h_offset);
-                const dim3 grid((n + 255) / 256), block(256);
-                if (has_register_form(prog))
-                    TAD_LAUNCH("k_sep_terms", (k_sep_terms<T, 1>), grid, block, 0, s, sub.fwd, prog, (int)sub.args.size(), A, d, direct, terms, n);
-                else
-                    TAD_LAUNCH("k_sep_terms", (k_sep_terms<T, 0>), grid, block, 0, s, sub.fwd, prog, (int)sub.args.size(), A, d, direct, terms, n);
-                if (launched()) return TAD_EDEVICE;
-                h = direct ? nullptr : terms;
-            }
+            // an aligned operand moves along the side's function index: the other side does not read it
+            direct[q][p] = side.aligned[p];
+            if (direct[q][p]) stored[op] = true;
+            rc = pass.add(side, args, side.sub->prog.dinner[p], reinterpret_cast<const double *>(ws + side.d_offset),
+                          direct[q][p] ? nullptr : reinterpret_cast<double *>(ws + side.h_offset[p]), dx[op]);
+            if (rc) return rc;
+        }
+    }
+    rc = pass.run();
+    if (rc) return rc;
+    // ... and the sums of those that read the same element
+    for (int q = 0; q < 2; ++q) {
+        const SepSide &side = sp.side[q];
+        if (!wanted[q] || !side.sub) continue;
+        for (int p = 0; p < (int)side.operands.size(); ++p) {
+            const int op = side.operands[p];
+            if (!dx[op] || direct[q][p]) continue;
+            const size_t at = side.operand >= 0 ? side.d_offset : side.h_offset[p];
             // (an operand may be read on both sides: the second one adds)
-            if (h) rc = sum_through_plan(sub.ap[p].dev, pl.arg_count[op], (double)sub.f_count, h, static_cast<T *>(dx[op]), stored[op], part, s);
+            rc = sum_through_plan(side.sub->ap[p].dev, pl.arg_count[op], (double)side.sub->f_count, reinterpret_cast<const double *>(ws + at),
+                                  static_cast<T *>(dx[op]), stored[op], part, s);
             if (rc) return rc;
             stored[op] = true;
         }

@@ -42,8 +42,25 @@ int contract_backward(const tad_plan &pl, const void *const *args, const void *d
 int product_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
 int product_backward(const tad_plan &pl, const void *const *args, const void *df, void **dx, void *ws, hipStream_t s);
 
-// one product; a64, b64, c64: 64-bit elements; ws: partial sums of shared tiles
-int product_run(const ProductDesc &d, const void *a, bool a64, const void *b, bool b64, void *c, bool c64, void *ws, hipStream_t s);
+// One product and its operands; a64, b64, c64: 64-bit elements; turned: the result is stored [c][r].
+struct ProductDesc;
+struct ProductJob {
+    const ProductDesc *desc;
+    const void *a;
+    bool a64;
+    const void *b;
+    bool b64;
+    void *c;
+    bool c64;
+    bool turned = false;
+};
+struct ProductOuter;
+// ws: partial sums of shared tiles
+int product_run(const ProductJob &j, void *ws, hipStream_t s);
+int product_run_two(const ProductJob &x, const ProductJob &y, void *ws, hipStream_t s);
+// the product's results through a program in register form (only where product_outer_fits)
+bool product_outer_fits(const ProductDesc &d);
+int product_run_outer(const ProductJob &j, const ProductOuter &o, hipStream_t s);
 
 // sums of products of two functions (separable.hpp)
 int separable_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);

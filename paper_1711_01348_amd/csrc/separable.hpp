@@ -34,7 +34,11 @@ struct SepSide {
     // is the factor and its gradient is the product (or not wanted)
     std::shared_ptr<tad_plan> sub;
     std::vector<int> operands;   // operand of sub -> operand of the expression
-    size_t value_offset = 0;     // workspace: the evaluated factor, in 64 bits
+    std::vector<char> aligned;   // ... every pair of indices reads an element of its own, numbered alike
+    // workspace, all in 64 bits
+    size_t value_offset = 0;     // the evaluated factor
+    size_t d_offset = 0;         // its derivative
+    std::vector<size_t> h_offset;   // per operand: terms of a gradient that several pairs of indices add to
 };
 
 struct SepPlan {
@@ -45,11 +49,13 @@ struct SepPlan {
     ProgramBody prog;            // outer function and its derivatives
     bool identity = false;       // the outer function is the sum
     bool term_is_g[TAD_MAX_ARGS] = {};   // d outer / d operand and d outer / d sum are the same program
+    // offsets of the outer function's operands along the two function indices, if these are single strides
+    bool outer_linear = true;
+    int64_t outer_r[TAD_MAX_ARGS] = {}, outer_c[TAD_MAX_ARGS] = {};
     // workspace
     size_t s_offset = 0;         // sums
     size_t g_offset = 0;         // g = df * d outer / d s
-    size_t h_offset = 0;         // 64-bit terms of a gradient that several pairs of indices add to
-    size_t d_offset = 0;         // derivative of a factor, in 64 bits
+    size_t h_offset = 0;         // 64-bit terms of an operand of the outer function
     size_t part_offset = 0;      // partial sums of the products and of the gathers
     size_t ws_bytes = 0;
 };

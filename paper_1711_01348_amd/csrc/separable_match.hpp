@@ -65,6 +65,17 @@ bool same_program(const DevProg &x, const DevProg &y) {
     return true;
 }
 
+// every pair of indices reads an element of its own, numbered alike
+bool pairs_are_elements(const tad_plan &sub, int p) {
+    if (sub.arg_count[p] != sub.f_count) return false;
+    int64_t stride = 1;
+    for (int d = sub.expr.n_f - 1; d >= 0; --d) {
+        if (sub.expr.f_shape[d] != 1 && sub.fwd.off[p][d] != stride) return false;
+        stride *= sub.expr.f_shape[d];
+    }
+    return true;
+}
+
 }  // namespace
 
 void match_separable(tad_plan &pl) {
@@ -232,7 +243,12 @@ void match_separable(tad_plan &pl) {
     f.ar = A.sm; f.aq = A.sk; f.bq = B.sk; f.bc = B.sm;
     if (!product_addressable(f)) return;
     product_shape(f, wide(A) && wide(B));
-    size_t part = product_partial_bytes(f), value = 0, derivative = 0, terms = 0;
+    size_t part = product_partial_bytes(f), ws = 0;
+    auto reserve = [&](size_t bytes) {
+        const size_t at = ws;
+        ws += align256(bytes);
+        return at;
+    };
     for (int q = 0; q < 2; ++q) {
         SepSide &s = sp.side[q];
         const SepSide &o = sp.side[1 - q];
@@ -244,16 +260,21 @@ void match_separable(tad_plan &pl) {
         if (!product_addressable(d)) return;
         product_shape(d, f64);
         part = std::max(part, product_partial_bytes(d));
-        if (s.operand < 0) {
-            s.value_offset = value;
-            value += align256((size_t)(s.X * K) * 8);
-        }
-        if (s.sub) {
-            derivative = std::max(derivative, align256((size_t)(s.X * K) * 8));
-            terms = std::max(terms, align256((size_t)(s.X * K) * 8));
+        const size_t matrix = (size_t)(s.X * K) * 8;
+        if (s.operand < 0) s.value_offset = reserve(matrix);
+        if (!s.sub) continue;
+        s.d_offset = reserve(matrix);
+        for (size_t p = 0; p < s.operands.size(); ++p) {
+            s.aligned.push_back(pairs_are_elements(*s.sub, (int)p));
+            s.h_offset.push_back(s.operand < 0 && s.sub->ap[p].derived && !s.aligned[p] ? reserve(matrix) : 0);
         }
     }
     for (int p = 0; p < n_ops; ++p) sp.term_is_g[p] = same_program(sp.prog.douter_arg[p], sp.prog.douter);
+    for (int p = 0; p < n_ops; ++p) {
+        if (!((sp.prog.outer_mask >> p) & 1u)) continue;
+        sp.outer_linear = sp.outer_linear && product_group_stride(pl.fwd.off[p], extent, lead, sp.outer_r[p]) &&
+                          product_group_stride(pl.fwd.off[p] + lead, extent + lead, e.n_f - lead, sp.outer_c[p]);
+    }
     sp.identity = sp.prog.outer.n == 1 && sp.prog.outer.op[0] == P_SUM;
     // partial sums of the gathers
     auto gathers = [&](const ArgPlan &ap, int64_t count, double pairs) {
@@ -266,14 +287,11 @@ void match_separable(tad_plan &pl) {
             for (size_t p = 0; p < s.operands.size(); ++p) gathers(s.sub->ap[p], s.sub->arg_count[p], (double)(s.X * K));
     for (int p = 0; p < n_ops; ++p)
         if ((sp.prog.outer_mask >> p) & 1u) gathers(pl.ap_outer[p], pl.arg_count[p], (double)pl.f_count);
-    const size_t sums = align256((size_t)pl.f_count * (f64 ? 8 : 4));
-    if (sp.prog.outer_mask) terms = std::max(terms, align256((size_t)pl.f_count * 8));
-    size_t ws = value;
-    sp.s_offset = ws; ws += sums;
-    sp.g_offset = ws; ws += sums;
-    sp.h_offset = ws; ws += terms;
-    sp.d_offset = ws; ws += derivative;
-    sp.part_offset = ws; ws += part;
+    const size_t sums = (size_t)pl.f_count * (f64 ? 8 : 4);
+    sp.s_offset = reserve(sums);
+    sp.g_offset = reserve(sums);
+    sp.h_offset = sp.prog.outer_mask ? reserve((size_t)pl.f_count * 8) : 0;
+    sp.part_offset = reserve(part);
     sp.ws_bytes = ws;
     sp.on = true;
 }
