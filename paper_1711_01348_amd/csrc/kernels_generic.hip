@@ -50,20 +50,23 @@ __device__ __forceinline__ double forward_sum(const ForwardPlan &P, const ArgPtr
     double acc = 0.0;
     const int last = P.n_sum - 1;
     const int32_t n_last = last >= 0 ? P.sum_n[last] : 1;
-    if (P.n_cons == 0 && last >= 0 && (parts == 1 || last == 0 || n_last >= parts)) {
-        // no extra conditions: the last summation index is a run of terms a constant stride apart; cooperating
+    if (last >= 0 && (parts == 1 || last == 0 || n_last >= parts)) {
+        // the last summation index is a run of terms a constant stride apart; cooperating
         // threads take its terms in turn.  Whole batches of four terms are loaded before the first is used (one wait
         // for memory per batch, pointers advanced by additions, no predicates), the rest of the run goes one term at
         // a time; added in ascending order.  An operand that does not move along the run is loaded once per run.
         constexpr int U = 4;
         int64_t stp[NA];
         for (int p = 0; p < NA; ++p) stp[p] = P.last_stride[p] * parts;
-        const int32_t mine = part < n_last ? (n_last - part + parts - 1) / parts : 0;
         for (;;) {
+            // terms of the run: first .. hi, of which this thread takes every parts-th
+            int32_t lo = 0, hi = n_last - 1;
+            if (P.n_cons) forward_range(P, ext, k, lo, hi);
+            const int32_t first = lo + part, mine = first <= hi ? (hi - first) / parts + 1 : 0;
             const T *ptr[NA];
             T still[NA];
             for (int p = 0; p < NA; ++p) {
-                int64_t o = base[p] + P.last_stride[p] * (int64_t)part;
+                int64_t o = base[p] + P.last_stride[p] * (int64_t)first;
                 for (int sidx = 0; sidx < last; ++sidx) o += P.off[p][P.n_f + sidx] * (int64_t)k[sidx];
                 ptr[p] = static_cast<const T *>(A.p[p]) + o;
                 still[p] = stp[p] == 0 && mine > 0 ? *ptr[p] : T(0);

@@ -92,8 +92,8 @@ __device__ double inner_sum(const ForwardPlan &P, const DevProg &inner, int n_op
     double acc = 0.0;
     const int last = P.n_sum - 1;
     const int32_t n_last = last >= 0 ? P.sum_n[last] : 1;
-    if (P.n_cons == 0 && last >= 0 && (parts == 1 || last == 0 || n_last >= parts)) {
-        // no extra conditions: the innermost summation index is a run of n_last terms with constant strides;
+    if (last >= 0 && (parts == 1 || last == 0 || n_last >= parts)) {
+        // the innermost summation index is a run of n_last terms with constant strides;
         // cooperating threads take its terms in turn
         const T *bp[kMaxArgs];
         int64_t stp[kMaxArgs];
@@ -102,8 +102,11 @@ __device__ double inner_sum(const ForwardPlan &P, const DevProg &inner, int n_op
             bp[p] = p < n_ops ? static_cast<const T *>(A.p[p]) + base[p] : nullptr;
             stp[p] = p < n_ops ? P.off[p][P.n_f + last] * parts : 0;
         }
-        const int32_t mine = part < n_last ? (n_last - part + parts - 1) / parts : 0;
         for (;;) {
+            // terms of the run: first .. hi, of which this thread takes every parts-th
+            int32_t lo = 0, hi = n_last - 1;
+            if (P.n_cons) forward_range(P, ext, k, lo, hi);
+            const int32_t first = lo + part, mine = first <= hi ? (hi - first) / parts + 1 : 0;
             const T *ptr[kMaxArgs];
 #pragma unroll
             for (int p = 0; p < kMaxArgs; ++p) {
@@ -112,7 +115,7 @@ __device__ double inner_sum(const ForwardPlan &P, const DevProg &inner, int n_op
 #pragma unroll
                     for (int sidx = 0; sidx < kMaxExt; ++sidx)
                         if (sidx < last) o += P.off[p][P.n_f + sidx] * (int64_t)k[sidx];
-                    o += P.off[p][P.n_f + last] * (int64_t)part;
+                    o += P.off[p][P.n_f + last] * (int64_t)first;
                 }
                 ptr[p] = bp[p] ? bp[p] + o : nullptr;
             }

@@ -222,6 +222,31 @@ TAD_HD int32_t ceil_div_i(int32_t a, int32_t b) {
     return (r > 0) ? q + 1 : q;
 }
 
+// Values lo .. hi of the last summation index (counted from its lower limit) whose terms the extra conditions leave in the sum,
+// for the function part ext[0..n_f) and the counters k of the other summation indices; hi < lo: none.  Each condition is linear
+// in that index, so a run of terms needs no test of its own (a causal convolution of 262144 x 33: 43 us with a test per
+// term, 11 us without).
+TAD_HD void forward_range(const ForwardPlan &P, const int32_t *ext, const int32_t *k, int32_t &lo, int32_t &hi) {
+    const int last = P.n_sum - 1;
+    lo = 0;
+    hi = P.sum_n[last] - 1;
+    for (int e = 0; e < P.n_cons; ++e) {
+        int32_t v = P.cons[e][P.n_f + P.n_sum] + P.cons[e][P.n_f + last] * P.sum_lo[last];
+        for (int d = 0; d < P.n_f; ++d) v += P.cons[e][d] * ext[d];
+        for (int s = 0; s < last; ++s) v += P.cons[e][P.n_f + s] * (P.sum_lo[s] + k[s]);
+        const int32_t c = P.cons[e][P.n_f + last];   // v + c * value >= 0
+        if (c > 0) {
+            const int32_t t = ceil_div_i(-v, c);
+            lo = t > lo ? t : lo;
+        } else if (c < 0) {
+            const int32_t t = floor_div_i(v, -c);
+            hi = t < hi ? t : hi;
+        } else if (v < 0) {
+            hi = -1;
+        }
+    }
+}
+
 // Masks and transformed index for one beta.  Returns false when the gradient element is zero
 // because of the cokernel condition, the divisibility condition or an infeasible range system.
 TAD_HD bool gather_prepare(const GatherPlan &P, const int32_t *beta, int32_t *y) {
