@@ -158,40 +158,48 @@ static bool unary_body(int body) {
 }
 
 // the three one-argument patterns of the introduction: f_ij = phi(x_i), f_i = phi(x_ii), f_ij = phi(x_{i+j})
-static bool match_patterns(tad_plan &pl) {
+static int pattern_of(tad_plan &pl) {
     const tad_expr &e = pl.expr;
-    if (!unary_body(e.body) || pl.dtype != TAD_F32 || e.n_sum != 0 || !all_derived(pl)) return false;
+    if (!unary_body(e.body) || e.n_sum != 0 || !all_derived(pl)) return TAD_FAMILY_GENERIC;
     const tad_arg &x = pl.args[0];
     const ArgPlan &px = pl.ap[0];
     int fam = TAD_FAMILY_GENERIC;
     if (e.n_f == 2 && index_is(x, 2, {{1, 0}})) {
         // kernel coordinate = j over its whole range, i = y_0
-        if (e.f_shape[1] % 4 != 0 || px.smith.R != 1 || px.K.cols != 1) return false;
-        if (px.VR(0, 0) != 1 || px.VR(1, 0) != 0 || px.K(0, 0) != 0 || px.K(1, 0) * px.K(1, 0) != 1) return false;
-        if (!y_is_beta(px.dev) || !flatten_feas(px.dev, pl.fast.feas)) return false;
+        if (px.smith.R != 1 || px.K.cols != 1) return fam;
+        if (px.VR(0, 0) != 1 || px.VR(1, 0) != 0 || px.K(0, 0) != 0 || px.K(1, 0) * px.K(1, 0) != 1) return TAD_FAMILY_GENERIC;
+        if (!y_is_beta(px.dev) || !flatten_feas(px.dev, pl.fast.feas)) return TAD_FAMILY_GENERIC;
         fam = TAD_FAMILY_ROW_REDUCE;
     } else if (e.n_f == 1 && index_is(x, 1, {{1}, {1}})) {
-        if (x.shape[1] % 4 != 0 || px.smith.R != 1 || px.K.cols != 0 || px.VR(0, 0) != 1) return false;
+        if (px.smith.R != 1 || px.K.cols != 0 || px.VR(0, 0) != 1) return TAD_FAMILY_GENERIC;
         // transformed index y = first gradient index; one cokernel row +-(1, -1)
         const GatherPlan &g = px.dev;
-        if (g.nC != 1 || g.C[0][0] + g.C[0][1] != 0 || g.C[0][0] * g.C[0][0] != 1) return false;
-        if (g.diag[0] != 1 || g.U[0][0] != 1 || g.U[0][1] != 0 || !flatten_feas(g, pl.fast.feas)) return false;
+        if (g.nC != 1 || g.C[0][0] + g.C[0][1] != 0 || g.C[0][0] * g.C[0][0] != 1) return TAD_FAMILY_GENERIC;
+        if (g.diag[0] != 1 || g.U[0][0] != 1 || g.U[0][1] != 0 || !flatten_feas(g, pl.fast.feas)) return TAD_FAMILY_GENERIC;
         pl.fast.c_ld = x.shape[1];
         fam = TAD_FAMILY_DIAGONAL;
     } else if (e.n_f == 2 && index_is(x, 2, {{1, 1}})) {
-        if (e.f_shape[1] % 4 != 0 || px.smith.R != 1 || px.K.cols != 1) return false;
-        if (px.K(0, 0) * px.K(0, 0) != 1 || px.K(1, 0) * px.K(1, 0) != 1) return false;
+        if (px.smith.R != 1 || px.K.cols != 1) return fam;
+        if (px.K(0, 0) * px.K(0, 0) != 1 || px.K(1, 0) * px.K(1, 0) != 1) return TAD_FAMILY_GENERIC;
         if (!y_is_beta(px.dev) || !flatten_feas(px.dev, pl.fast.feas) || !flatten_level(px.dev, 0, pl.fast.flat[0]))
-            return false;
+            return TAD_FAMILY_GENERIC;
         pl.fast.dd_iy = (int)px.VR(0, 0); pl.fast.dd_iz = (int)px.K(0, 0);
         pl.fast.jy = (int)px.VR(1, 0); pl.fast.jz = (int)px.K(1, 0);
-        pl.ws_bytes = antidiag_workspace_bytes(e.f_shape[0], e.f_shape[1]);
         fam = TAD_FAMILY_ANTIDIAGONAL;
     } else {
-        return false;
+        return TAD_FAMILY_GENERIC;
     }
     pl.fast.I = e.f_shape[0];
     pl.fast.J = e.n_f == 2 ? e.f_shape[1] : 1;
+    return fam;
+}
+
+static bool match_patterns(tad_plan &pl) {
+    const int fam = pl.dtype == TAD_F32 ? pattern_of(pl) : TAD_FAMILY_GENERIC;
+    if (fam == TAD_FAMILY_GENERIC) return false;
+    // rows must start 16-byte aligned for the vector loads and stores
+    if ((fam == TAD_FAMILY_DIAGONAL ? pl.args[0].shape[1] : pl.expr.f_shape[1]) % 4 != 0) return false;
+    if (fam == TAD_FAMILY_ANTIDIAGONAL) pl.ws_bytes = antidiag_workspace_bytes(pl.expr.f_shape[0], pl.expr.f_shape[1]);
     pl.fwd_family = fam;
     pl.ap[0].family = fam;
     return true;
@@ -363,12 +371,35 @@ void select_families(tad_plan &plan) {
 // 45 / 20 us, 1024 x 1024 x 5 44 / 24, 2048 x 2048 x 1 40 / 25, x 8 61 / 42, 4096 x 2048 x 5 58 / 57, 4096 x 4096 x 5 66 / 95 us.
 constexpr int64_t kWideElements = (int64_t)1 << 23;
 
-void select_worked_wide(tad_plan &plan) {
-    if ((plan.flags & TAD_PLAN_GENERIC_ONLY) || plan.has_alias || plan.expr.n_constraints > 0 || !plan.term_list.empty()) return;
+static void select_worked_wide(tad_plan &plan) {
     if (plan.fwd_family != TAD_FAMILY_GENERIC && (plan.fwd_family != TAD_FAMILY_WORKED || plan.f_count >= kWideElements)) return;
     if (!worked_structure(plan) || plan.fast.K > kWideMaxK) return;
     plan.worked_wide = true;
     plan.ws_full = std::max(plan.ws_bytes, worked_wide_geom(plan.fast.I, plan.fast.J, plan.fast.K).ws_bytes);
+}
+
+// Row reduce and antidiagonal patterns in a form their 32-bit kernels do not take; the family stays the general one.
+static void select_pattern_wide(tad_plan &plan) {
+    if (plan.fwd_family != TAD_FAMILY_GENERIC) return;
+    const int fam = pattern_of(plan);
+    if (fam != TAD_FAMILY_ROW_REDUCE && fam != TAD_FAMILY_ANTIDIAGONAL) return;
+    if (fam == TAD_FAMILY_ANTIDIAGONAL) {
+        // two launches backward: below, the one of the general kernels is as fast (40 x 41: 14.5 us against 16; 100 x 101: 19 against 15)
+        if (plan.f_count < 4096) return;
+        // the kernels address f as i * J + j with j = m - i
+        if (plan.fast.dd_iy + plan.fast.jy != 1 || plan.fast.dd_iz + plan.fast.jz != 0) return;
+        // short rows: the chunks' sums would be as large as f
+        const size_t ws = antidiag_wide_workspace_bytes(plan.fast.I, plan.fast.J);
+        if (plan.fast.J < 16 && ws > ((size_t)1 << 20)) return;
+        plan.ws_full = std::max(plan.ws_bytes, ws);
+    }
+    plan.pattern_wide = fam;
+}
+
+void select_wide(tad_plan &plan) {
+    if ((plan.flags & TAD_PLAN_GENERIC_ONLY) || plan.has_alias || plan.expr.n_constraints > 0 || !plan.term_list.empty()) return;
+    select_worked_wide(plan);
+    select_pattern_wide(plan);
 }
 
 static void reserve_partial_sums(tad_plan &plan) {

@@ -123,4 +123,15 @@ inline size_t antidiag_workspace_bytes(int64_t I, int64_t J) {
                     AD_TILE_SUMS * 4);
 }
 
+// The same with 64-bit sums and rows of any length (kernels_patterns_wide.hip): rows of a chunk, about 4096 wavefronts in all;
+// partial sums [chunk][J + rows].
+inline int antidiag_wide_rows(int64_t I, int64_t J) {
+    const int64_t rows = (I * J / 64 / 4096 + 31) / 32 * 32;
+    return (int)(rows < 32 ? 32 : rows > 512 ? 512 : rows);
+}
+inline size_t antidiag_wide_workspace_bytes(int64_t I, int64_t J) {
+    const int64_t rows = antidiag_wide_rows(I, J);
+    return align256((size_t)((I + rows - 1) / rows) * (size_t)(J + rows) * 8);
+}
+
 }  // namespace tad

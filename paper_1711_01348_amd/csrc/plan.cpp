@@ -520,7 +520,7 @@ int derive_plan(const tad_expr *expr, const tad_arg *args, int n_args, tad_dtype
     }
     select_families(*pl);
     list_terms(*pl);
-    select_worked_wide(*pl);
+    select_wide(*pl);
     guard.p = nullptr;
     *out = pl;
     return TAD_OK;

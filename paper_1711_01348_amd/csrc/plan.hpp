@@ -74,6 +74,7 @@ struct tad_plan {
     std::vector<tad::TermList> term_list;      // one entry if the terms of every gradient element are listed (small expressions)
     tad::ProductPlan prod;                     // products that separate over the function indices (on: some run as dense products)
     bool worked_wide = false;                  // worked expression on the kernels with 64-bit sums (workspace: ws_full)
+    int pattern_wide = TAD_FAMILY_GENERIC;     // row reduce or antidiagonal pattern on the kernels with 64-bit sums (workspace: ws_full)
     tad::SepPlan sep;                          // sums of products of two functions (on: the whole expression runs on dense products)
     size_t ws_bytes = 0;                       // workspace of the family's kernels
     size_t ws_full = 0;                        // ... and of the dense products; a smaller workspace runs without those
@@ -100,6 +101,6 @@ bool linear_form_range(const int64_t *a, int D, const int64_t *lo, const int64_t
                        const int64_t (*cons_in)[TAD_MAX_EXT + 1], int64_t &tmin, int64_t &tmax);
 // Pattern recognition of the specialised kernel families (device-independent; defined in families.cpp).
 void select_families(tad_plan &plan);
-// ... and, once small expressions have their terms listed, the worked expression with 64-bit sums.
-void select_worked_wide(tad_plan &plan);
+// ... and, once small expressions have their terms listed, the kernels with 64-bit sums of the worked expression and the patterns.
+void select_wide(tad_plan &plan);
 }  // namespace tad

@@ -1,0 +1,57 @@
+"""f_ij = phi(x_i) and f_ij = phi(x_{i+j}) with rows of any length, in either precision, on the kernels with 64-bit sums."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1711_01348_amd import check
+from paper_1711_01348_amd import workloads as wl
+from paper_1711_01348_amd.workloads import ArgSpec, ExprSpec
+from test_separable import run
+
+
+def expr_of(kind, I, J, dtype, body, extra):
+    arg = ArgSpec("x", (I + J - 1 + extra,), [[1, 1]]) if kind == "index_sum" else ArgSpec("x", (I + extra,), [[1, 0]])
+    return ExprSpec(body, (I, J), [], [arg], dtype)
+
+
+# one wavefront / one workgroup per row, whole and ragged vectors of the forward store, elements of x nothing reads, chunks of
+# 32 rows and their edges, tiles of 64 sums wholly inside and at the edges, rows shorter than a chunk
+SIZES = [(33, 33, 0, "exp"), (70, 1, 0, "sq"), (1, 71, 2, "sin"), (31, 257, 0, "cube"), (64, 66, 5, "sq"), (97, 31, 0, "exp"),
+         (2500, 513, 0, "sin"), (517, 999, 1, "exp"), (200, 4099, 0, "cube"), (5, 4097, 0, "sq"), (1300, 7, 3, "sin")]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("kind", ["index_sum", "broadcast"])
+@pytest.mark.parametrize("I,J,extra,body", SIZES)
+def test_rows_of_any_length(kind, I, J, extra, body, dtype):
+    """Against the oracle; a workspace of the general kernels' size gives the same."""
+    from paper_1711_01348_amd import binding as B
+    expr = expr_of(kind, I, J, dtype, body, extra)
+    w = wl.random_inputs(expr, 8)
+    plan, general = B.Plan(expr), B.Plan(expr, generic_only=True)
+    assert plan.forward_family == ("generic" if dtype == "f64" or J % 4 else plan.forward_family)
+    f_ref, g_ref = oracle.forward(expr, w.arg_list()), oracle.backward(expr, w.arg_list(), w.df)
+    for p, ws_bytes in ((plan, plan.workspace_bytes), (plan if plan.forward_family == "generic" else general, general.workspace_bytes)):
+        f, (g,) = run(p, w, ws_bytes)
+        assert check.within(f, f_ref, dtype), (ws_bytes, check.errors(f, f_ref))
+        assert check.within(g, g_ref[0], dtype), (ws_bytes, check.errors(g, g_ref[0]))
+        assert np.all(g[g_ref[0] == 0] == 0)
+
+
+@pytest.mark.gpu
+def test_an_output_off_its_alignment():
+    """f and dx one element behind a 16-byte boundary: the stores of whole vectors are not taken."""
+    import ctypes
+    import torch
+    from paper_1711_01348_amd import binding as B
+    expr = expr_of("index_sum", 45, 67, "f32", "exp", 0)
+    w = wl.random_inputs(expr, 9)
+    plan = B.Plan(expr)
+    x = torch.from_numpy(w.arg_list()[0]).cuda()
+    f = torch.zeros(45 * 67 + 1, device="cuda")[1:]
+    ws = torch.empty(max(plan.workspace_bytes, 1), dtype=torch.uint8, device="cuda")
+    ptrs = (ctypes.c_void_p * 1)(x.data_ptr())
+    assert B.lib.tad_eval_forward(plan._h, ptrs, f.data_ptr(), ws.data_ptr(), ws.numel(), None) == 0
+    torch.cuda.synchronize()
+    assert check.within(f.cpu().numpy().reshape(45, 67), oracle.forward(expr, w.arg_list()), "f32")
