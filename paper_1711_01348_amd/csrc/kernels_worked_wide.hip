@@ -235,11 +235,31 @@ __global__ __launch_bounds__(256) void k_worked_wide_finish(const FlatFeas feas,
                                                             const T *__restrict__ d, const double *__restrict__ rowp, int n_jt,
                                                             const double *__restrict__ colp, int n_it, T *__restrict__ da,
                                                             T *__restrict__ db, T *__restrict__ dc, T *__restrict__ dd, int I, int J,
-                                                            int c_ld, int n_d, int blocks_rows, int blocks_cols) {
+                                                            int c_ld, int n_d, int blocks_rows, int blocks_cols, int blocks_dd, int n_c) {
     constexpr int RP = K + 2;
     __shared__ double red[4][RP][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int blk = blockIdx.x;
+    if (blk >= blocks_rows + blocks_cols + blocks_dd) {
+        // dc is zero but for the first I elements of its diagonal, which the row blocks write
+        constexpr int V = 16 / (int)sizeof(T);
+        typedef T vec __attribute__((ext_vector_type(V)));
+        const unsigned at = ((unsigned)(blk - blocks_rows - blocks_cols - blocks_dd) * 256u + threadIdx.x) * V, step = (unsigned)c_ld + 1u;
+        if (at >= (unsigned)n_c) return;
+        const unsigned row = (at + step - 1) / step, diagonal = row < (unsigned)I ? row * step : 0xffffffffu;   // the first one from here on
+        if ((reinterpret_cast<uintptr_t>(dc) & 15) == 0 && at + V <= (unsigned)n_c && diagonal >= at + V) {
+            vec zero;
+#pragma unroll
+            for (int v = 0; v < V; ++v) zero[v] = T(0);
+            __builtin_nontemporal_store(zero, reinterpret_cast<vec *>(dc + at));
+        } else {
+            // (a row of one element: every element of c is on the diagonal's stride, step 2 -- more than one may be in here)
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (at + v < (unsigned)n_c && !((at + v) % step == 0 && (at + v) / step < (unsigned)I)) dc[at + v] = T(0);
+        }
+        return;
+    }
     if (blk < blocks_rows) {
         const int i = blk * 64 + lane;
         double acc[RP] = {};
@@ -324,14 +344,12 @@ static int bwd_k(const tad_plan &pl, const void *const *args, const void *f, con
     TAD_LAUNCH("k_worked_wide_backward", (k_worked_wide_backward<T, K>), dim3(g.n_jt, g.n_it), dim3(256), 0, s, (const T *)args[0],
                (const T *)args[1], (const T *)args[2], (const T *)f, (const T *)df, rowp, colp, I, J, c_ld, g.tile_rows);
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    if (dc) {   // after the read pass: a write burst right before it slows the reads down
-        TAD_LAUNCH("k_clear", (k_clear<T>), dim3(clear_blocks<T>(pl.arg_count[2])), dim3(256), 0, s, dc, (long long)pl.arg_count[2]);
-        if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    }
     const int br = (I + 63) / 64, bc = (J + 63) / 64, bd = (n_d + 63) / 64;
-    TAD_LAUNCH("k_worked_wide_finish", (k_worked_wide_finish<T, K>), dim3(br + bc + bd), dim3(256), 0, s, pl.fast.feas, pl.fast.flat[0],
+    // the zeros of dc in the same launch (behind the read pass: a write burst right before it slows the reads down)
+    const int n_c = (int)pl.arg_count[2], bz = dc ? (int)clear_blocks<T>(n_c) : 0;
+    TAD_LAUNCH("k_worked_wide_finish", (k_worked_wide_finish<T, K>), dim3(br + bc + bd + bz), dim3(256), 0, s, pl.fast.feas, pl.fast.flat[0],
                pl.fast.dd_iy, pl.fast.dd_iz, (const T *)args[2], (const T *)args[3], (const double *)rowp, g.n_jt, (const double *)colp,
-               g.n_it, (T *)dx[0], (T *)dx[1], dc, (T *)dx[3], I, J, c_ld, n_d, br, bc);
+               g.n_it, (T *)dx[0], (T *)dx[1], dc, (T *)dx[3], I, J, c_ld, n_d, br, bc, bd, n_c);
     return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
