@@ -79,7 +79,7 @@ int tad_eval_backward(const tad_plan *plan, const void *const *args_dev, const v
     bool any_wanted = false;
     for (size_t p = 0; p < plan->args.size(); ++p) any_wanted |= dx_dev[p] != nullptr;
     if (!any_wanted) return TAD_OK;
-    if (use_separable(*plan, ws_dev, ws_bytes)) return separable_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
+    if (use_separable(*plan, ws_dev, ws_bytes)) return separable_backward(*plan, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
     if (use_worked_wide(*plan, ws_dev, ws_bytes)) return worked_wide_backward(*plan, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
     if (use_pattern_wide(*plan, ws_dev, ws_bytes)) return pattern_wide_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
     void *rest[kMaxArgs];   // the gradients the dense products leave to the family
@@ -105,7 +105,7 @@ int tad_eval_backward(const tad_plan *plan, const void *const *args_dev, const v
     case TAD_FAMILY_ANTIDIAGONAL: return pattern_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
     case TAD_FAMILY_STRIDED: return strided_backward(*plan, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
     case TAD_FAMILY_CONTRACTION: return contract_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
-    case TAD_FAMILY_PROGRAM: return program_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
+    case TAD_FAMILY_PROGRAM: return program_backward(*plan, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
     default: return TAD_EUNSUPPORTED;
     }
 }

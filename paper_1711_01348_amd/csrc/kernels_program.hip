@@ -458,14 +458,17 @@ int program_forward(const tad_plan &pl, const void *const *args, void *f, void *
 }
 
 template <typename T>
-static int bwd_t(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws,
+static int bwd_t(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx, void *ws,
                  hipStream_t s) {
     // workspace: g = df * (d outer / d sum), then (only if the outer function reads operands) the sums themselves
-    T *const s_ws = pl.prog.outer_mask
+    // (not where the derivatives of the outer function can be written in f: that saves the sums)
+    T *const sums = pl.prog.outer_mask
                         ? reinterpret_cast<T *>(static_cast<char *>(ws) + align256((size_t)pl.f_count * sizeof(T)))
                         : nullptr;
-    int rc = fwd_t<T>(pl, args, df, ws, s_ws, ws, s);
+    const bool from_f = pl.expr.n_sum > 0 && outer_in_f(pl, pl.prog, dx);
+    const int rc = from_f ? program_outer(pl, pl.prog, pl.prog.douter_f, args, f, df, ws, s) : fwd_t<T>(pl, args, df, ws, sums, ws, s);
     if (rc) return rc;
+    const T *const s_ws = from_f ? static_cast<const T *>(f) : sums;
     ArgPtrs A{};
     for (size_t q = 0; q < pl.args.size(); ++q) A.p[q] = args[pl.root[q]];
     const int n_ops = (int)pl.args.size();
@@ -557,14 +560,15 @@ static int bwd_t(const tad_plan &pl, const void *const *args, const void *df, vo
         if (!in_outer) continue;
         if (!pl.ap_outer[q].derived) return TAD_EINVAL;
         const int no = (int)gather_launch_count(pl.ap_outer[q].dev, pl.arg_count[p]);
-        const int form_outer = program_form(has_register_form(pl.prog.douter_arg[q]), (double)pl.f_count / (double)(no > 0 ? no : 1));
+        const DevProg &douter_q = from_f ? pl.prog.douter_arg_f[q] : pl.prog.douter_arg[q];
+        const int form_outer = program_form(has_register_form(douter_q), (double)pl.f_count / (double)(no > 0 ? no : 1));
         const int add_outer = (q != p || !inner_zero || cleared) ? 1 : 0;
         if (use_cooperative_gather(no, (double)pl.f_count)) {
             const int splits = cooperative_splits(no, (double)pl.f_count);
             double *const partial = splits > 1 ? split_partial : nullptr;
             int32_t *const live = splits > 1 ? split_live(no, splits) : nullptr;
             TAD_LAUNCH_FORM(form_outer, "k_program_gather_outer_coop", k_program_gather_outer_coop, dim3(no, splits),
-                            dim3(256), 0, s, pl.ap_outer[q].dev, pl.prog.douter_arg[q], n_ops, pl.prog.outer_mask, A, s_ws,
+                            dim3(256), 0, s, pl.ap_outer[q].dev, douter_q, n_ops, pl.prog.outer_mask, A, s_ws,
                             static_cast<const T *>(df), static_cast<T *>(dx[p]), add_outer, partial, live);
             if (splits > 1) {
                 if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
@@ -573,7 +577,7 @@ static int bwd_t(const tad_plan &pl, const void *const *args, const void *df, vo
             }
         } else {
             TAD_LAUNCH_FORM(form_outer, "k_program_gather_outer", k_program_gather_outer, dim3((no + 255) / 256),
-                            dim3(256), 0, s, pl.ap_outer[q].dev, pl.prog.douter_arg[q], n_ops, pl.prog.outer_mask, A, s_ws,
+                            dim3(256), 0, s, pl.ap_outer[q].dev, douter_q, n_ops, pl.prog.outer_mask, A, s_ws,
                             static_cast<const T *>(df), static_cast<T *>(dx[p]), no, add_outer);
         }
         if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
@@ -581,9 +585,9 @@ static int bwd_t(const tad_plan &pl, const void *const *args, const void *df, vo
     return TAD_OK;
 }
 
-int program_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws,
+int program_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx, void *ws,
                      hipStream_t s) {
-    return pl.dtype == TAD_F64 ? bwd_t<double>(pl, args, df, dx, ws, s) : bwd_t<float>(pl, args, df, dx, ws, s);
+    return pl.dtype == TAD_F64 ? bwd_t<double>(pl, args, f, df, dx, ws, s) : bwd_t<float>(pl, args, f, df, dx, ws, s);
 }
 
 }  // namespace tad

@@ -206,16 +206,17 @@ static const void *factor(const SepSide &side, const void *const *args, const ch
 }
 
 template <typename T, typename TO>
-static int apply_outer(const tad_plan &pl, const DevProg &prog, const void *const *args, const T *sum, const void *df, TO *out, hipStream_t s) {
+static int apply_outer(const tad_plan &pl, const ProgramBody &pb, const DevProg &prog, const void *const *args, const T *sum, const void *df,
+                       TO *out, hipStream_t s) {
     const int n = (int)pl.f_count;
     ArgPtrs A{};
-    for (size_t q = 0; q < pl.args.size(); ++q) A.p[q] = args[q];
+    for (size_t q = 0; q < pl.args.size(); ++q) A.p[q] = args[pl.root[q]];
     const dim3 grid((n + 255) / 256), block(256);
     if (has_register_form(prog))
-        TAD_LAUNCH("k_sep_outer", (k_sep_outer<T, TO, 1>), grid, block, 0, s, pl.fwd, prog, (int)pl.args.size(), pl.sep.prog.outer_mask, A,
+        TAD_LAUNCH("k_sep_outer", (k_sep_outer<T, TO, 1>), grid, block, 0, s, pl.fwd, prog, (int)pl.args.size(), pb.outer_mask, A,
                    sum, static_cast<const T *>(df), out, n);
     else
-        TAD_LAUNCH("k_sep_outer", (k_sep_outer<T, TO, 0>), grid, block, 0, s, pl.fwd, prog, (int)pl.args.size(), pl.sep.prog.outer_mask, A,
+        TAD_LAUNCH("k_sep_outer", (k_sep_outer<T, TO, 0>), grid, block, 0, s, pl.fwd, prog, (int)pl.args.size(), pb.outer_mask, A,
                    sum, static_cast<const T *>(df), out, n);
     return launched();
 }
@@ -247,7 +248,7 @@ static int sums(const tad_plan &pl, const DevProg *prog, const void *const *args
     if (prog) j.c = sum;
     rc = product_run(j, ws + sp.part_offset, s);
     if (rc || !prog) return rc;
-    return apply_outer<T, T>(pl, *prog, args, sum, df, static_cast<T *>(out), s);
+    return apply_outer<T, T>(pl, sp.prog, *prog, args, sum, df, static_cast<T *>(out), s);
 }
 
 template <typename TI, typename T>
@@ -290,22 +291,31 @@ static int forward_t(const tad_plan &pl, const void *const *args, void *f, char 
 }
 
 template <typename T>
-static int backward_t(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, char *ws, hipStream_t s) {
+static int backward_t(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx, char *ws, hipStream_t s) {
     const SepPlan &sp = pl.sep;
     constexpr bool f64 = sizeof(T) == 8;
     const int n_ops = (int)pl.args.size();
     char *const part = ws + sp.part_offset;
-    T *sum = nullptr;   // the sums themselves: for the terms of operands of the outer function that are not g
-    for (int q = 0; q < n_ops; ++q)
-        if (dx[q] && ((sp.prog.outer_mask >> q) & 1u) && !sp.term_is_g[q]) sum = reinterpret_cast<T *>(ws + sp.s_offset);
-    const T *g = static_cast<const T *>(df);
+    const T *g = static_cast<const T *>(df), *sum = nullptr;
+    // the derivatives of the outer function are those of f where they can be: that saves the sums
+    const bool from_f = outer_in_f(pl, sp.prog, dx);
     int rc;
-    if (!sp.identity) {
-        T *const gw = reinterpret_cast<T *>(ws + sp.g_offset);
-        rc = sums<T>(pl, &sp.prog.douter, args, df, gw, sum, ws, s);
-        g = gw;
-    } else {
+    if (sp.identity || from_f) {
         rc = evaluate_factors<T>(sp, args, ws, s);
+        if (!rc && !sp.identity) {
+            T *const gw = reinterpret_cast<T *>(ws + sp.g_offset);
+            sum = static_cast<const T *>(f);
+            rc = apply_outer<T, T>(pl, sp.prog, sp.prog.douter_f, args, sum, df, gw, s);
+            g = gw;
+        }
+    } else {
+        T *s_out = nullptr;   // the sums themselves: for the terms of operands of the outer function that are not g
+        for (int q = 0; q < n_ops; ++q)
+            if (dx[q] && ((sp.prog.outer_mask >> q) & 1u) && !sp.term_is_g[q]) s_out = reinterpret_cast<T *>(ws + sp.s_offset);
+        T *const gw = reinterpret_cast<T *>(ws + sp.g_offset);
+        rc = sums<T>(pl, &sp.prog.douter, args, df, gw, s_out, ws, s);
+        g = gw;
+        sum = s_out;
     }
     if (rc) return rc;
     // the derivatives of the factors
@@ -372,13 +382,13 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *d
             continue;
         }
         // an operand of the outer function: the terms df * d outer / d x, which are g where the outer function adds it to the sum
-        const DevProg &prog = sp.prog.douter_arg[q];
+        const DevProg &prog = from_f ? sp.prog.douter_arg_f[q] : sp.prog.douter_arg[q];
         const int add = stored[q] ? 1 : 0;
         if (sp.term_is_g[q]) {
             rc = sum_through_plan(pl.ap_outer[q].dev, pl.arg_count[q], (double)pl.f_count, g, static_cast<T *>(dx[q]), add, part, s);
         } else {
             double *const h = reinterpret_cast<double *>(ws + sp.h_offset);
-            rc = apply_outer<T, double>(pl, prog, args, sum, df, h, s);
+            rc = apply_outer<T, double>(pl, sp.prog, prog, args, sum, df, h, s);
             if (rc) return rc;
             rc = sum_through_plan(pl.ap_outer[q].dev, pl.arg_count[q], (double)pl.f_count, (const double *)h, static_cast<T *>(dx[q]), add, part, s);
         }
@@ -392,9 +402,23 @@ int separable_forward(const tad_plan &pl, const void *const *args, void *f, void
                                : forward_t<float>(pl, args, f, static_cast<char *>(ws), s);
 }
 
-int separable_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws, hipStream_t s) {
-    return pl.dtype == TAD_F64 ? backward_t<double>(pl, args, df, dx, static_cast<char *>(ws), s)
-                               : backward_t<float>(pl, args, df, dx, static_cast<char *>(ws), s);
+int separable_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx, void *ws, hipStream_t s) {
+    return pl.dtype == TAD_F64 ? backward_t<double>(pl, args, f, df, dx, static_cast<char *>(ws), s)
+                               : backward_t<float>(pl, args, f, df, dx, static_cast<char *>(ws), s);
+}
+
+int program_outer(const tad_plan &pl, const ProgramBody &pb, const DevProg &prog, const void *const *args, const void *s, const void *df,
+                  void *out, hipStream_t stream) {
+    return pl.dtype == TAD_F64
+               ? apply_outer<double, double>(pl, pb, prog, args, static_cast<const double *>(s), df, static_cast<double *>(out), stream)
+               : apply_outer<float, float>(pl, pb, prog, args, static_cast<const float *>(s), df, static_cast<float *>(out), stream);
+}
+
+bool outer_in_f(const tad_plan &pl, const ProgramBody &pb, void *const *dx) {
+    uint32_t need = 1u << TAD_MAX_ARGS;
+    for (size_t q = 0; q < pl.args.size(); ++q)
+        if (dx[pl.root[q]] && ((pb.outer_mask >> q) & 1u)) need |= 1u << q;
+    return (pb.in_f & need) == need;
 }
 
 }  // namespace tad

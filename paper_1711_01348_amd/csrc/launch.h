@@ -68,10 +68,15 @@ int product_run_outer(const ProductJob &j, const ProductOuter &o, hipStream_t s)
 
 // sums of products of two functions (separable.hpp)
 int separable_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
-int separable_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws, hipStream_t s);
+int separable_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx, void *ws, hipStream_t s);
 
 int program_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
-int program_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws,
+// out = prog(s, operands), times df if that is given, for every function element; pb: the body `prog` belongs to
+int program_outer(const tad_plan &pl, const ProgramBody &pb, const DevProg &prog, const void *const *args, const void *s, const void *df,
+                  void *out, hipStream_t stream);
+// Can the derivatives of the outer function that these gradients need be written in f?
+bool outer_in_f(const tad_plan &pl, const ProgramBody &pb, void *const *dx);
+int program_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx, void *ws,
                      hipStream_t s);
 
 }  // namespace tad

@@ -457,7 +457,27 @@ struct ProgramBody {
     DevProg douter;                  // d outer / d sum
     DevProg douter_arg[TAD_MAX_ARGS];   // d outer / d operand p (identically zero unless the outer program reads p)
     uint32_t outer_mask = 0;         // operands the outer program reads
+    // The derivatives of the outer function written in its result f instead of the sum (tanh: 1 - f^2): the same operations on
+    // the same values, f taking the place of the sum operand.  Bit p: d outer / d operand p, bit TAD_MAX_ARGS: d outer / d sum.
+    DevProg douter_f, douter_arg_f[TAD_MAX_ARGS];
+    uint32_t in_f = 0;
 };
+
+// `node` of graph g as a program that reads the value of node `result` as its sum operand; false if it needs the sum itself.
+inline bool lower_in_result(const Graph &g, int result, int node, DevProg &out) {
+    if (node < 0) return lower(g, node, out);
+    Graph h = g;
+    result = simplify(g)[result];
+    if (g.nodes[result].op == P_SUM) return lower(g, node, out);
+    constexpr int kTheSum = 100;   // no operand has this number
+    for (Node &nd : h.nodes)
+        if (nd.op == P_SUM) nd = Node{P_ARG, -1, -1, kTheSum};
+    h.nodes[result] = Node{P_SUM};
+    if (!lower(h, node, out)) return false;
+    for (int i = 0; i < out.n; ++i)
+        if (out.op[i] == P_ARG && out.a[i] == kTheSum) return false;
+    return true;
+}
 
 // Parse, differentiate and lower both programs of an expression.  `outer_operands`: operands the outer program
 // may read; `wanted`: operands whose gradient will be asked for (the derivatives with respect to the others are
@@ -484,6 +504,10 @@ inline int build_program_body(const tad_expr &e, ProgramBody &pb, uint32_t outer
     if (!lower(go, wanted ? grads[e.n_operands] : -1, pb.douter)) return TAD_EUNSUPPORTED;
     for (int p = 0; p < e.n_operands; ++p)
         if (!lower(go, ((wanted >> p) & 1u) ? grads[p] : -1, pb.douter_arg[p])) return TAD_EUNSUPPORTED;
+    pb.in_f = 0;
+    for (int p = 0; p < e.n_operands; ++p)
+        if (lower_in_result(go, ro, ((wanted >> p) & 1u) ? grads[p] : -1, pb.douter_arg_f[p])) pb.in_f |= 1u << p;
+    if (lower_in_result(go, ro, wanted ? grads[e.n_operands] : -1, pb.douter_f)) pb.in_f |= 1u << TAD_MAX_ARGS;
     return TAD_OK;
 }
 
