@@ -29,9 +29,9 @@ int static_scratch(void **out) {
     *out = g_scratch_ptr[dev];
     return TAD_OK;
 }
-// Paths that keep 64-bit values in the workspace; with a smaller or oddly aligned one the family's kernels run.
+// Paths that keep 64-bit values or whole vectors in the workspace; with a smaller or oddly aligned one the family's kernels run.
 bool room(const tad_plan &pl, const void *ws, size_t ws_bytes) {
-    return ws_bytes >= pl.ws_full && (ws || pl.ws_full == 0) && (reinterpret_cast<uintptr_t>(ws) & 7) == 0;
+    return ws_bytes >= pl.ws_full && (ws || pl.ws_full == 0) && (reinterpret_cast<uintptr_t>(ws) & 15) == 0;
 }
 bool use_separable(const tad_plan &pl, const void *ws, size_t ws_bytes) { return pl.sep.on && room(pl, ws, ws_bytes); }
 bool use_worked_wide(const tad_plan &pl, const void *ws, size_t ws_bytes) { return pl.worked_wide && room(pl, ws, ws_bytes); }
@@ -61,7 +61,7 @@ int tad_eval_forward(const tad_plan *plan, const void *const *args_dev, void *f_
     case TAD_FAMILY_DIAGONAL:
     case TAD_FAMILY_ANTIDIAGONAL: return pattern_forward(*plan, args_dev, f_dev, s);
     case TAD_FAMILY_STRIDED: return strided_forward(*plan, args_dev, f_dev, s);
-    case TAD_FAMILY_CONTRACTION: return contract_forward(*plan, args_dev, f_dev, ws_dev, s);
+    case TAD_FAMILY_CONTRACTION: return contract_forward(*plan, args_dev, f_dev, ws_dev, plan->split && room(*plan, ws_dev, ws_bytes), s);
     case TAD_FAMILY_PROGRAM: return program_forward(*plan, args_dev, f_dev, ws_dev, s);
     default: return TAD_EUNSUPPORTED;
     }
@@ -104,7 +104,7 @@ int tad_eval_backward(const tad_plan *plan, const void *const *args_dev, const v
     case TAD_FAMILY_DIAGONAL:
     case TAD_FAMILY_ANTIDIAGONAL: return pattern_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
     case TAD_FAMILY_STRIDED: return strided_backward(*plan, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
-    case TAD_FAMILY_CONTRACTION: return contract_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
+    case TAD_FAMILY_CONTRACTION: return contract_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, plan->split && room(*plan, ws_dev, ws_bytes), s);
     case TAD_FAMILY_PROGRAM: return program_backward(*plan, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
     default: return TAD_EUNSUPPORTED;
     }

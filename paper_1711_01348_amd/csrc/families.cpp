@@ -8,6 +8,7 @@
 #include "launch_geom.h"
 #include "product_match.hpp"
 #include "separable_match.hpp"
+#include "split.h"
 
 namespace tad {
 
@@ -354,6 +355,7 @@ static void select_specialised(tad_plan &plan) {
 }
 
 static void reserve_partial_sums(tad_plan &plan);
+static void select_split(tad_plan &plan);
 
 void select_families(tad_plan &plan) {
     select_specialised(plan);
@@ -361,6 +363,7 @@ void select_families(tad_plan &plan) {
     match_product(plan);
     plan.prod.ws_offset = align256(plan.ws_bytes);
     plan.ws_full = plan.prod.on && plan.prod.ws_bytes ? plan.prod.ws_offset + plan.prod.ws_bytes : plan.ws_bytes;
+    select_split(plan);
     match_separable(plan);
     if (plan.sep.on) plan.ws_full = std::max(plan.ws_bytes, plan.sep.ws_bytes);   // one or the other
 }
@@ -400,6 +403,15 @@ void select_wide(tad_plan &plan) {
     if ((plan.flags & TAD_PLAN_GENERIC_ONLY) || plan.has_alias || plan.expr.n_constraints > 0 || !plan.term_list.empty()) return;
     select_worked_wide(plan);
     select_pattern_wide(plan);
+}
+
+static void select_split(tad_plan &plan) {
+    if (plan.fwd_family != TAD_FAMILY_CONTRACTION) return;
+    for (const GemmDesc &g : plan.fast.gemm)
+        if (split_pays(g.M, g.N, g.Kc)) {
+            plan.split = true;
+            plan.ws_full = std::max(plan.ws_full, split_geom(g.M, g.N, g.Kc).bytes);
+        }
 }
 
 static void reserve_partial_sums(tad_plan &plan) {

@@ -24,6 +24,9 @@
 // output tiles and a long contraction index is cut along that index (blockIdx.y): every piece writes its partial
 // product to the workspace and k_contract_reduce adds the pieces in a fixed order.
 //
+// Large products run on the bf16 matrix cores first (kernels_split.hip); this kernel then only does those whose operands are out of
+// the range that takes.
+//
 // MFMA operand layout (wave64): A operand lane l = A[m = l % 32][k = l / 32], B operand lane l = B[k = l / 32][n = l % 32],
 // result register r of lane l = D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
 #include <hip/hip_runtime.h>
@@ -32,6 +35,7 @@
 
 #include "launch.h"
 #include "profile.h"
+#include "split.h"
 
 namespace tad {
 
@@ -61,7 +65,8 @@ __device__ __forceinline__ void tile_of_block(int gm, int gn, int &tm, int &tn) 
 template <bool AT, bool BT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_contract(const float *__restrict__ a, const float *__restrict__ b, float *__restrict__ c, int M, int N, int Kc,
-                int lda, int ldb, int gm, int gn, int chunk, int lean_ok) {
+                int lda, int ldb, int gm, int gn, int chunk, int lean_ok, const int *__restrict__ range) {
+    if (range && split_in_range(range)) return;   // done on the bf16 matrix cores
     __shared__ __attribute__((aligned(16))) float smem[4 * CT_TILE];   // two sets of (A tile, B tile); reused as the output stage in the epilogue
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -286,7 +291,7 @@ __global__ __launch_bounds__(256) void k_contract_reduce(const float *__restrict
     reinterpret_cast<float4c *>(c)[i] = acc;
 }
 
-static int launch_gemm(const GemmDesc &g, const float *a, const float *b, float *c, float *ws, hipStream_t s) {
+static int launch_gemm(const GemmDesc &g, const float *a, const float *b, float *c, float *ws, const int *range, hipStream_t s) {
     const int gm = (g.M + 127) / 128, gn = (g.N + 127) / 128;
     const int pieces = (g.splits > 1 && ws) ? g.splits : 1;
     // whole tiles per piece; the last piece may be shorter, none is empty
@@ -297,13 +302,13 @@ static int launch_gemm(const GemmDesc &g, const float *a, const float *b, float 
     const int lean_ok = (long long)g.lda * 128 * 4 < (1ll << 31) && (long long)g.ldb * 128 * 4 < (1ll << 31) ? 1 : 0;
     float *dst = used > 1 ? ws : c;
     if (!g.at && !g.bt)
-        TAD_LAUNCH("k_contract", (k_contract<false, false>), grid, block, 0, s, a, b, dst, g.M, g.N, g.Kc, g.lda, g.ldb, gm, gn, chunk, lean_ok);
+        TAD_LAUNCH("k_contract", (k_contract<false, false>), grid, block, 0, s, a, b, dst, g.M, g.N, g.Kc, g.lda, g.ldb, gm, gn, chunk, lean_ok, range);
     else if (!g.at && g.bt)
-        TAD_LAUNCH("k_contract", (k_contract<false, true>), grid, block, 0, s, a, b, dst, g.M, g.N, g.Kc, g.lda, g.ldb, gm, gn, chunk, lean_ok);
+        TAD_LAUNCH("k_contract", (k_contract<false, true>), grid, block, 0, s, a, b, dst, g.M, g.N, g.Kc, g.lda, g.ldb, gm, gn, chunk, lean_ok, range);
     else if (g.at && !g.bt)
-        TAD_LAUNCH("k_contract", (k_contract<true, false>), grid, block, 0, s, a, b, dst, g.M, g.N, g.Kc, g.lda, g.ldb, gm, gn, chunk, lean_ok);
+        TAD_LAUNCH("k_contract", (k_contract<true, false>), grid, block, 0, s, a, b, dst, g.M, g.N, g.Kc, g.lda, g.ldb, gm, gn, chunk, lean_ok, range);
     else
-        TAD_LAUNCH("k_contract", (k_contract<true, true>), grid, block, 0, s, a, b, dst, g.M, g.N, g.Kc, g.lda, g.ldb, gm, gn, chunk, lean_ok);
+        TAD_LAUNCH("k_contract", (k_contract<true, true>), grid, block, 0, s, a, b, dst, g.M, g.N, g.Kc, g.lda, g.ldb, gm, gn, chunk, lean_ok, range);
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
     if (used > 1) {
         const long long n4 = (long long)g.M * g.N / 4;
@@ -313,20 +318,29 @@ static int launch_gemm(const GemmDesc &g, const float *a, const float *b, float 
     return TAD_OK;
 }
 
-// source -1 of a product is df, destination -1 is f
-int contract_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s) {
-    const GemmDesc &g = pl.fast.gemm[0];
-    return launch_gemm(g, (const float *)args[g.a_src], (const float *)args[g.b_src], (float *)f, (float *)ws, s);
+static int run_gemm(const GemmDesc &g, const float *a, const float *b, float *c, void *ws, bool full, hipStream_t s) {
+    const int *range = nullptr;
+    if (full && split_pays(g.M, g.N, g.Kc)) {
+        const int rc = split_product(g, a, b, c, ws, &range, s);
+        if (rc) return rc;
+    }
+    return launch_gemm(g, a, b, c, (float *)ws, range, s);
 }
 
-int contract_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws,
+// source -1 of a product is df, destination -1 is f; full: the workspace holds the parts of the products' operands
+int contract_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, bool full, hipStream_t s) {
+    const GemmDesc &g = pl.fast.gemm[0];
+    return run_gemm(g, (const float *)args[g.a_src], (const float *)args[g.b_src], (float *)f, ws, full, s);
+}
+
+int contract_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws, bool full,
                       hipStream_t s) {
     for (int q = 1; q <= 2; ++q) {
         const GemmDesc &g = pl.fast.gemm[q];
         if (!dx[g.out]) continue;
         const float *a = g.a_src < 0 ? (const float *)df : (const float *)args[g.a_src];
         const float *b = g.b_src < 0 ? (const float *)df : (const float *)args[g.b_src];
-        const int rc = launch_gemm(g, a, b, (float *)dx[g.out], (float *)ws, s);   // the products share the workspace in turn
+        const int rc = run_gemm(g, a, b, (float *)dx[g.out], ws, full, s);   // the products share the workspace in turn
         if (rc) return rc;
     }
     return TAD_OK;

@@ -1,0 +1,254 @@
+// Large 32-bit matrix products on the bf16 matrix cores, to no less than 32-bit precision.
+//
+// A 32-bit number is the sum of three bf16 numbers, x = x1 + x2 + x3 (8 + 8 + 8 bits of the significand, each the nearest to what
+// the ones before leave), and x y = x1 y1 + (x1 y2 + x2 y1) + (x1 y3 + x2 y2 + x3 y1) up to 2^-26 x y: six products of bf16
+// numbers, exact in 32 bits, accumulated in 32 bits.  v_mfma_f32_32x32x16_bf16 does sixteen times the work of v_mfma_f32_32x32x2f32
+// per cycle, so six of them take 0.375 of the time; it rounds the accumulator once per sixteen terms, and the error against
+// 64 bits is below that of the 32-bit instructions (4096 x 4096 x 4096: 1.0e-6 against 1.1e-6).  There 605 us per product, 1.36 PFLOP/s
+// of bf16 work, 227 TFLOP/s of 32-bit work where the 32-bit instructions end at 157; bound by the matrix cores and their power.
+//
+// Two passes.  k_split_planes (68 us for both operands there, 4.7 TB/s) writes the three parts of an operand fragment by fragment, in the order in which a wavefront
+// feeds them to the matrix cores ([16 terms][32 rows][part][lane][8 terms]), with zeros beyond the edges: the product then copies
+// contiguous memory to LDS, reads LDS without conflicts, and has no edge cases but its stores.  k_split_product: workgroup
+// tile 256 x 128, four wavefronts of 128 x 64, 36 KB of parts per 16 terms in two sets; a stage is 48 matrix instructions per
+// wavefront against 18 LDS reads and 9 loads and stores of 16 bytes.
+//
+// The parts of a very small number, or of products of small numbers, leave the range of normal numbers, and an infinity has no parts:
+// the first pass also finds the smallest and largest exponent of either operand, and outside the safe range the product leaves
+// its work to the 32-bit kernel, which is launched behind it and returns at once otherwise.
+#include <hip/hip_runtime.h>
+
+#include "launch.h"
+#include "profile.h"
+#include "split.h"
+
+namespace tad {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float float4s_ __attribute__((ext_vector_type(4)));
+typedef float float16s __attribute__((ext_vector_type(16)));
+typedef unsigned piece __attribute__((ext_vector_type(4)));   // 16 bytes
+
+// One operand.  turned: element (row, q) at src[q * ld + row], else at src[row * ld + q]; R, Q and ld are multiples of four.
+struct SplitOperand {
+    const float *src;
+    bf16x8 *out;
+    int R, Q, ld, turned, row_blocks;
+};
+struct SplitPass {
+    SplitOperand op[2];
+    int q_blocks, q_groups;   // fragments along the terms, groups of 16 of them
+    int first;                // workgroups of the first operand
+    int *seen;                // per workgroup: smallest and largest exponent
+};
+
+// A wavefront writes four fragments of 32 rows and 16 terms, a workgroup sixteen along the terms: 1 KB of a row.
+__global__ __launch_bounds__(256) void k_split_planes(const SplitPass P) {
+    __shared__ int red[2][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool second = (int)blockIdx.x >= P.first;
+    const SplitOperand &o = P.op[second ? 1 : 0];
+    const int id = (int)blockIdx.x - (second ? P.first : 0), rb = id / P.q_groups, group = id - rb * P.q_groups;
+    const int row = rb * 32 + (lane & 31);
+    int lo = 255, hi = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int qb = group * 16 + wave * 4 + k, q = qb * 16 + 8 * (lane >> 5);
+        if (qb >= P.q_blocks) break;   // the same for the wavefront
+        float v[8];
+        if (!o.turned) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float4s_ z = {0.f, 0.f, 0.f, 0.f};
+                const float4s_ x = row < o.R && q + 4 * h < o.Q ? *reinterpret_cast<const float4s_ *>(o.src + (size_t)row * o.ld + q + 4 * h) : z;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * h + e] = x[e];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = row < o.R && q + e < o.Q ? o.src[(size_t)(q + e) * o.ld + row] : 0.f;
+        }
+        bf16x8 p1, p2, p3;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const unsigned u = __float_as_uint(v[e]) & 0x7fffffffu;
+            const int ex = (int)(u >> 23);
+            lo = min(lo, u ? ex : 255);
+            hi = max(hi, ex);   // (zero: exponent 0)
+            p1[e] = (__bf16)v[e];
+            const float r1 = v[e] - (float)p1[e];
+            p2[e] = (__bf16)r1;
+            p3[e] = (__bf16)(r1 - (float)p2[e]);
+        }
+        bf16x8 *to = o.out + ((size_t)qb * o.row_blocks + rb) * 192 + lane;
+        to[0] = p1;
+        to[64] = p2;
+        to[128] = p3;
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        lo = min(lo, __shfl_xor(lo, m, 64));
+        hi = max(hi, __shfl_xor(hi, m, 64));
+    }
+    if (lane == 0) {
+        red[0][wave] = lo;
+        red[1][wave] = hi;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        P.seen[2 * blockIdx.x] = min(min(red[0][0], red[0][1]), min(red[0][2], red[0][3]));
+        P.seen[2 * blockIdx.x + 1] = max(max(red[1][0], red[1][1]), max(red[1][2], red[1][3]));
+    }
+}
+
+// range[0..3]: smallest and largest exponent of the first operand, of the second one
+__global__ __launch_bounds__(1024) void k_split_range(const int *__restrict__ seen, int first, int total, int *range) {
+    __shared__ int red[4][16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int v[4] = {255, 0, 255, 0};
+    for (int i = threadIdx.x; i < total; i += 1024) {
+        const int lo = seen[2 * i], hi = seen[2 * i + 1];
+        if (i < first) { v[0] = min(v[0], lo); v[1] = max(v[1], hi); }
+        else { v[2] = min(v[2], lo); v[3] = max(v[3], hi); }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) {
+            const int o = __shfl_xor(v[q], m, 64);
+            v[q] = q & 1 ? max(v[q], o) : min(v[q], o);
+        }
+        if (lane == 0) red[q][wave] = v[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int q = threadIdx.x;
+        int x = red[q][0];
+        for (int w = 1; w < 16; ++w) x = q & 1 ? max(x, red[q][w]) : min(x, red[q][w]);
+        range[q] = x;
+    }
+}
+
+__device__ __forceinline__ void split_tile(int gm, int gn, int &tm, int &tn) {
+    // the dies take workgroups in turn: each gets a contiguous range of tiles, in groups of four tile rows
+    const int total = gm * gn;
+    int lid = blockIdx.x;
+    if (total % 8 == 0) lid = (lid % 8) * (total / 8) + lid / 8;
+    const int group = 4 * gn, g0 = (lid / group) * 4, rows = min(4, gm - g0), in = lid - (lid / group) * group;
+    tm = g0 + in % rows;
+    tn = in / rows;
+}
+
+__global__ __launch_bounds__(256, 2) void k_split_product(const piece *__restrict__ a, const piece *__restrict__ b, float *__restrict__ c, int M,
+                                                          int N, int q_blocks, int gm, int gn, const int *__restrict__ range) {
+    if (!split_in_range(range)) return;   // the same for the whole launch
+    constexpr int PA = 8 * 192, PB = 4 * 192, STAGE = PA + PB;   // 16-byte pieces of a stage
+    __shared__ piece smem[2 * STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+    int tm, tn;
+    split_tile(gm, gn, tm, tn);
+    // the pieces of a stage are contiguous in either operand
+    const piece *pa = a + (size_t)tm * PA + tid, *pb = b + (size_t)tn * PB + tid;
+    const unsigned next_a = (unsigned)gm * PA, next_b = (unsigned)gn * PB;
+    piece reg[9];
+    auto load = [&]() {
+#pragma unroll
+        for (int p = 0; p < 9; ++p) reg[p] = p < 6 ? pa[256 * p] : pb[256 * (p - 6)];
+        pa += next_a;
+        pb += next_b;
+    };
+    auto stage = [&](int set) {
+#pragma unroll
+        for (int p = 0; p < 9; ++p) smem[set * STAGE + tid + 256 * p] = reg[p];
+    };
+    float16s acc[4][2];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
+    const int fa = wm * 4 * 192 + lane, fb = PA + wn * 2 * 192 + lane;
+    load();
+    stage(0);
+    if (q_blocks > 1) load();
+    __syncthreads();
+    auto step = [&](int t, int set) {
+        const bf16x8 *S = reinterpret_cast<const bf16x8 *>(smem) + set * STAGE;
+        bf16x8 bv[2][3], av[3];
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int s = 0; s < 3; ++s) bv[y][s] = S[fb + y * 192 + s * 64];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) av[s] = S[fa + s * 64];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            bf16x8 next[3];
+            if (x < 3)
+#pragma unroll
+                for (int s = 0; s < 3; ++s) next[s] = S[fa + (x + 1) * 192 + s * 64];
+            if (x == 1 && t + 1 < q_blocks) stage(set ^ 1);   // the same for the whole workgroup
+            if (x == 2 && t + 2 < q_blocks) load();
+            __builtin_amdgcn_sched_barrier(0);
+            // small products first
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[2], bv[y][0], acc[x][y], 0, 0, 0);
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[0], bv[y][2], acc[x][y], 0, 0, 0);
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[1], bv[y][1], acc[x][y], 0, 0, 0);
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[1], bv[y][0], acc[x][y], 0, 0, 0);
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[0], bv[y][1], acc[x][y], 0, 0, 0);
+#pragma unroll
+            for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[0], bv[y][0], acc[x][y], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (x < 3)
+#pragma unroll
+                for (int s = 0; s < 3; ++s) av[s] = next[s];
+        }
+        __syncthreads();
+    };
+    for (int t = 0; t < q_blocks; t += 2) {
+        step(t, 0);
+        if (t + 1 < q_blocks) step(t + 1, 1);
+    }
+    // result register r of lane l = D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32]
+    const int m0 = tm * 256 + wm * 128 + 4 * (lane >> 5), n0 = tn * 128 + wn * 64 + (lane & 31);
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int m = m0 + x * 32 + 8 * (r >> 2) + (r & 3), n = n0 + y * 32;
+                if (m < M && n < N) c[(size_t)m * N + n] = acc[x][y][r];
+            }
+}
+
+int split_product(const GemmDesc &g, const float *a, const float *b, float *c, void *ws, const int **range_out, hipStream_t s) {
+    const SplitGeom q = split_geom(g.M, g.N, g.Kc);
+    char *w = static_cast<char *>(ws);
+    int *const range = reinterpret_cast<int *>(w);
+    bf16x8 *const pa = reinterpret_cast<bf16x8 *>(w + q.a_offset), *const pb = reinterpret_cast<bf16x8 *>(w + q.b_offset);
+    SplitPass P;
+    P.q_blocks = q.q_blocks;
+    P.q_groups = (q.q_blocks + 15) / 16;
+    P.op[0] = SplitOperand{a, pa, g.M, g.Kc, g.lda, g.at, q.gm * 8};
+    P.op[1] = SplitOperand{b, pb, g.N, g.Kc, g.ldb, !g.bt, q.gn * 4};
+    P.first = P.op[0].row_blocks * P.q_groups;
+    const int total = P.first + P.op[1].row_blocks * P.q_groups;
+    P.seen = reinterpret_cast<int *>(w + 256);
+    TAD_LAUNCH("k_split_planes", k_split_planes, dim3(total), dim3(256), 0, s, P);
+    if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
+    TAD_LAUNCH("k_split_range", k_split_range, dim3(1), dim3(1024), 0, s, (const int *)P.seen, P.first, total, range);
+    if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
+    TAD_LAUNCH("k_split_product", k_split_product, dim3(q.gm * q.gn), dim3(256), 0, s, reinterpret_cast<const piece *>(pa),
+               reinterpret_cast<const piece *>(pb), c, g.M, g.N, q.q_blocks, q.gm, q.gn, (const int *)range);
+    *range_out = range;
+    return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
+}
+
+}  // namespace tad

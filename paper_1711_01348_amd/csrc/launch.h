@@ -37,9 +37,10 @@ int strided_forward(const tad_plan &pl, const void *const *args, void *f, hipStr
 int strided_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df,
                      void *const *dx, void *ws, hipStream_t s);
 
-int contract_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
-int contract_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws,
-                      hipStream_t s);
+int contract_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, bool full, hipStream_t s);
+int contract_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws, bool full, hipStream_t s);
+// one of their products on the bf16 matrix cores; *range: what the 32-bit kernel looks at to see whether it is still to be done
+int split_product(const GemmDesc &g, const float *a, const float *b, float *c, void *ws, const int **range, hipStream_t s);
 
 // Sums of products as dense products.  product_backward writes the gradients it is responsible for and clears their
 // entries of dx; the rest is left to the family's kernels.

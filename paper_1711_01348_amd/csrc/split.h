@@ -1,0 +1,41 @@
+// Products of 32-bit matrices on the bf16 matrix cores (kernels_split.hip): geometry and the range of operands they take.
+#pragma once
+#include <cstddef>
+#include <cstdint>
+
+#include "launch_geom.h"
+
+namespace tad {
+
+struct SplitGeom {
+    int gm, gn, q_blocks;               // tiles of 256 and 128 rows, fragments of 16 terms
+    size_t a_offset, b_offset, bytes;   // workspace: exponents, parts of A, parts of B
+};
+inline SplitGeom split_geom(int64_t M, int64_t N, int64_t K) {
+    SplitGeom g;
+    g.gm = (int)((M + 255) / 256);
+    g.gn = (int)((N + 127) / 128);
+    g.q_blocks = (int)((K + 15) / 16);
+    g.a_offset = 256 + align256((size_t)(g.gm * 8 + g.gn * 4) * (size_t)((g.q_blocks + 15) / 16) * 8);
+    g.b_offset = g.a_offset + (size_t)g.gm * 8 * g.q_blocks * 3072;
+    g.bytes = g.b_offset + (size_t)g.gn * 4 * g.q_blocks * 3072;
+    return g;
+}
+// A tile for every compute unit (one round of tiles takes as long however few they are), and a sum long enough for the passes
+// around the product: splitting, which moves ten bytes per element of the operands, and two short launches.  Split against 32-bit
+// kernel: 4096 x 4096 x 4096 675 / 1030 us, 4096 x 4096 x 1024 188 / 258 us, 4096 x 2048 x 512 75 / 70 us.
+inline bool split_pays(int64_t M, int64_t N, int64_t K) {
+    const SplitGeom g = split_geom(M, N, K);
+    return (int64_t)g.gm * g.gn >= 256 && K >= 1024;
+}
+
+#if defined(__HIPCC__)
+// Every part of every number and every product of parts is zero or a normal number, and no sum overflows for a product that does
+// not: exponents (biased by 127) of the non-zero elements.  range: smallest and largest of A, of B.
+__device__ __forceinline__ bool split_in_range(const int *range) {
+    const int a0 = range[0], a1 = range[1], b0 = range[2], b1 = range[3];
+    return a0 >= 27 && b0 >= 27 && a0 + b0 >= 2 * 127 - 90 && a1 <= 227 && b1 <= 227 && a1 + b1 <= 2 * 127 + 100;
+}
+#endif
+
+}  // namespace tad

@@ -1,0 +1,71 @@
+"""Large 32-bit products on the bf16 matrix cores: no further from 64 bits than the 32-bit kernel, and left to it where the parts
+of the operands do not fit."""
+import ctypes
+
+import pytest
+
+from paper_1711_01348_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def plan_and_tensors(I, J, K, xt=False, yt=False):
+    import torch
+    from paper_1711_01348_amd import binding as B
+    expr = wl.matmul_expr(I, J, K, "f32", xt, yt)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(I + J + K)
+    draw = lambda shape: torch.rand(shape, generator=gen, device="cuda") * 2 - 1
+    return B.Plan(expr), [draw(a.shape) for a in expr.args], draw((I, J))
+
+
+def evaluate(plan, args, df, ws_bytes):
+    """Forward and gradients with ws_bytes of workspace, everything behind it watched."""
+    import torch
+    from paper_1711_01348_amd import binding as B
+    f, grads = torch.full_like(df, float("nan")), [torch.full_like(a, float("nan")) for a in args]
+    ws = torch.full((ws_bytes + (1 << 20),), 255, dtype=torch.uint8, device="cuda")
+    ptrs = (ctypes.c_void_p * 2)(*[t.data_ptr() for t in args])
+    outs = (ctypes.c_void_p * 2)(*[t.data_ptr() for t in grads])
+    assert B.lib.tad_eval_forward(plan._h, ptrs, f.data_ptr(), ws.data_ptr(), ws_bytes, None) == 0
+    assert B.lib.tad_eval_backward(plan._h, ptrs, f.data_ptr(), df.data_ptr(), outs, ws.data_ptr(), ws_bytes, None) == 0
+    torch.cuda.synchronize()
+    assert bool((ws[ws_bytes:] == 255).all()), "written beyond the workspace"
+    return [f] + grads
+
+
+@pytest.mark.parametrize("I,J,K,xt,yt", [(4100, 2052, 2052, 0, 0), (2052, 4100, 2188, 1, 0), (4096, 2048, 2048, 0, 1),
+                                         (2180, 3844, 2052, 1, 1)])
+def test_error_is_no_larger_than_that_of_the_32_bit_kernel(I, J, K, xt, yt):
+    import torch
+    plan, args, df = plan_and_tensors(I, J, K, xt, yt)
+    x, y = (args[0].t() if xt else args[0]).double(), (args[1].t() if yt else args[1]).double()
+    dx, dy = df.double() @ y.t().contiguous(), x.t().contiguous() @ df.double()
+    want = [x @ y, dx.t().contiguous() if xt else dx, dy.t().contiguous() if yt else dy]
+    split, plain = evaluate(plan, args, df, plan.workspace_bytes), evaluate(plan, args, df, plan.workspace_bytes - 16)
+    for s, p, w in zip(split, plain, want):
+        e = [((t.double() - w).norm() / w.norm()).item() for t in (s, p)]
+        assert e[0] <= 1.02 * e[1] and e[0] < 2e-6, e
+
+
+@pytest.mark.parametrize("what", ["inf", "nan", "tiny", "huge", "denormal", "small_products"])
+def test_operands_out_of_range_are_left_to_the_32_bit_kernel(what):
+    import torch
+    plan, args, df = plan_and_tensors(4096, 2048, 2048)
+    x, y = args
+    if what == "small_products":
+        x *= 2.0 ** -70
+        y *= 2.0 ** -70
+    else:
+        x[4095, 2047] = {"inf": float("inf"), "nan": float("nan"), "tiny": 1e-32, "huge": 3.3e38, "denormal": 1e-42}[what]
+    split, plain = evaluate(plan, args, df, plan.workspace_bytes), evaluate(plan, args, df, plan.workspace_bytes - 16)
+    for s, p in zip(split[::2], plain[::2]):     # f and the gradient of y, the products x takes part in
+        assert torch.equal(torch.nan_to_num(s, nan=7.0), torch.nan_to_num(p, nan=7.0))
+
+
+def test_zero_operands():
+    import torch
+    plan, args, df = plan_and_tensors(4096, 2048, 2048)
+    args[0].zero_()
+    f, _, dy = evaluate(plan, args, df, plan.workspace_bytes)
+    assert not f.any() and not dy.any()
