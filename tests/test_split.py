@@ -4,6 +4,7 @@ import ctypes
 
 import pytest
 
+from paper_1711_01348_amd import check
 from paper_1711_01348_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -61,6 +62,18 @@ def test_operands_out_of_range_are_left_to_the_32_bit_kernel(what):
     split, plain = evaluate(plan, args, df, plan.workspace_bytes), evaluate(plan, args, df, plan.workspace_bytes - 16)
     for s, p in zip(split[::2], plain[::2]):     # f and the gradient of y, the products x takes part in
         assert torch.equal(torch.nan_to_num(s, nan=7.0), torch.nan_to_num(p, nan=7.0))
+
+
+@pytest.mark.parametrize("I,J,K,xt,yt", [(1028, 1036, 264, 0, 0), (132, 516, 4100, 1, 0), (516, 1300, 404, 0, 1), (2052, 20, 6600, 1, 1)])
+def test_32_bit_kernel_on_ragged_tiles_and_pieces_of_the_sum(I, J, K, xt, yt):
+    """Sizes just above those that the products with 64-bit sums take."""
+    plan, args, df = plan_and_tensors(I, J, K, xt, yt)
+    x, y = (args[0].t() if xt else args[0]).double(), (args[1].t() if yt else args[1]).double()
+    dx, dy = df.double() @ y.t().contiguous(), x.t().contiguous() @ df.double()
+    want = [x @ y, dx.t().contiguous() if xt else dx, dy.t().contiguous() if yt else dy]
+    assert plan.forward_family == "contraction"
+    for g, w in zip(evaluate(plan, args, df, plan.workspace_bytes), want):
+        assert check.within(g.cpu().numpy(), w.cpu().numpy(), "f32")
 
 
 def test_zero_operands():
