@@ -263,10 +263,25 @@ __global__ __launch_bounds__(256) void k_worked_wide_finish(const FlatFeas feas,
     if (blk < blocks_rows) {
         const int i = blk * 64 + lane;
         double acc[RP] = {};
-        if (i < I)
-            for (int jt = wave; jt < n_jt; jt += 4)
+        if (i < I) {
+            // the loads of U tiles go out together: one after the other, the chain of them is longer than the pass over df and f
+            constexpr int U = K <= 4 ? 4 : 2;
+            int jt = wave;
+            for (; jt + 4 * (U - 1) < n_jt; jt += 4 * U) {
+                double v[U][RP];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int p = 0; p < RP; ++p) v[u][p] = rowp[((size_t)(jt + 4 * u) * RP + p) * I + i];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int p = 0; p < RP; ++p) acc[p] += v[u][p];
+            }
+            for (; jt < n_jt; jt += 4)
 #pragma unroll
                 for (int p = 0; p < RP; ++p) acc[p] += rowp[((size_t)jt * RP + p) * I + i];
+        }
 #pragma unroll
         for (int p = 0; p < RP; ++p) red[wave][p][lane] = acc[p];
         __syncthreads();
@@ -284,10 +299,24 @@ __global__ __launch_bounds__(256) void k_worked_wide_finish(const FlatFeas feas,
     if (blk < blocks_cols) {
         const int j = blk * 64 + lane;
         double acc[K] = {};
-        if (j < J && db)
-            for (int it = wave; it < n_it; it += 4)
+        if (j < J && db) {
+            constexpr int U = K <= 4 ? 8 : 4;   // as above
+            int it = wave;
+            for (; it + 4 * (U - 1) < n_it; it += 4 * U) {
+                double v[U][K];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int k = 0; k < K; ++k) v[u][k] = colp[((size_t)(it + 4 * u) * K + k) * J + j];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int k = 0; k < K; ++k) acc[k] += v[u][k];
+            }
+            for (; it < n_it; it += 4)
 #pragma unroll
                 for (int k = 0; k < K; ++k) acc[k] += colp[((size_t)it * K + k) * J + j];
+        }
 #pragma unroll
         for (int k = 0; k < K; ++k) red[wave][k][lane] = acc[k];
         __syncthreads();

@@ -24,7 +24,7 @@ constexpr int kWideMaxK = 16, kWideMaxRows = 128;
 // columns of a lane: as many as their sums and factors fit in registers
 constexpr int wide_lane_columns(int K) { return K <= 7 ? 4 : 2; }
 struct WideGeom {
-    int tile_rows;       // rows of a tile, a multiple of 8
+    int tile_rows;       // rows of a tile, a multiple of 16
     int n_jt, n_it;      // tiles along the columns and the rows
     size_t col_offset, ws_bytes;   // row sums [n_jt][K + 2][I], then column sums [n_it][K][J]
 };
@@ -34,7 +34,7 @@ inline WideGeom worked_wide_geom(int64_t I, int64_t J, int64_t K) {
     g.n_jt = (int)((J + tj - 1) / tj);
     // about two workgroups per compute unit; fewer rows per tile mean more column sums in memory
     int64_t rows = (I * g.n_jt + 511) / 512;
-    rows = (rows + 7) / 8 * 8;
+    rows = (rows + 15) / 16 * 16;
     g.tile_rows = (int)(rows > kWideMaxRows ? kWideMaxRows : rows);
     g.n_it = (int)((I + g.tile_rows - 1) / g.tile_rows);
     g.col_offset = align256((size_t)g.n_jt * (size_t)I * (size_t)(K + 2) * 8);
