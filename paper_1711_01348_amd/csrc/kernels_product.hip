@@ -3,29 +3,33 @@
 // sum in 64 bits, so these do: a 32-bit operand is widened when it is staged, its products are then exact, and the
 // result is rounded once.
 //
-// C[r][c] = sum_q A(r, q) B(q, c).  A workgroup of four wavefronts computes one square tile of the output.  The operands go
-// through registers into LDS, [row][q] with an odd row length (conflict-free for the stores, along q or along the rows,
-// and for the fragment loads); the loads of a stage are issued before the matrix instructions of the stage before it.
+// C[r][c] = sum_q A(r, q) B(q, c).  A workgroup of eight wavefronts computes a tile of 16 NR x 64 results: a wavefront owns 16 columns
+// of it and one half of every stage's values of q, and the two halves are added at the end.  What the tile's height is for: a 16 x 16 x 4
+// instruction occupies its matrix core for 64 cycles (78.6 TFLOP/s), everything else is to fit under that, so the best that can be done is
+// to give the 1024 matrix cores equal numbers of 16 x 16 blocks.  product_shape picks NR (1 .. 8, up to 5 with 64-bit operands) and the
+// orientation for that: 1000 x 1203 is 247 tiles of 80 x 64, one for each compute unit and 93 % of an even share, where tiles of 32 x 32 are
+// 2.4 rounds that cost three and fetch twice the operands through L2.
+// The operands go through registers into LDS, widened to 64 bits on the way, [row][q] with 16 bytes behind each row (fragment reads of 16
+// bytes without conflicts); there are two sets of tiles, so that a stage takes one barrier.
+// Instructions that are issued beside a matrix instruction cost nothing, in a row of their own they hold it back: every read, store and
+// load has its place between two matrix instructions, and the fragments are read one chunk ahead.  1000 x 1203 x 777 in 64 bits, forward:
+// 32 x 32 tiles 72 us, these tiles 55, fragments read ahead 47, everything in its place 42 (44 TFLOP/s; 247 of 256 compute units,
+// each of them 64000 cycles of matrix instructions in 97000); both gradients 104 -> 90; 512 x 1024 x 768 in 32 bits 24 -> 20,
+// gradients 43 -> 36; 2000 x 2000 x 2000 311 -> 287.
 // Everything that depends on the tile's place is settled before the loop: a row beyond the edge repeats the last row (its
 // results are not stored), so that the loads are unconditional, from a uniform base plus a constant 32-bit offset per thread,
-// and only the last stage looks at the end of the sum, where it stages zeros.
-// A 16 x 16 x 4 instruction occupies its matrix core for 64 cycles: the matrix cores bound these kernels (78.6 TFLOP/s), two
-// operand fragments per instruction are cheap, and what counts is that the barriers are covered: two sets of tiles in LDS, so
-// that a stage takes one barrier and the stores of the next one go on under its matrix instructions (1000 x 1203 x 777 in 64 bits,
-// forward and gradients: 193 -> 176 us, 32 TFLOP/s; the results of 32 x 32 tiles leave a third of the last round of workgroups
-// idle, and 64 x 64 tiles with 64-bit operands spill: 237 us), and small tiles:
-//   edge 64  a wavefront owns 32 x 32 results; 32 values of q per stage
-//   edge 32  every wavefront computes the whole tile over a quarter of each stage's 64 values of q, and the four sums are added
-//            in a fixed order at the end: four times as many workgroups for small results (512 x 1024 x 768: 21 us against
-//            36 us), and a chain of additions a quarter as long
+// and only the last stages look at the end of the sum, where zeros are staged.
 // Operands of 64 bits: the rounding of the sum is all there is, so it is kept as small as that of the general kernels, which
-// share a sum among 64 lanes: a wavefront adds up 16 products at a time and adds those to two totals in turn (1000 x 1203 x 777:
-// relative error 2e-16, against 5e-16 in one chain).
+// share a sum among 64 lanes: a wavefront adds up 16 products at a time, those sums to a subtotal, and every so many stages the subtotal
+// to a total, the last two chains of about the same length (60 x 50 x 777: 1.87e-16 of the norm, 40 x 40 x 1203 1.91e-16).
 //
 // MFMA operand layout: A operand lane l = A[l % 16][l / 16], B operand lane l = B[l / 16][l % 16], result register i of
-// lane l = D[4 i + l / 16][l % 16].
+// lane l = D[4 i + l / 16][l % 16].  Which q a lane group takes is free as long as both operands agree: each takes
+// consecutive ones, for wide reads from LDS.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -47,6 +51,7 @@ struct ProductTask {
     int pieces, chunk; // pieces of q, values of q per piece
     int wide;          // store 64-bit results
     int turned;        // store the result [c][r]
+    int flush;         // stages of a subtotal (64-bit operands)
 };
 // One or two products (the derivatives of the two factors of a sum) in one launch: workgroup b works on the first one for
 // b < first, else on the second one.
@@ -68,203 +73,273 @@ __device__ __forceinline__ void product_tile(int lid, int gr, int gc, int &tr, i
     tc = in / rows;
 }
 
-template <typename TA, typename TB, int EDGE, typename TO>
+typedef double double2p __attribute__((ext_vector_type(2)));
+
+template <typename TA, typename TB, int NR, typename TO>
 __device__ __forceinline__ void product_kernel(const ProductArgs &M, const ProductOuter *O) {
-    constexpr bool SHARE = EDGE == 32;              // the wavefronts share the tile's sum; else each owns a quarter of the tile
-    constexpr int KT = SHARE ? 64 : 32;             // values of q per stage
-    constexpr int KW = SHARE ? 16 : 32;             // ... of one wavefront
-    constexpr int LDK = KT + 1;                     // row length in LDS
-    constexpr int WT = 2;                           // 16 x 16 results of a wavefront, per direction
-    constexpr int PER = EDGE * KT / 256;            // elements of each operand a thread stages
-    constexpr bool BLOCKED = sizeof(TA) == 8 && sizeof(TB) == 8;   // sums of 16 products added to a total
-    constexpr int TILES = 2 * EDGE * LDK * (int)(sizeof(TA) + sizeof(TB)), SUMS = SHARE ? 4 * EDGE * EDGE * 8 : 0;
-    __shared__ __attribute__((aligned(16))) char lds[TILES > SUMS ? TILES : SUMS];
-    // the wider operand first: both regions then start on a multiple of their element
-    constexpr bool A_FIRST = sizeof(TA) >= sizeof(TB);
-    TA *const As = reinterpret_cast<TA *>(lds + (A_FIRST ? 0 : 2 * EDGE * LDK * (int)sizeof(TB)));
-    TB *const Bs = reinterpret_cast<TB *>(lds + (A_FIRST ? 2 * EDGE * LDK * (int)sizeof(TA) : 0));
+    constexpr bool BLOCKED = sizeof(TA) == 8 && sizeof(TB) == 8;   // sums of 16 products added to a subtotal
+    constexpr int NT = 512, ER = 16 * NR, EC = kProductCols;
+    constexpr int KT = kProductStage;               // values of q per stage
+    constexpr int KL = KT / 8;                      // ... of one lane: half a stage among the four lane groups
+    constexpr int CHUNKS = KL / 2;                  // ... read two at a time
+    constexpr int LDK = KT + 2;                     // row length in LDS
+    constexpr int PA = ER * KT / NT, PB = EC * KT / NT;   // elements of each operand a thread stages
+    constexpr int AHEAD = NR <= 2 ? 2 : 1;          // stages in registers: one lasts about as long as a load with low tiles
+    constexpr int LDS_SUM = EC + 1;
+    constexpr int SIZE_A = ER * LDK, SIZE_B = EC * LDK, TILES = 2 * (SIZE_A + SIZE_B), SUMS = ER * LDS_SUM;
+    static_assert(PA * NT == ER * KT && PB * NT == EC * KT && CHUNKS % 2 == 0, "whole stages");
+    __shared__ __attribute__((aligned(16))) double lds[TILES > SUMS ? TILES : SUMS];
+    double *const As = lds, *const Bs = lds + 2 * SIZE_A;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const ProductTask &P = M.task[(int)blockIdx.x < M.first ? 0 : 1];   // the same for the whole workgroup
     const int id = (int)blockIdx.x - ((int)blockIdx.x < M.first ? 0 : M.first), tiles = P.gr * P.gc, piece = id / tiles;
     int tr, tc;
     product_tile(id - piece * tiles, P.gr, P.gc, tr, tc);
-    const int r0 = tr * EDGE, c0 = tc * EDGE;
+    const int r0 = tr * ER, c0 = tc * EC;
     const int q_begin = piece * P.chunk, q_end = min(P.Q, q_begin + P.chunk);
     // staging: neighbouring threads along q or along the rows, whichever is contiguous in memory
     const bool a_q = P.aq <= P.ar, b_q = P.bq <= P.bc;   // uniform
-    const int a_row = a_q ? tid / KT : tid % EDGE, a_k = a_q ? tid % KT : tid / EDGE;
-    const int b_row = b_q ? tid / KT : tid % EDGE, b_k = b_q ? tid % KT : tid / EDGE;
-    const int a_dr = a_q ? 256 / KT : 0, a_dk = a_q ? 0 : 256 / EDGE;   // from one element of a thread to the next
-    const int b_dr = b_q ? 256 / KT : 0, b_dk = b_q ? 0 : 256 / EDGE;
-    unsigned ao[PER], bo[PER];   // byte offsets within a stage
+    // (groups of G rows, the largest power of two in ER: constant steps from one element of a thread to the next)
+    constexpr int G = ER & -ER, PG = KT * G / NT;
+    const int a_row = a_q ? tid / KT : tid % G, a_k = a_q ? tid % KT : tid / G;
+    const int b_row = b_q ? tid / KT : tid % EC, b_k = b_q ? tid % KT : tid / EC;
+    auto a_dr = [&](int p) { return a_q ? p * (NT / KT) : p / PG * G; };
+    auto a_dk = [&](int p) { return a_q ? 0 : p % PG * (NT / G); };
+    auto b_dr = [&](int p) { return b_q ? p * (NT / KT) : 0; };
+    auto b_dk = [&](int p) { return b_q ? 0 : p * (NT / EC); };
+    unsigned ao[PA], bo[PB];       // byte offsets within a stage
 #pragma unroll
-    for (int p = 0; p < PER; ++p) {
-        ao[p] = (unsigned)(min(a_row + p * a_dr, P.R - 1 - r0) * P.ar + (a_k + p * a_dk) * P.aq) * (unsigned)sizeof(TA);
-        bo[p] = (unsigned)(min(b_row + p * b_dr, P.C - 1 - c0) * P.bc + (b_k + p * b_dk) * P.bq) * (unsigned)sizeof(TB);
-    }
+    for (int p = 0; p < PA; ++p)
+        ao[p] = (unsigned)(min(a_row + a_dr(p), P.R - 1 - r0) * P.ar + (a_k + a_dk(p)) * P.aq) * (unsigned)sizeof(TA);
+#pragma unroll
+    for (int p = 0; p < PB; ++p)
+        bo[p] = (unsigned)(min(b_row + b_dr(p), P.C - 1 - c0) * P.bc + (b_k + b_dk(p)) * P.bq) * (unsigned)sizeof(TB);
     const char *pa = reinterpret_cast<const char *>(static_cast<const TA *>(P.a) + (size_t)r0 * P.ar + (size_t)q_begin * P.aq);
     const char *pb = reinterpret_cast<const char *>(static_cast<const TB *>(P.b) + (size_t)c0 * P.bc + (size_t)q_begin * P.bq);
-    TA va[PER];
-    TB vb[PER];
-    auto load = [&](int q0) {
+    struct Staged { TA a[PA]; TB b[PB]; } regs[AHEAD];
+    auto load = [&](int q0, Staged &v) {
         if (q0 + KT <= q_end) {   // the same for the whole workgroup
 #pragma unroll
-            for (int p = 0; p < PER; ++p) va[p] = *reinterpret_cast<const TA *>(pa + ao[p]);
+            for (int p = 0; p < PA; ++p) v.a[p] = *reinterpret_cast<const TA *>(pa + ao[p]);
 #pragma unroll
-            for (int p = 0; p < PER; ++p) vb[p] = *reinterpret_cast<const TB *>(pb + bo[p]);
+            for (int p = 0; p < PB; ++p) v.b[p] = *reinterpret_cast<const TB *>(pb + bo[p]);
         } else {                  // the last stage: beyond the end of the sum the last value is read and a zero staged
 #pragma unroll
-            for (int p = 0; p < PER; ++p) {
-                const int over = max(q0 + a_k + p * a_dk - (q_end - 1), 0);
-                const TA v = *reinterpret_cast<const TA *>(pa + (ao[p] - (unsigned)(over * P.aq) * (unsigned)sizeof(TA)));
-                va[p] = over ? TA(0) : v;
+            for (int p = 0; p < PA; ++p) {
+                const int over = max(q0 + a_k + a_dk(p) - (q_end - 1), 0);
+                const TA t = *reinterpret_cast<const TA *>(pa + (ao[p] - (unsigned)(over * P.aq) * (unsigned)sizeof(TA)));
+                v.a[p] = over ? TA(0) : t;
             }
 #pragma unroll
-            for (int p = 0; p < PER; ++p) {
-                const int over = max(q0 + b_k + p * b_dk - (q_end - 1), 0);
-                const TB v = *reinterpret_cast<const TB *>(pb + (bo[p] - (unsigned)(over * P.bq) * (unsigned)sizeof(TB)));
-                vb[p] = over ? TB(0) : v;
+            for (int p = 0; p < PB; ++p) {
+                const int over = max(q0 + b_k + b_dk(p) - (q_end - 1), 0);
+                const TB t = *reinterpret_cast<const TB *>(pb + (bo[p] - (unsigned)(over * P.bq) * (unsigned)sizeof(TB)));
+                v.b[p] = over ? TB(0) : t;
             }
         }
         pa += (size_t)KT * P.aq * sizeof(TA);
         pb += (size_t)KT * P.bq * sizeof(TB);
     };
-    const int as = a_row * LDK + a_k, as_inc = a_dr * LDK + a_dk, bs = b_row * LDK + b_k, bs_inc = b_dr * LDK + b_dk;
-    auto stage = [&](int set) {
+    const int as = a_row * LDK + a_k, bs = b_row * LDK + b_k;
+    auto stage = [&](int set, const Staged &v) {
 #pragma unroll
-        for (int p = 0; p < PER; ++p) As[set * EDGE * LDK + as + p * as_inc] = va[p];
+        for (int p = 0; p < PA; ++p) As[set * SIZE_A + as + a_dr(p) * LDK + a_dk(p)] = (double)v.a[p];
 #pragma unroll
-        for (int p = 0; p < PER; ++p) Bs[set * EDGE * LDK + bs + p * bs_inc] = vb[p];
+        for (int p = 0; p < PB; ++p) Bs[set * SIZE_B + bs + b_dr(p) * LDK + b_dk(p)] = (double)v.b[p];
     };
     const double4p zero = {0., 0., 0., 0.};
-    double4p acc[WT][WT], even[WT][WT], odd[WT][WT];   // even, odd: totals of every other stage (64-bit operands)
+    double4p acc[NR], sub[BLOCKED ? NR : 1], total[BLOCKED ? NR : 1];
 #pragma unroll
-    for (int x = 0; x < WT; ++x)
+    for (int x = 0; x < NR; ++x) {
+        acc[x] = zero;
+        if constexpr (BLOCKED) sub[x] = total[x] = zero;
+    }
+    const int col = wave & 3, half = wave >> 2;
+    const int fk = half * (KT / 2) + (lane >> 4) * KL;
+    const int fa = (lane & 15) * LDK + fk, fb = (16 * col + (lane & 15)) * LDK + fk;
+    double2p fragments[2][NR + 1];
+    auto read = [&](int set, int c, double2p (&v)[NR + 1]) {
 #pragma unroll
-        for (int y = 0; y < WT; ++y) acc[x][y] = even[x][y] = odd[x][y] = zero;
-    const int wr = SHARE ? 0 : (wave >> 1) * (EDGE / 2), wc = SHARE ? 0 : (wave & 1) * (EDGE / 2);
-    const int fk = (SHARE ? wave * KW : 0) + (lane >> 4);
-    const int fa = (wr + (lane & 15)) * LDK + fk, fb = (wc + (lane & 15)) * LDK + fk;
-    load(q_begin);
-    stage(0);
-    if (q_begin + KT < q_end) load(q_begin + KT);
+        for (int x = 0; x < NR; ++x) v[x] = *reinterpret_cast<const double2p *>(As + set * SIZE_A + fa + x * 16 * LDK + c * 2);
+        v[NR] = *reinterpret_cast<const double2p *>(Bs + set * SIZE_B + fb + c * 2);
+    };
+    {
+        Staged begin;   // the first loads all go out before the first of them is waited for
+        load(q_begin, begin);
+#pragma unroll
+        for (int n = 1; n <= AHEAD; ++n)
+            if (q_begin + n * KT < q_end) load(q_begin + n * KT, regs[n % AHEAD]);
+        stage(0, begin);
+    }
     __syncthreads();
-    // one stage: what the registers hold of the next one goes into the other set of tiles, the loads of the one behind it are
-    // issued, and the matrix instructions cover both
-    auto step = [&](int q0, int set, double4p (&total)[WT][WT]) {
-        if (q0 + KT < q_end) stage(set ^ 1);   // the same for the whole workgroup
-        if (q0 + 2 * KT < q_end) load(q0 + 2 * KT);
-        const int ab = set * EDGE * LDK + fa, bb = set * EDGE * LDK + fb;
+    read(0, 0, fragments[0]);
+    // One stage.  The fragments of a chunk are read among the matrix instructions of the chunk before it, also across the barrier, and so
+    // is everything else that goes to memory: a wavefront that sends its loads and stores out in a row holds back its own matrix
+    // instructions and, being in step with it, those of the other wavefront of its SIMD.  WHOLE: the stage that is to be loaded exists and
+    // is a whole one, so that there is nothing to ask.  The scheduling barriers keep the compiler from moving the reads down to their use.
+    auto step = [&](int q0, auto parity, auto whole) {
+        constexpr int SET = decltype(parity)::value, MF = 2 * NR;   // matrix instructions of a chunk
+        constexpr bool WHOLE = decltype(whole)::value;
+        Staged &v = regs[(SET + 1) % AHEAD];
+        int as_now = as, bs_now = bs;
+        asm volatile("" : "+v"(as_now), "+v"(bs_now));   // an address is one addition at its use, and a register each if they are kept
 #pragma unroll
-        for (int ks = 0; ks < KW / 4; ++ks) {
-            double a[WT], b[WT];
+        for (int c = 0; c < CHUNKS; ++c) {
+            const bool last = c + 1 == CHUNKS;
+            const double2p(&now)[NR + 1] = fragments[c & 1];
+            double2p(&next)[NR + 1] = fragments[(c + 1) & 1];
+            // elements of the stage that this chunk takes from registers to LDS and loads again
+            const int e0 = last ? 0 : c * (PA + PB) / (CHUNKS - 1), e1 = last ? 0 : (c + 1) * (PA + PB) / (CHUNKS - 1);
+            const int first = last ? MF / 2 : 0;   // matrix instructions before the barrier
+            const int ops = NR + 1 + (WHOLE ? e1 - e0 : 0), slots = MF - first;
 #pragma unroll
-            for (int x = 0; x < WT; ++x) {
-                a[x] = (double)As[ab + x * 16 * LDK + ks * 4];
-                b[x] = (double)Bs[bb + x * 16 * LDK + ks * 4];
+            for (int m = 0; m < MF; ++m) {
+                const int x = m % NR, i = m / NR;
+                if (last && m == first) __syncthreads();
+                if (m >= first) {
+#pragma unroll
+                    for (int o = 0; o < ops; ++o) {
+                        if (o < (m - first) * ops / slots || o >= (m - first + 1) * ops / slots) continue;
+                        if (o <= NR) {   // (behind the last stage: whatever is there, it is not used)
+                            const int set = last ? SET ^ 1 : SET, at = last ? 0 : (c + 1) * 2, row = (o + NR) % (NR + 1);   // the common fragment first
+                            next[row] = *reinterpret_cast<const double2p *>(row < NR ? As + set * SIZE_A + fa + row * 16 * LDK + at : Bs + set * SIZE_B + fb + at);
+                        } else {
+                            const int e = e0 + o - NR - 1, p = e < PA ? e : e - PA;
+                            unsigned from = e < PA ? ao[p] : bo[p];
+                            asm volatile("" : "+v"(from));   // 32 bits beside a uniform base, not widened ahead of time
+                            if (e < PA) {
+                                As[(SET ^ 1) * SIZE_A + as_now + a_dr(p) * LDK + a_dk(p)] = (double)v.a[p];
+                                v.a[p] = *reinterpret_cast<const TA *>(pa + from);
+                            } else {
+                                Bs[(SET ^ 1) * SIZE_B + bs_now + b_dr(p) * LDK + b_dk(p)] = (double)v.b[p];
+                                v.b[p] = *reinterpret_cast<const TB *>(pb + from);
+                            }
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(now[x][i], now[NR][i], BLOCKED && i == 0 && c % 2 == 0 ? zero : acc[x], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            if constexpr (BLOCKED) {
+                if (c % 2 == 1) {
 #pragma unroll
-            for (int x = 0; x < WT; ++x)
-#pragma unroll
-                for (int y = 0; y < WT; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[y], BLOCKED && ks % 4 == 0 ? zero : acc[x][y], 0, 0, 0);
-            if (BLOCKED && ks % 4 == 3) {
-#pragma unroll
-                for (int x = 0; x < WT; ++x)
-#pragma unroll
-                    for (int y = 0; y < WT; ++y) total[x][y] += acc[x][y];
+                    for (int x = 0; x < NR; ++x) sub[x] += acc[x];
+                }
+            }
+            if constexpr (!WHOLE) {
+                if (c == CHUNKS / 2 - 1) {
+                    if (q0 + KT < q_end) stage(SET ^ 1, v);   // the same for the whole workgroup
+                    if (q0 + (1 + AHEAD) * KT < q_end) load(q0 + (1 + AHEAD) * KT, v);
+                }
             }
         }
-        __syncthreads();
+        if constexpr (WHOLE) {
+            pa += (size_t)KT * P.aq * sizeof(TA);
+            pb += (size_t)KT * P.bq * sizeof(TB);
+        }
     };
-    for (int q0 = q_begin; q0 < q_end; q0 += 2 * KT) {
-        step(q0, 0, even);
-        if (q0 + KT < q_end) step(q0 + KT, 1, odd);
+    int left = P.flush;
+    auto flush = [&] {
+        if constexpr (BLOCKED) {
+            if (--left) return;
+            left = P.flush;
+#pragma unroll
+            for (int x = 0; x < NR; ++x) {
+                total[x] += sub[x];
+                sub[x] = zero;
+            }
+        }
+    };
+    // (two stages at a time, and no way out in between: that would cost a second set of registers for the sums)
+    const std::integral_constant<int, 0> even{};
+    const std::integral_constant<int, 1> odd{};
+    int q0 = q_begin;
+    for (; q0 + (3 + AHEAD) * KT <= q_end; q0 += 2 * KT) {
+        step(q0, even, std::true_type());
+        flush();
+        step(q0 + KT, odd, std::true_type());
+        flush();
     }
+    for (; q0 + KT < q_end; q0 += 2 * KT) {
+        step(q0, even, std::false_type());
+        flush();
+        step(q0 + KT, odd, std::false_type());
+        flush();
+    }
+    if (q0 < q_end) step(q0, even, std::false_type());
     if constexpr (BLOCKED) {
 #pragma unroll
-        for (int x = 0; x < WT; ++x)
-#pragma unroll
-            for (int y = 0; y < WT; ++y) acc[x][y] = even[x][y] + odd[x][y];
+        for (int x = 0; x < NR; ++x) acc[x] = total[x] + sub[x];
     }
+    // the two halves of the sum (behind the last barrier of the loop the tiles are free)
+    double *const sums = lds;
+    const int own = (lane >> 4) * LDS_SUM + 16 * col + (lane & 15);
+    if (half) {
+#pragma unroll
+        for (int x = 0; x < NR; ++x)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sums[own + (16 * x + 4 * i) * LDS_SUM] = acc[x][i];
+    }
+    __syncthreads();
+    if (!half) {
+#pragma unroll
+        for (int x = 0; x < NR; ++x)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sums[own + (16 * x + 4 * i) * LDS_SUM] += acc[x][i];
+    }
+    __syncthreads();
     char *out = static_cast<char *>(P.c) + (size_t)piece * P.R * P.C * sizeof(double);   // (one piece: 0)
-    auto store = [&](int r, int c, double v) {
-        if (r >= P.R || c >= P.C) return;
-        const size_t at = P.turned ? (size_t)c * P.R + r : (size_t)r * P.C + c;
-        if (P.wide) reinterpret_cast<double *>(out)[at] = v;
-        else reinterpret_cast<float *>(out)[at] = (float)v;
-    };
-    if constexpr (!SHARE) {
-#pragma unroll
-        for (int x = 0; x < WT; ++x)
-#pragma unroll
-            for (int y = 0; y < WT; ++y)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    store(r0 + wr + x * 16 + 4 * i + (lane >> 4), c0 + wc + y * 16 + (lane & 15), acc[x][y][i]);
-    } else {
-        // the wavefronts' sums of the tile, added in ascending order (behind the last barrier of the loop the tiles are free)
-        double *const sums = reinterpret_cast<double *>(lds);
-#pragma unroll
-        for (int x = 0; x < WT; ++x)
-#pragma unroll
-            for (int y = 0; y < WT; ++y)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    sums[wave * EDGE * EDGE + (x * 16 + 4 * i + (lane >> 4)) * EDGE + y * 16 + (lane & 15)] = acc[x][y][i];
-        __syncthreads();
+    constexpr int RESULTS = ER * EC / NT;
+    if constexpr (std::is_same<TO, void>::value) {
         // neighbouring threads along the direction that is contiguous in the result
-        auto place = [&](int p, int &r, int &c) {
-            const int n = tid + 256 * p, at = P.turned ? (n % EDGE) * EDGE + n / EDGE : n;
-            r = r0 + at / EDGE;
-            c = c0 + at % EDGE;
-            return (sums[at] + sums[EDGE * EDGE + at]) + (sums[2 * EDGE * EDGE + at] + sums[3 * EDGE * EDGE + at]);
-        };
-        if constexpr (std::is_same<TO, void>::value) {
 #pragma unroll
-            for (int p = 0; p < EDGE * EDGE / 256; ++p) {
-                int r, c;
-                const double v = place(p, r, c);
-                store(r, c, v);
-            }
-        } else {
-            // U results per pass of the interpreter: an operation costs more to fetch than to carry out
-            constexpr int U = ProgWidth<TO>::U;
+        for (int p = 0; p < RESULTS; ++p) {
+            const int n = tid + NT * p, ir = P.turned ? n % ER : n / EC, ic = P.turned ? n / ER : n % EC, r = r0 + ir, c = c0 + ic;
+            const double v = sums[ir * LDS_SUM + ic];
+            if (r >= P.R || c >= P.C) continue;
+            const size_t at = P.turned ? (size_t)c * P.R + r : (size_t)r * P.C + c;
+            if (P.wide) reinterpret_cast<double *>(out)[at] = v;
+            else reinterpret_cast<float *>(out)[at] = (float)v;
+        }
+    } else {
+        // U results per pass of the interpreter: an operation costs more to fetch than to carry out
+        constexpr int U = ProgWidth<TO>::U;
 #pragma unroll 1
-            for (int p0 = 0; p0 < EDGE * EDGE / 256; p0 += U) {
-                TO s[U], w[kMaxArgs][U], o[U];
-                int at[U];
-                bool inside[U];
+        for (int p0 = 0; p0 < RESULTS; p0 += U) {
+            TO s[U], w[kMaxArgs][U], o[U];
+            int at[U];
+            bool inside[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    int r, c;
-                    s[u] = (TO)place(p0 + u, r, c);
-                    inside[u] = r < P.R && c < P.C;
-                    at[u] = inside[u] ? r * P.C + c : 0;
+            for (int u = 0; u < U; ++u) {
+                const int n = min(tid + NT * (p0 + u), ER * EC - 1), ir = P.turned ? n % ER : n / EC, ic = P.turned ? n / ER : n % EC;
+                const int r = r0 + ir, c = c0 + ic;
+                s[u] = (TO)sums[ir * LDS_SUM + ic];
+                inside[u] = p0 + u < RESULTS && r < P.R && c < P.C;
+                at[u] = !inside[u] ? 0 : P.turned ? c * P.R + r : r * P.C + c;
 #pragma unroll
-                    for (int q = 0; q < kMaxArgs; ++q)
-                        w[q][u] = O->args.p[q] ? static_cast<const TO *>(O->args.p[q])[inside[u] ? O->off_r[q] * r + O->off_c[q] * c : 0] : TO(0);
-                }
-                prog_eval_block<TO, U, true>(O->prog, w, s, o);
+                for (int q = 0; q < kMaxArgs; ++q)
+                    w[q][u] = O->args.p[q] ? static_cast<const TO *>(O->args.p[q])[inside[u] ? O->off_r[q] * r + O->off_c[q] * c : 0] : TO(0);
+            }
+            prog_eval_block<TO, U, true>(O->prog, w, s, o);
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (!inside[u]) continue;
-                    reinterpret_cast<TO *>(out)[at[u]] = O->df ? static_cast<const TO *>(O->df)[at[u]] * o[u] : o[u];
-                    if (O->s_out) static_cast<TO *>(O->s_out)[at[u]] = s[u];
-                }
+            for (int u = 0; u < U; ++u) {
+                if (!inside[u]) continue;
+                reinterpret_cast<TO *>(out)[at[u]] = O->df ? static_cast<const TO *>(O->df)[at[u]] * o[u] : o[u];
+                if (O->s_out) static_cast<TO *>(O->s_out)[at[u]] = s[u];
             }
         }
     }
 }
 
-template <typename TA, typename TB, int EDGE>
-__global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) void k_product(const ProductArgs M) {
-    product_kernel<TA, TB, EDGE, void>(M, nullptr);
+template <typename TA, typename TB, int NR>
+__global__ __launch_bounds__(512, 2) void k_product(const ProductArgs M) {
+    product_kernel<TA, TB, NR, void>(M, nullptr);
 }
 // sums of type TO that go through a program first
-template <typename TA, typename TB, typename TO>
-__global__ __launch_bounds__(256, sizeof(TA) == 8 && sizeof(TB) == 8 ? 2 : 3) void k_product_outer(const ProductArgs M, const ProductOuter O) {
-    product_kernel<TA, TB, 32, TO>(M, &O);
+template <typename TA, typename TB, typename TO, int NR>
+__global__ __launch_bounds__(512, 2) void k_product_outer(const ProductArgs M, const ProductOuter O) {
+    product_kernel<TA, TB, NR, TO>(M, &O);
 }
 
 // c[i] = the pieces' partial sums of element i.  A workgroup takes 256 / GROUPS elements, GROUPS threads for each, whose loads go out
@@ -308,72 +383,58 @@ static int reduce_pieces(const void *part, void *c, long long n, int pieces, hip
     return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
-static ProductTask product_task(const ProductJob &j, void *ws) {
+static ProductTask product_task(const ProductJob &j, int rows, bool share, void *ws) {
     const ProductDesc &d = *j.desc;
+    const int edge = 16 * rows;
     ProductTask P;
     P.a = j.a; P.b = j.b;
-    P.c = d.pieces > 1 ? ws : j.c;
+    P.pieces = share ? d.pieces : 1;
+    P.chunk = P.pieces > 1 ? d.chunk : d.Q;
+    P.c = P.pieces > 1 ? ws : j.c;
     P.R = d.R; P.C = d.C; P.Q = d.Q;
     P.ar = (int)d.ar; P.aq = (int)d.aq; P.bq = (int)d.bq; P.bc = (int)d.bc;
-    P.gr = (d.R + d.tile - 1) / d.tile; P.gc = (d.C + d.tile - 1) / d.tile;
-    P.pieces = d.pieces;
-    P.chunk = d.pieces > 1 ? d.chunk : d.Q;
-    P.wide = j.c64 || d.pieces > 1;
+    P.gr = (d.R + edge - 1) / edge; P.gc = (d.C + kProductCols - 1) / kProductCols;
+    P.wide = j.c64 || P.pieces > 1;
     P.turned = j.turned;
+    // 16 products in a row, then `flush` stages of a subtotal, then the total: the last two chains of about the same length
+    const double blocks = P.chunk / 32.0, per_stage = kProductStage / 32.0;   // of a wavefront: half the sum
+    P.flush = std::max(1, (int)(std::sqrt(blocks) / per_stage + 0.5));
     return P;
 }
 
-template <typename TA, typename TB>
-static int launch_product(const ProductArgs &M, int tile, unsigned blocks, const ProductOuter *outer, bool c64, hipStream_t s) {
-    const dim3 grid(blocks), block(256);
-    if (outer) {
-        if (c64) TAD_LAUNCH("k_product_outer", (k_product_outer<TA, TB, double>), grid, block, 0, s, M, *outer);
-        else TAD_LAUNCH("k_product_outer", (k_product_outer<TA, TB, float>), grid, block, 0, s, M, *outer);
-    } else {
-        if constexpr (sizeof(TA) == 4 || sizeof(TB) == 4) {
-            if (tile == 64) {
-                TAD_LAUNCH("k_product", (k_product<TA, TB, 64>), grid, block, 0, s, M);
-                return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
-            }
-        }
-        TAD_LAUNCH("k_product", (k_product<TA, TB, 32>), grid, block, 0, s, M);
+template <typename TA, typename TB, int NR>
+static int launch_product(const ProductArgs &M, unsigned blocks, const ProductOuter *outer, bool c64, hipStream_t s) {
+    const dim3 grid(blocks), block(512);
+    if (!outer) TAD_LAUNCH("k_product", (k_product<TA, TB, NR>), grid, block, 0, s, M);
+    else if constexpr (sizeof(TA) == 8 && sizeof(TB) == 8) {
+        if (c64) TAD_LAUNCH("k_product_outer", (k_product_outer<TA, TB, double, NR>), grid, block, 0, s, M, *outer);
+        else TAD_LAUNCH("k_product_outer", (k_product_outer<TA, TB, float, NR>), grid, block, 0, s, M, *outer);
+    } else {   // (a 32-bit operand is one of a 32-bit expression)
+        TAD_LAUNCH("k_product_outer", (k_product_outer<TA, TB, float, NR>), grid, block, 0, s, M, *outer);
     }
     return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
-
-// count (1 or 2) products of the same operand types and tile; two of them only without shared tiles
-static int launch_jobs(const ProductJob *jobs, int count, const ProductOuter *outer, void *ws, hipStream_t s) {
-    ProductArgs M{};
-    unsigned blocks = 0;
-    for (int q = 0; q < count; ++q) {
-        M.task[q] = product_task(jobs[q], ws);
-        blocks += (unsigned)(M.task[q].gr * M.task[q].gc * M.task[q].pieces);
-        if (q == 0) M.first = (int)blocks;
+template <typename TA, typename TB>
+static int launch_rows(const ProductArgs &M, int rows, unsigned blocks, const ProductOuter *outer, bool c64, hipStream_t s) {
+    switch (rows) {
+    case 1: return launch_product<TA, TB, 1>(M, blocks, outer, c64, s);
+    case 2: return launch_product<TA, TB, 2>(M, blocks, outer, c64, s);
+    case 3: return launch_product<TA, TB, 3>(M, blocks, outer, c64, s);
+    case 4: return launch_product<TA, TB, 4>(M, blocks, outer, c64, s);
+    case 5: return launch_product<TA, TB, 5>(M, blocks, outer, c64, s);
+    default:
+        if constexpr (sizeof(TA) == 4 || sizeof(TB) == 4) {
+            if (rows == 6) return launch_product<TA, TB, 6>(M, blocks, outer, c64, s);
+            if (rows == 7) return launch_product<TA, TB, 7>(M, blocks, outer, c64, s);
+            if (rows == 8) return launch_product<TA, TB, 8>(M, blocks, outer, c64, s);
+        }
+        return TAD_EUNSUPPORTED;
     }
-    const ProductJob &j = jobs[0];
-    const int tile = j.desc->tile;
-    int rc;
-    if (j.a64 && j.b64) rc = launch_product<double, double>(M, tile, blocks, outer, j.c64, s);
-    else if (j.a64) rc = launch_product<double, float>(M, tile, blocks, outer, j.c64, s);
-    else if (j.b64) rc = launch_product<float, double>(M, tile, blocks, outer, j.c64, s);
-    else rc = launch_product<float, float>(M, tile, blocks, outer, j.c64, s);
-    if (rc || j.desc->pieces == 1) return rc;
-    const long long n = (long long)j.desc->R * j.desc->C;
-    return j.c64 ? reduce_pieces<double>(ws, j.c, n, j.desc->pieces, s) : reduce_pieces<float>(ws, j.c, n, j.desc->pieces, s);
 }
 
-int product_run(const ProductJob &j, void *ws, hipStream_t s) { return launch_jobs(&j, 1, nullptr, ws, s); }
-
-bool product_outer_fits(const ProductDesc &d) { return d.tile == 32 && d.pieces == 1; }
-
-int product_run_outer(const ProductJob &j, const ProductOuter &o, hipStream_t s) { return launch_jobs(&j, 1, &o, nullptr, s); }
-
-// the same product with its operands exchanged: the result's transpose, stored back in place
-static ProductJob turned(const ProductJob &j, ProductDesc &d) {
-    d = *j.desc;
-    std::swap(d.R, d.C);
-    std::swap(d.ar, d.bc);
-    std::swap(d.aq, d.bq);
+// the product with its operands exchanged, stored back in place
+static ProductJob exchanged(const ProductJob &j, ProductDesc &d) {
+    d = product_turned(*j.desc);
     ProductJob t = j;
     t.desc = &d;
     std::swap(t.a, t.b);
@@ -382,14 +443,51 @@ static ProductJob turned(const ProductJob &j, ProductDesc &d) {
     return t;
 }
 
-int product_run_two(const ProductJob &x, const ProductJob &y, void *ws, hipStream_t s) {
-    // one launch for both: a launch costs as much as a small product, and two products fill the chip better than one
-    // (operands of mixed widths: one of the two with its operands exchanged)
-    ProductJob jobs[2] = {x, y};
+// count (1 or 2) products of the same operand types in one launch; share: their sums in pieces (one product only)
+static int launch_jobs(const ProductJob *jobs, int count, int rows, bool share, const ProductOuter *outer, void *ws, hipStream_t s) {
+    ProductArgs M{};
+    unsigned blocks = 0;
+    for (int q = 0; q < count; ++q) {
+        M.task[q] = product_task(jobs[q], rows, share, ws);
+        blocks += (unsigned)(M.task[q].gr * M.task[q].gc * M.task[q].pieces);
+        if (q == 0) M.first = (int)blocks;
+    }
+    const ProductJob &j = jobs[0];
+    int rc;
+    if (j.a64 && j.b64) rc = launch_rows<double, double>(M, rows, blocks, outer, j.c64, s);
+    else if (j.a64) rc = launch_rows<double, float>(M, rows, blocks, outer, j.c64, s);
+    else if (j.b64) rc = launch_rows<float, double>(M, rows, blocks, outer, j.c64, s);
+    else rc = launch_rows<float, float>(M, rows, blocks, outer, j.c64, s);
+    if (rc || !share || j.desc->pieces == 1) return rc;
+    const long long n = (long long)j.desc->R * j.desc->C;
+    return j.c64 ? reduce_pieces<double>(ws, j.c, n, j.desc->pieces, s) : reduce_pieces<float>(ws, j.c, n, j.desc->pieces, s);
+}
+
+int product_run(const ProductJob &j, void *ws, hipStream_t s) {
     ProductDesc d;
-    if (x.a64 != y.a64 && x.a64 == y.b64 && x.b64 == y.a64) jobs[1] = turned(y, d);
-    if (jobs[0].a64 == jobs[1].a64 && jobs[0].b64 == jobs[1].b64 && x.desc->tile == y.desc->tile && x.desc->pieces == 1 && y.desc->pieces == 1)
-        return launch_jobs(jobs, 2, nullptr, ws, s);
+    const ProductJob job = j.desc->flip ? exchanged(j, d) : j;
+    return launch_jobs(&job, 1, j.desc->rows, true, nullptr, ws, s);
+}
+
+bool product_outer_fits(const ProductDesc &d) { return d.pieces == 1; }
+
+int product_run_outer(const ProductJob &j, const ProductOuter &o, hipStream_t s) {
+    if (!j.desc->flip) return launch_jobs(&j, 1, j.desc->rows, false, &o, nullptr, s);
+    ProductDesc d;
+    const ProductJob job = exchanged(j, d);
+    ProductOuter t = o;
+    for (int q = 0; q < kMaxArgs; ++q) std::swap(t.off_r[q], t.off_c[q]);
+    return launch_jobs(&job, 1, d.rows, false, &t, nullptr, s);
+}
+
+int product_run_two(const ProductJob &x, const ProductJob &y, void *ws, hipStream_t s) {
+    // one launch for both where that is faster: two products fill the chip better than one (product_pair)
+    if (x.desc->pair_rows) {
+        ProductDesc d[2];
+        ProductJob jobs[2] = {x.desc->pair_flip ? exchanged(x, d[0]) : x, y.desc->pair_flip ? exchanged(y, d[1]) : y};
+        if (x.desc->Q < y.desc->Q) std::swap(jobs[0], jobs[1]);   // the longer ones first
+        return launch_jobs(jobs, 2, x.desc->pair_rows, false, nullptr, ws, s);
+    }
     const int rc = product_run(x, ws, s);
     return rc ? rc : product_run(y, ws, s);
 }

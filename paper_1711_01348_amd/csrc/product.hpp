@@ -18,9 +18,13 @@ namespace tad {
 struct ProductDesc {
     int R = 0, C = 0, Q = 0;
     int64_t ar = 0, aq = 0, bq = 0, bc = 0;
-    int tile = 0;      // output tile edge, 32 or 64
+    bool a64 = false, b64 = false;   // 64-bit operands
+    int rows = 1;      // an output tile has 16 rows x kProductCols results
+    bool flip = false; // ... of the product with its operands exchanged, whose results are stored transposed
     int pieces = 1;    // pieces of q computed by separate workgroups (few output tiles, long sum)
     int chunk = 0;     // values of q per piece (pieces > 1)
+    int pair_rows = 0; // `rows` of one launch for this product and the other gradient (0: a launch each)
+    bool pair_flip = false;
 };
 
 // One factor of the product.
@@ -48,11 +52,21 @@ constexpr int64_t kProductExtent = 16, kProductSum = 8;
 // Offset of one tensor along a group of extended indices as a single stride: the group's indices, the last one
 // fastest, count through 0 .. n - 1 and the offset is stride * that number.  False if it is not linear in it.
 bool product_group_stride(const int64_t *off, const int64_t *extent, int count, int64_t &stride);
-// The kernels address the elements of a stage (up to 128 rows, up to 64 values of q) with 32-bit byte offsets from
+// The kernels address the elements of a stage (up to 128 rows, 32 values of q) with 32-bit byte offsets from
 // a 64-bit base.
 bool product_addressable(const ProductDesc &d);
-// Tile and pieces for a product of these extents.
-void product_shape(ProductDesc &d, bool f64);
+// Columns of an output tile.
+constexpr int kProductCols = 64;
+// Values of q per stage: two stages of the tallest tile take 104 KB of LDS, and the low ones leave room for a second and a third
+// workgroup on a compute unit, which covers the beginning and end of the other one (stages of 64 there: both gradients of
+// 512 x 1024 x 768 40.8 us instead of 36.2, a product that is one round of tiles the same).
+constexpr int kProductStage = 32;
+// Tile and pieces for a product of these extents and operands.
+void product_shape(ProductDesc &d);
+// Two products that run one after the other: would they be faster in one launch (pair_rows of both)?
+void product_pair(ProductDesc &x, ProductDesc &y);
+// The product with its operands exchanged: the transposed result.
+ProductDesc product_turned(const ProductDesc &d);
 // Bytes of partial sums a product needs (0: none).
 size_t product_partial_bytes(const ProductDesc &d);
 // Is a forward sum of K terms for M x N results so short that a thread per result of the general kernels is the faster one?

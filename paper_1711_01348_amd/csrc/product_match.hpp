@@ -2,24 +2,110 @@
 // families.cpp.
 #pragma once
 #include <algorithm>
+#include <cmath>
 
 #include "plan.hpp"
 #include "product.hpp"
 
 namespace tad {
 
-void product_shape(ProductDesc &d, bool f64) {
-    auto tiles = [&](int t) { return (long long)((d.R + t - 1) / t) * ((d.C + t - 1) / t); };
-    d.pieces = 1;
-    d.chunk = d.Q;
-    // Tile edge 64 from three workgroups per compute unit on (2001 x 2002 x 2003: 311 us against 348 us with edge 32; with one
-    // workgroup per compute unit it is the slower one, 1000 x 1203 x 777: 72 us against 60 us).  64-bit operands always take
-    // edge 32, whose sums are shared by the wavefronts and therefore rounded less.
-    d.tile = !f64 && tiles(64) >= 768 ? 64 : 32;
-    if (d.tile == 32 && tiles(32) < 256 && d.Q >= 512) {
-        const long long want = std::min<long long>((512 + tiles(32) - 1) / tiles(32), d.Q / 256);
-        d.chunk = (int)(((d.Q + want - 1) / want + 63) / 64 * 64);
-        d.pieces = (d.Q + d.chunk - 1) / d.chunk;
+// Time of a product in cycles of 2.2 GHz: tiles go to the 256 compute units in turn, whose matrix cores take 16 `rows` cycles per
+// value of q; a tile takes some time to begin and to end, which another one on the same unit covers.  Fitted to 32-bit products: 512 x 1024
+// x 768 with rows = 1 .. 4 (two tiles a unit, one, one, one) 21.7, 20.1, 25.8, 31.7 us, 512 x 512 x 512 with 1 and 2 9.7 and 13.7 us.
+// kReduceCycles: the launch that adds pieces up.
+constexpr double kTileCycles = 7000, kReduceCycles = 9000, kLaunchCycles = 6000;
+// Cycles of `each` tiles that a compute unit works on at once.  A stage of a low tile that is alone there takes as long as its barrier, LDS and
+// the loads behind it (512 x 43 x 1832: one round of 58 stages 24 us).
+static double sum_cycles(int rows, int64_t q, int64_t each) {
+    const double cycles = rows == 1 ? 20.0 : rows == 2 ? 18.0 : 17.0;   // (low tiles: more fragments to read per instruction)
+    return (double)((q + kProductStage - 1) / kProductStage) * std::max(900.0, cycles * kProductStage * (double)(rows * each));
+}
+// tiles that share a compute unit: what registers and LDS leave room for
+static int tiles_per_unit(const ProductDesc &d, int rows) {
+    if (d.a64 && d.b64) return rows == 1 ? 2 : 1;
+    return rows == 1 ? 3 : rows <= (d.a64 || d.b64 ? 3 : 4) ? 2 : 1;
+}
+static int64_t tile_count(const ProductDesc &d, int rows, bool flip) {
+    const int64_t R = flip ? d.C : d.R, C = flip ? d.R : d.C;
+    return ((R + 16 * rows - 1) / (16 * rows)) * ((C + kProductCols - 1) / kProductCols);
+}
+// sums of 64-bit operands take three sets of registers: a tile of six does not fit
+static int rows_limit(const ProductDesc &d) { return d.a64 && d.b64 ? 5 : 8; }
+static double product_cycles(const ProductDesc &d, int rows, bool flip, int pieces, int chunk) {
+    const int64_t each = (tile_count(d, rows, flip) * pieces + 255) / 256, at_once = tiles_per_unit(d, rows);
+    const int64_t rounds = (each + at_once - 1) / at_once;
+    const double t = (double)rounds * kTileCycles + (double)(rounds - 1) * sum_cycles(rows, chunk, at_once) +
+                     sum_cycles(rows, chunk, each - (rounds - 1) * at_once);
+    return pieces == 1 ? t : t + kReduceCycles + (double)pieces * d.R * d.C * 16.0 / 2000.0;   // written and read
+}
+
+void product_shape(ProductDesc &d) {
+    d.pair_rows = 0;
+    double best = -1;
+    for (int flip = 0; flip < 2; ++flip)   // 16 x 100000 results are tiles of 16 x 64, not of 64 x 64 a quarter full
+        for (int rows = 1; rows <= rows_limit(d); ++rows) {
+            const int64_t tiles = tile_count(d, rows, flip);
+            // more pieces than one only where the tiles leave compute units idle, and none shorter than 128
+            const int64_t most = tiles < 256 ? std::max<int64_t>(1, std::min<int64_t>(512 / tiles, d.Q / 128)) : 1;
+            for (int64_t want = 1; want <= most; want += 1 + want / 8) {
+                const int chunk = want == 1 ? d.Q : (int)(((d.Q + want - 1) / want + 127) / 128 * 128);
+                const int pieces = (d.Q + chunk - 1) / chunk;
+                const double t = product_cycles(d, rows, flip, pieces, chunk);
+                if (best >= 0 && t >= best) continue;
+                best = t;
+                d.rows = rows;
+                d.flip = flip;
+                d.pieces = pieces;
+                d.chunk = chunk;
+            }
+        }
+}
+
+ProductDesc product_turned(const ProductDesc &d) {
+    ProductDesc t = d;
+    std::swap(t.R, t.C);
+    std::swap(t.ar, t.bc);
+    std::swap(t.aq, t.bq);
+    std::swap(t.a64, t.b64);
+    return t;
+}
+
+// n0 tiles of t0 cycles, then n1 of t1 <= t0, on 256 compute units that take at_once tiles and the next one when one of them is done
+static double pair_cycles(int64_t n0, double t0, int64_t n1, double t1, int at_once) {
+    if (at_once > 1 && n0 + n1 <= 256 * at_once) {   // all in their places from the start: the first unit has the most
+        const int64_t of0 = (n0 + 255) / 256, all = (n0 + n1 + 255) / 256;
+        return kTileCycles + (double)of0 * t0 + (double)(all - of0) * t1;
+    }
+    t0 += kTileCycles / at_once;
+    t1 += kTileCycles / at_once;
+    const int64_t late = n0 % 256;   // units that are free one tile after the others
+    const double from[2] = {(double)(n0 / 256) * t0, (double)(n0 / 256 + 1) * t0};
+    const int64_t units[2] = {256 - late, late};
+    const double even = ((double)n0 * t0 + (double)n1 * t1) / 256.0;   // no earlier than this
+    int64_t k[2];                    // tiles of the second kind that a unit has done
+    for (int c = 0; c < 2; ++c) k[c] = std::max<int64_t>(0, (int64_t)((even - from[c]) / t1));
+    while (units[0] * k[0] + units[1] * k[1] < n1) ++k[late && from[1] + (double)k[1] * t1 < from[0] + (double)k[0] * t1 ? 1 : 0];
+    return std::max(from[0] + (double)k[0] * t1, late ? from[1] + (double)k[1] * t1 : 0.0);
+}
+
+void product_pair(ProductDesc &x, ProductDesc &y) {
+    x.pair_rows = y.pair_rows = 0;
+    double best = product_cycles(x, x.rows, x.flip, x.pieces, x.chunk) + product_cycles(y, y.rows, y.flip, y.pieces, y.chunk) + kLaunchCycles;
+    for (int flips = 0; flips < 4; ++flips) {
+        const bool fx = flips & 1, fy = flips >> 1;
+        // one kernel: both with operands of the same widths in the same order
+        if ((fx ? x.b64 : x.a64) != (fy ? y.b64 : y.a64) || (fx ? x.a64 : x.b64) != (fy ? y.a64 : y.b64)) continue;
+        for (int rows = 1; rows <= rows_limit(x); ++rows) {
+            const int64_t nx = tile_count(x, rows, fx), ny = tile_count(y, rows, fy);
+            const double tx = sum_cycles(rows, x.Q, 1), ty = sum_cycles(rows, y.Q, 1);
+            const int at_once = tiles_per_unit(x, rows);
+            const double t = x.Q >= y.Q ? pair_cycles(nx, tx, ny, ty, at_once) : pair_cycles(ny, ty, nx, tx, at_once);
+            if (t >= best) continue;
+            best = t;
+            x.pair_rows = y.pair_rows = rows;
+            x.pair_flip = fx;
+            y.pair_flip = fy;
+        }
     }
 }
 
@@ -107,8 +193,9 @@ void match_product(tad_plan &pl) {
     ProductDesc &f = pp.forward;
     f.R = (int)M; f.C = (int)N; f.Q = (int)K;
     f.ar = A.sm; f.aq = A.sk; f.bq = B.sk; f.bc = B.sm;
+    f.a64 = f.b64 = f64;
     if (!product_addressable(f)) return;
-    product_shape(f, f64);
+    product_shape(f);
     const bool contraction = pl.fwd_family == TAD_FAMILY_CONTRACTION;
     pp.forward_on = contraction ? !contraction_stores(f) : !product_sum_short(f64, M, N, K);
     size_t ws = pp.forward_on ? product_partial_bytes(f) : 0;
@@ -125,11 +212,13 @@ void match_product(tad_plan &pl) {
         d.Q = (int)Y;
         if (rows) { d.R = (int)X; d.C = (int)K; d.ar = gx; d.aq = gy; d.bq = o.sm; d.bc = o.sk; }   // sum_y g(x, y) O(k, y)
         else { d.R = (int)K; d.C = (int)X; d.ar = o.sk; d.aq = o.sm; d.bq = gy; d.bc = gx; }        // sum_y O(k, y) g(x, y)
+        d.a64 = d.b64 = f64;
         if (!product_addressable(d) || (contraction && contraction_stores(d))) continue;
-        product_shape(d, f64);
+        product_shape(d);
         s.grad = true;
         ws = std::max(ws, product_partial_bytes(d));
     }
+    if (pp.side[0].grad && pp.side[1].grad) product_pair(pp.side[0].desc, pp.side[1].desc);
     pp.ws_bytes = ws;
     pp.on = pp.forward_on || pp.side[0].grad || pp.side[1].grad;
 }

@@ -257,8 +257,9 @@ void match_separable(tad_plan &pl) {
     ProductDesc &f = sp.forward;
     f.R = (int)M; f.C = (int)N; f.Q = (int)K;
     f.ar = A.sm; f.aq = A.sk; f.bq = B.sk; f.bc = B.sm;
+    f.a64 = wide(A); f.b64 = wide(B);
     if (!product_addressable(f)) return;
-    product_shape(f, wide(A) && wide(B));
+    product_shape(f);
     size_t part = product_partial_bytes(f);
     for (int q = 0; q < 2; ++q) {
         SepSide &s = sp.side[q];
@@ -268,12 +269,15 @@ void match_separable(tad_plan &pl) {
         d.Q = (int)o.X;
         if (!s.k_major) { d.R = (int)s.X; d.C = (int)K; d.ar = gx; d.aq = gy; d.bq = o.sm; d.bc = o.sk; }
         else { d.R = (int)K; d.C = (int)s.X; d.ar = o.sk; d.aq = o.sm; d.bq = gy; d.bc = gx; }
+        d.a64 = s.k_major ? wide(o) : f64;
+        d.b64 = s.k_major ? f64 : wide(o);
         if (!product_addressable(d)) return;
-        product_shape(d, f64);
+        product_shape(d);
         part = std::max(part, product_partial_bytes(d));
         if (!s.sub) continue;
         for (size_t p = 0; p < s.operands.size(); ++p) s.aligned.push_back(pairs_are_elements(*s.sub, (int)p));
     }
+    product_pair(sp.side[0].grad, sp.side[1].grad);
     for (int p = 0; p < n_ops; ++p) sp.term_is_g[p] = same_program(sp.prog.douter_arg[p], sp.prog.douter);
     for (int p = 0; p < n_ops; ++p) {
         if (!((sp.prog.outer_mask >> p) & 1u)) continue;

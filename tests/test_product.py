@@ -143,3 +143,42 @@ def test_families_and_workspace_are_those_of_the_general_kernels():
     assert B.Plan(e).forward_family == "generic" and B.Plan(e, generic_only=True).forward_family == "generic"
     e = wl.matmul_expr(40, 23, 5000, "f64")             # few tiles, long sum: partial sums
     assert B.Plan(e).workspace_bytes > B.Plan(e, generic_only=True).workspace_bytes
+
+
+# tiles of every height, either orientation, sums that end in every part of the loop over stages of 32 (none, one, several stages with loads ahead,
+# odd and even numbers, a partial last one); the last two: pieces of the sum
+HEIGHTS = [(138, 379, 81, "f32"), (1621, 137, 39, "f32"), (611, 1631, 33, "f32"), (821, 577, 57, "f32"), (1173, 518, 65, "f32"), (927, 775, 25, "f32"),
+           (1210, 673, 97, "f32"), (623, 1643, 27, "f32"), (743, 1607, 129, "f32"), (1303, 1293, 18, "f32"), (1127, 1477, 13, "f32"), (1999, 2003, 14, "f32"),
+           (1871, 1601, 34, "f32"), (200, 941, 161, "f64"), (1449, 175, 38, "f64"), (538, 903, 193, "f64"), (825, 601, 61, "f64"), (488, 1155, 49, "f64"),
+           (1595, 466, 31, "f64"), (1217, 1315, 225, "f64"), (1181, 906, 27, "f64"), (1141, 1110, 96, "f64"), (45, 51, 777, "f32"), (30, 1201, 640, "f64")]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("I,J,K,dtype", HEIGHTS)
+def test_tiles_of_every_height(I, J, K, dtype):
+    """Against numpy in 64 bits with the limits of check.py; 64-bit sums: within 16 units in the last place of the sum of the terms' magnitudes
+    (chains of at most 16 + sqrt(K) additions, twice)."""
+    from paper_1711_01348_amd import binding as B
+    expr = wl.matmul_expr(I, J, K, dtype)
+    w = wl.random_inputs(expr, 79)
+    x, y = (a.astype(np.float64) for a in w.arg_list())
+    d = w.df.astype(np.float64)
+    f, (dx, dy) = _run(B.Plan(expr), w)
+    for got, p, q in ((f, x, y), (dx, d, y.T), (dy, x.T, d)):
+        ref = p @ q
+        assert check.within(got, ref, dtype), check.errors(got, ref)
+        if dtype == "f64":
+            assert np.all(np.abs(got - ref) <= 16 * 2.0**-52 * (np.abs(p) @ np.abs(q)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("I,J,K", [(1003, 701, 33), (1622, 137, 39), (137, 1622, 70), (2100, 1700, 19)])
+def test_tiles_of_functions_and_with_an_outer_function(I, J, K):
+    """Operands of either width, the outer function on tiles of either orientation."""
+    from paper_1711_01348_amd import binding as B
+    for expr in (wl.softplus_ratio_expr(I, J, K, "f32"), wl.dense_layer_expr(I, J, K, "f32")):
+        w = wl.random_inputs(expr, 80)
+        f, grads = _run(B.Plan(expr), w)
+        assert check.within(f, oracle.forward(expr, w.arg_list()), "f32")
+        for g, r in zip(grads, oracle.backward(expr, w.arg_list(), w.df)):
+            assert check.within(g, r, "f32"), check.errors(g, r)
