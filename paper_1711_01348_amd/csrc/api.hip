@@ -56,6 +56,7 @@ int tad_eval_forward(const tad_plan *plan, const void *const *args_dev, void *f_
     if (plan->sep.forward_on && use_separable(*plan, ws_dev, ws_bytes)) return separable_forward(*plan, args_dev, f_dev, ws_dev, s);
     if (use_worked_wide(*plan, ws_dev, ws_bytes)) return worked_wide_forward(*plan, args_dev, f_dev, s);
     if (use_pattern_wide(*plan, ws_dev, ws_bytes)) return pattern_wide_forward(*plan, args_dev, f_dev, s);
+    if (plan->window.on) return window_forward(*plan, args_dev, f_dev, s);
     if (plan->prod.forward_on && use_product(*plan, ws_dev, ws_bytes)) return product_forward(*plan, args_dev, f_dev, ws_dev, s);
     switch (plan->fwd_family) {
     case TAD_FAMILY_GENERIC: return generic_forward(*plan, args_dev, f_dev, ws_dev, s);
@@ -86,6 +87,7 @@ int tad_eval_backward(const tad_plan *plan, const void *const *args_dev, const v
     if (use_separable(*plan, ws_dev, ws_bytes)) return separable_backward(*plan, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
     if (use_worked_wide(*plan, ws_dev, ws_bytes)) return worked_wide_backward(*plan, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
     if (plan->pattern_wide_sums && use_pattern_wide(*plan, ws_dev, ws_bytes)) return pattern_wide_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
+    if (plan->window.on && room(*plan, ws_dev, ws_bytes)) return window_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
     void *rest[kMaxArgs];   // the gradients the dense products leave to the family
     if (use_product(*plan, ws_dev, ws_bytes)) {
         for (size_t p = 0; p < plan->args.size(); ++p) rest[p] = dx_dev[p];

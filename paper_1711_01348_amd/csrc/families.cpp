@@ -9,6 +9,7 @@
 #include "product_match.hpp"
 #include "separable_match.hpp"
 #include "split.h"
+#include "window_match.hpp"
 
 namespace tad {
 
@@ -424,9 +425,11 @@ static void select_pattern_wide(tad_plan &plan) {
 }
 
 void select_wide(tad_plan &plan) {
-    if ((plan.flags & TAD_PLAN_GENERIC_ONLY) || plan.has_alias || plan.expr.n_constraints > 0) return;
+    if ((plan.flags & TAD_PLAN_GENERIC_ONLY) || plan.has_alias) return;
     // its terms are listed, or the plan is to have its ranges walked
     if (!plan.term_list.empty() || ((plan.flags & TAD_PLAN_NO_TERM_LISTS) && small_expression(plan))) return;
+    match_window(plan);
+    if (plan.expr.n_constraints > 0) return;
     select_worked_wide(plan);
     select_pattern_wide(plan);
 }

@@ -33,6 +33,10 @@ int pattern_backward(const tad_plan &pl, const void *const *args, const void *df
 int pattern_wide_forward(const tad_plan &pl, const void *const *args, void *f, hipStream_t s);
 int pattern_wide_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws, hipStream_t s);
 
+// sums over a moving window
+int window_forward(const tad_plan &pl, const void *const *args, void *f, hipStream_t s);
+int window_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws, hipStream_t s);
+
 int strided_forward(const tad_plan &pl, const void *const *args, void *f, hipStream_t s);
 int strided_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df,
                      void *const *dx, void *ws, hipStream_t s);

@@ -11,6 +11,7 @@
 #include "program.hpp"
 #include "separable.hpp"
 #include "snf.hpp"
+#include "window.hpp"
 
 namespace tad {
 
@@ -77,6 +78,7 @@ struct tad_plan {
     int pattern_wide = TAD_FAMILY_GENERIC;     // row reduce or antidiagonal pattern on the kernels with 64-bit sums (workspace: ws_full)
     bool pattern_wide_sums = false;            // ... its gradient as well (else the forward pass alone)
     bool split = false;                        // contraction family: some products run on the bf16 matrix cores (workspace: ws_full)
+    tad::WindowPlan window;                    // sums over a moving window (workspace of the gradients: ws_full)
     tad::SepPlan sep;                          // sums of products of two functions (on: the whole expression runs on dense products)
     size_t ws_bytes = 0;                       // workspace of the family's kernels
     size_t ws_full = 0;                        // ... and of the dense products; a smaller workspace runs without those
@@ -105,6 +107,7 @@ bool linear_form_range(const int64_t *a, int D, const int64_t *lo, const int64_t
 void select_families(tad_plan &plan);
 // An expression on the plan-driven kernels whose terms fit in a list (listed unless the plan's flags say otherwise).
 bool small_expression(const tad_plan &plan);
-// ... and, once small expressions have their terms listed, the kernels with 64-bit sums of the worked expression and the patterns.
+// ... and, once small expressions have their terms listed, the kernels with 64-bit sums of the worked expression, the patterns
+// and moving windows.
 void select_wide(tad_plan &plan);
 }  // namespace tad

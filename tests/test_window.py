@@ -1,0 +1,113 @@
+"""Sums over a window that moves with one function index: on kernels of their own, against the oracle and the plan-driven kernels."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1711_01348_amd import check
+from paper_1711_01348_amd import workloads as wl
+from paper_1711_01348_amd.workloads import ArgSpec, ExprSpec
+
+
+def window_expr(N, K, q, dtype, swap=False, more_x=0, more_w=0, limits=None):
+    """f_i = sum_k x_{i + q k} w_k; limits (first, last): conditions on the element of x that is read."""
+    row = [1, q]
+    limits = (0, None) if q < 0 and limits is None else limits
+    cons = []
+    if limits:
+        first, last = limits
+        cons = ([(row, -first)] if first is not None else []) + ([([-1, -q], last)] if last is not None else [])
+    n_x = (N if q < 0 else N + K - 1) + more_x
+    args = [ArgSpec("x", (n_x,), [row]), ArgSpec("w", (K + more_w,), [[0, 1]])]
+    return ExprSpec("mul", (N,), [(0, K - 1)], args[::-1] if swap else args, dtype, constraints=cons)
+
+
+CASES = [(1025, 33, -1, {}), (1024, 2, -1, {}), (700, 128, -1, dict(swap=True)), (2047, 256, -1, dict(more_x=3, more_w=2)), (1000, 255, 1, {}),
+         (1281, 7, 1, dict(more_x=5, more_w=1, swap=True)), (1500, 64, 1, dict(limits=(100, None))), (1500, 61, 1, dict(limits=(3, 1200))),
+         (1500, 60, -1, dict(limits=(700, 1201))), (1030, 17, 1, dict(limits=(None, 40))), (131072, 5, -1, {}), (131077, 33, 1, dict(more_x=1)),
+         (133000, 130, -1, dict(limits=(1000, 131000))), (400100, 9, -1, {}), (750100, 24, 1, {})]
+
+
+def _run(plan, w, ws_bytes=None, skip=()):
+    import torch
+    from paper_1711_01348_amd import binding as B
+    args = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in w.arg_list()]
+    df = torch.from_numpy(w.df).cuda()
+    f = torch.full_like(df, float("nan"))
+    grads = [torch.full_like(a, float("nan")) for a in args]
+    n = plan.workspace_bytes if ws_bytes is None else ws_bytes
+    ws = torch.empty(n + 256, dtype=torch.uint8, device="cuda")
+    ws[n:] = 77
+    ptrs = (ctypes.c_void_p * 2)(*[t.data_ptr() for t in args])
+    outs = (ctypes.c_void_p * 2)(*[None if p in skip else t.data_ptr() for p, t in enumerate(grads)])
+    assert B.lib.tad_eval_forward(plan._h, ptrs, f.data_ptr(), ws.data_ptr() if n else None, n, None) == 0
+    assert B.lib.tad_eval_backward(plan._h, ptrs, f.data_ptr(), df.data_ptr(), outs, ws.data_ptr() if n else None, n, None) == 0
+    torch.cuda.synchronize()
+    assert bool((ws[n:] == 77).all())
+    return f.cpu().numpy(), [g.cpu().numpy() for g in grads]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("N,K,q,more", CASES)
+def test_windows_of_either_direction(N, K, q, more, dtype):
+    """Also each gradient alone, and in the least workspace the plan accepts, where the gradients are the general kernels'."""
+    from paper_1711_01348_amd import binding as B
+    e = window_expr(N, K, q, dtype, **more)
+    w = wl.random_inputs(e, 11)
+    plan, general = B.Plan(e), B.Plan(e, generic_only=True)
+    f_ref, g_ref = oracle.forward(e, w.arg_list()), oracle.backward(e, w.arg_list(), w.df)
+    f, grads = _run(plan, w)
+    assert check.within(f, f_ref, dtype), check.errors(f, f_ref)
+    for g, r in zip(grads, g_ref):
+        assert check.within(g, r, dtype), check.errors(g, r)
+        assert np.all(g[r == 0] == 0)
+    for p in (0, 1):
+        assert np.array_equal(_run(plan, w, skip=(p,))[1][1 - p], grads[1 - p])
+    f, grads = _run(plan, w, general.workspace_bytes)
+    assert check.within(f, f_ref, dtype) and all(check.within(g, r, dtype) for g, r in zip(grads, g_ref))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("q", [1, -1])
+def test_terms_outside_the_sum_do_not_reach_it(q):
+    """An infinite window element and a NaN of x reach the results whose sums have them, at the ends of the signal too."""
+    from paper_1711_01348_amd import binding as B
+    N, K = 1300, 40
+    e = window_expr(N, K, q, "f32", limits=(20, 1250))
+    w = wl.random_inputs(e, 12)
+    x, v = w.arg_list()
+    v[K - 1] = np.inf
+    x[600] = np.nan
+    x[5] = np.nan            # read by no term
+    f, (dx, dw) = _run(B.Plan(e), w)
+    x64, v64, d64 = x.astype(np.float64), v.astype(np.float64), w.df.astype(np.float64)
+    fr, dxr, dwr = np.zeros(N), np.zeros(len(x)), np.zeros(K)
+    i = np.arange(N)
+    with np.errstate(invalid="ignore"):
+        for k in range(K):
+            m = i + q * k
+            ok = (m >= 20) & (m <= 1250)
+            fr[i[ok]] += x64[m[ok]] * v64[k]
+            dxr[m[ok]] += d64[i[ok]] * v64[k]
+            dwr[k] = np.sum(d64[i[ok]] * x64[m[ok]])
+    for got, ref in ((f, fr), (dx, dxr), (dw, dwr)):
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+        ok = np.isfinite(ref)
+        assert check.within(np.where(ok, got, 0), np.where(ok, ref, 0), "f32")
+
+
+def test_what_is_no_window_stays_on_the_general_kernels():
+    """The workspace says which: the partial sums of the window are asked for beyond what the general kernels need."""
+    from paper_1711_01348_amd import binding as B
+
+    def asks(e):
+        return B.Plan(e).workspace_bytes > B.Plan(e, generic_only=True).workspace_bytes
+
+    N, K = 200000, 40
+    assert asks(window_expr(N, K, -1, "f32", limits=(0, None))) and asks(window_expr(N, K, 1, "f64"))
+    strided = ExprSpec("mul", (N,), [(0, K - 1)], [ArgSpec("x", (2 * N + K,), [[2, 1]]), ArgSpec("w", (K,), [[0, 1]])], "f32")
+    other = ExprSpec("mul", (N,), [(0, K - 1)], [ArgSpec("x", (N + K,), [[1, 1]]), ArgSpec("w", (K,), [[0, 1]])], "f32", constraints=[([1, -1], 0)])
+    assert not asks(strided) and not asks(other)
+    assert not asks(window_expr(N, 257, 1, "f32"))
