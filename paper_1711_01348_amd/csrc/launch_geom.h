@@ -76,44 +76,65 @@ inline size_t split_workspace_bytes(long long n_elements, int splits) {
 
 constexpr int kStridedDwElems = 1024;  // function elements per dw block of the strided family, direct form (multiple of 256)
 
-// Strided family: the tiled kernels stage contiguous slices of x (forward, dw) and of df (1 - f^2) (dx) in LDS.
-//   ti  rows i of f per forward / dw block (0: the slice of x does not fit, direct kernels)
-//   tp  rows p of x per dx wavefront       (0: the slice of f does not fit, direct kernel)
+// Strided family, forward: a workgroup takes ti rows i of f and stages the slice of x they read in LDS (0: the slice does not
+// fit, direct kernel).
 struct StridedTiling {
-    int ti, tp;
-    int x_slice;    // floats of LDS for the slice of x (with room for the alignment shift)
-    int t_slice;    // floats of LDS for the slice of df (1 - f^2), per wavefront
+    int ti;
+    int x_slice;    // floats of LDS for the slice of x
 };
 constexpr int kStridedLdsFloats = 10240;   // 40 KiB per block: four blocks per compute unit
-constexpr int kStridedMaxPerThread = 4;    // function elements per thread of a dw block
-constexpr int kStridedWaveFloats = 1280;   // LDS of one wavefront of a dx block: its slice of df (1 - f^2)
-inline StridedTiling strided_tiling(int64_t N, int64_t I, int64_t J, int64_t U, int64_t s, int64_t P, int64_t Q) {
-    StridedTiling t{0, 0, 0, 0};
-    // forward / dw: rows s*i0 .. s*(i0+ti-1)+U-1 of x, whole rows; prefer at least 1024 blocks
+constexpr int kStridedMaxPerThread = 4;    // function elements per thread
+inline StridedTiling strided_tiling(int64_t N, int64_t I, int64_t J, int64_t U, int64_t s, int64_t Q) {
+    StridedTiling t{0, 0};
+    if (N > 65535) return t;   // N along the second axis of the grid
+    // rows s*i0 .. s*(i0+ti-1)+U-1 of x, whole rows; prefer at least 1024 blocks
     for (int ti = 8; ti >= 1; --ti) {
-        const int64_t slice = (s * (ti - 1) + U) * Q + 8;   // + alignment shift and the ragged last vector
+        const int64_t slice = (s * (ti - 1) + U) * Q;
         if (ti * J > 256 * kStridedMaxPerThread || slice > kStridedLdsFloats) continue;
         if (t.ti == 0) { t.ti = ti; t.x_slice = (int)slice; }
         if (N * ((I + ti - 1) / ti) >= 1024) { t.ti = ti; t.x_slice = (int)slice; break; }
     }
-    // dx: a wavefront takes tp rows p and 64 columns q; the rows ceil((p0-U+1)/s) .. floor((p0+tp-1)/s) of f carry its
-    // terms.  Whole rows of f between the first and the last term: (rows - 1) J + about 64 / s + U columns.
-    for (int tp = 16; tp >= 1; --tp) {
-        const int64_t rows = (tp - 1 + U - 1) / s + 2;
-        const int64_t piece = (rows - 1) * J + 64 / s + U + 2 + 8;
-        if (piece > kStridedWaveFloats) continue;
-        t.tp = tp;
-        t.t_slice = (int)kStridedWaveFloats;
-        break;
-    }
-    (void)P;
     return t;
 }
-inline size_t strided_workspace_bytes(int64_t N, int64_t I, int64_t J, int64_t U, int64_t V, int64_t s, int64_t P, int64_t Q) {
-    const StridedTiling t = strided_tiling(N, I, J, U, s, P, Q);
-    const int64_t direct = (N * I * J + kStridedDwElems - 1) / kStridedDwElems;
-    const int64_t tiled = t.ti ? N * ((I + t.ti - 1) / t.ti) : 0;
-    return align256((size_t)(direct > tiled ? direct : tiled) * (size_t)(U * V) * 4);
+// sums of dw of as many workgroups as the direct or the tiled forward kernel has
+inline int64_t strided_parts(int64_t N, int64_t I, int64_t J, int64_t U, int64_t s, int64_t Q) {
+    const StridedTiling t = strided_tiling(N, I, J, U, s, Q);
+    const int64_t direct = (N * I * J + kStridedDwElems - 1) / kStridedDwElems, tiled = t.ti ? N * ((I + t.ti - 1) / t.ti) : 0;
+    return direct > tiled ? direct : tiled;
+}
+inline size_t strided_workspace_bytes(int64_t N, int64_t I, int64_t J, int64_t U, int64_t V, int64_t s, int64_t Q) {
+    return align256((size_t)strided_parts(N, I, J, U, s, Q) * (size_t)(U * V) * 4);
+}
+// Gradients: a workgroup takes ti steps of the stride along p, `each` pairs (i, j) per thread (ti = 0: direct kernel).
+struct StridedGrad {
+    int ti, each, blocks;          // blocks: workgroups per n
+    int width, n_i, hu, hv;        // pairs in a row and the columns of t in front of them; rows of pairs; see StridedRows
+    int t_floats, x_floats;        // LDS
+};
+inline StridedGrad strided_grad(int64_t N, int64_t I, int64_t J, int64_t U, int64_t V, int64_t s, int64_t P, int64_t Q) {
+    const int64_t hu = (U - 1) / s, hv = (V - 1) / s, width = (Q + s - 1) / s + hv, n_i = (P + s - 1) / s;
+    const int64_t parts = strided_parts(N, I, J, U, s, Q);
+    StridedGrad best{0, 0, 0, 0, 0, 0, 0, 0, 0};
+    // elements of dx that a wavefront stores together are s apart; a grid has up to 65535 n
+    if (s > 8 || N > 65535) return best;
+    // many pairs per thread share the waits; but at least two workgroups per compute unit, and no more sums than the workspace holds
+    const int order[] = {8, 1, 2, 4};
+    for (int each : order) {
+        int64_t ti = 256 * each / width;
+        if (ti > n_i) ti = n_i;
+        int64_t t = 0, x = 0;
+        for (; ti >= 1; --ti) {
+            t = (hv + hu * width + 256 * each + 3) & ~(int64_t)3;
+            x = (s * (ti - 1) + U) * Q;
+            if (t + x <= kStridedLdsFloats || (ti == 1 && t + x <= 15872)) break;
+        }
+        if (ti < 1) continue;
+        const int64_t blocks = (n_i + ti - 1) / ti;
+        if (N * blocks > parts) continue;
+        if (best.ti == 0 || best.each == 8 || N * blocks >= 512)
+            best = {(int)ti, each, (int)blocks, (int)width, (int)n_i, (int)hu, (int)hv, (int)t, (int)x};
+    }
+    return best;
 }
 
 // antidiagonal pattern, backward: aligned tiles of df; a tile yields AD_TILE_ROWS + AD_TILE_COLS antidiagonal sums
