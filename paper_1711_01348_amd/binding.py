@@ -122,6 +122,14 @@ def _load():
 
 
 lib = _load()
+from . import _calls  # noqa: E402  (checks of tensors and the call in one native function; needs torch in the process)
+
+
+def _entry(function) -> int:
+    return ctypes.cast(function, ctypes.c_void_p).value
+
+
+_FORWARD, _BACKWARD, _DERIVED = _entry(lib.tad_eval_forward), _entry(lib.tad_eval_backward), _entry(lib.tad_eval_derived)
 
 
 _torch = None
@@ -225,6 +233,7 @@ class Plan:
         self._operands = [(None if getattr(q, "same_as", None) is not None else tuple(int(n) for n in q.shape), q.name)
                           for q in expr.args]
         self._pointers = ctypes.c_void_p * len(expr.args)
+        self._spec = _calls.spec(self.dtype == F64, self._f_shape, tuple(shape for shape, _ in self._operands))
 
     def __del__(self):
         h, self._h = getattr(self, "_h", None), None
@@ -377,6 +386,12 @@ class Plan:
 
     def forward(self, args, out=None, ws=None):
         torch = _torch or _import_torch()
+        if out is not None and ws is not None:
+            rc = _calls.forward(_FORWARD, self._h.value, self._spec, args, out, ws, _current_stream())
+            if rc is not None:
+                if rc:
+                    raise TadError(rc, "tad_eval_forward")
+                return out
         dtype = torch.float64 if self.dtype == F64 else torch.float32
         ptrs = self._arg_ptrs(args, dtype)
         if out is None:
@@ -391,6 +406,12 @@ class Plan:
     def backward(self, args, f, df, wanted: Optional[Sequence[bool]] = None, out=None, ws=None, static=False):
         """static=True: tad_eval_backward_static (the library's own fixed scratch array instead of a workspace)."""
         torch = _torch or _import_torch()
+        if out is not None and ws is not None and not static:
+            rc = _calls.backward(_BACKWARD, self._h.value, self._spec, args, f, df, out, ws, _current_stream())
+            if rc is not None:
+                if rc:
+                    raise TadError(rc, "tad_eval_backward")
+                return out
         dtype = torch.float64 if self.dtype == F64 else torch.float32
         ptrs = self._arg_ptrs(args, dtype)
         f_ptr = self._pointer(f, self._f_shape, dtype, "f")
@@ -440,6 +461,11 @@ class DerivedGradient:
     def evaluate(self, args, df, out=None, ws=None):
         torch = _torch or _import_torch()
         plan = self.plan
+        if out is not None and ws is not None:
+            rc = _calls.derived(_DERIVED, self._h.value, plan._spec, args, df, self.arg, out, ws, _current_stream())
+            if rc is not None:
+                _check(rc, "tad_eval_derived")
+                return out
         dtype = plan._torch_dtype()
         ptrs = plan._arg_ptrs(args, dtype)
         df_ptr = plan._pointer(df, plan._f_shape, dtype, "df")

@@ -1,4 +1,4 @@
-"""Build libtad.so (host planner + gfx950 kernels + C ABI) in-tree with hipcc."""
+"""Build libtad.so (host planner + gfx950 kernels + C ABI) with hipcc and the module of native calls with g++, in-tree."""
 from __future__ import annotations
 
 import concurrent.futures as cf
@@ -11,6 +11,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libtad.so")
+CALLS = os.path.join(PKG, "_calls.so")   # Python module: calls with torch tensors
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CXX = os.environ.get("CXX", "g++")
@@ -40,11 +41,29 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.cpp")) + glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def _build_calls() -> None:
+    import sysconfig
+    import torch
+    root = os.path.join(os.path.dirname(torch.__file__))
+    include = os.path.join(root, "include")
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"], "-isystem", include,
+           "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", os.path.join(PKG, "calls.cpp"), "-o", CALLS,
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+
+
 def build(jobs: int = 8) -> str:
-    """Compile every source and link the shared library.  Always rebuilds."""
+    """Compile every source and link the shared libraries.  Always rebuilds."""
     os.makedirs(OBJ, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        calls = ex.submit(_build_calls)
         objs = list(ex.map(_compile, sources()))
+        calls.result()
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
