@@ -52,6 +52,10 @@ struct ProductTask {
     int wide;          // store 64-bit results
     int turned;        // store the result [c][r]
     int flush;         // stages of a subtotal (64-bit operands)
+    int scaled;        // see ProductJob
+    const double *by[2];
+    void *to[2];
+    int to_wide[2];
 };
 // One or two products (the derivatives of the two factors of a sum) in one launch: workgroup b works on the first one for
 // b < first, else on the second one.
@@ -293,6 +297,28 @@ __device__ __forceinline__ void product_kernel(const ProductArgs &M, const Produ
     constexpr int RESULTS = ER * EC / NT;
     if constexpr (std::is_same<TO, void>::value) {
         // neighbouring threads along the direction that is contiguous in the result
+#pragma unroll 1
+        for (int t = 0; t < P.scaled; ++t) {   // the same for the whole workgroup
+            const double *const by = P.by[t];
+            double v[RESULTS];
+            int at[RESULTS];
+#pragma unroll
+            for (int p = 0; p < RESULTS; ++p) {
+                const int n = tid + NT * p, ir = P.turned ? n % ER : n / EC, ic = P.turned ? n / ER : n % EC, r = r0 + ir, c = c0 + ic;
+                const int place = P.turned ? c * P.R + r : r * P.C + c;
+                at[p] = r < P.R && c < P.C ? place : -1;
+                v[p] = by[max(at[p], 0)];
+            }
+#pragma unroll
+            for (int p = 0; p < RESULTS; ++p) {
+                const int n = tid + NT * p, ir = P.turned ? n % ER : n / EC, ic = P.turned ? n / ER : n % EC;
+                v[p] *= sums[ir * LDS_SUM + ic];
+                if (at[p] < 0) continue;
+                if (P.to_wide[t]) static_cast<double *>(P.to[t])[at[p]] = v[p];
+                else static_cast<float *>(P.to[t])[at[p]] = (float)v[p];
+            }
+        }
+        if (P.scaled) return;
 #pragma unroll
         for (int p = 0; p < RESULTS; ++p) {
             const int n = tid + NT * p, ir = P.turned ? n % ER : n / EC, ic = P.turned ? n / ER : n % EC, r = r0 + ir, c = c0 + ic;
@@ -396,6 +422,12 @@ static ProductTask product_task(const ProductJob &j, int rows, bool share, void 
     P.gr = (d.R + edge - 1) / edge; P.gc = (d.C + kProductCols - 1) / kProductCols;
     P.wide = j.c64 || P.pieces > 1;
     P.turned = j.turned;
+    P.scaled = j.scaled;
+    for (int t = 0; t < 2; ++t) {
+        P.by[t] = j.by[t];
+        P.to[t] = j.to[t];
+        P.to_wide[t] = j.to64[t];
+    }
     // 16 products in a row, then `flush` stages of a subtotal, then the total: the last two chains of about the same length
     const double blocks = P.chunk / 32.0, per_stage = kProductStage / 32.0;   // of a wavefront: half the sum
     P.flush = std::max(1, (int)(std::sqrt(blocks) / per_stage + 0.5));
@@ -468,6 +500,8 @@ int product_run(const ProductJob &j, void *ws, hipStream_t s) {
     const ProductJob job = j.desc->flip ? exchanged(j, d) : j;
     return launch_jobs(&job, 1, j.desc->rows, true, nullptr, ws, s);
 }
+
+bool product_scales(const ProductDesc &d, bool one_of_two) { return (one_of_two && d.pair_rows) || d.pieces == 1; }
 
 bool product_outer_fits(const ProductDesc &d) { return d.pieces == 1; }
 

@@ -1,13 +1,17 @@
 // Sums of products of two functions as dense products (separable.hpp): the element-wise passes around the products.
 //
 //   forward    values of the factors that are functions of operands (64 bits), product, outer function
-//   backward   the same values and sums again, g = df * d outer / d s; then per factor its derivative (a product) and per
-//              operand of the factor dx_beta = sum over the pairs of indices that read x_beta of derivative * partial derivative:
-//              in one pass where every pair reads an element of its own, else through the terms in the workspace and a
-//              sum through the operand's plan
+//   backward   the same values and sums again, and with the values the partial derivatives of the factors; g = df * d outer / d s; then
+//              per factor its derivative (a product) and per operand of the factor dx_beta = sum over the pairs of indices that
+//              read x_beta of derivative * partial derivative: the product's results are multiplied where they leave it, and that is the
+//              gradient where every pair reads an element of its own, else terms in the workspace that are summed through the
+//              operand's plan
 // What a factor or a partial derivative costs is paid once per pair of indices instead of once per term, which leaves
 // the products as the bound (64-bit matrix instructions) and, below some 10^8 terms, the launches: 512 x 1024 x 768 with one
 // interpreted term per thread 9895 us, 1.2 10^9 interpreted terms.
+// The passes over pairs are bound by the interpreted operations and 64-bit functions.  Softplus 512 x 384 x 200, forward and gradients: partial
+// derivatives in a pass of their own after the products 61.9 us (passes over pairs 7.9 and 13.2 us); in one launch with the values, the products
+// scaled, 60.1 (17.7 us: as much work in a row); value and partial derivatives of a side as one program, which shares exp and cos, 53.5 (11.3 us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -32,6 +36,7 @@ struct PairTask {
     const double *d;       // null: out = prog, else out = d * prog
     double *out;           // 64-bit results, or null:
     void *dx;              // ... results of the operands' type
+    double *results[3];    // a program of several results (all else null): where they go, null for those nobody wants
     int32_t n_ops, n, first;
 };
 template <int N> struct PairTasks {
@@ -48,7 +53,12 @@ __global__ __launch_bounds__(256) void k_sep_pairs(const PairTasks<N> M) {
     if (lin >= t.n) return;
     double v[kMaxArgs];
     element_values<T>(t.plan, t.n_ops, ~0u, t.args, lin, v);
-    const double o = prog_eval<double, FORM>(t.prog, v, 0.0), r = t.d ? t.d[lin] * o : o;
+    const double o = prog_eval<double, FORM>(t.prog, v, 0.0, [&](int n, double value) {
+        double *const to = n == 0 ? t.results[0] : n == 1 ? t.results[1] : t.results[2];
+        if (to) to[lin] = value;
+    });
+    if (!t.out && !t.dx) return;
+    const double r = t.d ? t.d[lin] * o : o;
     if (t.out) t.out[lin] = r;
     else static_cast<T *>(t.dx)[lin] = (T)r;
 }
@@ -149,14 +159,17 @@ template <typename T>
 struct PairPass {
     PairTasks<6> tasks{};
     int blocks = 0;
-    bool registers = true;
+    bool registers = true, joint = false;
     hipStream_t stream;
     explicit PairPass(hipStream_t s) : stream(s) {}
-    int add(const SepSide &side, const void *const *args, const DevProg &prog, const double *d, double *out, void *dx) {
-        if (tasks.count == 6) {
+    int add(const SepSide &side, const void *const *args, const DevProg &prog, const double *d, double *out, void *dx,
+            double *const *results = nullptr) {
+        // a launch is of one form, and programs of several results are in registers
+        if (tasks.count == 6 || (results && !registers) || (joint && !has_register_form(prog))) {
             const int rc = run();
             if (rc) return rc;
         }
+        joint = joint || results;
         const tad_plan &sub = *side.sub;
         PairTask &t = tasks.task[tasks.count++];
         t.plan = sub.fwd;
@@ -165,6 +178,7 @@ struct PairPass {
         t.d = d;
         t.out = out;
         t.dx = dx;
+        for (int n = 0; n < 3; ++n) t.results[n] = results ? results[n] : nullptr;
         t.n_ops = (int)sub.args.size();
         t.n = (int)sub.f_count;
         t.first = blocks;
@@ -185,17 +199,75 @@ struct PairPass {
         const int rc = tasks.count <= 2 ? launch<2>() : tasks.count == 3 ? launch<3>() : launch<6>();
         tasks.count = blocks = 0;
         registers = true;
+        joint = false;
         return rc;
     }
 };
 
-// the factors that are functions of operands
+// Where a gradient's partial derivative is kept for the product to scale its results by: an aligned operand's in the place of the
+// factor's derivative, which is not stored then, another one's where its terms go.
+static double *partial_place(const SepSide &side, int p, char *ws) {
+    return reinterpret_cast<double *>(ws + (side.aligned[p] ? side.d_offset : side.h_offset[p]));
+}
+
+// a factor like exp(x) r: the partial derivative is the value
+static bool partial_is_value(const SepSide &side, int p) { return same_program(side.sub->prog.inner, side.sub->prog.dinner[p]); }
+
+// Is there one program for the value and the partial derivatives that are wanted?  (Derivatives of one node have one place: equal ones share
+// it with the value only.)
+static bool joint_side(const SepSide &side, const void *const *dx) {
+    if (!side.joint_on) return false;
+    uint32_t taken = 1u << side.joint_place[0];
+    for (size_t p = 0; p < side.operands.size(); ++p) {
+        const int place = side.joint_place[1 + p];
+        if ((place >= 0) != (dx[side.operands[p]] != nullptr)) return false;
+        if (place < 0) continue;
+        if (place == side.joint_place[0]) {
+            if (!partial_is_value(side, (int)p)) return false;
+            continue;
+        }
+        if (place > 2 || (taken >> place & 1u)) return false;
+        taken |= 1u << place;
+    }
+    return side.joint_place[0] <= 2;
+}
+
+// Can the product that yields a side's derivative multiply it by the partial derivatives?  (In a large workspace the terms of an operand take the
+// place of the factor's values, which the products read.)
+static bool scaled_side(const SepSide &side, const void *const *dx, bool one_of_two) {
+    if (!side.sub || side.operand >= 0 || !product_scales(side.grad, one_of_two)) return false;
+    int wanted = 0, aligned = 0;
+    for (size_t p = 0; p < side.operands.size(); ++p) {
+        if (!dx[side.operands[p]]) continue;
+        ++wanted;
+        if (side.aligned[p]) ++aligned;
+        else if (side.h_offset[p] == side.value_offset) return false;
+    }
+    return wanted >= 1 && wanted <= 2 && aligned <= 1;
+}
+
+// the factors that are functions of operands, and with them the partial derivatives (dx: the gradients wanted) of the sides that `scaled` says
 template <typename T>
-static int evaluate_factors(const SepPlan &sp, const void *const *args, char *ws, hipStream_t s) {
+static int evaluate_factors(const SepPlan &sp, const void *const *args, char *ws, hipStream_t s, const bool *scaled = nullptr,
+                            const void *const *dx = nullptr) {
     PairPass<T> pass(s);
-    for (const SepSide &side : sp.side) {
+    for (int q = 0; q < 2; ++q) {
+        const SepSide &side = sp.side[q];
         if (side.operand >= 0) continue;
-        const int rc = pass.add(side, args, side.sub->prog.inner, nullptr, reinterpret_cast<double *>(ws + side.value_offset), nullptr);
+        double *const value = reinterpret_cast<double *>(ws + side.value_offset);
+        int rc;
+        if (scaled && scaled[q] && joint_side(side, dx)) {   // functions that value and partial derivatives share are evaluated once
+            double *results[3] = {};
+            for (size_t p = 0; p < side.operands.size(); ++p)
+                if (dx[side.operands[p]]) results[side.joint_place[1 + p]] = partial_place(side, (int)p, ws);
+            results[side.joint_place[0]] = value;
+            rc = pass.add(side, args, side.joint, nullptr, nullptr, nullptr, results);
+            if (rc) return rc;
+            continue;
+        }
+        rc = pass.add(side, args, side.sub->prog.inner, nullptr, value, nullptr);
+        for (int p = 0; !rc && scaled && scaled[q] && p < (int)side.operands.size(); ++p)
+            if (dx[side.operands[p]] && !partial_is_value(side, p)) rc = pass.add(side, args, side.sub->prog.dinner[p], nullptr, partial_place(side, p, ws), nullptr);
         if (rc) return rc;
     }
     return pass.run();
@@ -224,9 +296,10 @@ static int apply_outer(const tad_plan &pl, const ProgramBody &pb, const DevProg 
 // Sums through `prog` (null: stored as they are) into out; s_out (may be null): where the sums themselves are needed as well.
 // df: see k_sep_outer.
 template <typename T>
-static int sums(const tad_plan &pl, const DevProg *prog, const void *const *args, const void *df, void *out, T *s_out, char *ws, hipStream_t s) {
+static int sums(const tad_plan &pl, const DevProg *prog, const void *const *args, const void *df, void *out, T *s_out, char *ws, hipStream_t s,
+                const bool *scaled = nullptr, const void *const *dx = nullptr) {
     const SepPlan &sp = pl.sep;
-    int rc = evaluate_factors<T>(sp, args, ws, s);
+    int rc = evaluate_factors<T>(sp, args, ws, s, scaled, dx);
     if (rc) return rc;
     constexpr bool f64 = sizeof(T) == 8;
     const SepSide &a = sp.side[0], &b = sp.side[1];
@@ -299,9 +372,18 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *f
     const T *g = static_cast<const T *>(df), *sum = nullptr;
     // the derivatives of the outer function are those of f where they can be: that saves the sums
     const bool from_f = outer_in_f(pl, sp.prog, dx);
+    bool wanted[2] = {}, scaled[2];
+    for (int q = 0; q < 2; ++q) {
+        const SepSide &side = sp.side[q];
+        if (side.sub)
+            for (int p : side.operands) wanted[q] = wanted[q] || dx[p];
+        else
+            wanted[q] = dx[side.operand] != nullptr;
+    }
+    for (int q = 0; q < 2; ++q) scaled[q] = scaled_side(sp.side[q], dx, wanted[0] && wanted[1]);
     int rc;
     if (sp.identity || from_f) {
-        rc = evaluate_factors<T>(sp, args, ws, s);
+        rc = evaluate_factors<T>(sp, args, ws, s, scaled, dx);
         if (!rc && !sp.identity) {
             T *const gw = reinterpret_cast<T *>(ws + sp.g_offset);
             sum = static_cast<const T *>(f);
@@ -313,21 +395,17 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *f
         for (int q = 0; q < n_ops; ++q)
             if (dx[q] && ((sp.prog.outer_mask >> q) & 1u) && !sp.term_is_g[q]) s_out = reinterpret_cast<T *>(ws + sp.s_offset);
         T *const gw = reinterpret_cast<T *>(ws + sp.g_offset);
-        rc = sums<T>(pl, &sp.prog.douter, args, df, gw, s_out, ws, s);
+        rc = sums<T>(pl, &sp.prog.douter, args, df, gw, s_out, ws, s, scaled, dx);
         g = gw;
         sum = s_out;
     }
     if (rc) return rc;
     // the derivatives of the factors
-    bool stored[kMaxArgs] = {}, wanted[2] = {};
+    bool stored[kMaxArgs] = {};
     ProductJob jobs[2];
     int n_jobs = 0;
     for (int q = 0; q < 2; ++q) {
         const SepSide &side = sp.side[q], &other = sp.side[1 - q];
-        if (side.sub)
-            for (int p : side.operands) wanted[q] = wanted[q] || dx[p];
-        else
-            wanted[q] = dx[side.operand] != nullptr;
         if (!wanted[q]) continue;
         const void *o = factor(other, args, ws);
         const bool o64 = f64 || other.operand < 0, wide = f64 || side.sub;
@@ -335,6 +413,14 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *f
         if (side.k_major) jobs[n_jobs++] = {&side.grad, o, o64, g, f64, to, wide};
         else jobs[n_jobs++] = {&side.grad, g, f64, o, o64, to, wide};
         if (!side.sub) stored[side.operand] = true;
+        for (int p = 0; scaled[q] && p < (int)side.operands.size(); ++p) {
+            void *const d = dx[side.operands[p]];
+            if (!d) continue;
+            ProductJob &j = jobs[n_jobs - 1];
+            j.by[j.scaled] = partial_is_value(side, p) ? reinterpret_cast<const double *>(ws + side.value_offset) : partial_place(side, p, ws);
+            j.to[j.scaled] = side.aligned[p] ? d : partial_place(side, p, ws);
+            j.to64[j.scaled++] = f64 || !side.aligned[p];
+        }
     }
     rc = n_jobs == 2 ? product_run_two(jobs[0], jobs[1], part, s) : n_jobs == 1 ? product_run(jobs[0], part, s) : TAD_OK;
     if (rc) return rc;
@@ -350,6 +436,7 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *f
             // an aligned operand moves along the side's function index: the other side does not read it
             direct[q][p] = side.aligned[p];
             if (direct[q][p]) stored[op] = true;
+            if (scaled[q]) continue;
             rc = pass.add(side, args, side.sub->prog.dinner[p], reinterpret_cast<const double *>(ws + side.d_offset),
                           direct[q][p] ? nullptr : reinterpret_cast<double *>(ws + side.h_offset[p]), dx[op]);
             if (rc) return rc;

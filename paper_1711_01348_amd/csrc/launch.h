@@ -62,11 +62,18 @@ struct ProductJob {
     void *c;
     bool c64;
     bool turned = false;
+    // not 0: instead of the result v itself, to[n] = v * by[n] for n < scaled, element by element (a product of a single piece)
+    int scaled = 0;
+    const double *by[2] = {};
+    void *to[2] = {};
+    bool to64[2] = {};
 };
 struct ProductOuter;
 // ws: partial sums of shared tiles
 int product_run(const ProductJob &j, void *ws, hipStream_t s);
 int product_run_two(const ProductJob &x, const ProductJob &y, void *ws, hipStream_t s);
+// can the results of this product, run alone or as one of two, be scaled?
+bool product_scales(const ProductDesc &d, bool one_of_two);
 // the product's results through a program in register form (only where product_outer_fits)
 bool product_outer_fits(const ProductDesc &d);
 int product_run_outer(const ProductJob &j, const ProductOuter &o, hipStream_t s);

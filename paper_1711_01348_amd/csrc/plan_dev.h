@@ -187,7 +187,8 @@ struct DevProg {
     // registers (indexed by a wave-uniform number) instead of the thread's private memory.
     //   word[i] = op | first << 8 | second << 16 | destination << 24        (n_words of them)
     //   first, second: an operand code (prog_code_*: register, tensor operand, constant, the sum); for P_POWI
-    //   `second` is the exponent; destination: a register.  result_code: operand code of the result.
+    //   `second` is the exponent; destination: a register (and, in programs of several results, in the four uppermost bits
+    //   the number of the result that the operation yields, from 1).  result_code: operand code of the result.
     // n_regs < 0: the program needs more registers than there are; only the form above exists.
     int32_t n_regs;
     int32_t n_words;

@@ -3,6 +3,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "plan_dev.h"
 
 namespace tad {
@@ -79,8 +81,12 @@ template <typename T> struct ProgWidth { static constexpr int U = sizeof(T) == 4
 // for much of it).  The kernels below are built in three forms (template parameter FORM): 0 one temporary per
 // operation, one term per pass; 1 registers, one term per pass (elements with one or two terms: several terms per
 // pass would only cost registers, i.e. waves per SIMD); 2 registers, ProgWidth<T>::U terms per pass.
-template <typename T, int U, bool REGS>
-__device__ __forceinline__ void prog_eval_block(const DevProg &P, const T (&v)[kMaxArgs][U], const T (&s)[U], T (&out)[U]) {
+// sink(n, value of the first term): results of a program of several (register form); nothing in all others.
+struct NoSink {
+    template <typename T> __device__ __forceinline__ void operator()(int, T) const {}
+};
+template <typename T, int U, bool REGS, typename SINK = NoSink>
+__device__ __forceinline__ void prog_eval_block(const DevProg &P, const T (&v)[kMaxArgs][U], const T (&s)[U], T (&out)[U], SINK sink = SINK()) {
     static_assert(U >= 1 && U <= 4, "one register array per term below");
     if (P.result < 0) {
 #pragma unroll
@@ -161,6 +167,9 @@ __device__ __forceinline__ void prog_eval_block(const DevProg &P, const T (&v)[k
 #pragma unroll
             for (int u = 0; u < U; ++u) o[u] = prog_unary<T>(op, x[u], second);
         }
+        if constexpr (!std::is_same<SINK, NoSink>::value) {
+            if (w >> 28) sink((int)(w >> 28) - 1, o[0]);   // the same for the whole wavefront
+        }
         r0[dst] = o[0];
         if (U > 1) r1[dst] = o[U > 1 ? 1 : 0];
         if (U > 2) r2[dst] = o[U > 2 ? 2 : 0];
@@ -173,12 +182,12 @@ __device__ __forceinline__ void prog_eval_block(const DevProg &P, const T (&v)[k
 }
 
 // one term
-template <typename T, int FORM>
-__device__ __forceinline__ T prog_eval(const DevProg &P, const T *v, T s) {
+template <typename T, int FORM, typename SINK = NoSink>
+__device__ __forceinline__ T prog_eval(const DevProg &P, const T *v, T s, SINK sink = SINK()) {
     T vv[kMaxArgs][1], ss[1] = {s}, out[1];
 #pragma unroll
     for (int q = 0; q < kMaxArgs; ++q) vv[q][0] = v[q];
-    prog_eval_block<T, 1, (FORM > 0)>(P, vv, ss, out);
+    prog_eval_block<T, 1, (FORM > 0), SINK>(P, vv, ss, out, sink);
     return out[0];
 }
 

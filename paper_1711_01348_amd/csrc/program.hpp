@@ -269,7 +269,7 @@ inline double eval_host_registers(const DevProg &P, const double *v, double s) {
     for (int i = 0; i < P.n_words; ++i) {
         const uint32_t w = P.word[i];
         const uint8_t op = (uint8_t)(w & 0xff);
-        const int first = (int)((w >> 8) & 0xff), second = (int)((w >> 16) & 0xff), dst = (int)(w >> 24);
+        const int first = (int)((w >> 8) & 0xff), second = (int)((w >> 16) & 0xff), dst = (int)(w >> 24) & (kProgRegs - 1);
         r[dst] = op == P_POWI ? prog_apply(op, fetch(first), 0.0, second)
                               : prog_apply(op, fetch(first), prog_is_binary(op) ? fetch(second) : 0.0, 0);
     }
@@ -327,28 +327,27 @@ inline void allocate_registers(DevProg &P) {
     P.n_regs = high;
 }
 
-// The nodes that `node` depends on (itself included), after simplification.
-inline std::vector<char> nodes_below(const Graph &g, const std::vector<int> &alias, int node) {
-    std::vector<char> live(g.nodes.size(), 0);
-    live[alias[node]] = 1;
+// live: marks the nodes that the marked ones depend on, after simplification.
+inline void mark_below(const Graph &g, const std::vector<int> &alias, std::vector<char> &live) {
     for (int i = (int)g.nodes.size() - 1; i >= 0; --i) {
         if (!live[i]) continue;
         if (g.nodes[i].a >= 0) live[alias[g.nodes[i].a]] = 1;
         if (g.nodes[i].b >= 0) live[alias[g.nodes[i].b]] = 1;
     }
+}
+inline std::vector<char> nodes_below(const Graph &g, const std::vector<int> &alias, int node) {
+    std::vector<char> live(g.nodes.size(), 0);
+    live[alias[node]] = 1;
+    mark_below(g, alias, live);
     return live;
 }
 
-// Lower the part of the graph that `result` depends on: simplified as above, equal constants share a slot, the
-// nodes are renumbered densely.  False if it does not fit or reads an operand that an expression cannot have.
-inline bool lower(const Graph &g, int result, DevProg &out) {
+// Lower the live nodes of a graph: equal constants share a slot, the nodes are renumbered densely (slot).  False if it does not
+// fit or reads an operand that an expression cannot have.
+inline bool lower_nodes(const Graph &g, const std::vector<int> &alias, const std::vector<char> &live, std::vector<int> &slot, DevProg &out) {
     out = DevProg{};
-    if (result < 0) { out.n = 0; out.result = -1; return true; }
     const int N = (int)g.nodes.size();
-    const std::vector<int> alias = simplify(g);
-    result = alias[result];
-    const std::vector<char> live = nodes_below(g, alias, result);
-    std::vector<int> slot(N, -1);
+    slot.assign(N, -1);
     int n = 0, nc = 0;
     for (int i = 0; i < N; ++i) {
         if (!live[i]) continue;
@@ -376,8 +375,62 @@ inline bool lower(const Graph &g, int result, DevProg &out) {
         slot[i] = n++;
     }
     out.n = n;
-    out.result = slot[result];
+    return true;
+}
+
+// Lower the part of the graph that `result` depends on, simplified as above.
+inline bool lower(const Graph &g, int result, DevProg &out) {
+    out = DevProg{};
+    if (result < 0) { out.n = 0; out.result = -1; return true; }
+    const std::vector<int> alias = simplify(g);
+    std::vector<int> slot;
+    if (!lower_nodes(g, alias, nodes_below(g, alias, alias[result]), slot, out)) return false;
+    out.result = slot[alias[result]];
     allocate_registers(out);
+    return true;
+}
+
+// One program for several results (register form only): the operation that yields result n carries n + 1 in the four uppermost bits
+// of its word, for the interpreter to store it where it comes about.  place[i]: the number of roots[i] among the results (roots
+// of one node share it).  False if a root is no operation (zero, an operand, a constant) or the program has no register form.
+inline bool lower_joint(const Graph &g, const std::vector<int> &roots, DevProg &out, std::vector<int> &place) {
+    const std::vector<int> alias = simplify(g);
+    std::vector<char> live(g.nodes.size(), 0);
+    for (int r : roots) {
+        if (r < 0 || prog_is_leaf(g.nodes[alias[r]].op)) return false;
+        live[alias[r]] = 1;
+    }
+    mark_below(g, alias, live);
+    std::vector<int> slot;
+    if (!lower_nodes(g, alias, live, slot, out)) return false;
+    out.result = 0;
+    for (int r : roots) out.result = std::max(out.result, slot[alias[r]]);
+    allocate_registers(out);
+    if (out.n_regs < 0) return false;
+    // operations in the order of their words
+    std::vector<int> word(out.n, -1);
+    for (int i = 0, w = 0; i < out.n; ++i)
+        if (!prog_is_leaf(out.op[i])) word[i] = w++;
+    place.clear();
+    uint32_t results = 0;
+    for (int r : roots) {
+        uint32_t &w = out.word[word[slot[alias[r]]]];
+        if (!(w >> 28)) {
+            if (results == 15) return false;
+            w |= ++results << 28;
+        }
+        place.push_back((int)(w >> 28) - 1);
+    }
+    return true;
+}
+
+// do two programs carry out the same operations?
+inline bool same_program(const DevProg &x, const DevProg &y) {
+    if (x.n != y.n || x.result != y.result) return false;
+    for (int i = 0; i < x.n; ++i)
+        if (x.op[i] != y.op[i] || x.a[i] != y.a[i] || x.b[i] != y.b[i] || x.k[i] != y.k[i]) return false;
+    for (int c = 0; c < kMaxProgConst; ++c)
+        if (x.cst[c] != y.cst[c]) return false;
     return true;
 }
 

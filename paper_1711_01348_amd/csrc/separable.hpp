@@ -34,6 +34,11 @@ struct SepSide {
     // is the factor and its gradient is the product (or not wanted)
     std::shared_ptr<tad_plan> sub;
     std::vector<int> operands;   // operand of sub -> operand of the expression
+    // a factor that is a function of operands: its value and the partial derivatives of the operands with a gradient in one program, if
+    // that has a register form; joint_place[0]: which of its results is the value, [1 + p]: the derivative by operand p (-1: none)
+    bool joint_on = false;
+    DevProg joint;
+    int joint_place[1 + TAD_MAX_ARGS];
     std::vector<char> aligned;   // ... every pair of indices reads an element of its own, numbered alike
     // workspace, all in 64 bits
     size_t value_offset = 0;     // the evaluated factor

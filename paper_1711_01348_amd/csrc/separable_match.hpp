@@ -56,15 +56,6 @@ int side_expression(Graph &g, const std::vector<Factor> &factors) {
     return negative ? g.add(P_NEG, q) : q;
 }
 
-bool same_program(const DevProg &x, const DevProg &y) {
-    if (x.n != y.n || x.result != y.result) return false;
-    for (int i = 0; i < x.n; ++i)
-        if (x.op[i] != y.op[i] || x.a[i] != y.a[i] || x.b[i] != y.b[i] || x.k[i] != y.k[i]) return false;
-    for (int c = 0; c < kMaxProgConst; ++c)
-        if (x.cst[c] != y.cst[c]) return false;
-    return true;
-}
-
 // every pair of indices reads an element of its own, numbered alike
 bool pairs_are_elements(const tad_plan &sub, int p) {
     if (sub.arg_count[p] != sub.f_count) return false;
@@ -241,6 +232,18 @@ void match_separable(tad_plan &pl) {
             // KEEP_PROGRAM: the derivatives of the factor are read from its program
             if (derive_plan(&se, sa, se.n_operands, pl.dtype, TAD_PLAN_KEEP_PROGRAM, &sub)) return;
             s.sub.reset(sub);
+            if (s.operand < 0 && wanted) {
+                Graph gs;
+                const int value = parse_postfix(se.inner, se.n_inner, false, se.n_operands, gs);
+                std::vector<int> grads, roots{value}, place;
+                reverse_accumulate(gs, value, se.n_operands, grads);
+                for (int p = 0; p < se.n_operands; ++p)
+                    if (sa[p].needs_grad) roots.push_back(grads[p]);
+                s.joint_on = lower_joint(gs, roots, s.joint, place);
+                size_t at_root = 0;
+                s.joint_place[0] = s.joint_on ? place[at_root++] : -1;
+                for (int p = 0; p < se.n_operands; ++p) s.joint_place[1 + p] = s.joint_on && sa[p].needs_grad ? place[at_root++] : -1;
+            }
         }
         if (s.operand >= 0) {
             s.sm = sm;
