@@ -62,6 +62,8 @@ struct ProductTask {
 struct ProductArgs {
     ProductTask task[2];
     int first;
+    int columns_first;      // workgroups from here on: column sums
+    ProductColumns columns;
 };
 // Neighbouring workgroups go to different dies: each die gets a contiguous range of tiles, walked in groups of eight
 // tile rows, so that workgroups that run together share operand tiles in their L2.
@@ -79,6 +81,30 @@ __device__ __forceinline__ void product_tile(int lid, int gr, int gc, int &tr, i
 
 typedef double double2p __attribute__((ext_vector_type(2)));
 
+// Sums of 16 columns: 32 threads to a column, whose loads go out eight at a time, added in a fixed order.
+constexpr int kColumnSums = 16;
+template <typename T>
+__device__ __forceinline__ void column_sums(const ProductColumns &S, int block, double *red) {
+    constexpr int PARTS = 512 / kColumnSums, U = 8;
+    const int tid = threadIdx.x, col = tid % kColumnSums, part = tid / kColumnSums, c = block * kColumnSums + col;
+    const T *at = static_cast<const T *>(S.g) + (size_t)min(part, S.R - 1) * S.C + min(c, S.C - 1);
+    double sum = 0.0;
+    for (int r = part; r < S.R; r += U * PARTS, at += (size_t)U * PARTS * S.C) {
+        T v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = at[(size_t)(r + u * PARTS < S.R ? u * PARTS : 0) * S.C];
+#pragma unroll
+        for (int u = 0; u < U; ++u) sum += r + u * PARTS < S.R ? (double)v[u] : 0.0;
+    }
+    red[tid] = sum;
+    __syncthreads();
+    if (part != 0 || c >= S.C) return;
+    sum = 0.0;
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) sum += red[p * kColumnSums + col];
+    static_cast<T *>(S.out)[c] = (T)sum;
+}
+
 template <typename TA, typename TB, int NR, typename TO>
 __device__ __forceinline__ void product_kernel(const ProductArgs &M, const ProductOuter *O) {
     constexpr bool BLOCKED = sizeof(TA) == 8 && sizeof(TB) == 8;   // sums of 16 products added to a subtotal
@@ -94,6 +120,13 @@ __device__ __forceinline__ void product_kernel(const ProductArgs &M, const Produ
     static_assert(PA * NT == ER * KT && PB * NT == EC * KT && CHUNKS % 2 == 0, "whole stages");
     __shared__ __attribute__((aligned(16))) double lds[TILES > SUMS ? TILES : SUMS];
     double *const As = lds, *const Bs = lds + 2 * SIZE_A;
+    if constexpr (std::is_same<TO, void>::value) {
+        if (__builtin_expect((int)blockIdx.x >= M.columns_first, 0)) {
+            if (M.columns.wide) column_sums<double>(M.columns, (int)blockIdx.x - M.columns_first, lds);
+            else column_sums<float>(M.columns, (int)blockIdx.x - M.columns_first, lds);
+            return;
+        }
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const ProductTask &P = M.task[(int)blockIdx.x < M.first ? 0 : 1];   // the same for the whole workgroup
     const int id = (int)blockIdx.x - ((int)blockIdx.x < M.first ? 0 : M.first), tiles = P.gr * P.gc, piece = id / tiles;
@@ -298,7 +331,7 @@ __device__ __forceinline__ void product_kernel(const ProductArgs &M, const Produ
     if constexpr (std::is_same<TO, void>::value) {
         // neighbouring threads along the direction that is contiguous in the result
 #pragma unroll 1
-        for (int t = 0; t < P.scaled; ++t) {   // the same for the whole workgroup
+        for (int t = 0; __builtin_expect(t < P.scaled, 0); ++t) {   // the same for the whole workgroup
             const double *const by = P.by[t];
             double v[RESULTS];
             int at[RESULTS];
@@ -476,13 +509,19 @@ static ProductJob exchanged(const ProductJob &j, ProductDesc &d) {
 }
 
 // count (1 or 2) products of the same operand types in one launch; share: their sums in pieces (one product only)
-static int launch_jobs(const ProductJob *jobs, int count, int rows, bool share, const ProductOuter *outer, void *ws, hipStream_t s) {
+static int launch_jobs(const ProductJob *jobs, int count, int rows, bool share, const ProductOuter *outer, void *ws, hipStream_t s,
+                       const ProductColumns *columns = nullptr) {
     ProductArgs M{};
     unsigned blocks = 0;
     for (int q = 0; q < count; ++q) {
         M.task[q] = product_task(jobs[q], rows, share, ws);
         blocks += (unsigned)(M.task[q].gr * M.task[q].gc * M.task[q].pieces);
         if (q == 0) M.first = (int)blocks;
+    }
+    M.columns_first = (int)blocks;
+    if (columns) {
+        M.columns = *columns;
+        blocks += (unsigned)((columns->C + kColumnSums - 1) / kColumnSums);
     }
     const ProductJob &j = jobs[0];
     int rc;
@@ -495,10 +534,10 @@ static int launch_jobs(const ProductJob *jobs, int count, int rows, bool share, 
     return j.c64 ? reduce_pieces<double>(ws, j.c, n, j.desc->pieces, s) : reduce_pieces<float>(ws, j.c, n, j.desc->pieces, s);
 }
 
-int product_run(const ProductJob &j, void *ws, hipStream_t s) {
+int product_run(const ProductJob &j, void *ws, hipStream_t s, const ProductColumns *columns) {
     ProductDesc d;
     const ProductJob job = j.desc->flip ? exchanged(j, d) : j;
-    return launch_jobs(&job, 1, j.desc->rows, true, nullptr, ws, s);
+    return launch_jobs(&job, 1, j.desc->rows, true, nullptr, ws, s, columns);
 }
 
 bool product_scales(const ProductDesc &d, bool one_of_two) { return (one_of_two && d.pair_rows) || d.pieces == 1; }
@@ -514,15 +553,15 @@ int product_run_outer(const ProductJob &j, const ProductOuter &o, hipStream_t s)
     return launch_jobs(&job, 1, d.rows, false, &t, nullptr, s);
 }
 
-int product_run_two(const ProductJob &x, const ProductJob &y, void *ws, hipStream_t s) {
+int product_run_two(const ProductJob &x, const ProductJob &y, void *ws, hipStream_t s, const ProductColumns *columns) {
     // one launch for both where that is faster: two products fill the chip better than one (product_pair)
     if (x.desc->pair_rows) {
         ProductDesc d[2];
         ProductJob jobs[2] = {x.desc->pair_flip ? exchanged(x, d[0]) : x, y.desc->pair_flip ? exchanged(y, d[1]) : y};
         if (x.desc->Q < y.desc->Q) std::swap(jobs[0], jobs[1]);   // the longer ones first
-        return launch_jobs(jobs, 2, x.desc->pair_rows, false, nullptr, ws, s);
+        return launch_jobs(jobs, 2, x.desc->pair_rows, false, nullptr, ws, s, columns);
     }
-    const int rc = product_run(x, ws, s);
+    const int rc = product_run(x, ws, s, columns);
     return rc ? rc : product_run(y, ws, s);
 }
 

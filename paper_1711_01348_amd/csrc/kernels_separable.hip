@@ -358,6 +358,16 @@ static int sum_through_plan(const GatherPlan &g, int64_t count, double pairs, co
     return TAD_OK;
 }
 
+// is the operand part of a factor (whose gradient is added to that of the outer function)?
+static bool inner_reads(const SepPlan &sp, int operand) {
+    for (const SepSide &side : sp.side) {
+        if (side.operand == operand) return true;
+        for (int p : side.operands)
+            if (p == operand) return true;
+    }
+    return false;
+}
+
 template <typename T>
 static int forward_t(const tad_plan &pl, const void *const *args, void *f, char *ws, hipStream_t s) {
     return sums<T>(pl, pl.sep.identity ? nullptr : &pl.sep.prog.outer, args, nullptr, f, nullptr, ws, s);
@@ -422,7 +432,18 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *f
             j.to64[j.scaled++] = f64 || !side.aligned[p];
         }
     }
-    rc = n_jobs == 2 ? product_run_two(jobs[0], jobs[1], part, s) : n_jobs == 1 ? product_run(jobs[0], part, s) : TAD_OK;
+    // the gradient of a bias along the trailing indices, the column sums of g, beside the first product: in a launch of its own it takes as long
+    // as launches do (512 x 1024 x 768 6.7 us of 68).  Its 32 threads per column are not to outlast the product: up to 4096 rows.
+    ProductColumns columns{};
+    bool summed[kMaxArgs] = {};
+    for (int q = 0; n_jobs && !columns.out && q < n_ops; ++q) {
+        if (!dx[q] || !((sp.prog.outer_mask >> q) & 1u) || !sp.term_is_g[q] || stored[q] || !sp.outer_linear) continue;
+        if (sp.outer_r[q] != 0 || sp.outer_c[q] != 1 || pl.arg_count[q] != sp.N || sp.M > 4096 || inner_reads(sp, q)) continue;
+        columns = {g, dx[q], (int)sp.M, (int)sp.N, f64};
+        summed[q] = true;
+    }
+    const ProductColumns *const beside = columns.out ? &columns : nullptr;
+    rc = n_jobs == 2 ? product_run_two(jobs[0], jobs[1], part, s, beside) : n_jobs == 1 ? product_run(jobs[0], part, s, beside) : TAD_OK;
     if (rc) return rc;
     // derivative of the factor * derivative by its operand, at every pair of indices ...
     PairPass<T> pass(s);
@@ -460,7 +481,7 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *f
         }
     }
     for (int q = 0; q < n_ops; ++q) {
-        if (!dx[q]) continue;
+        if (!dx[q] || summed[q]) continue;
         if (!((sp.prog.outer_mask >> q) & 1u)) {
             if (stored[q]) continue;
             TAD_LAUNCH("k_clear", (k_clear<T>), dim3(clear_blocks<T>(pl.arg_count[q])), dim3(256), 0, s, static_cast<T *>(dx[q]),

@@ -69,9 +69,16 @@ struct ProductJob {
     bool to64[2] = {};
 };
 struct ProductOuter;
-// ws: partial sums of shared tiles
-int product_run(const ProductJob &j, void *ws, hipStream_t s);
-int product_run_two(const ProductJob &x, const ProductJob &y, void *ws, hipStream_t s);
+// Column sums out[c] = sum_r g[r][c] beside a product (64 bits on the way; wide: 64-bit elements)
+struct ProductColumns {
+    const void *g;
+    void *out;
+    int R, C;
+    bool wide;
+};
+// ws: partial sums of shared tiles; columns: null, or sums that the first launch does as well
+int product_run(const ProductJob &j, void *ws, hipStream_t s, const ProductColumns *columns = nullptr);
+int product_run_two(const ProductJob &x, const ProductJob &y, void *ws, hipStream_t s, const ProductColumns *columns = nullptr);
 // can the results of this product, run alone or as one of two, be scaled?
 bool product_scales(const ProductDesc &d, bool one_of_two);
 // the product's results through a program in register form (only where product_outer_fits)

@@ -82,3 +82,27 @@ def test_scaled_gradients(make, I, J, K):
         ws.fill_(255)
         alone = plan.backward(args, f, df, wanted=[p == only for p in range(len(args))], ws=ws)[only].cpu().numpy()
         assert check.within(alone, reference[only], expr.dtype), (only, check.errors(alone, reference[only]))
+
+
+@pytest.mark.gpu
+# fewer rows than threads to a column, one batch and more than one, either side of the line; columns that do not fill a workgroup's
+@pytest.mark.parametrize("I,J,K", [(17, 16, 9), (31, 33, 20), (256, 17, 16), (257, 250, 40), (4096, 18, 16), (4097, 18, 16)])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_bias_gradients_beside_the_products(I, J, K, dtype):
+    import torch
+    from paper_1711_01348_amd import binding as B
+    expr = wl.dense_layer_expr(I, J, K, dtype)
+    w = wl.random_inputs(expr, 23, -0.5, 0.5)
+    plan = B.Plan(expr)
+    args = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in w.arg_list()]
+    df, ws = torch.from_numpy(w.df).cuda(), plan.workspace()
+    f = plan.forward(args, ws=ws)
+    reference = oracle.backward(expr, w.arg_list(), w.df)
+    n = len(args)
+    # all of them; the bias with one factor; the bias alone (no product to go with)
+    for wanted in ([True] * n, [True] + [False] * (n - 2) + [True], [False] * (n - 1) + [True]):
+        grads = plan.backward(args, f, df, wanted=wanted, ws=ws)
+        for a, g, r, is_wanted in zip(expr.args, grads, reference, wanted):
+            assert (g is not None) == is_wanted
+            if is_wanted:
+                assert check.within(g.cpu().numpy(), r, dtype), (a.name, check.errors(g.cpu().numpy(), r))
