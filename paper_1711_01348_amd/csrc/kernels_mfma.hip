@@ -44,15 +44,6 @@ __device__ __forceinline__ float wave_sum63m(float v) {   // total valid in lane
     return v;
 }
 
-__device__ __forceinline__ void zero_acc(float16v (&acc)[2][2]) {
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-}
-
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
 // ---------------------------------------------------------------------------------------------
@@ -94,43 +85,47 @@ __global__ __launch_bounds__(256) void k_mfma_prep(const float *__restrict__ a, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// forward: block tile 128 x 128, 2 x 2 waves of 64 x 64, k tile 32, global -> register -> LDS staging
+// forward: block tile 64 x 64, 2 x 2 waves of 32 x 32, k tile 32, global -> register -> LDS staging.  Four wavefronts per SIMD, which
+// wait for their barriers, loads and stores in turn; with 128 x 128 and two, forward and gradients of 700 x 1000 x 96 56.6 us instead of 47.5,
+// 3000 x 300 x 224 94 / 81, 4096 x 4096 x 256 285.5 / 281.8 (both together with the gradients' eight waves below).
 // ---------------------------------------------------------------------------------------------
 constexpr int MF_KT = 32;
 constexpr int MF_LD = 33;   // odd row stride: conflict-free ds_read_b32 of [row][k] tiles
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mfma_forward(const float *__restrict__ a, const float *__restrict__ b,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_mfma_forward(const float *__restrict__ a, const float *__restrict__ b,
                                                       const float *__restrict__ rowv, const float *__restrict__ nb,
                                                       float *__restrict__ f, int I, int J, int K) {
-    __shared__ float smem[2 * 128 * MF_LD];   // A tile then B tile; reused as the output stage in the epilogue
-    __shared__ float rv[128][4];
+    constexpr int LO = 34;   // row stride of the output stage
+    __shared__ float smem[4 * 32 * LO > 2 * 64 * MF_LD ? 4 * 32 * LO : 2 * 64 * MF_LD];   // A tile then B tile; reused as the output stage in the epilogue
+    __shared__ float rv[64][4];
     float (*As)[MF_LD] = reinterpret_cast<float (*)[MF_LD]>(smem);
-    float (*Bs)[MF_LD] = reinterpret_cast<float (*)[MF_LD]>(smem + 128 * MF_LD);
+    float (*Bs)[MF_LD] = reinterpret_cast<float (*)[MF_LD]>(smem + 64 * MF_LD);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int i0 = blockIdx.y * 128, j0 = blockIdx.x * 128;
-    if (tid < 128) {
+    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
+    if (tid < 64) {
         const int i = i0 + tid;
 #pragma unroll
         for (int q = 0; q < 4; ++q) rv[tid][q] = i < I ? rowv[i * 4 + q] : 0.f;
     }
-    float16v acc[2][2];
-    zero_acc(acc);
-    float4v ra[4], rb[4];
-    const float4v zero4 = {0.f, 0.f, 0.f, 0.f};
+    float16v acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    float4v ra[2], rb[2];
     auto gload = [&](int k0) {
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
+        for (int p = 0; p < 2; ++p) {
             const int idx = tid + 256 * p, row = idx >> 3, kq = idx & 7;
-            ra[p] = (i0 + row < I) ? *reinterpret_cast<const float4v *>(a + (size_t)(i0 + row) * K + k0 + 4 * kq) : zero4;
-            rb[p] = (j0 + row < J) ? *reinterpret_cast<const float4v *>(b + (size_t)(j0 + row) * K + k0 + 4 * kq) : zero4;
+            // (rows beyond the edge repeat the last one: their results are not stored)
+            ra[p] = *reinterpret_cast<const float4v *>(a + (size_t)min(i0 + row, I - 1) * K + k0 + 4 * kq);
+            rb[p] = *reinterpret_cast<const float4v *>(b + (size_t)min(j0 + row, J - 1) * K + k0 + 4 * kq);
         }
     };
     gload(0);
     const int mrow = lane & 31, kof = lane >> 5;
     for (int k0 = 0; k0 < K; k0 += MF_KT) {
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
+        for (int p = 0; p < 2; ++p) {
             const int idx = tid + 256 * p, row = idx >> 3, kq = idx & 7;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -141,62 +136,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         __syncthreads();
         if (k0 + MF_KT < K) gload(k0 + MF_KT);
         // the operands of step ks + 1 are read from LDS before the MFMAs of step ks are issued
-        float a0 = As[wm * 64 + mrow][kof], a1 = As[wm * 64 + 32 + mrow][kof];
-        float b0 = Bs[wn * 64 + mrow][kof], b1 = Bs[wn * 64 + 32 + mrow][kof];
+        const float *ap = &As[wm * 32 + mrow][kof], *bp = &Bs[wn * 32 + mrow][kof];
+        float a0 = ap[0], b0 = bp[0];
 #pragma unroll
         for (int ks = 0; ks < MF_KT / 2; ++ks) {
-            float na0 = 0.f, na1 = 0.f, nb0 = 0.f, nb1 = 0.f;
+            float na0 = 0.f, nb0 = 0.f;
             if (ks + 1 < MF_KT / 2) {
-                na0 = As[wm * 64 + mrow][2 * ks + 2 + kof];
-                na1 = As[wm * 64 + 32 + mrow][2 * ks + 2 + kof];
-                nb0 = Bs[wn * 64 + mrow][2 * ks + 2 + kof];
-                nb1 = Bs[wn * 64 + 32 + mrow][2 * ks + 2 + kof];
+                na0 = ap[2 * ks + 2];
+                nb0 = bp[2 * ks + 2];
             }
             __builtin_amdgcn_sched_barrier(0);
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc, 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-            a0 = na0; a1 = na1; b0 = nb0; b1 = nb1;
+            a0 = na0; b0 = nb0;
         }
         __syncthreads();
     }
-    // epilogue: f = exp2(c' (|a|^2 + |b|^2 + 2 a.b) + D').  Each wave stages 32 x 64 results at a time in its own
-    // quarter of the tile memory (32 rows of 66 floats) and writes them as 16-byte stores, 256 bytes per row.
+    // epilogue: f = exp2(c' (|a|^2 + |b|^2 + 2 a.b) + D').  Each wave stages its 32 x 32 results in its own
+    // quarter of the tile memory and writes them as 16-byte stores, 128 bytes per row.
     // (the last barrier of the loop guarantees that nobody still reads the tiles)
-    float *stage = smem + wave * (32 * 66);
-    constexpr int kStageOk = (4 * 32 * 66 <= 2 * 128 * MF_LD) ? 1 : -1;
-    static_assert(kStageOk == 1, "output stage does not fit in the tile memory");
+    float *stage = smem + wave * (32 * LO);
+    {
+        const int j = j0 + wn * 32 + mrow;
+        const float nbj = j < J ? nb[j] : 0.f;
 #pragma unroll
-    for (int tm = 0; tm < 2; ++tm) {
-#pragma unroll
-        for (int tn = 0; tn < 2; ++tn) {
-            const int j = j0 + wn * 64 + tn * 32 + mrow;
-            const float nbj = j < J ? nb[j] : 0.f;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int mloc = acc_row(r, lane), m = wm * 64 + tm * 32 + mloc;
-                const float s = rv[m][0] + nbj + 2.f * acc[tm][tn][r];
-                stage[mloc * 66 + tn * 32 + mrow] = __builtin_amdgcn_exp2f(fmaf(rv[m][1], s, rv[m][2]));
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int mloc = acc_row(r, lane), m = wm * 32 + mloc;
+            const float s = rv[m][0] + nbj + 2.f * acc[r];
+            stage[mloc * LO + mrow] = __builtin_amdgcn_exp2f(fmaf(rv[m][1], s, rv[m][2]));
         }
-        // the wave reads back only what it wrote itself: no barrier needed, LDS operations of a wave are ordered
+    }
+    // the wave reads back only what it wrote itself: no barrier needed, LDS operations of a wave are ordered
 #pragma unroll
-        for (int it = 0; it < 8; ++it) {
-            const int rl = it * 4 + (lane >> 4), c = (lane & 15) * 4;
-            const int i = i0 + wm * 64 + tm * 32 + rl, j = j0 + wn * 64 + c;
-            if (i < I && j < J) {   // J % 4 == 0: the four columns exist together
-                const float4v v = {stage[rl * 66 + c], stage[rl * 66 + c + 1], stage[rl * 66 + c + 2],
-                                   stage[rl * 66 + c + 3]};
-                *reinterpret_cast<float4v *>(f + (size_t)i * J + j) = v;
-            }
+    for (int it = 0; it < 4; ++it) {
+        const int rl = it * 8 + (lane >> 3), c = (lane & 7) * 4;
+        const int i = i0 + wm * 32 + rl, j = j0 + wn * 32 + c;
+        if (i < I && j < J) {   // J % 4 == 0: the four columns exist together
+            const float4v v = {stage[rl * LO + c], stage[rl * LO + c + 1], stage[rl * LO + c + 2], stage[rl * LO + c + 3]};
+            *reinterpret_cast<float4v *>(f + (size_t)i * J + j) = v;
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// backward contractions.  Block tile 64 (M) x 256 (N = k), 1 x 4 waves of 64 x 64, contraction tile 32.
+// backward contractions.  Block tile 64 (M) x 256 (N = k), 2 x 4 waves of 32 x 64, contraction tile 32 (four waves of 64 x 64 are two per
+// SIMD instead of four: 93.0 us instead of 89.8 for 4096 x 4096 x 256, not transposed; the other one the same).
 //   TRANS_A = false:  M = i, contraction over j in [cs, ce):  A[m][kk] = df f            B[kk][n] = b[j][k]
 //   TRANS_A = true:   M = j, contraction over i in [cs, ce):  A[m][kk] = c_ii df f (read transposed), B[kk][n] = a[i][k]
 // out[(split * Mtot + m) * K + n]
@@ -206,31 +190,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 //   TRANS_A = false:  sums[(split * 2 + 0) * I + i] = sum_j G_ij,  sums[(split * 2 + 1) * I + i] = sum_j G_ij |b_j|^2
 //   TRANS_A = true:   sums[split * J + j] = sum_i c_ii G_ij
 template <bool TRANS_A>
-__global__ __launch_bounds__(256) void k_mfma_backward(const float *__restrict__ f, const float *__restrict__ df,
+__global__ __launch_bounds__(512, 4) void k_mfma_backward(const float *__restrict__ f, const float *__restrict__ df,
                                                        const float *__restrict__ bmat, const float *__restrict__ rowv,
                                                        const float *__restrict__ nb, float *__restrict__ out,
                                                        float *__restrict__ sums, int I, int J, int K, int chunk) {
     __shared__ float As[TRANS_A ? 32 : 64][TRANS_A ? 64 : MF_LD];
     __shared__ float Bs[32][256];
-    __shared__ float tred[4][64];
-    const int tid = threadIdx.x, lane = tid & 63, wn = tid >> 6;
+    __shared__ float tred[8][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave & 1, wn = wave >> 1;
     const int Mtot = TRANS_A ? J : I, Ctot = TRANS_A ? I : J;
     const int m0 = blockIdx.x * 64, split = blockIdx.y, n0 = blockIdx.z * 256;
     const int cs = split * chunk, ce = min(Ctot, cs + chunk);
-    float16v acc[2][2];
-    zero_acc(acc);
-    float4v ga[2], gb[8];
+    float16v acc[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[x][r] = 0.f;
+    float4v ga[1], gb[4];
     // what the loads of G bring in; the products and the sums on the side are formed one tile later, when the
     // tile is staged, so that nothing waits for these loads before the matrix instructions of the current tile
-    float4v rdf[2], rf[2], rnv[2];
-    float rc[2];
+    float4v rdf[1], rf[1], rnv[1];
+    float rc[1];
     const float4v zero4 = {0.f, 0.f, 0.f, 0.f};
-    float sr[2] = {0.f, 0.f}, sq[2] = {0.f, 0.f};   // TRANS_A = false: row sums of the thread's two rows
+    float sr[1] = {0.f}, sq[1] = {0.f};   // TRANS_A = false: row sums of the thread's row
     float4v st = zero4;                               // TRANS_A = true: column sums of the thread's four columns
     auto gload = [&](int c0) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int idx = tid + 256 * p;
+        for (int p = 0; p < 1; ++p) {
+            const int idx = tid + 512 * p;
             rdf[p] = zero4; rf[p] = zero4; rnv[p] = zero4; rc[p] = 0.f;
             if (!TRANS_A) {
                 const int row = idx >> 3, q = idx & 7;            // i = m0 + row, j = c0 + 4 q
@@ -253,15 +240,15 @@ __global__ __launch_bounds__(256) void k_mfma_backward(const float *__restrict__
             }
         }
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int idx = tid + 256 * p, kk = idx >> 6, q = idx & 63;
+        for (int p = 0; p < 4; ++p) {
+            const int idx = tid + 512 * p, kk = idx >> 6, q = idx & 63;
             const int cc = c0 + kk, n = n0 + 4 * q;
             gb[p] = (cc < ce && n < K) ? *reinterpret_cast<const float4v *>(bmat + (size_t)cc * K + n) : zero4;
         }
     };
     auto gprep = [&]() {   // G of the loaded tile and its plain sums (zeros where nothing was loaded)
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
+        for (int p = 0; p < 1; ++p) {
             if (!TRANS_A) {
                 ga[p] = rdf[p] * rf[p];
                 sr[p] += (ga[p][0] + ga[p][1]) + (ga[p][2] + ga[p][3]);
@@ -277,8 +264,8 @@ __global__ __launch_bounds__(256) void k_mfma_backward(const float *__restrict__
     for (int c0 = cs; c0 < ce; c0 += MF_KT) {
         gprep();
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int idx = tid + 256 * p;
+        for (int p = 0; p < 1; ++p) {
+            const int idx = tid + 512 * p;
             if (!TRANS_A) {
                 const int row = idx >> 3, q = idx & 7;
 #pragma unroll
@@ -289,34 +276,28 @@ __global__ __launch_bounds__(256) void k_mfma_backward(const float *__restrict__
             }
         }
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const int idx = tid + 256 * p, kk = idx >> 6, q = idx & 63;
+        for (int p = 0; p < 4; ++p) {
+            const int idx = tid + 512 * p, kk = idx >> 6, q = idx & 63;
             *reinterpret_cast<float4v *>(&Bs[kk][4 * q]) = gb[p];
         }
         __syncthreads();
         if (c0 + MF_KT < ce) gload(c0 + MF_KT);
-        auto afrag = [&](int kk, int half) -> float {
-            return TRANS_A ? As[kk + kof][32 * half + mrow] : As[32 * half + mrow][kk + kof];
-        };
+        auto afrag = [&](int kk) -> float { return TRANS_A ? As[kk + kof][32 * wm + mrow] : As[32 * wm + mrow][kk + kof]; };
         // the operands of step ks + 1 are read from LDS before the MFMAs of step ks are issued
-        float a0 = afrag(0, 0), a1 = afrag(0, 1);
-        float b0 = Bs[kof][wn * 64 + mrow], b1 = Bs[kof][wn * 64 + 32 + mrow];
+        float a0 = afrag(0), b0 = Bs[kof][wn * 64 + mrow], b1 = Bs[kof][wn * 64 + 32 + mrow];
 #pragma unroll
         for (int ks = 0; ks < MF_KT / 2; ++ks) {
-            float na0 = 0.f, na1 = 0.f, nb0 = 0.f, nb1 = 0.f;
+            float na0 = 0.f, nb0 = 0.f, nb1 = 0.f;
             if (ks + 1 < MF_KT / 2) {
-                na0 = afrag(2 * ks + 2, 0);
-                na1 = afrag(2 * ks + 2, 1);
+                na0 = afrag(2 * ks + 2);
                 nb0 = Bs[2 * ks + 2 + kof][wn * 64 + mrow];
                 nb1 = Bs[2 * ks + 2 + kof][wn * 64 + 32 + mrow];
             }
             __builtin_amdgcn_sched_barrier(0);
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[1], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-            a0 = na0; a1 = na1; b0 = nb0; b1 = nb1;
+            a0 = na0; b0 = nb0; b1 = nb1;
         }
         __syncthreads();
     }
@@ -324,24 +305,22 @@ __global__ __launch_bounds__(256) void k_mfma_backward(const float *__restrict__
     for (int tn = 0; tn < 2; ++tn) {
         const int n = n0 + wn * 64 + tn * 32 + mrow;
 #pragma unroll
-        for (int tm = 0; tm < 2; ++tm)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int m = m0 + tm * 32 + acc_row(r, lane);
-                if (m < Mtot && n < K) out[((size_t)split * Mtot + m) * K + n] = acc[tm][tn][r];
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int m = m0 + wm * 32 + acc_row(r, lane);
+            if (m < Mtot && n < K) out[((size_t)split * Mtot + m) * K + n] = acc[tn][r];
+        }
     }
     if (blockIdx.z != 0) return;
     if (!TRANS_A) {
         // eight consecutive lanes share a row: add them in a fixed order
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
+        for (int p = 0; p < 1; ++p) {
 #pragma unroll
             for (int m = 1; m <= 4; m <<= 1) {
                 sr[p] += __shfl_xor(sr[p], m, 64);
                 sq[p] += __shfl_xor(sq[p], m, 64);
             }
-            const int i = m0 + (tid >> 3) + 32 * p;
+            const int i = m0 + (tid >> 3);
             if ((tid & 7) == 0 && i < I) {
                 sums[((size_t)split * 2 + 0) * I + i] = sr[p];
                 sums[((size_t)split * 2 + 1) * I + i] = sq[p];
@@ -356,11 +335,11 @@ __global__ __launch_bounds__(256) void k_mfma_backward(const float *__restrict__
         }
         if (lane < 16)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) tred[wn][lane * 4 + e] = st[e];
+            for (int e = 0; e < 4; ++e) tred[wave][lane * 4 + e] = st[e];
         __syncthreads();
         if (tid < 64) {
             const int j = m0 + tid;
-            if (j < J) sums[(size_t)split * J + j] = (tred[0][tid] + tred[1][tid]) + (tred[2][tid] + tred[3][tid]);
+            if (j < J) sums[(size_t)split * J + j] = ((tred[0][tid] + tred[1][tid]) + (tred[2][tid] + tred[3][tid])) + ((tred[4][tid] + tred[5][tid]) + (tred[6][tid] + tred[7][tid]));
         }
     }
 }
@@ -553,7 +532,7 @@ int mfma_forward(const tad_plan &pl, const void *const *args, void *f, void *ws,
                    (const float *)args[0], (const float *)args[1], w.rowv, (float *)f, I, J, K);
         return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
     }
-    TAD_LAUNCH("k_mfma_forward", k_mfma_forward, dim3((J + 127) / 128, (I + 127) / 128), dim3(256), 0, s,
+    TAD_LAUNCH("k_mfma_forward", k_mfma_forward, dim3((J + 63) / 64, (I + 63) / 64), dim3(256), 0, s,
                (const float *)args[0], (const float *)args[1], w.rowv, w.nb, (float *)f, I, J, K);
     return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
@@ -568,11 +547,11 @@ int mfma_backward(const tad_plan &pl, const void *const *args, const void *f_, c
     if (rc) return rc;
     const int nz = (K + 255) / 256;
     // the row pass always runs: r_i feeds da, dc and dd; the column pass only for db
-    TAD_LAUNCH("k_mfma_backward", (k_mfma_backward<false>), dim3((I + 63) / 64, w.n_split, nz), dim3(256), 0, s, f, df,
+    TAD_LAUNCH("k_mfma_backward", (k_mfma_backward<false>), dim3((I + 63) / 64, w.n_split, nz), dim3(512), 0, s, f, df,
                b, w.rowv, w.nb, w.Ppart, w.rowp, I, J, K, w.chunk_j);
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
     if (dx[1]) {
-        TAD_LAUNCH("k_mfma_backward", (k_mfma_backward<true>), dim3((J + 63) / 64, w.n_split, nz), dim3(256), 0, s, f,
+        TAD_LAUNCH("k_mfma_backward", (k_mfma_backward<true>), dim3((J + 63) / 64, w.n_split, nz), dim3(512), 0, s, f,
                    df, a, w.rowv, w.nb, w.Tpart, w.colp, I, J, K, w.chunk_i);
         if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
     }
