@@ -19,7 +19,8 @@ void match_window(tad_plan &pl) {
     if (!row_is(pl.args[p.w], 0, 1)) return;
     p.q = row_is(pl.args[p.x], 1, 1) ? 1 : -1;
     if (!row_is(pl.args[p.x], 1, p.q)) return;
-    const int64_t N = e.f_shape[0], K = e.sum_hi[0] + 1;
+    // conditions may keep every term away from the end of the window, and w may then end before it: the terms are those of a window as long as w
+    const int64_t N = e.f_shape[0], K = std::min(e.sum_hi[0] + 1, pl.arg_count[p.w]);
     if (N < 1 || K < 1 || N > kWindowResults || K > kWindowSum || pl.arg_count[p.x] > 2 * kWindowResults || pl.arg_count[p.w] > kWindowResults) return;
     int64_t first = p.q > 0 ? 0 : 1 - K, last = p.q > 0 ? N + K - 2 : N - 1;
     for (int c = 0; c < e.n_constraints; ++c) {   // s (i + q k) + c0 >= 0 with s = 1 or -1: a limit of the element of x

@@ -98,6 +98,38 @@ def test_terms_outside_the_sum_do_not_reach_it(q):
         assert check.within(np.where(ok, got, 0), np.where(ok, ref, 0), "f32")
 
 
+# conditions that no term beyond the end of w meets, and tensors that end with the last element that is read
+SHORT = [(70000, 200, 1, (None, 100), 101, 101), (70001, 256, 1, (3, 254), 255, 255), (70000, 150, -1, (69900, None), 70000, 100), (70001, 90, 1, (None, 0), 1, 1)]
+
+
+def short_expr(N, K, q, limits, n_x, n_w, dtype):
+    e = window_expr(N, K, q, dtype, limits=limits)
+    e.args[0].shape, e.args[1].shape = (n_x,), (n_w,)
+    return e
+
+
+@pytest.mark.parametrize("N,K,q,limits,n_x,n_w", SHORT)
+def test_a_window_ends_where_w_does(N, K, q, limits, n_x, n_w):
+    """The partial sums of the window are one per element of w, as for a sum that ends with w: no kernel reads behind it."""
+    from paper_1711_01348_amd import binding as B
+    whole = B.Plan(short_expr(N, K, q, limits, n_x, n_w, "f64")).workspace_bytes
+    assert whole == B.Plan(short_expr(N, n_w, q, limits, n_x, n_w, "f64")).workspace_bytes >= 8 * n_w * -(-N // 256)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("N,K,q,limits,n_x,n_w", SHORT)
+def test_windows_longer_than_w(N, K, q, limits, n_x, n_w, dtype):
+    from paper_1711_01348_amd import binding as B
+    e = short_expr(N, K, q, limits, n_x, n_w, dtype)
+    w = wl.random_inputs(e, 13)
+    f, grads = _run(B.Plan(e), w)
+    f_ref, g_ref = oracle.forward(e, w.arg_list()), oracle.backward(e, w.arg_list(), w.df)
+    assert check.within(f, f_ref, dtype), check.errors(f, f_ref)
+    for g, r in zip(grads, g_ref):
+        assert check.within(g, r, dtype), check.errors(g, r)
+
+
 def test_what_is_no_window_stays_on_the_general_kernels():
     """The workspace says which: the partial sums of the window are asked for beyond what the general kernels need."""
     from paper_1711_01348_amd import binding as B
