@@ -7,6 +7,11 @@
 //              bounds rounded exactly and clipped at the border, are the i, j with p - s i and q - s j among the taps)
 //     dw_uv  = sum_{n,i,j} t_nij x_{n, s i + u, s j + v}                  (all three kernel coordinates collapse:
 //              block-level reduction to per-block partials, finished in fixed order)
+//
+// Gradients of 32 x 128 x 128, 3 x 3, stride 2 (21 MB in the caches, bound by latency): wavefronts that evaluated the plan's range rows beside
+// others for dw 19.0 us; one pass over pairs (i, j) for both 12.0; dx by pairs and dw in workgroups of their own 10.0.  Forward and gradients of 8 x 33 x 61,
+// 7 x 7, stride 1: 89 / 22 / 18 us.  The pass for both was slower where a filter has many taps or the stride is large: dw of 32 x 128 x 128, 7 x 7, stride 1
+// 16.8 / 20.7 / 16.1 us, both of 64 x 64 x 64, 7 x 7, stride 4 26.5 / 30.2 / 19.0, 3 x 3, stride 9 56 / 126 / 34, 256 x 14 x 14, 3 x 3, stride 16 39 / 64 / 21.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,7 +31,7 @@ struct StridedGeom {
 
 struct StridedRows {   // rows of `width` elements over 256 threads
     int width, magic, step_row, step_col;
-    int n_i, hu, hv;   // gradients: steps of the stride along p, rows and columns of t in front of a pair's own that its taps read
+    int hu, hv;        // gradients: rows and columns of t in front of a pair's own that its taps read
 };
 
 template <int CTRL, int ROW_MASK>
@@ -58,116 +63,6 @@ __global__ __launch_bounds__(256) void k_strided_forward_direct(const StridedGeo
     for (int u = 0; u < g.U; ++u)
         for (int v = 0; v < g.V; ++v) acc = fmaf(xp[(size_t)u * g.Q + v], ws[u * g.V + v], acc);
     f[lin] = tanhf(acc);
-}
-
-// Everything the dx role needs from the plan of x, in loop-free form (y = beta for this family).
-struct StridedDx {
-    FlatFeas feas;
-    FlatLevel lvl[2];
-    int32_t fY[3], fZ[2];   // element offset of f / df:  fY . beta + fZ . z
-    int32_t wY[3], wZ[2];   // element offset of w
-};
-
-// Block roles in one launch.
-//  * blocks [blocks_dw, ...): one thread per gradient element (n, p, q) of x.  Masks and both ranges come from
-//    the plan (feasibility rows, rational range rows rounded exactly); the two ranges do not depend on each other.
-//  * blocks [0, blocks_dw) reduce dw over kStridedDwElems function elements each into part[block][taps].
-template <int TAPS>
-__global__ __launch_bounds__(256) void k_strided_backward_direct(const StridedGeom g, const StridedDx D,
-                                                          const float *__restrict__ x, const float *__restrict__ w,
-                                                          const float *__restrict__ f, const float *__restrict__ df,
-                                                          float *__restrict__ dx, float *__restrict__ part, int n_x,
-                                                          int nf, int blocks_dw) {
-    __shared__ float ws[kMaxTaps];
-    __shared__ float red[4][TAPS];
-    __shared__ int tapoff[TAPS];
-    const int taps = g.U * g.V;
-    // the few long-running dw blocks come first in launch order so that they overlap the dx stream
-    if ((int)blockIdx.x >= blocks_dw) {
-        const int lin = ((int)blockIdx.x - blocks_dw) * 256 + threadIdx.x;
-        const bool inside = lin < n_x;
-        const int q = lin % g.Q, t = lin / g.Q;
-        const int32_t y[3] = {t / g.P, t % g.P, q};
-        int32_t lo1 = 0, hi1 = -1, lo0 = 0, hi0 = -1;
-        if (inside && flat_feasible(D.feas, y)) {
-            flat_bounds(D.lvl[1], y, lo1, hi1);
-            flat_bounds(D.lvl[0], y, lo0, hi0);
-        }
-        const int base_f = D.fY[0] * y[0] + D.fY[1] * y[1] + D.fY[2] * y[2];
-        const int base_w = D.wY[0] * y[0] + D.wY[1] * y[1] + D.wY[2] * y[2];
-        const int n1 = hi1 - lo1 + 1, n0 = hi0 - lo0 + 1;
-        // Up to two values per coordinate (a stride of two or more under a 3 x 3 filter, ...): the loads of all
-        // terms are issued together, before the filter taps are staged, so that the wavefront waits for memory
-        // once instead of once per term.  Terms are added in the order of the loops below.
-        const bool few = n1 <= 2 && n0 <= 2;
-        float fv[2][2], dv[2][2];
-        if (few) {
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    const bool on = a < n1 && b < n0;
-                    const int of = base_f + D.fZ[1] * (lo1 + a) + D.fZ[0] * (lo0 + b);
-                    fv[a][b] = on ? f[of] : 0.f;
-                    dv[a][b] = on ? df[of] : 0.f;
-                }
-        }
-        if (threadIdx.x < taps) ws[threadIdx.x] = w[threadIdx.x];
-        __syncthreads();
-        if (!inside) return;
-        float acc = 0.f;
-        if (few) {
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    if (a < n1 && b < n0)
-                        acc = fmaf(dv[a][b] * (1.f - fv[a][b] * fv[a][b]),
-                                   ws[base_w + D.wZ[1] * (lo1 + a) + D.wZ[0] * (lo0 + b)], acc);
-        } else {
-            for (int32_t z1 = lo1; z1 <= hi1; ++z1) {
-                int of = base_f + D.fZ[1] * z1 + D.fZ[0] * lo0;
-                int ow = base_w + D.wZ[1] * z1 + D.wZ[0] * lo0;
-                for (int32_t z0 = lo0; z0 <= hi0; ++z0) {
-                    const float fval = f[of];
-                    acc = fmaf(df[of] * (1.f - fval * fval), ws[ow], acc);
-                    of += D.fZ[0];
-                    ow += D.wZ[0];
-                }
-            }
-        }
-        dx[lin] = acc;
-        return;
-    }
-    if (threadIdx.x < taps) tapoff[threadIdx.x] = (threadIdx.x / g.V) * g.Q + (threadIdx.x % g.V);
-    __syncthreads();
-    const int blk = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float acc[TAPS];
-#pragma unroll
-    for (int q = 0; q < TAPS; ++q) acc[q] = 0.f;
-#pragma unroll
-    for (int e = 0; e < kStridedDwElems / 256; ++e) {
-        const int lin = blk * kStridedDwElems + e * 256 + threadIdx.x;
-        if (lin < nf) {
-            const int j = lin % g.J, i = (lin / g.J) % g.I, n = lin / (g.J * g.I);
-            const float fv = f[lin];
-            const float t = df[lin] * (1.f - fv * fv);
-            const float *xp = x + ((size_t)n * g.P + (size_t)g.s * i) * g.Q + (size_t)g.s * j;
-#pragma unroll
-            for (int q = 0; q < TAPS; ++q)
-                if (q < taps) acc[q] = fmaf(t, xp[tapoff[q]], acc[q]);
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < TAPS; ++q) {
-        const float sum = wave_sum63s(acc[q]);
-        if (lane == 63) red[wave][q] = sum;
-    }
-    __syncthreads();
-    if (threadIdx.x < taps)
-        part[(size_t)blk * taps + threadIdx.x] =
-            (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -257,32 +152,158 @@ TAD_NOUNROLL
         if (tid + 256 * k < ne) out[tid + 256 * k] = tanhf(acc[k]);
 }
 
-// Both gradients of `ti` steps of the stride in p of one n: a thread owns E pairs (i, j), reads each f_ij and df_ij once for
-// everything, and writes the s x s elements of dx at (s i, s j).  With u = a + s u', v = b + s v':
-//     dx_{n, s i + a, s j + b} = sum_{u', v'} t_{n, i - u', j - v'} w_uv,   dw_uv += t_nij x_{n, s i + u, s j + v}
-// so that the taps (u, v) of one (a, b) serve an element of dx, every tap once.  The ranges of u', v' are the plan's (there is a
-// single i for given p and u, if any); t is 0 in LDS outside the function indices, where the terms do not exist.  Indices run
-// over i < ceil(P / s), j < ceil(Q / s) (rows and columns of x behind the last term: zeros), rows of t start with the
+// The gradients: one launch in which some workgroups sum dw and the others write dx (the few that sum come first: they run longest).
+struct StridedBackward {
+    StridedGeom g;
+    const float *x, *w, *f, *df;
+    float *dx, *part;
+    int blocks_dw, dw_ti;          // workgroups of dw, and their rows i (0: elements of f in memory order)
+    int n_i;                       // steps of the stride along p
+    unsigned n_dx;                 // by columns: threads
+    StridedRows W;                 // by pairs
+    int ti, blocks;                // ... steps of a workgroup, workgroups per n
+};
+
+// dw over a few function elements into part[blk][taps]: every tap has its sum in a register, and all are added over the wavefront at the end.
+// dw_ti > 0: that many rows i of one n, up to kStridedMaxPerThread elements per thread, the slice of x in LDS; else kStridedDwElems elements, x
+// from memory.
+template <int TAPS>
+__device__ __forceinline__ void strided_dw(const StridedBackward &A, int blk, float *xs) {
+    __shared__ float red[4][TAPS];
+    __shared__ int tapoff[TAPS];
+    constexpr int E = kStridedMaxPerThread;
+    static_assert(E * 256 == kStridedDwElems, "elements of a thread");
+    const StridedGeom &g = A.g;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, taps = g.U * g.V;
+    if (tid < taps) tapoff[tid] = (tid / g.V) * g.Q + (tid % g.V);
+    float acc[TAPS];
+#pragma unroll
+    for (int q = 0; q < TAPS; ++q) acc[q] = 0.f;
+    if (A.dw_ti > 0) {
+        const int n_it = (g.I + A.dw_ti - 1) / A.dw_ti, n = blk / n_it, i0 = (blk % n_it) * A.dw_ti, rows = min(A.dw_ti, g.I - i0), ne = rows * g.J;
+        const size_t first = ((size_t)n * g.I + i0) * g.J;
+        float fv[E], dv[E];
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            const int e = min(tid + 256 * k, ne - 1);
+            fv[k] = A.f[first + e];
+            dv[k] = A.df[first + e];
+        }
+        slice_to_lds(A.x, (n * g.P + g.s * i0) * g.Q, (g.s * (rows - 1) + g.U) * g.Q, xs, tid);
+        __syncthreads();
+        int il = 0, j = tid;
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            if (tid + 256 * k < ne) {
+                while (j >= g.J) { j -= g.J; ++il; }
+                const float t = dv[k] * (1.f - fv[k] * fv[k]), *xp = xs + g.s * (il * g.Q + j);
+#pragma unroll
+                for (int q = 0; q < TAPS; ++q)
+                    if (q < taps) acc[q] = fmaf(t, xp[tapoff[q]], acc[q]);
+                j += 256;
+            }
+        }
+    } else {
+        __syncthreads();
+        const int nf = g.N * g.I * g.J;
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            const int lin = blk * kStridedDwElems + k * 256 + tid;
+            if (lin < nf) {
+                const int j = lin % g.J, i = (lin / g.J) % g.I, n = lin / (g.J * g.I);
+                const float fv = A.f[lin], t = A.df[lin] * (1.f - fv * fv);
+                const float *xp = A.x + ((size_t)n * g.P + (size_t)g.s * i) * g.Q + (size_t)g.s * j;
+#pragma unroll
+                for (int q = 0; q < TAPS; ++q)
+                    if (q < taps) acc[q] = fmaf(t, xp[tapoff[q]], acc[q]);
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < TAPS; ++q) {
+        const float sum = wave_sum63s(acc[q]);
+        if (lane == 63) red[wave][q] = sum;
+    }
+    __syncthreads();
+    if (tid < taps) A.part[(size_t)blk * taps + tid] = (float)(((double)red[0][tid] + (double)red[1][tid]) + ((double)red[2][tid] + (double)red[3][tid]));
+}
+
+// dx by columns: a thread per (n, i, q) writes the elements (s i + a, q), a < s, so that a wavefront stores 64 neighbouring columns.  Their taps
+// are u = a + s u', v = q % s + s v' with t_{i - u', j - v'}, j = q / s.  NEAR: u' and v' are at most 1, the four t are read once for all a.
+template <bool NEAR>
+__device__ __forceinline__ void strided_dx_columns(const StridedBackward &A, unsigned e, const float *ws) {
+    const StridedGeom &g = A.g;
+    if (e >= A.n_dx) return;
+    const int q = (int)(e % (unsigned)g.Q), r = (int)(e / (unsigned)g.Q), taps = g.U * g.V;
+    const int i = r % A.n_i, n = r / A.n_i, j = q / g.s, b = q - j * g.s;
+    const int p0 = g.s * i, rows = min(g.s, g.P - p0);
+    const float *f = A.f + (size_t)n * g.I * g.J, *df = A.df + (size_t)n * g.I * g.J;
+    float *out = A.dx + ((size_t)n * g.P + p0) * g.Q + q;
+    if constexpr (NEAR) {
+        float t[2][2];
+        bool on[2][2];
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int z = 0; z < 2; ++z) {
+                const int ii = i - y, jj = j - z;
+                on[y][z] = (unsigned)ii < (unsigned)g.I && (unsigned)jj < (unsigned)g.J && b + z * g.s < g.V && y * g.s < g.U;
+                const int o = on[y][z] ? ii * g.J + jj : 0;
+                const float fv = f[o], dv = df[o];
+                t[y][z] = dv * (1.f - fv * fv);
+            }
+TAD_NOUNROLL
+        for (int a = 0; a < rows; ++a, out += g.Q) {
+            float acc = 0.f;
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                const int u = a + y * g.s;   // the same for the whole workgroup
+                if (u >= g.U) break;
+#pragma unroll
+                for (int z = 0; z < 2; ++z) acc = on[y][z] ? fmaf(t[y][z], ws[min(u * g.V + b + z * g.s, taps - 1)], acc) : acc;
+            }
+            *out = acc;
+        }
+    } else {
+        // the terms of a thread in one loop, several of whose loads go out together
+        const int n_v = b < g.V ? min((g.V - 1 - b) / g.s, j) + 1 : 0, v_skip = max(j - (g.J - 1), 0);   // v' from v_skip to n_v - 1
+TAD_NOUNROLL
+        for (int a = 0; a < rows; ++a, out += g.Q) {
+            const int n_u = a < g.U ? min((g.U - 1 - a) / g.s, i) + 1 : 0, u_skip = max(i - (g.I - 1), 0);
+            const int width = max(n_v - v_skip, 0), terms = width * max(n_u - u_skip, 0);
+            float acc = 0.f;
+            int o = (i - u_skip) * g.J + j - v_skip, k = (a + u_skip * g.s) * g.V + b + v_skip * g.s, c = 0;
+#pragma unroll 4
+            for (int m = 0; m < terms; ++m) {
+                const float fv = f[o];
+                acc = fmaf(df[o] * (1.f - fv * fv), ws[k], acc);
+                --o;
+                k += g.s;
+                if (++c == width) {
+                    c = 0;
+                    o += width - g.J;
+                    k += (g.V - width) * g.s;
+                }
+            }
+            *out = acc;
+        }
+    }
+}
+
+// dx by pairs: `ti` steps of the stride in p of one n.  A thread owns E pairs (i, j) and writes the s x s elements of dx at (s i, s j).  With
+// u = a + s u', v = b + s v':
+//     dx_{n, s i + a, s j + b} = sum_{u', v'} t_{n, i - u', j - v'} w_uv
+// so that the taps (u, v) of one (a, b) serve an element of dx, every tap once.  t is 0 in LDS outside the function indices, where the terms do not
+// exist.  Indices run over i < ceil(P / s), j < ceil(Q / s) (rows and columns of x behind the last term: zeros), rows of t start with the
 // (V - 1) / s columns in front of j = 0, so that a term is at the same distance in LDS for every element.
-// Bound by latency (21 MB of traffic in the caches for 32 x 128 x 128, 3 x 3, stride 2): everything is loaded up front, a
-// tap is 2 E independent LDS reads, and the code is short.  dx by wavefronts of their own that evaluated the plan's range rows, dw by
-// others: 16.4 us in the trace; this kernel 10.3, of which dx alone takes 8.4 and dw alone 8.3.  Over the range (N x I x J, taps, stride;
-// forward and gradients): 32 x 128 x 128, 3 x 3, 2: 24.2 -> 18.0 us; 4 x 60 x 60, 3 x 3, 1: 37.2 -> 16.9; 16 x 100 x 100, 7 x 7, 2:
-// 52.7 -> 26.4; 8 x 33 x 61, 7 x 7, 1: 89.3 -> 22.1.
 template <int E>
-__global__ __launch_bounds__(256) void k_strided_backward(const StridedGeom g, const StridedRows W, int ti, int t_floats,
-                                                          const float *__restrict__ x, const float *__restrict__ w,
-                                                          const float *__restrict__ f, const float *__restrict__ df,
-                                                          float *__restrict__ dx, float *__restrict__ part) {
-    extern __shared__ float4s dyn4[];
+__device__ __forceinline__ void strided_dx_pairs(const StridedBackward &A, int blk, const float *ws, float *lds) {
     // a thread without a pair (in front of j = 0) reaches hv floats in front of t
-    const int tid = threadIdx.x, s = g.s, taps = g.U * g.V, width = W.width, hu = W.hu, hv = W.hv;
-    float *ts = reinterpret_cast<float *>(dyn4) + hv, *xs = reinterpret_cast<float *>(dyn4) + t_floats;
-    __shared__ float ws[kMaxTaps];
-    __shared__ float red[4][kMaxTaps];
-    const int n = blockIdx.y, i0 = blockIdx.x * ti;
-    const int rows = min(ti, W.n_i - i0), f_rows = min(rows, g.I - i0);   // f_rows <= 0: behind the last row of f
-    const bool want_dw = part != nullptr;
+    const StridedGeom &g = A.g;
+    const StridedRows &W = A.W;
+    const int tid = threadIdx.x, s = g.s, width = W.width, hu = W.hu, hv = W.hv;
+    const int n = blk / A.blocks, i0 = (blk - n * A.blocks) * A.ti, rows = min(A.ti, A.n_i - i0);
+    float *ts = lds + hv;
     // t on rows i0 - hu .. i0 + rows - 1
     const int nt = (hu + rows) * width;
     {
@@ -297,8 +318,8 @@ TAD_NOUNROLL
                 const int i = i0 - hu + at.row, j = at.col - hv;
                 in[k] = (unsigned)i < (unsigned)g.I && (unsigned)j < (unsigned)g.J;
                 const int o = in[k] ? f0 + i * g.J + j : f0;
-                fv[k] = f[o];
-                dv[k] = df[o];
+                fv[k] = A.f[o];
+                dv[k] = A.df[o];
                 at.next();
             }
 #pragma unroll
@@ -308,29 +329,20 @@ TAD_NOUNROLL
             }
         }
     }
-    if (tid < taps) ws[tid] = w[tid];
-    if (want_dw && f_rows > 0) slice_to_lds(x, (n * g.P + s * i0) * g.Q, (s * (f_rows - 1) + g.U) * g.Q, xs, tid);
     __syncthreads();
     const float *const mine = ts + tid + hu * width;   // t of pair k: mine[256 k]
-    int pi[E], pj[E], xo[E];
-    float t[E];
-    bool live[E];
+    int pi[E], pj[E];
     {
         RowWalk at(tid, W);
 #pragma unroll
         for (int k = 0; k < E; ++k) {
             const int j = at.col - hv;
-            const bool pair = at.row < rows && j >= 0;
-            live[k] = pair && at.row < f_rows && j < g.J;
-            xo[k] = live[k] ? s * (at.row * g.Q + j) : 0;
-            t[k] = live[k] ? mine[256 * k] : 0.f;
-            pi[k] = pair ? i0 + at.row : W.n_i;        // no element of dx has a row from s n_i on
+            pi[k] = at.row < rows && j >= 0 ? i0 + at.row : A.n_i;   // no element of dx has a row from s n_i on
             pj[k] = j;
             at.next();
         }
     }
-    float *const out = dx ? dx + (size_t)n * g.P * g.Q : nullptr;
-    const int wave = tid >> 6;
+    float *const out = A.dx + (size_t)n * g.P * g.Q;
     int a = 0, b = 0;
 TAD_NOUNROLL
     for (;;) {
@@ -341,18 +353,14 @@ TAD_NOUNROLL
         int du = 0;
 TAD_NOUNROLL
         for (int u = a; u < g.U; u += s, t_row -= width, ++du) {
-            const float *tp = t_row, *xp = xs + u * g.Q + b, *wp = ws + u * g.V + b;
+            const float *tp = t_row, *wp = ws + u * g.V + b;
             int dv = 0;
 TAD_NOUNROLL
-            for (int v = b; v < g.V; v += s, --tp, xp += s, wp += s, ++dv) {
+            for (int v = b; v < g.V; v += s, --tp, wp += s, ++dv) {
                 const float wv = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(*wp)));
-                float tv[E], xv[E];
+                float tv[E];
 #pragma unroll
                 for (int k = 0; k < E; ++k) tv[k] = tp[256 * k];
-                if (want_dw) {
-#pragma unroll
-                    for (int k = 0; k < E; ++k) xv[k] = xp[xo[k]];
-                }
                 if (__builtin_isfinite(wv)) {
 #pragma unroll
                     for (int k = 0; k < E; ++k) acc[k] = fmaf(tv[k], wv, acc[k]);
@@ -361,29 +369,37 @@ TAD_NOUNROLL
                     for (int k = 0; k < E; ++k)
                         if ((unsigned)(pi[k] - du) < (unsigned)g.I && (unsigned)(pj[k] - dv) < (unsigned)g.J) acc[k] = fmaf(tv[k], wv, acc[k]);
                 }
-                if (want_dw) {
-                    float sum = 0.f;
-#pragma unroll
-                    for (int k = 0; k < E; ++k) sum = fmaf(t[k], live[k] ? xv[k] : 0.f, sum);
-                    sum = wave_sum63s(sum);
-                    if ((tid & 63) == 63) red[wave][wp - ws] = sum;
-                }
             }
         }
-        if (out) {
 #pragma unroll
-            for (int k = 0; k < E; ++k) {
-                const int p = s * pi[k] + a, q = s * pj[k] + b;
-                if (p < g.P && q < g.Q) out[p * g.Q + q] = acc[k];
-            }
+        for (int k = 0; k < E; ++k) {
+            const int p = s * pi[k] + a, q = s * pj[k] + b;
+            if (p < g.P && q < g.Q) out[p * g.Q + q] = acc[k];
         }
         if (++b < s) continue;
         b = 0;
         if (++a == s) break;
     }
-    if (!want_dw) return;
-    __syncthreads();
-    if (tid < taps) part[(size_t)(blockIdx.y * gridDim.x + blockIdx.x) * taps + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+}
+
+// E: pairs per thread, or 0 by columns, -1 by columns that are NEAR
+template <int TAPS, int E>
+__global__ __launch_bounds__(256) void k_strided_backward(const StridedBackward A) {
+    extern __shared__ float4s dyn4[];
+    float *const lds = reinterpret_cast<float *>(dyn4);
+    if ((int)blockIdx.x < A.blocks_dw) {
+        strided_dw<TAPS>(A, (int)blockIdx.x, lds);
+        return;
+    }
+    __shared__ float ws[kMaxTaps];
+    if (threadIdx.x < A.g.U * A.g.V) ws[threadIdx.x] = A.w[threadIdx.x];
+    const unsigned blk = blockIdx.x - (unsigned)A.blocks_dw;
+    if constexpr (E > 0) {
+        strided_dx_pairs<E>(A, (int)blk, ws, lds);
+    } else {
+        __syncthreads();
+        strided_dx_columns<E != 0>(A, blk * 256u + threadIdx.x, ws);
+    }
 }
 
 // dw_q = sum over the per-block partials, fixed order; one block of four waves per tap
@@ -408,18 +424,18 @@ static StridedGeom geom(const tad_plan &pl) {
 
 // (tid * magic) >> 16 is tid / width for tid < 256: the error of magic, below width,
 // times tid stays below 2^16 for width <= 256, and beyond that the quotient is 0.
-static StridedRows row_walk(int width, int n_i, int hu, int hv) {
-    return {width, (65536 + width - 1) / width, 256 / width, 256 % width, n_i, hu, hv};
+static StridedRows row_walk(int width, int hu, int hv) {
+    return {width, (65536 + width - 1) / width, 256 / width, 256 % width, hu, hv};
 }
 
 int strided_forward(const tad_plan &pl, const void *const *args, void *f, hipStream_t s) {
     const int nf = (int)pl.f_count;
     const StridedTiling t = strided_tiling(pl.fast.N, pl.fast.I, pl.fast.J, pl.fast.U, pl.fast.stride, pl.fast.Q);
     const float *x = (const float *)args[0], *w = (const float *)args[1];
-    if (t.ti) {
+    if (t.ti && pl.fast.N <= 65535) {   // N along the second axis of the grid
         const dim3 grid((unsigned)((pl.fast.I + t.ti - 1) / t.ti), (unsigned)pl.fast.N), block(256);
         const size_t lds = (size_t)t.x_slice * 4;
-        const StridedRows rows = row_walk((int)pl.fast.J, 0, 0, 0);
+        const StridedRows rows = row_walk((int)pl.fast.J, 0, 0);
         const int64_t each = (t.ti * pl.fast.J + 255) / 256;
         if (each <= 1) TAD_LAUNCH("k_strided_forward", (k_strided_forward<1>), grid, block, lds, s, geom(pl), rows, t.ti, x, w, (float *)f);
         else if (each <= 2) TAD_LAUNCH("k_strided_forward", (k_strided_forward<2>), grid, block, lds, s, geom(pl), rows, t.ti, x, w, (float *)f);
@@ -430,23 +446,19 @@ int strided_forward(const tad_plan &pl, const void *const *args, void *f, hipStr
     return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
-static StridedDx dx_plan(const tad_plan &pl) {
-    StridedDx D;
-    D.feas = pl.fast.feas;
-    D.lvl[0] = pl.fast.flat[0];
-    D.lvl[1] = pl.fast.flat[1];
-    const GatherPlan &gp = pl.ap[0].dev;
-    for (int c = 0; c < 3; ++c) { D.fY[c] = (int32_t)gp.offY[kSlotF][c]; D.wY[c] = (int32_t)gp.offY[1][c]; }
-    for (int m = 0; m < 2; ++m) { D.fZ[m] = (int32_t)gp.offZ[kSlotF][m]; D.wZ[m] = (int32_t)gp.offZ[1][m]; }
-    return D;
-}
-
 template <int TAPS>
-static void launch_bwd_direct(const tad_plan &pl, const void *const *args, const void *f, const void *df,
-                              void *const *dx, void *ws, int blocks_dx, int blocks_dw, hipStream_t s) {
-    TAD_LAUNCH("k_strided_backward_direct", (k_strided_backward_direct<TAPS>), dim3(blocks_dx + blocks_dw), dim3(256), 0, s,
-               geom(pl), dx_plan(pl), (const float *)args[0], (const float *)args[1], (const float *)f, (const float *)df,
-               (float *)dx[0], (float *)ws, (int)pl.arg_count[0], (int)pl.f_count, blocks_dw);
+static void launch_backward(const StridedBackward &A, int each, unsigned blocks, size_t lds, hipStream_t s) {
+    const dim3 grid(blocks), block(256);
+#define TAD_STRIDED_BACKWARD(E) TAD_LAUNCH("k_strided_backward", (k_strided_backward<TAPS, E>), grid, block, lds, s, A)
+    switch (each) {
+    case 1: TAD_STRIDED_BACKWARD(1); break;
+    case 2: TAD_STRIDED_BACKWARD(2); break;
+    case 4: TAD_STRIDED_BACKWARD(4); break;
+    case 8: TAD_STRIDED_BACKWARD(8); break;
+    case 0: TAD_STRIDED_BACKWARD(0); break;
+    default: TAD_STRIDED_BACKWARD(-1);
+    }
+#undef TAD_STRIDED_BACKWARD
 }
 
 #define TAD_TAPS_SWITCH(taps, CALL)                                   \
@@ -460,34 +472,42 @@ static void launch_bwd_direct(const tad_plan &pl, const void *const *args, const
 
 int strided_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df,
                      void *const *dx, void *ws, hipStream_t s) {
-    const int nf = (int)pl.f_count;
-    const int taps = (int)(pl.fast.U * pl.fast.V);
-    int blocks_dw = 0;
-    const StridedGrad t = strided_grad(pl.fast.N, pl.fast.I, pl.fast.J, pl.fast.U, pl.fast.V, pl.fast.stride, pl.fast.P, pl.fast.Q);
-    if (t.ti) {
-        if (!dx[0] && !dx[1]) return TAD_OK;
-        blocks_dw = t.blocks * (int)pl.fast.N;
-        const dim3 grid((unsigned)t.blocks, (unsigned)pl.fast.N), block(256);
-        const size_t lds = (size_t)(t.t_floats + t.x_floats) * 4;
-        const StridedRows rows = row_walk(t.width, t.n_i, t.hu, t.hv);
-        float *const part = dx[1] ? (float *)ws : nullptr;
-#define TAD_STRIDED_BACKWARD(E)                                                                                                              \
-    TAD_LAUNCH("k_strided_backward", (k_strided_backward<E>), grid, block, lds, s, geom(pl), rows, t.ti, t.t_floats, (const float *)args[0], \
-               (const float *)args[1], (const float *)f, (const float *)df, (float *)dx[0], part)
-        if (t.each == 1) TAD_STRIDED_BACKWARD(1);
-        else if (t.each == 2) TAD_STRIDED_BACKWARD(2);
-        else if (t.each == 4) TAD_STRIDED_BACKWARD(4);
-        else TAD_STRIDED_BACKWARD(8);
-#undef TAD_STRIDED_BACKWARD
-    } else {
-        const int blocks_dx = dx[0] ? (int)((pl.arg_count[0] + 255) / 256) : 0;
-        blocks_dw = dx[1] ? (nf + kStridedDwElems - 1) / kStridedDwElems : 0;
-        if (blocks_dx + blocks_dw == 0) return TAD_OK;
-        TAD_TAPS_SWITCH(taps, (launch_bwd_direct<T_>(pl, args, f, df, dx, ws, blocks_dx, blocks_dw, s)));
+    if (!dx[0] && !dx[1]) return TAD_OK;
+    StridedBackward A{};
+    A.g = geom(pl);
+    A.x = (const float *)args[0]; A.w = (const float *)args[1]; A.f = (const float *)f; A.df = (const float *)df;
+    A.dx = (float *)dx[0]; A.part = (float *)ws;
+    const StridedGeom &g = A.g;
+    const int taps = g.U * g.V;
+    size_t lds = 0;
+    if (dx[1]) {
+        const StridedTiling t = strided_dw_tiling(g.N, g.I, g.J, g.U, g.V, g.s, g.P, g.Q);
+        A.dw_ti = t.ti;
+        A.blocks_dw = (int)(t.ti ? (int64_t)g.N * ((g.I + t.ti - 1) / t.ti) : (pl.f_count + kStridedDwElems - 1) / kStridedDwElems);
+        lds = (size_t)t.x_slice * 4;
     }
+    A.n_i = (g.P + g.s - 1) / g.s;
+    int each = 0;
+    unsigned blocks_dx = 0;
+    if (dx[0]) {
+        const StridedPairs t = strided_pairs(g.N, g.U, g.V, g.s, g.P, g.Q);
+        each = t.each;
+        if (each) {
+            A.W = row_walk(t.width, t.hu, t.hv);
+            A.ti = t.ti;
+            A.blocks = t.blocks;
+            blocks_dx = (unsigned)(t.blocks * g.N);
+            lds = std::max(lds, (size_t)t.t_floats * 4);
+        } else {
+            A.n_dx = (unsigned)g.N * A.n_i * g.Q;
+            blocks_dx = (A.n_dx + 255) / 256;
+            if ((g.U - 1) / g.s <= 1 && (g.V - 1) / g.s <= 1) each = -1;
+        }
+    }
+    TAD_TAPS_SWITCH(taps, (launch_backward<T_>(A, each, (unsigned)A.blocks_dw + blocks_dx, lds, s)));
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
     if (dx[1]) {
-        TAD_LAUNCH("k_strided_finish", k_strided_finish, dim3(taps), dim3(256), 0, s, (const float *)ws, blocks_dw,
+        TAD_LAUNCH("k_strided_finish", k_strided_finish, dim3(taps), dim3(256), 0, s, (const float *)ws, A.blocks_dw,
                    taps, (float *)dx[1]);
         if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
     }

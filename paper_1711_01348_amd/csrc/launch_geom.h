@@ -86,7 +86,6 @@ constexpr int kStridedLdsFloats = 10240;   // 40 KiB per block: four blocks per 
 constexpr int kStridedMaxPerThread = 4;    // function elements per thread
 inline StridedTiling strided_tiling(int64_t N, int64_t I, int64_t J, int64_t U, int64_t s, int64_t Q) {
     StridedTiling t{0, 0};
-    if (N > 65535) return t;   // N along the second axis of the grid
     // rows s*i0 .. s*(i0+ti-1)+U-1 of x, whole rows; prefer at least 1024 blocks
     for (int ti = 8; ti >= 1; --ti) {
         const int64_t slice = (s * (ti - 1) + U) * Q;
@@ -105,36 +104,56 @@ inline int64_t strided_parts(int64_t N, int64_t I, int64_t J, int64_t U, int64_t
 inline size_t strided_workspace_bytes(int64_t N, int64_t I, int64_t J, int64_t U, int64_t V, int64_t s, int64_t Q) {
     return align256((size_t)strided_parts(N, I, J, U, s, Q) * (size_t)(U * V) * 4);
 }
-// Gradients: a workgroup takes ti steps of the stride along p, `each` pairs (i, j) per thread (ti = 0: direct kernel).
-struct StridedGrad {
+// dx by pairs (i, j): a workgroup takes ti steps of the stride along p, `each` pairs per thread (each = 0: by columns).
+struct StridedPairs {
     int ti, each, blocks;          // blocks: workgroups per n
-    int width, n_i, hu, hv;        // pairs in a row and the columns of t in front of them; rows of pairs; see StridedRows
-    int t_floats, x_floats;        // LDS
+    int width, hu, hv;             // pairs in a row and the columns of t in front of them; see StridedRows
+    int t_floats;                  // LDS
 };
-inline StridedGrad strided_grad(int64_t N, int64_t I, int64_t J, int64_t U, int64_t V, int64_t s, int64_t P, int64_t Q) {
+inline StridedPairs strided_pairs(int64_t N, int64_t U, int64_t V, int64_t s, int64_t P, int64_t Q) {
     const int64_t hu = (U - 1) / s, hv = (V - 1) / s, width = (Q + s - 1) / s + hv, n_i = (P + s - 1) / s;
-    const int64_t parts = strided_parts(N, I, J, U, s, Q);
-    StridedGrad best{0, 0, 0, 0, 0, 0, 0, 0, 0};
-    // elements of dx that a wavefront stores together are s apart; a grid has up to 65535 n
-    if (s > 8 || N > 65535) return best;
-    // many pairs per thread share the waits; but at least two workgroups per compute unit, and no more sums than the workspace holds
+    StridedPairs best{0, 0, 0, 0, 0, 0, 0};
+    // What a pair stores is s apart from its neighbour's.  Columns / pairs, dx alone, taps and stride: 64 x 64 x 64 3 x 3, 4 8.1 / 11.7 us, 7 x 7, 4
+    // 9.6 / 20, 7 x 7, 5 12 / 26; small tensors: 128 x 28 x 28 3 x 3, 3 3.9 / 4.9, 5 x 5, 3 (two taps at most in a direction) 4.3 / 6.5, 7 x 7, 2 7.9 / 7.8,
+    // 64 x 56 x 56 5 x 5, 2 7.4 / 6.0; large ones 32 x 128 x 128 3 x 3, 2 8.2 / 6.4, 7 x 7, 2 24 / 11, 3 x 3, 3 10.8 / 8.5.
+    const bool near = hu <= 1 && hv <= 1;
+    if (s > 3 || (s > 1 && N * P * Q < ((int64_t)1 << (near ? 20 : 19)))) return best;
+    // many pairs per thread share the waits; but at least two workgroups per compute unit
     const int order[] = {8, 1, 2, 4};
     for (int each : order) {
         int64_t ti = 256 * each / width;
         if (ti > n_i) ti = n_i;
-        int64_t t = 0, x = 0;
-        for (; ti >= 1; --ti) {
-            t = (hv + hu * width + 256 * each + 3) & ~(int64_t)3;
-            x = (s * (ti - 1) + U) * Q;
-            if (t + x <= kStridedLdsFloats || (ti == 1 && t + x <= 15872)) break;
-        }
-        if (ti < 1) continue;
+        const int64_t t = (hv + hu * width + 256 * each + 3) & ~(int64_t)3;
+        // rows of t in front of a workgroup's own are read again by every workgroup: 8 x 256 x 200, 49 x 1 pairs 25 us, columns 13; 16 x 200 x 200, 16 x 3
+        // (hu = 15, ti = 5) 11 / 18
+        if (ti < 1 || t > kStridedLdsFloats || hu > 4 * ti) continue;
         const int64_t blocks = (n_i + ti - 1) / ti;
-        if (N * blocks > parts) continue;
         if (best.ti == 0 || best.each == 8 || N * blocks >= 512)
-            best = {(int)ti, each, (int)blocks, (int)width, (int)n_i, (int)hu, (int)hv, (int)t, (int)x};
+            best = {(int)ti, each, (int)blocks, (int)width, (int)hu, (int)hv, (int)t};
     }
     return best;
+}
+// dw: rows i of f per workgroup (ti = 0: elements in memory order).  As many as its threads take in as few passes as leave no more workgroups than
+// compute units work on at once: a workgroup adds up all its taps over its wavefronts, whatever it has summed before.  Few taps: half as many, the
+// workgroups of dx run beside them.  dw alone, old rows (at least 1024 workgroups, threads idle) / these: 128 x 28 x 28 7 x 7 13.0 / 10.9 us, 3 x 3 7.7 / 6.9;
+// both gradients 32 x 112 x 112 3 x 3 9.9 / 8.6, 32 x 128 x 128 3 x 3, 2 10.9 / 9.9 (7 x 7 with 512 workgroups 24, with 1024 19).  Columns of dx have no LDS of
+// their own: half of it leaves them eight workgroups per compute unit (32 x 112 x 112 3 x 3, 4 18 us with 20 KB, 22 with 40).
+inline StridedTiling strided_dw_tiling(int64_t N, int64_t I, int64_t J, int64_t U, int64_t V, int64_t s, int64_t P, int64_t Q) {
+    const int64_t parts = strided_parts(N, I, J, U, s, Q), most = U * V <= 9 ? 512 : 1024;
+    const int64_t room = strided_pairs(N, U, V, s, P, Q).each ? kStridedLdsFloats : kStridedLdsFloats / 2;
+    StridedTiling t{0, 0};
+    for (int64_t passes = 1; passes <= kStridedMaxPerThread; ++passes) {
+        int64_t ti = 256 * passes / J;
+        if (ti > I) ti = I;
+        while (ti > 1 && (s * (ti - 1) + U) * Q > room) --ti;
+        if (ti < 1) continue;
+        const int64_t slice = (s * (ti - 1) + U) * Q, blocks = N * ((I + ti - 1) / ti);
+        if (slice > room || blocks > parts) continue;   // (the workspace holds `parts` sums)
+        t.ti = (int)ti;
+        t.x_slice = (int)slice;
+        if (blocks <= most) break;
+    }
+    return t.ti ? t : strided_tiling(N, I, J, U, s, Q);
 }
 
 // antidiagonal pattern, backward: aligned tiles of df; a tile yields AD_TILE_ROWS + AD_TILE_COLS antidiagonal sums
