@@ -34,10 +34,19 @@ int static_scratch(void **out) {
 bool room(const tad_plan &pl, const void *ws, size_t ws_bytes) {
     return pl.ws_full == 0 || (ws && ws_bytes >= pl.ws_full && (reinterpret_cast<uintptr_t>(ws) & 15) == 0);
 }
-bool use_product(const tad_plan &pl, const void *ws, size_t ws_bytes) {
-    return pl.prod.on && (pl.prod.ws_bytes == 0 || room(pl, ws, ws_bytes));
+// The products to run in this workspace, or null.
+const ProductSet *products_in(const tad_plan &pl, const ProductSet &set, const ProductSet *lean, const void *ws, size_t ws_bytes) {
+    if (room(pl, ws, ws_bytes)) return &set;
+    return lean && ws && ws_bytes >= pl.ws_lean && (reinterpret_cast<uintptr_t>(ws) & 15) == 0 ? lean : nullptr;
 }
-bool use_separable(const tad_plan &pl, const void *ws, size_t ws_bytes) { return pl.sep.on && room(pl, ws, ws_bytes); }
+const ProductSet *use_product(const tad_plan &pl, const void *ws, size_t ws_bytes) {
+    if (!pl.prod.on) return nullptr;
+    if (pl.prod.set.ws_bytes == 0) return &pl.prod.set;
+    return products_in(pl, pl.prod.set, pl.prod.lean_on ? &pl.prod.lean : nullptr, ws, ws_bytes);
+}
+const ProductSet *use_separable(const tad_plan &pl, const void *ws, size_t ws_bytes) {
+    return pl.sep.on ? products_in(pl, pl.sep.set, pl.sep.lean_on ? &pl.sep.lean : nullptr, ws, ws_bytes) : nullptr;
+}
 bool use_worked_wide(const tad_plan &pl, const void *ws, size_t ws_bytes) { return pl.worked_wide && room(pl, ws, ws_bytes); }
 bool use_pattern_wide(const tad_plan &pl, const void *ws, size_t ws_bytes) {
     return pl.pattern_wide != TAD_FAMILY_GENERIC && room(pl, ws, ws_bytes);
@@ -53,11 +62,13 @@ int tad_eval_forward(const tad_plan *plan, const void *const *args_dev, void *f_
         if (!args_dev[plan->root[p]]) return TAD_EINVAL;
     if (plan->ws_bytes && (!ws_dev || ws_bytes < plan->ws_bytes)) return TAD_ENOMEM;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (plan->sep.forward_on && use_separable(*plan, ws_dev, ws_bytes)) return separable_forward(*plan, args_dev, f_dev, ws_dev, s);
+    if (plan->sep.forward_on)
+        if (const ProductSet *set = use_separable(*plan, ws_dev, ws_bytes)) return separable_forward(*plan, *set, args_dev, f_dev, ws_dev, s);
     if (use_worked_wide(*plan, ws_dev, ws_bytes)) return worked_wide_forward(*plan, args_dev, f_dev, s);
     if (use_pattern_wide(*plan, ws_dev, ws_bytes)) return pattern_wide_forward(*plan, args_dev, f_dev, s);
     if (plan->window.on) return window_forward(*plan, args_dev, f_dev, s);
-    if (plan->prod.forward_on && use_product(*plan, ws_dev, ws_bytes)) return product_forward(*plan, args_dev, f_dev, ws_dev, s);
+    if (plan->prod.forward_on)
+        if (const ProductSet *set = use_product(*plan, ws_dev, ws_bytes)) return product_forward(*plan, *set, args_dev, f_dev, ws_dev, s);
     switch (plan->fwd_family) {
     case TAD_FAMILY_GENERIC: return generic_forward(*plan, args_dev, f_dev, ws_dev, s);
     case TAD_FAMILY_WORKED: return worked_forward(*plan, args_dev, f_dev, s);
@@ -84,14 +95,14 @@ int tad_eval_backward(const tad_plan *plan, const void *const *args_dev, const v
     bool any_wanted = false;
     for (size_t p = 0; p < plan->args.size(); ++p) any_wanted |= dx_dev[p] != nullptr;
     if (!any_wanted) return TAD_OK;
-    if (use_separable(*plan, ws_dev, ws_bytes)) return separable_backward(*plan, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
+    if (const ProductSet *set = use_separable(*plan, ws_dev, ws_bytes)) return separable_backward(*plan, *set, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
     if (use_worked_wide(*plan, ws_dev, ws_bytes)) return worked_wide_backward(*plan, args_dev, f_dev, df_dev, dx_dev, ws_dev, s);
     if (plan->pattern_wide_sums && use_pattern_wide(*plan, ws_dev, ws_bytes)) return pattern_wide_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
     if (plan->window.on && room(*plan, ws_dev, ws_bytes)) return window_backward(*plan, args_dev, df_dev, dx_dev, ws_dev, s);
     void *rest[kMaxArgs];   // the gradients the dense products leave to the family
-    if (use_product(*plan, ws_dev, ws_bytes)) {
+    if (const ProductSet *set = use_product(*plan, ws_dev, ws_bytes)) {
         for (size_t p = 0; p < plan->args.size(); ++p) rest[p] = dx_dev[p];
-        const int rc = product_backward(*plan, args_dev, df_dev, rest, ws_dev, s);
+        const int rc = product_backward(*plan, *set, args_dev, df_dev, rest, ws_dev, s);
         if (rc) return rc;
         dx_dev = rest;
         any_wanted = false;

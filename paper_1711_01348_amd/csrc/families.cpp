@@ -363,10 +363,14 @@ void select_families(tad_plan &plan) {
     reserve_partial_sums(plan);
     match_product(plan);
     plan.prod.ws_offset = align256(plan.ws_bytes);
-    plan.ws_full = plan.prod.on && plan.prod.ws_bytes ? plan.prod.ws_offset + plan.prod.ws_bytes : plan.ws_bytes;
+    plan.ws_full = plan.prod.on && plan.prod.set.ws_bytes ? plan.prod.ws_offset + plan.prod.set.ws_bytes : plan.ws_bytes;
+    if (plan.prod.on && plan.prod.lean_on) plan.ws_lean = plan.prod.ws_offset + plan.prod.lean.ws_bytes;
     select_split(plan);
     match_separable(plan);
-    if (plan.sep.on) plan.ws_full = std::max(plan.ws_bytes, plan.sep.ws_bytes);   // one or the other
+    if (plan.sep.on) {   // one or the other
+        plan.ws_full = std::max(plan.ws_bytes, plan.sep.set.ws_bytes);
+        if (plan.sep.lean_on) plan.ws_lean = std::max(plan.ws_bytes, plan.sep.lean.ws_bytes);
+    }
 }
 
 // The worked expression on the kernels with 64-bit sums; the reported family stays what it is without them.  They take the

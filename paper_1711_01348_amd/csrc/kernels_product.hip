@@ -574,14 +574,14 @@ int product_run_two(const ProductJob &x, const ProductJob &y, void *ws, hipStrea
     return rc ? rc : product_run(y, ws, s);
 }
 
-int product_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s) {
+int product_forward(const tad_plan &pl, const ProductSet &set, const void *const *args, void *f, void *ws, hipStream_t s) {
     const ProductPlan &pp = pl.prod;
     const bool f64 = pl.dtype == TAD_F64;
-    const ProductJob j = {&pp.forward, args[pp.side[0].operand], f64, args[pp.side[1].operand], f64, f, f64};
+    const ProductJob j = {&set.forward, args[pp.side[0].operand], f64, args[pp.side[1].operand], f64, f, f64};
     return product_run(j, static_cast<char *>(ws) + pp.ws_offset, s);
 }
 
-int product_backward(const tad_plan &pl, const void *const *args, const void *df, void **dx, void *ws, hipStream_t s) {
+int product_backward(const tad_plan &pl, const ProductSet &set, const void *const *args, const void *df, void **dx, void *ws, hipStream_t s) {
     const ProductPlan &pp = pl.prod;
     const bool f64 = pl.dtype == TAD_F64;
     void *const part = static_cast<char *>(ws) + pp.ws_offset;   // used by the products in turn
@@ -591,7 +591,7 @@ int product_backward(const tad_plan &pl, const void *const *args, const void *df
         const ProductSide &sd = pp.side[q];
         if (!sd.grad || !dx[sd.operand]) continue;
         const void *other = args[pp.side[1 - q].operand];
-        jobs[n++] = {&sd.desc, sd.k_major ? other : df, f64, sd.k_major ? df : other, f64, dx[sd.operand], f64};
+        jobs[n++] = {&set.grad[q], sd.k_major ? other : df, f64, sd.k_major ? df : other, f64, dx[sd.operand], f64};
         dx[sd.operand] = nullptr;
     }
     return n == 2 ? product_run_two(jobs[0], jobs[1], part, s) : n == 1 ? product_run(jobs[0], part, s) : TAD_OK;

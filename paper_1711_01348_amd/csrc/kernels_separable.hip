@@ -234,8 +234,8 @@ static bool joint_side(const SepSide &side, const void *const *dx) {
 
 // Can the product that yields a side's derivative multiply it by the partial derivatives?  (In a large workspace the terms of an operand take the
 // place of the factor's values, which the products read.)
-static bool scaled_side(const SepSide &side, const void *const *dx, bool one_of_two) {
-    if (!side.sub || side.operand >= 0 || !product_scales(side.grad, one_of_two)) return false;
+static bool scaled_side(const SepSide &side, const ProductDesc &d, const void *const *dx, bool one_of_two) {
+    if (!side.sub || side.operand >= 0 || !product_scales(d, one_of_two)) return false;
     int wanted = 0, aligned = 0;
     for (size_t p = 0; p < side.operands.size(); ++p) {
         if (!dx[side.operands[p]]) continue;
@@ -296,15 +296,15 @@ static int apply_outer(const tad_plan &pl, const ProgramBody &pb, const DevProg 
 // Sums through `prog` (null: stored as they are) into out; s_out (may be null): where the sums themselves are needed as well.
 // df: see k_sep_outer.
 template <typename T>
-static int sums(const tad_plan &pl, const DevProg *prog, const void *const *args, const void *df, void *out, T *s_out, char *ws, hipStream_t s,
+static int sums(const tad_plan &pl, const ProductSet &set, const DevProg *prog, const void *const *args, const void *df, void *out, T *s_out, char *ws, hipStream_t s,
                 const bool *scaled = nullptr, const void *const *dx = nullptr) {
     const SepPlan &sp = pl.sep;
     int rc = evaluate_factors<T>(sp, args, ws, s, scaled, dx);
     if (rc) return rc;
     constexpr bool f64 = sizeof(T) == 8;
     const SepSide &a = sp.side[0], &b = sp.side[1];
-    ProductJob j = {&sp.forward, factor(a, args, ws), f64 || a.operand < 0, factor(b, args, ws), f64 || b.operand < 0, out, f64};
-    if (prog && has_register_form(*prog) && sp.outer_linear && product_outer_fits(sp.forward)) {
+    ProductJob j = {&set.forward, factor(a, args, ws), f64 || a.operand < 0, factor(b, args, ws), f64 || b.operand < 0, out, f64};
+    if (prog && has_register_form(*prog) && sp.outer_linear && product_outer_fits(set.forward)) {
         ProductOuter o{};
         o.prog = *prog;
         for (size_t q = 0; q < pl.args.size(); ++q) {
@@ -369,12 +369,12 @@ static bool inner_reads(const SepPlan &sp, int operand) {
 }
 
 template <typename T>
-static int forward_t(const tad_plan &pl, const void *const *args, void *f, char *ws, hipStream_t s) {
-    return sums<T>(pl, pl.sep.identity ? nullptr : &pl.sep.prog.outer, args, nullptr, f, nullptr, ws, s);
+static int forward_t(const tad_plan &pl, const ProductSet &set, const void *const *args, void *f, char *ws, hipStream_t s) {
+    return sums<T>(pl, set, pl.sep.identity ? nullptr : &pl.sep.prog.outer, args, nullptr, f, nullptr, ws, s);
 }
 
 template <typename T>
-static int backward_t(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx, char *ws, hipStream_t s) {
+static int backward_t(const tad_plan &pl, const ProductSet &set, const void *const *args, const void *f, const void *df, void *const *dx, char *ws, hipStream_t s) {
     const SepPlan &sp = pl.sep;
     constexpr bool f64 = sizeof(T) == 8;
     const int n_ops = (int)pl.args.size();
@@ -390,7 +390,7 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *f
         else
             wanted[q] = dx[side.operand] != nullptr;
     }
-    for (int q = 0; q < 2; ++q) scaled[q] = scaled_side(sp.side[q], dx, wanted[0] && wanted[1]);
+    for (int q = 0; q < 2; ++q) scaled[q] = scaled_side(sp.side[q], set.grad[q], dx, wanted[0] && wanted[1]);
     int rc;
     if (sp.identity || from_f) {
         rc = evaluate_factors<T>(sp, args, ws, s, scaled, dx);
@@ -405,7 +405,7 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *f
         for (int q = 0; q < n_ops; ++q)
             if (dx[q] && ((sp.prog.outer_mask >> q) & 1u) && !sp.term_is_g[q]) s_out = reinterpret_cast<T *>(ws + sp.s_offset);
         T *const gw = reinterpret_cast<T *>(ws + sp.g_offset);
-        rc = sums<T>(pl, &sp.prog.douter, args, df, gw, s_out, ws, s, scaled, dx);
+        rc = sums<T>(pl, set, &sp.prog.douter, args, df, gw, s_out, ws, s, scaled, dx);
         g = gw;
         sum = s_out;
     }
@@ -420,8 +420,8 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *f
         const void *o = factor(other, args, ws);
         const bool o64 = f64 || other.operand < 0, wide = f64 || side.sub;
         void *const to = side.sub ? ws + side.d_offset : dx[side.operand];
-        if (side.k_major) jobs[n_jobs++] = {&side.grad, o, o64, g, f64, to, wide};
-        else jobs[n_jobs++] = {&side.grad, g, f64, o, o64, to, wide};
+        if (side.k_major) jobs[n_jobs++] = {&set.grad[q], o, o64, g, f64, to, wide};
+        else jobs[n_jobs++] = {&set.grad[q], g, f64, o, o64, to, wide};
         if (!side.sub) stored[side.operand] = true;
         for (int p = 0; scaled[q] && p < (int)side.operands.size(); ++p) {
             void *const d = dx[side.operands[p]];
@@ -505,14 +505,14 @@ static int backward_t(const tad_plan &pl, const void *const *args, const void *f
     return TAD_OK;
 }
 
-int separable_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s) {
-    return pl.dtype == TAD_F64 ? forward_t<double>(pl, args, f, static_cast<char *>(ws), s)
-                               : forward_t<float>(pl, args, f, static_cast<char *>(ws), s);
+int separable_forward(const tad_plan &pl, const ProductSet &set, const void *const *args, void *f, void *ws, hipStream_t s) {
+    return pl.dtype == TAD_F64 ? forward_t<double>(pl, set, args, f, static_cast<char *>(ws), s)
+                               : forward_t<float>(pl, set, args, f, static_cast<char *>(ws), s);
 }
 
-int separable_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx, void *ws, hipStream_t s) {
-    return pl.dtype == TAD_F64 ? backward_t<double>(pl, args, f, df, dx, static_cast<char *>(ws), s)
-                               : backward_t<float>(pl, args, f, df, dx, static_cast<char *>(ws), s);
+int separable_backward(const tad_plan &pl, const ProductSet &set, const void *const *args, const void *f, const void *df, void *const *dx, void *ws, hipStream_t s) {
+    return pl.dtype == TAD_F64 ? backward_t<double>(pl, set, args, f, df, dx, static_cast<char *>(ws), s)
+                               : backward_t<float>(pl, set, args, f, df, dx, static_cast<char *>(ws), s);
 }
 
 int program_outer(const tad_plan &pl, const ProgramBody &pb, const DevProg &prog, const void *const *args, const void *s, const void *df,

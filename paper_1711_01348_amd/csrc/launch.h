@@ -48,8 +48,8 @@ int split_product(const GemmDesc &g, const float *a, const float *b, float *c, v
 
 // Sums of products as dense products.  product_backward writes the gradients it is responsible for and clears their
 // entries of dx; the rest is left to the family's kernels.
-int product_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
-int product_backward(const tad_plan &pl, const void *const *args, const void *df, void **dx, void *ws, hipStream_t s);
+int product_forward(const tad_plan &pl, const ProductSet &set, const void *const *args, void *f, void *ws, hipStream_t s);
+int product_backward(const tad_plan &pl, const ProductSet &set, const void *const *args, const void *df, void **dx, void *ws, hipStream_t s);
 
 // One product and its operands; a64, b64, c64: 64-bit elements; turned: the result is stored [c][r].
 struct ProductDesc;
@@ -86,8 +86,8 @@ bool product_outer_fits(const ProductDesc &d);
 int product_run_outer(const ProductJob &j, const ProductOuter &o, hipStream_t s);
 
 // sums of products of two functions (separable.hpp)
-int separable_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
-int separable_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx, void *ws, hipStream_t s);
+int separable_forward(const tad_plan &pl, const ProductSet &set, const void *const *args, void *f, void *ws, hipStream_t s);
+int separable_backward(const tad_plan &pl, const ProductSet &set, const void *const *args, const void *f, const void *df, void *const *dx, void *ws, hipStream_t s);
 
 int program_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
 // out = prog(s, operands), times df if that is given, for every function element; pb: the body `prog` belongs to

@@ -82,6 +82,9 @@ struct tad_plan {
     tad::SepPlan sep;                          // sums of products of two functions (on: the whole expression runs on dense products)
     size_t ws_bytes = 0;                       // workspace of the family's kernels
     size_t ws_full = 0;                        // ... and of the dense products; a smaller workspace runs without those
+    // The least workspace in which the dense products run, where that is no more than the array of tad_eval_backward_static and ws_full is
+    // more, for their partial sums alone: with other tiles and fewer pieces, which take longer (0: ws_full).
+    size_t ws_lean = 0;
     size_t split_ws_offset = 0;                // fallback kernels: where the partial sums of shared elements start
 };
 

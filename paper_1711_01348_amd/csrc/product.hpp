@@ -27,22 +27,28 @@ struct ProductDesc {
     bool pair_flip = false;
 };
 
+// The products of a sum and of its gradients, with the workspace that their partial sums make it (lean: see tad_plan::ws_lean).
+struct ProductSet {
+    ProductDesc forward, grad[2];
+    size_t ws_bytes = 0;
+};
+
 // One factor of the product.
 struct ProductSide {
     int operand = -1;          // the tensor that is the factor
     int64_t sm = 0, sk = 0;    // element strides along m (first factor) or n (second one) and along k
     bool grad = false;         // its gradient is a dense product that fills the tensor in its own memory order
     bool k_major = false;      // ... whose rows run over k
-    ProductDesc desc;          // ... this one
 };
 
 struct ProductPlan {
     bool on = false;
     int64_t M = 0, N = 0, K = 0;
-    ProductDesc forward;
     bool forward_on = false;   // the sum itself is a dense product (else the gradients alone)
     ProductSide side[2];
-    size_t ws_offset = 0, ws_bytes = 0;   // partial sums of shared tiles, behind the workspace of the other kernels
+    ProductSet set, lean;      // (ws_bytes: partial sums of shared tiles, behind the workspace of the other kernels)
+    bool lean_on = false;
+    size_t ws_offset = 0;
 };
 
 // Extents from which the dense products are used, and the least number of terms of the whole sum: below that the
@@ -61,8 +67,8 @@ constexpr int kProductCols = 64;
 // workgroup on a compute unit, which covers the beginning and end of the other one (stages of 64 there: both gradients of
 // 512 x 1024 x 768 40.8 us instead of 36.2, a product that is one round of tiles the same).
 constexpr int kProductStage = 32;
-// Tile and pieces for a product of these extents and operands.
-void product_shape(ProductDesc &d);
+// Tile and pieces for a product of these extents and operands, with no more than `most` bytes of partial sums.
+void product_shape(ProductDesc &d, size_t most);
 // Two products that run one after the other: would they be faster in one launch (pair_rows of both)?
 void product_pair(ProductDesc &x, ProductDesc &y);
 // The product with its operands exchanged: the transposed result.

@@ -39,7 +39,7 @@ static double product_cycles(const ProductDesc &d, int rows, bool flip, int piec
     return pieces == 1 ? t : t + kReduceCycles + (double)pieces * d.R * d.C * 16.0 / 2000.0;   // written and read
 }
 
-void product_shape(ProductDesc &d) {
+void product_shape(ProductDesc &d, size_t most_bytes) {
     d.pair_rows = 0;
     double best = -1;
     for (int flip = 0; flip < 2; ++flip)   // 16 x 100000 results are tiles of 16 x 64, not of 64 x 64 a quarter full
@@ -50,6 +50,7 @@ void product_shape(ProductDesc &d) {
             for (int64_t want = 1; want <= most; want += 1 + want / 8) {
                 const int chunk = want == 1 ? d.Q : (int)(((d.Q + want - 1) / want + 127) / 128 * 128);
                 const int pieces = (d.Q + chunk - 1) / chunk;
+                if (pieces > 1 && (size_t)pieces * d.R * d.C * sizeof(double) > most_bytes) break;
                 const double t = product_cycles(d, rows, flip, pieces, chunk);
                 if (best >= 0 && t >= best) continue;
                 best = t;
@@ -190,15 +191,13 @@ void match_product(tad_plan &pl) {
         if (!product_group_stride(off + e.n_f, extent + e.n_f, e.n_sum, s.sk)) return;
     }
     const ProductSide &A = pp.side[0], &B = pp.side[1];
-    ProductDesc &f = pp.forward;
+    ProductDesc &f = pp.set.forward;
     f.R = (int)M; f.C = (int)N; f.Q = (int)K;
     f.ar = A.sm; f.aq = A.sk; f.bq = B.sk; f.bc = B.sm;
     f.a64 = f.b64 = f64;
     if (!product_addressable(f)) return;
-    product_shape(f);
     const bool contraction = pl.fwd_family == TAD_FAMILY_CONTRACTION;
     pp.forward_on = contraction ? !contraction_stores(f) : !product_sum_short(f64, M, N, K);
-    size_t ws = pp.forward_on ? product_partial_bytes(f) : 0;
     for (int q = 0; q < 2; ++q) {
         ProductSide &s = pp.side[q];
         const ProductSide &o = pp.side[1 - q];
@@ -208,18 +207,31 @@ void match_product(tad_plan &pl) {
         const bool rows = s.sm == K && s.sk == 1, cols = s.sm == 1 && s.sk == X;
         if (!pl.ap[s.operand].derived || pl.arg_count[s.operand] != X * K || !(rows || cols)) continue;
         s.k_major = !rows;
-        ProductDesc &d = s.desc;
+        ProductDesc &d = pp.set.grad[q];
         d.Q = (int)Y;
         if (rows) { d.R = (int)X; d.C = (int)K; d.ar = gx; d.aq = gy; d.bq = o.sm; d.bc = o.sk; }   // sum_y g(x, y) O(k, y)
         else { d.R = (int)K; d.C = (int)X; d.ar = o.sk; d.aq = o.sm; d.bq = gy; d.bc = gx; }        // sum_y O(k, y) g(x, y)
         d.a64 = d.b64 = f64;
         if (!product_addressable(d) || (contraction && contraction_stores(d))) continue;
-        product_shape(d);
         s.grad = true;
-        ws = std::max(ws, product_partial_bytes(d));
     }
-    if (pp.side[0].grad && pp.side[1].grad) product_pair(pp.side[0].desc, pp.side[1].desc);
-    pp.ws_bytes = ws;
+    auto shape = [&](ProductSet &set, size_t most) {
+        size_t bytes = 0;
+        for (ProductDesc *d : {&set.forward, &set.grad[0], &set.grad[1]}) {
+            if (!(d == &set.forward ? pp.forward_on : pp.side[d - set.grad].grad)) continue;
+            product_shape(*d, most);
+            bytes = std::max(bytes, product_partial_bytes(*d));
+        }
+        if (pp.side[0].grad && pp.side[1].grad) product_pair(set.grad[0], set.grad[1]);
+        set.ws_bytes = bytes;
+    };
+    shape(pp.set, SIZE_MAX);
+    const size_t family = align256(pl.ws_bytes), array = TAD_STATIC_SCRATCH_BYTES;
+    if (family <= array && family + pp.set.ws_bytes > array) {
+        pp.lean = pp.set;
+        shape(pp.lean, array - family);
+        pp.lean_on = true;
+    }
     pp.on = pp.forward_on || pp.side[0].grad || pp.side[1].grad;
 }
 

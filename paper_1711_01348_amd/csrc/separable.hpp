@@ -29,7 +29,6 @@ struct SepSide {
     int64_t X = 0;               // values of the side's function index
     int64_t sm = 0, sk = 0;      // element strides of the factor along the function index and along k
     bool k_major = false;        // rows of the factor's derivative run over k
-    ProductDesc grad;            // the factor's derivative
     // the factor as an expression over its pairs of indices, in the order of its derivative's elements; null if the tensor
     // is the factor and its gradient is the product (or not wanted)
     std::shared_ptr<tad_plan> sub;
@@ -50,7 +49,8 @@ struct SepSide {
 struct SepPlan {
     bool on = false;
     int64_t M = 0, N = 0, K = 0;
-    ProductDesc forward;
+    ProductSet set, lean;        // the sums, and the derivatives of the factors
+    bool lean_on = false;
     bool forward_on = false;     // the forward pass too runs on the dense product (else the gradients alone)
     SepSide side[2];
     ProgramBody prog;            // outer function and its derivatives
@@ -64,7 +64,6 @@ struct SepPlan {
     size_t g_offset = 0;         // g = df * d outer / d s
     size_t h_offset = 0;         // 64-bit terms of an operand of the outer function
     size_t part_offset = 0;      // partial sums of the products and of the gathers
-    size_t ws_bytes = 0;
 };
 
 // Workspace the dense form may ask for beyond four times the operands and f.  A factor's pairs of indices can be any number of

@@ -255,50 +255,57 @@ void match_separable(tad_plan &pl) {
     }
     // ---- products -------------------------------------------------------------------------------------------------
     const bool f64 = pl.dtype == TAD_F64;
-    const SepSide &A = sp.side[0], &B = sp.side[1];
-    auto wide = [&](const SepSide &s) { return f64 || s.operand < 0; };
-    ProductDesc &f = sp.forward;
-    f.R = (int)M; f.C = (int)N; f.Q = (int)K;
-    f.ar = A.sm; f.aq = A.sk; f.bq = B.sk; f.bc = B.sm;
-    f.a64 = wide(A); f.b64 = wide(B);
-    if (!product_addressable(f)) return;
-    product_shape(f);
-    size_t part = product_partial_bytes(f);
-    for (int q = 0; q < 2; ++q) {
-        SepSide &s = sp.side[q];
-        const SepSide &o = sp.side[1 - q];
-        const int64_t gx = q == 0 ? N : 1, gy = q == 0 ? 1 : N;   // strides of g along the side's own and the other function index
-        ProductDesc &d = s.grad;
-        d.Q = (int)o.X;
-        if (!s.k_major) { d.R = (int)s.X; d.C = (int)K; d.ar = gx; d.aq = gy; d.bq = o.sm; d.bc = o.sk; }
-        else { d.R = (int)K; d.C = (int)s.X; d.ar = o.sk; d.aq = o.sm; d.bq = gy; d.bc = gx; }
-        d.a64 = s.k_major ? wide(o) : f64;
-        d.b64 = s.k_major ? f64 : wide(o);
-        if (!product_addressable(d)) return;
-        product_shape(d);
-        part = std::max(part, product_partial_bytes(d));
-        if (!s.sub) continue;
-        for (size_t p = 0; p < s.operands.size(); ++p) s.aligned.push_back(pairs_are_elements(*s.sub, (int)p));
-    }
-    product_pair(sp.side[0].grad, sp.side[1].grad);
-    for (int p = 0; p < n_ops; ++p) sp.term_is_g[p] = same_program(sp.prog.douter_arg[p], sp.prog.douter);
     for (int p = 0; p < n_ops; ++p) {
         if (!((sp.prog.outer_mask >> p) & 1u)) continue;
         sp.outer_linear = sp.outer_linear && product_group_stride(pl.fwd.off[p], extent, lead, sp.outer_r[p]) &&
                           product_group_stride(pl.fwd.off[p] + lead, extent + lead, e.n_f - lead, sp.outer_c[p]);
     }
     sp.identity = sp.prog.outer.n == 1 && sp.prog.outer.op[0] == P_SUM;
+    const SepSide &A = sp.side[0], &B = sp.side[1];
+    auto wide = [&](const SepSide &s) { return f64 || s.operand < 0; };
+    ProductDesc &f = sp.set.forward;
+    f.R = (int)M; f.C = (int)N; f.Q = (int)K;
+    f.ar = A.sm; f.aq = A.sk; f.bq = B.sk; f.bc = B.sm;
+    f.a64 = wide(A); f.b64 = wide(B);
+    if (!product_addressable(f)) return;
+    for (int q = 0; q < 2; ++q) {
+        SepSide &s = sp.side[q];
+        const SepSide &o = sp.side[1 - q];
+        const int64_t gx = q == 0 ? N : 1, gy = q == 0 ? 1 : N;   // strides of g along the side's own and the other function index
+        ProductDesc &d = sp.set.grad[q];
+        d.Q = (int)o.X;
+        if (!s.k_major) { d.R = (int)s.X; d.C = (int)K; d.ar = gx; d.aq = gy; d.bq = o.sm; d.bc = o.sk; }
+        else { d.R = (int)K; d.C = (int)s.X; d.ar = o.sk; d.aq = o.sm; d.bq = gy; d.bc = gx; }
+        d.a64 = s.k_major ? wide(o) : f64;
+        d.b64 = s.k_major ? f64 : wide(o);
+        if (!product_addressable(d)) return;
+        if (!s.sub) continue;
+        for (size_t p = 0; p < s.operands.size(); ++p) s.aligned.push_back(pairs_are_elements(*s.sub, (int)p));
+    }
+    for (int p = 0; p < n_ops; ++p) sp.term_is_g[p] = same_program(sp.prog.douter_arg[p], sp.prog.douter);
     // partial sums of the gathers
+    size_t gather_part = 0;
     auto gathers = [&](const ArgPlan &ap, int64_t count, double pairs) {
         if (!ap.derived) return;
         const long long n = gather_launch_count(ap.dev, count);
-        part = std::max(part, split_workspace_bytes(n, sum_shape(ap.dev, n, pairs).splits));
+        gather_part = std::max(gather_part, split_workspace_bytes(n, sum_shape(ap.dev, n, pairs).splits));
     };
     for (const SepSide &s : sp.side)
         if (s.sub)
             for (size_t p = 0; p < s.operands.size(); ++p) gathers(s.sub->ap[p], s.sub->arg_count[p], (double)(s.X * K));
     for (int p = 0; p < n_ops; ++p)
         if ((sp.prog.outer_mask >> p) & 1u) gathers(pl.ap_outer[p], pl.arg_count[p], (double)pl.f_count);
+    // ... and those of the products, no more of them than `most` bytes
+    auto shape = [&](ProductSet &set, size_t most) {
+        size_t bytes = gather_part;
+        for (ProductDesc *d : {&set.forward, &set.grad[0], &set.grad[1]}) {
+            product_shape(*d, most);
+            bytes = std::max(bytes, product_partial_bytes(*d));
+        }
+        product_pair(set.grad[0], set.grad[1]);
+        return bytes;
+    };
+    size_t part = shape(sp.set, SIZE_MAX);
     // workspace.  reuse: the first of a side's terms go where the factor's values were, which the products before them read last
     // (512 x 384 x 200, softplus: 73.0 us apart, 74.0 in the same place)
     auto layout = [&](bool reuse) {
@@ -326,15 +333,34 @@ void match_separable(tad_plan &pl) {
         sp.g_offset = reserve(sums);
         sp.h_offset = sp.prog.outer_mask ? reserve((size_t)pl.f_count * 8) : 0;
         sp.part_offset = reserve(part);
-        sp.ws_bytes = ws;
+        sp.set.ws_bytes = ws;
     };
     double data = (double)pl.f_count;
     for (int p = 0; p < n_ops; ++p) data += (double)pl.arg_count[p];
+    // (the partial sums come last)
+    auto rest = [&] { return sp.set.ws_bytes - align256(part); };
+    // partial sums of the products give way where they alone are what lifts the workspace above a limit
+    auto fit = [&](double limit, bool reuse) {
+        if ((double)sp.set.ws_bytes <= limit || (double)(rest() + align256(gather_part)) > limit) return;
+        part = shape(sp.set, ((size_t)limit - rest()) & ~(size_t)255);
+        layout(reuse);
+    };
+    const double limit = kSeparableWorkspace, elements = 4.0 * data * (f64 ? 8 : 4);
     layout(false);
-    if ((double)sp.ws_bytes > kSeparableWorkspace) layout(true);
-    if ((double)sp.ws_bytes > kSeparableWorkspace + 4.0 * data * (f64 ? 8 : 4)) {
+    fit(limit, false);
+    if ((double)sp.set.ws_bytes > limit) {
+        layout(true);
+        fit(limit + elements, true);
+    }
+    if ((double)sp.set.ws_bytes > limit + elements) {
         sp = SepPlan{};
         return;
+    }
+    const size_t array = TAD_STATIC_SCRATCH_BYTES;
+    if (sp.set.ws_bytes > array && rest() + align256(gather_part) <= array) {
+        sp.lean = sp.set;
+        sp.lean.ws_bytes = rest() + align256(shape(sp.lean, (array - rest()) & ~(size_t)255));
+        sp.lean_on = true;
     }
     sp.on = true;
     sp.forward_on = !forward_general(pl.dtype == TAD_F64, !program, M, N, K);

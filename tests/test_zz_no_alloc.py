@@ -81,3 +81,31 @@ def test_a_plan_that_would_like_more_runs_on_the_kernels_that_do_with_less(make)
     for a, s, x, y in zip(expr.args, plan.backward(args, f, df, static=True), same, full):
         assert torch.equal(s, x), a.name
         assert check.within(s.cpu().numpy(), y.cpu().numpy(), "f32"), a.name
+
+
+# partial sums of products in pieces are a choice: they alone do not keep the dense products out of the array
+@pytest.mark.parametrize("kind,M,N,K,dtype", [("dense", 320, 2701, 932, "f32"), ("dense", 481, 405, 5519, "f32"), ("dense", 535, 1043, 1732, "f32"),
+                                              ("dense", 430, 1366, 684, "f64"), ("matmul", 3163, 2693, 98, "f32"), ("matmul", 6957, 1055, 104, "f32"),
+                                              ("matmul", 2479, 2045, 237, "f64"), ("softplus", 282, 4919, 48, "f32")])
+def test_dense_products_run_in_the_array(kind, M, N, K, dtype):
+    """With fewer pieces where need be: the gradients of a workspace of any size from the array's to what the plan asks for."""
+    import torch
+    from paper_1711_01348_amd import binding as B, check
+    expr = dict(dense=wl.dense_layer_expr, matmul=wl.matmul_expr, softplus=wl.softplus_ratio_expr)[kind](M, N, K, dtype)
+    plan = B.Plan(expr)
+    w = wl.random_inputs(expr, 32, -0.2, 0.2)
+    args = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in w.arg_list()]
+    df = torch.from_numpy(w.df).cuda()
+    f = plan.forward(args)
+    full = plan.backward(args, f, df)
+    for static, n in ((True, None), (False, B.STATIC_SCRATCH_BYTES), (False, max(B.STATIC_SCRATCH_BYTES, plan.workspace_bytes - 1))):
+        ws = None if static else torch.empty(n, dtype=torch.uint8, device="cuda")
+        ms, launches = ctypes.c_double(0), ctypes.c_int(0)
+        assert B.lib.tad_profile_begin(b"k_product", 1) == 0
+        grads = plan.backward(args, f, df, static=True) if static else plan.backward(args, f, df, ws=ws)
+        assert B.lib.tad_profile_end(ctypes.byref(ms), ctypes.byref(launches)) == 0
+        assert launches.value >= 1
+        for a, x, y in zip(expr.args, grads, full):
+            assert check.within(x.cpu().numpy(), y.cpu().numpy(), dtype), a.name
+    ws = torch.empty(B.STATIC_SCRATCH_BYTES, dtype=torch.uint8, device="cuda")
+    assert check.within(plan.forward(args, ws=ws).cpu().numpy(), f.cpu().numpy(), dtype)
