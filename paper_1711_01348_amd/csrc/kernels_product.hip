@@ -6,7 +6,7 @@
 // C[r][c] = sum_q A(r, q) B(q, c).  A workgroup of eight wavefronts computes a tile of 16 NR x 64 results: a wavefront owns 16 columns
 // of it and one half of every stage's values of q, and the two halves are added at the end.  What the tile's height is for: a 16 x 16 x 4
 // instruction occupies its matrix core for 64 cycles (78.6 TFLOP/s), everything else is to fit under that, so the best that can be done is
-// to give the 1024 matrix cores equal numbers of 16 x 16 blocks.  product_shape picks NR (1 .. 8, up to 5 with 64-bit operands) and the
+// to give the 1024 matrix cores equal numbers of 16 x 16 blocks.  product_shape picks NR (1 .. 7, up to 5 with 64-bit operands) and the
 // orientation for that: 1000 x 1203 is 247 tiles of 80 x 64, one for each compute unit and 93 % of an even share, where tiles of 32 x 32 are
 // 2.4 rounds that cost three and fetch twice the operands through L2.
 // The operands go through registers into LDS, widened to 64 bits on the way, [row][q] with 16 bytes behind each row (fragment reads of 16
@@ -500,7 +500,6 @@ static int launch_rows(const ProductArgs &M, int rows, unsigned blocks, const Pr
         if constexpr (sizeof(TA) == 4 || sizeof(TB) == 4) {
             if (rows == 6) return launch_product<TA, TB, 6>(M, blocks, outer, c64, s);
             if (rows == 7) return launch_product<TA, TB, 7>(M, blocks, outer, c64, s);
-            if (rows == 8) return launch_product<TA, TB, 8>(M, blocks, outer, c64, s);
         }
         return TAD_EUNSUPPORTED;
     }

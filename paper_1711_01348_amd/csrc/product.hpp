@@ -23,6 +23,8 @@ struct ProductDesc {
     bool flip = false; // ... of the product with its operands exchanged, whose results are stored transposed
     int pieces = 1;    // pieces of q computed by separate workgroups (few output tiles, long sum)
     int chunk = 0;     // values of q per piece (pieces > 1)
+    int outer = 0;     // results per pass of the interpreter where a program is applied to them (0: none)
+    bool scaled = false;   // results that are multiplied where they are stored, if the sum is not in pieces
     int pair_rows = 0; // `rows` of one launch for this product and the other gradient (0: a launch each)
     bool pair_flip = false;
 };
@@ -58,12 +60,12 @@ constexpr int64_t kProductExtent = 16, kProductSum = 8;
 // Offset of one tensor along a group of extended indices as a single stride: the group's indices, the last one
 // fastest, count through 0 .. n - 1 and the offset is stride * that number.  False if it is not linear in it.
 bool product_group_stride(const int64_t *off, const int64_t *extent, int count, int64_t &stride);
-// The kernels address the elements of a stage (up to 128 rows, 32 values of q) with 32-bit byte offsets from
+// The kernels address the elements of a stage (up to 112 rows, 32 values of q) with 32-bit byte offsets from
 // a 64-bit base.
 bool product_addressable(const ProductDesc &d);
 // Columns of an output tile.
 constexpr int kProductCols = 64;
-// Values of q per stage: two stages of the tallest tile take 104 KB of LDS, and the low ones leave room for a second and a third
+// Values of q per stage: two stages of the tallest tile take 96 KB of LDS, and the low ones leave room for a second and a third
 // workgroup on a compute unit, which covers the beginning and end of the other one (stages of 64 there: both gradients of
 // 512 x 1024 x 768 40.8 us instead of 36.2, a product that is one round of tiles the same).
 constexpr int kProductStage = 32;

@@ -10,15 +10,26 @@
 namespace tad {
 
 // Time of a product in cycles of 2.2 GHz: tiles go to the 256 compute units in turn, whose matrix cores take 16 `rows` cycles per
-// value of q; a tile takes some time to begin and to end, which another one on the same unit covers.  Fitted to 32-bit products: 512 x 1024
-// x 768 with rows = 1 .. 4 (two tiles a unit, one, one, one) 21.7, 20.1, 25.8, 31.7 us, 512 x 512 x 512 with 1 and 2 9.7 and 13.7 us.
-// kReduceCycles: the launch that adds pieces up.
-constexpr double kTileCycles = 7000, kReduceCycles = 9000, kLaunchCycles = 6000;
+// value of q; a tile takes some time to begin and to end, which another one on the same unit covers (where there is none, storing a tall one takes
+// the longer: 3163 x 2693 x 98 in 32 bits, rows = 7 62 us, 4 with two tiles a unit 55).  kReduceCycles: the launch that adds pieces up.
+// Fitted to the forward passes of 197 products, half of them of 64-bit operands, 17 .. 6957 x 16 .. 5000 x 20 .. 5400, each with every height, both
+// orientations and several numbers of pieces: what is picked takes 0.8 % longer than the fastest in the mean, 14 % at most (1381 x 190 x 884 in 64 bits 22.4 /
+// 19.6 us); both gradients of 43 products in one launch of every height, or in two: 1.9 % in the mean, 19 % at most (1253 x 45 x 930 23.4 / 19.6).  Heights that
+// earn their place: 5 1000 x 1203 x 777 in 64 bits 41 us instead of 53; 7 1433 x 1190 x 306 24.6 / 26.7, 1665 x 1019 x 147 15.8 / 16.7; 6 where a program
+// follows, 3000 x 1500 x 64 44 / 48, 4710 x 315 x 76 17.9 / 21.8 (8 was the fastest nowhere).
+constexpr double kTileCycles = 7000, kAloneCycles = 300, kReduceCycles = 4000, kLaunchCycles = 6000;
+// A program that is applied to the results: per pass over a thread's results of every tile on a unit; and for sums in pieces its launch of its own.
+// Dense layers with tanh, 27 sizes: 0.5 % and 7 % from the fastest; without these costs 160 x 4296 x 83 13.3 us instead of 12.4, 1500 x 1024 x 200 28.6
+// instead of 24.1.
+constexpr double kOuterCycles = 3000, kOuterLaunch = 5000;
+// Results that could be scaled where they are stored, of a sum in pieces: a launch over them (softplus 538 x 473 x 29, the gradient of one operand 25.0 us
+// whole, 29.2 in pieces).
+constexpr double kScaleLaunch = 10000;
 // Cycles of `each` tiles that a compute unit works on at once.  A stage of a low tile that is alone there takes as long as its barrier, LDS and
 // the loads behind it (512 x 43 x 1832: one round of 58 stages 24 us).
 static double sum_cycles(int rows, int64_t q, int64_t each) {
     const double cycles = rows == 1 ? 20.0 : rows == 2 ? 18.0 : 17.0;   // (low tiles: more fragments to read per instruction)
-    return (double)((q + kProductStage - 1) / kProductStage) * std::max(900.0, cycles * kProductStage * (double)(rows * each));
+    return (double)((q + kProductStage - 1) / kProductStage) * std::max(800.0, cycles * kProductStage * (double)(rows * each));
 }
 // tiles that share a compute unit: what registers and LDS leave room for
 static int tiles_per_unit(const ProductDesc &d, int rows) {
@@ -30,12 +41,15 @@ static int64_t tile_count(const ProductDesc &d, int rows, bool flip) {
     return ((R + 16 * rows - 1) / (16 * rows)) * ((C + kProductCols - 1) / kProductCols);
 }
 // sums of 64-bit operands take three sets of registers: a tile of six does not fit
-static int rows_limit(const ProductDesc &d) { return d.a64 && d.b64 ? 5 : 8; }
+static int rows_limit(const ProductDesc &d) { return d.a64 && d.b64 ? 5 : 7; }
 static double product_cycles(const ProductDesc &d, int rows, bool flip, int pieces, int chunk) {
     const int64_t each = (tile_count(d, rows, flip) * pieces + 255) / 256, at_once = tiles_per_unit(d, rows);
     const int64_t rounds = (each + at_once - 1) / at_once;
-    const double t = (double)rounds * kTileCycles + (double)(rounds - 1) * sum_cycles(rows, chunk, at_once) +
-                     sum_cycles(rows, chunk, each - (rounds - 1) * at_once);
+    double t = (double)rounds * kTileCycles + (double)(rounds - 1) * sum_cycles(rows, chunk, at_once) +
+               sum_cycles(rows, chunk, each - (rounds - 1) * at_once);
+    if (at_once == 1) t += kAloneCycles * rows * (double)(rounds - 1);
+    if (d.scaled && pieces > 1) t += kScaleLaunch;
+    if (d.outer) t += pieces > 1 ? kOuterLaunch : kOuterCycles * (double)((2 * rows + d.outer - 1) / d.outer * each);
     return pieces == 1 ? t : t + kReduceCycles + (double)pieces * d.R * d.C * 16.0 / 2000.0;   // written and read
 }
 

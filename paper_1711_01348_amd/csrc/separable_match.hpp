@@ -267,6 +267,7 @@ void match_separable(tad_plan &pl) {
     f.R = (int)M; f.C = (int)N; f.Q = (int)K;
     f.ar = A.sm; f.aq = A.sk; f.bq = B.sk; f.bc = B.sm;
     f.a64 = wide(A); f.b64 = wide(B);
+    if (!sp.identity && sp.outer_linear && sp.prog.outer.n_regs >= 0) f.outer = f64 ? 2 : 4;   // ProgWidth
     if (!product_addressable(f)) return;
     for (int q = 0; q < 2; ++q) {
         SepSide &s = sp.side[q];
@@ -278,6 +279,7 @@ void match_separable(tad_plan &pl) {
         else { d.R = (int)K; d.C = (int)s.X; d.ar = o.sk; d.aq = o.sm; d.bq = gy; d.bc = gx; }
         d.a64 = s.k_major ? wide(o) : f64;
         d.b64 = s.k_major ? f64 : wide(o);
+        d.scaled = s.sub && s.operand < 0;
         if (!product_addressable(d)) return;
         if (!s.sub) continue;
         for (size_t p = 0; p < s.operands.size(); ++p) s.aligned.push_back(pairs_are_elements(*s.sub, (int)p));

@@ -182,3 +182,30 @@ def test_tiles_of_functions_and_with_an_outer_function(I, J, K):
         assert check.within(f, oracle.forward(expr, w.arg_list()), "f32")
         for g, r in zip(grads, oracle.backward(expr, w.arg_list(), w.df)):
             assert check.within(g, r, "f32"), check.errors(g, r)
+
+
+# every height of a tile: of plain products, with a program behind them, with column sums and scaled results beside them
+HEIGHTS = [("matmul", 1433, 1190, 306, "f32"), ("matmul", 719, 1729, 381, "f32"), ("dense", 4710, 315, 76, "f32"), ("dense", 160, 4296, 83, "f32"),
+           ("dense", 1500, 1024, 200, "f32"), ("dense", 2000, 300, 20, "f64"), ("matmul", 1077, 74, 14, "f32")]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,M,N,K,dtype", HEIGHTS)
+def test_heights_of_tiles(kind, M, N, K, dtype):
+    import torch
+    from paper_1711_01348_amd import binding as B, check
+    e = dict(dense=wl.dense_layer_expr, matmul=wl.matmul_expr)[kind](M, N, K, dtype)
+    w = wl.random_inputs(e, 17, -0.2, 0.2)
+    plan = B.Plan(e)
+    args = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in w.arg_list()]
+    f = plan.forward(args)
+    grads = plan.backward(args, f, torch.from_numpy(w.df).cuda())
+    x, y = (a.astype(np.float64) for a in w.arg_list()[:2])
+    df = w.df.astype(np.float64)
+    f_ref = x @ y
+    if kind == "dense":
+        f_ref = np.tanh(f_ref + w.arg_list()[2].astype(np.float64))
+        df = df * (1 - f_ref ** 2)
+    refs = [f_ref, df @ y.T, x.T @ df] + ([df.sum(0)] if kind == "dense" else [])
+    for g, r in zip([f] + list(grads), refs):
+        assert check.within(g.cpu().numpy(), r, dtype), check.errors(g.cpu().numpy(), r)
