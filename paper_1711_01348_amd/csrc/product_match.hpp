@@ -14,10 +14,10 @@ namespace tad {
 // the longer: 3163 x 2693 x 98 in 32 bits, rows = 7 62 us, 4 with two tiles a unit 55).  kReduceCycles: the launch that adds pieces up.
 // Fitted to the forward passes of 197 products, half of them of 64-bit operands, 17 .. 6957 x 16 .. 5000 x 20 .. 5400, each with every height, both
 // orientations and several numbers of pieces: what is picked takes 0.8 % longer than the fastest in the mean, 14 % at most (1381 x 190 x 884 in 64 bits 22.4 /
-// 19.6 us); both gradients of 43 products in one launch of every height, or in two: 1.9 % in the mean, 19 % at most (1253 x 45 x 930 23.4 / 19.6).  Heights that
+// 19.6 us); both gradients of 75 products in one launch of every height, or in two: 1.3 % in the mean, 24 % at most (2067 x 284 x 597 44.4 / 35.8).  Heights that
 // earn their place: 5 1000 x 1203 x 777 in 64 bits 41 us instead of 53; 7 1433 x 1190 x 306 24.6 / 26.7, 1665 x 1019 x 147 15.8 / 16.7; 6 where a program
 // follows, 3000 x 1500 x 64 44 / 48, 4710 x 315 x 76 17.9 / 21.8 (8 was the fastest nowhere).
-constexpr double kTileCycles = 7000, kAloneCycles = 300, kReduceCycles = 4000, kLaunchCycles = 6000;
+constexpr double kTileCycles = 7000, kAloneCycles = 300, kReduceCycles = 4000, kLaunchCycles = 7000;
 // A program that is applied to the results: per pass over a thread's results of every tile on a unit; and for sums in pieces its launch of its own.
 // Dense layers with tanh, 27 sizes: 0.5 % and 7 % from the fastest; without these costs 160 x 4296 x 83 13.3 us instead of 12.4, 1500 x 1024 x 200 28.6
 // instead of 24.1.
@@ -25,12 +25,13 @@ constexpr double kOuterCycles = 3000, kOuterLaunch = 5000;
 // Results that could be scaled where they are stored, of a sum in pieces: a launch over them (softplus 538 x 473 x 29, the gradient of one operand 25.0 us
 // whole, 29.2 in pieces).
 constexpr double kScaleLaunch = 10000;
-// Cycles of `each` tiles that a compute unit works on at once.  A stage of a low tile that is alone there takes as long as its barrier, LDS and
-// the loads behind it (512 x 43 x 1832: one round of 58 stages 24 us).
-static double sum_cycles(int rows, int64_t q, int64_t each) {
-    const double cycles = rows == 1 ? 20.0 : rows == 2 ? 18.0 : 17.0;   // (low tiles: more fragments to read per instruction)
-    return (double)((q + kProductStage - 1) / kProductStage) * std::max(800.0, cycles * kProductStage * (double)(rows * each));
-}
+// Cycles of a stage for the matrix cores of a compute unit, per tile, and of the barrier, LDS and the loads behind a stage, which take as long where the
+// tiles of a unit leave the matrix cores idle (512 x 43 x 1832: one round of 58 stages 24 us).
+static double tile_cycles(int rows) { return (rows == 1 ? 20.0 : rows == 2 ? 18.0 : 17.0) * kProductStage * rows; }   // (low tiles: more fragments per instruction)
+constexpr double kStageCycles = 800;
+static int64_t stages_of(int64_t q) { return (q + kProductStage - 1) / kProductStage; }
+// Cycles of `each` tiles that a compute unit works on at once.
+static double sum_cycles(int rows, int64_t q, int64_t each) { return (double)stages_of(q) * std::max(kStageCycles, tile_cycles(rows) * (double)each); }
 // tiles that share a compute unit: what registers and LDS leave room for
 static int tiles_per_unit(const ProductDesc &d, int rows) {
     if (d.a64 && d.b64) return rows == 1 ? 2 : 1;
@@ -85,22 +86,27 @@ ProductDesc product_turned(const ProductDesc &d) {
     return t;
 }
 
-// n0 tiles of t0 cycles, then n1 of t1 <= t0, on 256 compute units that take at_once tiles and the next one when one of them is done
-static double pair_cycles(int64_t n0, double t0, int64_t n1, double t1, int at_once) {
-    if (at_once > 1 && n0 + n1 <= 256 * at_once) {   // all in their places from the start: the first unit has the most
+// n0 tiles of s0 stages, then n1 of s1 <= s0, on 256 compute units that take at_once tiles and the next one when one of them is done
+static double pair_cycles(int64_t n0, int64_t s0, int64_t n1, int64_t s1, int rows, int at_once) {
+    const double c = tile_cycles(rows);
+    if (at_once > 1 && n0 + n1 <= 256 * at_once) {   // all in their places from the start: the first unit has the most, and its long ones to itself in the end
         const int64_t of0 = (n0 + 255) / 256, all = (n0 + n1 + 255) / 256;
-        return kTileCycles + (double)of0 * t0 + (double)(all - of0) * t1;
+        return kTileCycles + (double)s1 * std::max(kStageCycles, (double)all * c) + (double)(s0 - s1) * std::max(kStageCycles, (double)of0 * c);
     }
-    t0 += kTileCycles / at_once;
-    t1 += kTileCycles / at_once;
+    const double stage = std::max(kStageCycles / at_once, c);
+    const double t0 = (double)s0 * stage + kTileCycles / at_once, t1 = (double)s1 * stage + kTileCycles / at_once;
     const int64_t late = n0 % 256;   // units that are free one tile after the others
     const double from[2] = {(double)(n0 / 256) * t0, (double)(n0 / 256 + 1) * t0};
     const int64_t units[2] = {256 - late, late};
     const double even = ((double)n0 * t0 + (double)n1 * t1) / 256.0;   // no earlier than this
     int64_t k[2];                    // tiles of the second kind that a unit has done
-    for (int c = 0; c < 2; ++c) k[c] = std::max<int64_t>(0, (int64_t)((even - from[c]) / t1));
+    for (int i = 0; i < 2; ++i) k[i] = std::max<int64_t>(0, (int64_t)((even - from[i]) / t1));
     while (units[0] * k[0] + units[1] * k[1] < n1) ++k[late && from[1] + (double)k[1] * t1 < from[0] + (double)k[0] * t1 ? 1 : 0];
-    return std::max(from[0] + (double)k[0] * t1, late ? from[1] + (double)k[1] * t1 : 0.0);
+    const double t = std::max(from[0] + (double)k[0] * t1, late ? from[1] + (double)k[1] * t1 : 0.0);
+    // a long tile shares its unit as long as there are others, and has what is left of it to itself (321 x 2701 x 932, rows = 3: 90 us, 65 without this)
+    const double done = std::max(0.0, even - kTileCycles) / std::max(kStageCycles, (double)at_once * c);
+    const double alone = std::max(kStageCycles, c * (double)std::min<int64_t>(at_once, (n0 + 255) / 256));
+    return std::max(t, std::max(even, kTileCycles) + ((double)s0 - done) * alone);
 }
 
 void product_pair(ProductDesc &x, ProductDesc &y) {
@@ -112,9 +118,9 @@ void product_pair(ProductDesc &x, ProductDesc &y) {
         if ((fx ? x.b64 : x.a64) != (fy ? y.b64 : y.a64) || (fx ? x.a64 : x.b64) != (fy ? y.a64 : y.b64)) continue;
         for (int rows = 1; rows <= rows_limit(x); ++rows) {
             const int64_t nx = tile_count(x, rows, fx), ny = tile_count(y, rows, fy);
-            const double tx = sum_cycles(rows, x.Q, 1), ty = sum_cycles(rows, y.Q, 1);
+            const int64_t sx = stages_of(x.Q), sy = stages_of(y.Q);
             const int at_once = tiles_per_unit(x, rows);
-            const double t = x.Q >= y.Q ? pair_cycles(nx, tx, ny, ty, at_once) : pair_cycles(ny, ty, nx, tx, at_once);
+            const double t = sx >= sy ? pair_cycles(nx, sx, ny, sy, rows, at_once) : pair_cycles(ny, sy, nx, sx, rows, at_once);
             if (t >= best) continue;
             best = t;
             x.pair_rows = y.pair_rows = rows;
