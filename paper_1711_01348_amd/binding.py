@@ -121,8 +121,17 @@ def _load():
     return lib
 
 
+def _load_calls():
+    # checks of tensors and the call in one native function; needs torch in the process
+    path = os.path.join(_PKG, "_calls.so")
+    if not os.path.exists(path):
+        raise ImportError(f"{path} is missing: run `python -c 'import __graft_entry__ as g; g.build()'`")
+    from . import _calls
+    return _calls
+
+
 lib = _load()
-from . import _calls  # noqa: E402  (checks of tensors and the call in one native function; needs torch in the process)
+_calls = _load_calls()
 
 
 def _entry(function) -> int:

@@ -1,4 +1,7 @@
 """Calls with torch tensors: the native checks accept what the checks in Python accept, and refuse what they refuse."""
+import os
+import subprocess
+import sys
 import threading
 
 import numpy as np
@@ -29,6 +32,20 @@ def test_host_tensors_are_refused_in_words():
         B._calls.forward(B._FORWARD, plan._h.value, plan._spec, args, f, ws)
     with pytest.raises(TypeError):
         B._calls.spec(True, (2,), ((2, "3"),))
+
+
+@pytest.mark.parametrize("missing", ["libtad.so", "_calls.so"])
+def test_a_tree_that_is_not_built_says_what_to_run(tmp_path, missing):
+    import paper_1711_01348_amd as package
+    tree, here = tmp_path / "paper_1711_01348_amd", os.path.dirname(package.__file__)
+    tree.mkdir()
+    for name in os.listdir(here):
+        if name.endswith((".py", ".so")) and name != missing:
+            os.symlink(os.path.join(here, name), tree / name)
+    run = subprocess.run([sys.executable, "-c", "import paper_1711_01348_amd.binding"], cwd=tmp_path, capture_output=True, text=True,
+                         env=dict(os.environ, PYTHONPATH=str(tmp_path)))
+    assert run.returncode != 0
+    assert f"{missing} is missing: run `python -c 'import __graft_entry__ as g; g.build()'`" in run.stderr
 
 
 @pytest.mark.gpu
