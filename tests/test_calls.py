@@ -48,6 +48,70 @@ def test_a_tree_that_is_not_built_says_what_to_run(tmp_path, missing):
     assert f"{missing} is missing: run `python -c 'import __graft_entry__ as g; g.build()'`" in run.stderr
 
 
+def _layer():
+    """tanh(b + x w): b is read by the outer function."""
+    from paper_1711_01348_amd import binding as B
+    e = wl.dense_layer_expr(40, 33, 50, "f32")
+    return B.Plan(e), wl.random_inputs(e, 4, -0.3, 0.3)
+
+
+def test_the_native_derived_call_leaves_the_rest_to_python():
+    """Answered with None before anything is called: host tensors, an operand that is none, one that has no gradient of its own."""
+    import torch
+    from paper_1711_01348_amd import binding as B
+    plan, w = _layer()
+    args = [torch.from_numpy(a) for a in w.arg_list()]
+    df, ws = torch.from_numpy(w.df), torch.empty(64, dtype=torch.uint8)
+    for which, out in ((0, args[0]), (3, args[0]), (-1, args[0])):
+        assert B._calls.derived(B._DERIVED, plan._h.value, plan._spec, args, df, which, out, ws, 0) is None
+    with pytest.raises(TypeError):
+        B._calls.derived(B._DERIVED, plan._h.value, plan._spec, args, df, 0, args[0], ws)
+
+
+@pytest.mark.gpu
+def test_derived_gradients_with_tensors_of_the_callers():
+    import torch
+    from paper_1711_01348_amd import binding as B
+    plan, w = _layer()
+    args = [torch.from_numpy(a).cuda() for a in w.arg_list()]
+    df = torch.from_numpy(w.df).cuda()
+    wide = torch.empty(args[0].shape[0], 2 * args[0].shape[1], device="cuda")
+    for p in range(3):
+        d = B.DerivedGradient(plan, p)
+        ws = torch.empty(max(d.workspace_bytes, 1), dtype=torch.uint8, device="cuda")
+        want = d.evaluate(args, df)
+        out = torch.full_like(args[p], float("nan"))
+        assert d.evaluate(args, df, out=out, ws=ws) is out
+        assert torch.equal(out, want)
+        assert torch.equal(d.evaluate(_List(args), df, out=torch.empty_like(out), ws=ws), want)
+        kept = out.clone()
+        for bad in (out.double(), out.cpu(), out.reshape(-1, 1) if out.dim() == 1 else out.reshape(-1), out[:-1]):
+            with pytest.raises(ValueError):
+                d.evaluate(args, df, out=bad, ws=ws)
+        for bad in (df.double(), df.cpu(), df[:-1], df.t()):
+            with pytest.raises(ValueError):
+                d.evaluate(args, bad, out=out, ws=ws)
+        with pytest.raises(ValueError):
+            d.evaluate([wide[:, ::2]] + args[1:], df, out=out, ws=ws)
+        assert torch.equal(out, kept)
+
+
+@pytest.mark.gpu
+def test_an_alias_has_no_native_derived_call():
+    import torch
+    from paper_1711_01348_amd import binding as B
+    e = wl.matrix_square_expr(20, "f64")
+    plan, w = B.Plan(e), wl.random_inputs(e, 5)
+    alias = next(p for p, a in enumerate(e.args) if a.same_as is not None)
+    root = e.args[alias].same_as
+    args = [torch.from_numpy(a).cuda() if a is not None else None for a in w.arg_list()]
+    df = torch.from_numpy(w.df).cuda()
+    d = B.DerivedGradient(plan, root)
+    out, ws = torch.empty_like(args[root]), torch.empty(max(d.workspace_bytes, 1), dtype=torch.uint8, device="cuda")
+    assert B._calls.derived(B._DERIVED, d._h.value, plan._spec, args, df, alias, out, ws, 0) is None
+    assert torch.equal(d.evaluate(args, df, out=out, ws=ws), d.evaluate(args, df))
+
+
 @pytest.mark.gpu
 def test_both_ways_of_checking_give_the_same():
     import torch
