@@ -85,36 +85,49 @@ __global__ __launch_bounds__(256) void k_mfma_prep(const float *__restrict__ a, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// forward: block tile 64 x 64, 2 x 2 waves of 32 x 32, k tile 32, global -> register -> LDS staging.  Four wavefronts per SIMD, which
-// wait for their barriers, loads and stores in turn; with 128 x 128 and two, forward and gradients of 700 x 1000 x 96 56.6 us instead of 47.5,
-// 3000 x 300 x 224 94 / 81, 4096 x 4096 x 256 285.5 / 281.8 (both together with the gradients' eight waves below).
+// forward: block tile 64 NX x 64 NX, 2 x 2 waves of 32 NX x 32 NX, k tile 32, global -> register -> LDS staging.  NX = 1: four wavefronts
+// per SIMD, which wait for their barriers, loads and stores in turn, and tiles that fill the chip sooner; NX = 2: two, half the LDS reads per
+// matrix instruction.  Forward passes with 128 x 128 / 64 x 64: 1024 x 1024 x 256 26 / 11 us, 3000 x 300 x 224 24 / 11, 3000 x 3000 x 256 66 / 50 (a second round
+// of 64 tiles), 130 x 32636 x 288 54.0 / 52.0 (half empty), 4096 x 4096 x 64 34.1 / 31.5, x 128 50.4 / 47.8, x 256 81.0 / 83.6, x 512 146 / 153,
+// 4096 x 2048 x 512 78.1 / 81.3, 8192 x 4096 x 256 155 / 162: the large tiles from K = 256 on, where they and their last round are nearly full.
 // ---------------------------------------------------------------------------------------------
 constexpr int MF_KT = 32;
 constexpr int MF_LD = 33;   // odd row stride: conflict-free ds_read_b32 of [row][k] tiles
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_mfma_forward(const float *__restrict__ a, const float *__restrict__ b,
-                                                      const float *__restrict__ rowv, const float *__restrict__ nb,
-                                                      float *__restrict__ f, int I, int J, int K) {
-    constexpr int LO = 34;   // row stride of the output stage
-    __shared__ float smem[4 * 32 * LO > 2 * 64 * MF_LD ? 4 * 32 * LO : 2 * 64 * MF_LD];   // A tile then B tile; reused as the output stage in the epilogue
-    __shared__ float rv[64][4];
+static bool large_forward_tiles(int64_t I, int64_t J, int64_t K) {
+    const int64_t tiles = ((I + 127) / 128) * ((J + 127) / 128), last = (tiles - 1) % 512 + 1;   // 512 at once
+    return K >= 256 && last >= 480 && 16 * I * J >= 15 * tiles * 128 * 128;
+}
+
+template <int NX>
+__device__ __forceinline__ void mfma_forward_tile(const float *__restrict__ a, const float *__restrict__ b, const float *__restrict__ rowv,
+                                                  const float *__restrict__ nb, float *__restrict__ f, int I, int J, int K) {
+    constexpr int T = 64 * NX, W = 32 * NX, P = 2 * NX;
+    constexpr int LO = W + 2;                     // row stride of the output stage
+    constexpr int TILES = 2 * T * MF_LD, STAGE = 4 * 32 * LO;
+    __shared__ float smem[TILES > STAGE ? TILES : STAGE];   // A tile then B tile; reused as the output stage in the epilogue
+    __shared__ float rv[T][4];
     float (*As)[MF_LD] = reinterpret_cast<float (*)[MF_LD]>(smem);
-    float (*Bs)[MF_LD] = reinterpret_cast<float (*)[MF_LD]>(smem + 64 * MF_LD);
+    float (*Bs)[MF_LD] = reinterpret_cast<float (*)[MF_LD]>(smem + T * MF_LD);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-    if (tid < 64) {
+    const int i0 = blockIdx.y * T, j0 = blockIdx.x * T;
+    if (tid < T) {
         const int i = i0 + tid;
 #pragma unroll
         for (int q = 0; q < 4; ++q) rv[tid][q] = i < I ? rowv[i * 4 + q] : 0.f;
     }
-    float16v acc;
+    float16v acc[NX][NX];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    float4v ra[2], rb[2];
+    for (int x = 0; x < NX; ++x)
+#pragma unroll
+        for (int y = 0; y < NX; ++y)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
+    float4v ra[P], rb[P];
     auto gload = [&](int k0) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
+        for (int p = 0; p < P; ++p) {
             const int idx = tid + 256 * p, row = idx >> 3, kq = idx & 7;
             // (rows beyond the edge repeat the last one: their results are not stored)
             ra[p] = *reinterpret_cast<const float4v *>(a + (size_t)min(i0 + row, I - 1) * K + k0 + 4 * kq);
@@ -125,7 +138,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     const int mrow = lane & 31, kof = lane >> 5;
     for (int k0 = 0; k0 < K; k0 += MF_KT) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
+        for (int p = 0; p < P; ++p) {
             const int idx = tid + 256 * p, row = idx >> 3, kq = idx & 7;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -136,46 +149,68 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         __syncthreads();
         if (k0 + MF_KT < K) gload(k0 + MF_KT);
         // the operands of step ks + 1 are read from LDS before the MFMAs of step ks are issued
-        const float *ap = &As[wm * 32 + mrow][kof], *bp = &Bs[wn * 32 + mrow][kof];
-        float a0 = ap[0], b0 = bp[0];
+        const float *ap = &As[wm * W + mrow][kof], *bp = &Bs[wn * W + mrow][kof];
+        float fa[NX], fb[NX];
+#pragma unroll
+        for (int x = 0; x < NX; ++x) { fa[x] = ap[32 * x * MF_LD]; fb[x] = bp[32 * x * MF_LD]; }
 #pragma unroll
         for (int ks = 0; ks < MF_KT / 2; ++ks) {
-            float na0 = 0.f, nb0 = 0.f;
+            float na[NX] = {}, nf[NX] = {};
             if (ks + 1 < MF_KT / 2) {
-                na0 = ap[2 * ks + 2];
-                nb0 = bp[2 * ks + 2];
+#pragma unroll
+                for (int x = 0; x < NX; ++x) { na[x] = ap[32 * x * MF_LD + 2 * ks + 2]; nf[x] = bp[32 * x * MF_LD + 2 * ks + 2]; }
             }
             __builtin_amdgcn_sched_barrier(0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc, 0, 0, 0);
+#pragma unroll
+            for (int x = 0; x < NX; ++x)
+#pragma unroll
+                for (int y = 0; y < NX; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[x], fb[y], acc[x][y], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-            a0 = na0; b0 = nb0;
+#pragma unroll
+            for (int x = 0; x < NX; ++x) { fa[x] = na[x]; fb[x] = nf[x]; }
         }
         __syncthreads();
     }
-    // epilogue: f = exp2(c' (|a|^2 + |b|^2 + 2 a.b) + D').  Each wave stages its 32 x 32 results in its own
-    // quarter of the tile memory and writes them as 16-byte stores, 128 bytes per row.
+    // epilogue: f = exp2(c' (|a|^2 + |b|^2 + 2 a.b) + D').  Each wave stages 32 x W results at a time in its own
+    // quarter of the tile memory and writes them as 16-byte stores, whole rows of the wave's tile.
     // (the last barrier of the loop guarantees that nobody still reads the tiles)
+    constexpr int ROWS = 256 / W;                 // rows per store of the wavefront
     float *stage = smem + wave * (32 * LO);
-    {
-        const int j = j0 + wn * 32 + mrow;
-        const float nbj = j < J ? nb[j] : 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int mloc = acc_row(r, lane), m = wm * 32 + mloc;
-            const float s = rv[m][0] + nbj + 2.f * acc[r];
-            stage[mloc * LO + mrow] = __builtin_amdgcn_exp2f(fmaf(rv[m][1], s, rv[m][2]));
+    for (int x = 0; x < NX; ++x) {
+#pragma unroll
+        for (int y = 0; y < NX; ++y) {
+            const int j = j0 + wn * W + 32 * y + mrow;
+            const float nbj = j < J ? nb[j] : 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int mloc = acc_row(r, lane), m = wm * W + 32 * x + mloc;
+                const float s = rv[m][0] + nbj + 2.f * acc[x][y][r];
+                stage[mloc * LO + 32 * y + mrow] = __builtin_amdgcn_exp2f(fmaf(rv[m][1], s, rv[m][2]));
+            }
+        }
+        // the wave reads back only what it wrote itself: no barrier needed, LDS operations of a wave are ordered
+#pragma unroll
+        for (int it = 0; it < 32 / ROWS; ++it) {
+            const int rl = it * ROWS + lane / (W / 4), c = lane % (W / 4) * 4;
+            const int i = i0 + wm * W + 32 * x + rl, j = j0 + wn * W + c;
+            if (i < I && j < J) {   // J % 4 == 0: the four columns exist together
+                const float4v v = {stage[rl * LO + c], stage[rl * LO + c + 1], stage[rl * LO + c + 2], stage[rl * LO + c + 3]};
+                *reinterpret_cast<float4v *>(f + (size_t)i * J + j) = v;
+            }
         }
     }
-    // the wave reads back only what it wrote itself: no barrier needed, LDS operations of a wave are ordered
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int rl = it * 8 + (lane >> 3), c = (lane & 7) * 4;
-        const int i = i0 + wm * 32 + rl, j = j0 + wn * 32 + c;
-        if (i < I && j < J) {   // J % 4 == 0: the four columns exist together
-            const float4v v = {stage[rl * LO + c], stage[rl * LO + c + 1], stage[rl * LO + c + 2], stage[rl * LO + c + 3]};
-            *reinterpret_cast<float4v *>(f + (size_t)i * J + j) = v;
-        }
-    }
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_mfma_forward(const float *__restrict__ a, const float *__restrict__ b,
+                                                      const float *__restrict__ rowv, const float *__restrict__ nb,
+                                                      float *__restrict__ f, int I, int J, int K) {
+    mfma_forward_tile<1>(a, b, rowv, nb, f, I, J, K);
+}
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mfma_forward_large(const float *__restrict__ a, const float *__restrict__ b,
+                                                      const float *__restrict__ rowv, const float *__restrict__ nb,
+                                                      float *__restrict__ f, int I, int J, int K) {
+    mfma_forward_tile<2>(a, b, rowv, nb, f, I, J, K);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -532,8 +567,13 @@ int mfma_forward(const tad_plan &pl, const void *const *args, void *f, void *ws,
                    (const float *)args[0], (const float *)args[1], w.rowv, (float *)f, I, J, K);
         return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
     }
-    TAD_LAUNCH("k_mfma_forward", k_mfma_forward, dim3((J + 63) / 64, (I + 63) / 64), dim3(256), 0, s,
-               (const float *)args[0], (const float *)args[1], w.rowv, w.nb, (float *)f, I, J, K);
+    // (c has at least I x I elements, fewer than 2^31 in all: the tiles along i fit the second axis of a grid)
+    if (large_forward_tiles(I, J, K))
+        TAD_LAUNCH("k_mfma_forward", k_mfma_forward_large, dim3((J + 127) / 128, (I + 127) / 128), dim3(256), 0, s,
+                   (const float *)args[0], (const float *)args[1], w.rowv, w.nb, (float *)f, I, J, K);
+    else
+        TAD_LAUNCH("k_mfma_forward", k_mfma_forward, dim3((J + 63) / 64, (I + 63) / 64), dim3(256), 0, s,
+                   (const float *)args[0], (const float *)args[1], w.rowv, w.nb, (float *)f, I, J, K);
     return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
