@@ -433,12 +433,14 @@ static int backward_t(const tad_plan &pl, const ProductSet &set, const void *con
         }
     }
     // the gradient of a bias along the trailing indices, the column sums of g, beside the first product: in a launch of its own it takes as long
-    // as launches do (512 x 1024 x 768 6.7 us of 68).  Its 32 threads per column are not to outlast the product: up to 4096 rows.
+    // as launches do (512 x 1024 x 768 6.7 us of 68).  Its 32 threads per column are not to outlast the product.  Gradients of M x N x K, beside / in a launch
+    // of its own: 1000 x 16 x 16 16.4 / 25.0 us, 4000 x 16 x 16 21.6 / 26.7, 6000 x 16 x 16 25.6 / 27.8, x 512 x 512 167 / 176; 8000 x 16 x 16 28.4 / 27.7, x 512 x 512 194 / 194,
+    // 16000 x 64 x 64 52 / 39.
     ProductColumns columns{};
     bool summed[kMaxArgs] = {};
     for (int q = 0; n_jobs && !columns.out && q < n_ops; ++q) {
         if (!dx[q] || !((sp.prog.outer_mask >> q) & 1u) || !sp.term_is_g[q] || stored[q] || !sp.outer_linear) continue;
-        if (sp.outer_r[q] != 0 || sp.outer_c[q] != 1 || pl.arg_count[q] != sp.N || sp.M > 4096 || inner_reads(sp, q)) continue;
+        if (sp.outer_r[q] != 0 || sp.outer_c[q] != 1 || pl.arg_count[q] != sp.N || sp.M > 6144 || inner_reads(sp, q)) continue;
         columns = {g, dx[q], (int)sp.M, (int)sp.N, f64};
         summed[q] = true;
     }

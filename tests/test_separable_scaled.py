@@ -86,7 +86,7 @@ def test_scaled_gradients(make, I, J, K):
 
 @pytest.mark.gpu
 # fewer rows than threads to a column, one batch and more than one, either side of the line; columns that do not fill a workgroup's
-@pytest.mark.parametrize("I,J,K", [(17, 16, 9), (31, 33, 20), (256, 17, 16), (257, 250, 40), (4096, 18, 16), (4097, 18, 16)])
+@pytest.mark.parametrize("I,J,K", [(17, 16, 9), (31, 33, 20), (256, 17, 16), (257, 250, 40), (4096, 18, 16), (4097, 18, 16), (6144, 18, 16), (6145, 18, 16)])
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 def test_bias_gradients_beside_the_products(I, J, K, dtype):
     import torch
