@@ -241,38 +241,25 @@ __global__ __launch_bounds__(512, 4) void k_mfma_backward(const float *__restric
     for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[x][r] = 0.f;
-    float4v ga[1], gb[4];
+    float4v ga, gb[4];
     // what the loads of G bring in; the products and the sums on the side are formed one tile later, when the
     // tile is staged, so that nothing waits for these loads before the matrix instructions of the current tile
-    float4v rdf[1], rf[1], rnv[1];
-    float rc[1];
+    float4v rdf, rf, rnv;
+    float rc;
     const float4v zero4 = {0.f, 0.f, 0.f, 0.f};
-    float sr[1] = {0.f}, sq[1] = {0.f};   // TRANS_A = false: row sums of the thread's row
-    float4v st = zero4;                               // TRANS_A = true: column sums of the thread's four columns
+    float sr = 0.f, sq = 0.f;   // TRANS_A = false: row sums of the thread's row
+    float4v st = zero4;         // TRANS_A = true: column sums of the thread's four columns
+    // the four elements of G of the thread: i = m0 + g_row, j = c0 + 4 g_quad, or (TRANS_A) i = c0 + g_row, j = m0 + 4 g_quad
+    const int g_row = TRANS_A ? tid >> 4 : tid >> 3, g_quad = TRANS_A ? tid & 15 : tid & 7;
     auto gload = [&](int c0) {
-#pragma unroll
-        for (int p = 0; p < 1; ++p) {
-            const int idx = tid + 512 * p;
-            rdf[p] = zero4; rf[p] = zero4; rnv[p] = zero4; rc[p] = 0.f;
-            if (!TRANS_A) {
-                const int row = idx >> 3, q = idx & 7;            // i = m0 + row, j = c0 + 4 q
-                const int i = m0 + row, j = c0 + 4 * q;
-                if (i < I && j < ce) {
-                    const size_t off = (size_t)i * J + j;
-                    rdf[p] = *reinterpret_cast<const float4v *>(df + off);
-                    rf[p] = *reinterpret_cast<const float4v *>(f + off);
-                    rnv[p] = *reinterpret_cast<const float4v *>(nb + j);
-                }
-            } else {
-                const int kk = idx >> 4, q = idx & 15;            // i = c0 + kk, j = m0 + 4 q
-                const int i = c0 + kk, j = m0 + 4 * q;
-                if (i < ce && j < J) {
-                    const size_t off = (size_t)i * J + j;
-                    rdf[p] = *reinterpret_cast<const float4v *>(df + off);
-                    rf[p] = *reinterpret_cast<const float4v *>(f + off);
-                    rc[p] = rowv[i * 4 + 3];
-                }
-            }
+        rdf = zero4; rf = zero4; rnv = zero4; rc = 0.f;
+        const int i = (TRANS_A ? c0 : m0) + g_row, j = (TRANS_A ? m0 : c0) + 4 * g_quad;
+        if (i < (TRANS_A ? ce : I) && j < (TRANS_A ? J : ce)) {
+            const size_t off = (size_t)i * J + j;
+            rdf = *reinterpret_cast<const float4v *>(df + off);
+            rf = *reinterpret_cast<const float4v *>(f + off);
+            if (TRANS_A) rc = rowv[i * 4 + 3];
+            else rnv = *reinterpret_cast<const float4v *>(nb + j);
         }
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -282,33 +269,24 @@ __global__ __launch_bounds__(512, 4) void k_mfma_backward(const float *__restric
         }
     };
     auto gprep = [&]() {   // G of the loaded tile and its plain sums (zeros where nothing was loaded)
-#pragma unroll
-        for (int p = 0; p < 1; ++p) {
-            if (!TRANS_A) {
-                ga[p] = rdf[p] * rf[p];
-                sr[p] += (ga[p][0] + ga[p][1]) + (ga[p][2] + ga[p][3]);
-                sq[p] += (ga[p][0] * rnv[p][0] + ga[p][1] * rnv[p][1]) + (ga[p][2] * rnv[p][2] + ga[p][3] * rnv[p][3]);
-            } else {
-                ga[p] = rdf[p] * rf[p] * rc[p];
-                st += ga[p];
-            }
+        if (!TRANS_A) {
+            ga = rdf * rf;
+            sr += (ga[0] + ga[1]) + (ga[2] + ga[3]);
+            sq += (ga[0] * rnv[0] + ga[1] * rnv[1]) + (ga[2] * rnv[2] + ga[3] * rnv[3]);
+        } else {
+            ga = rdf * rf * rc;
+            st += ga;
         }
     };
     gload(cs);
     const int mrow = lane & 31, kof = lane >> 5;
     for (int c0 = cs; c0 < ce; c0 += MF_KT) {
         gprep();
+        if (!TRANS_A) {
 #pragma unroll
-        for (int p = 0; p < 1; ++p) {
-            const int idx = tid + 512 * p;
-            if (!TRANS_A) {
-                const int row = idx >> 3, q = idx & 7;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) As[row][4 * q + e] = ga[p][e];
-            } else {
-                const int kk = idx >> 4, q = idx & 15;
-                *reinterpret_cast<float4v *>(&As[kk][4 * q]) = ga[p];
-            }
+            for (int e = 0; e < 4; ++e) As[g_row][4 * g_quad + e] = ga[e];
+        } else {
+            *reinterpret_cast<float4v *>(&As[g_row][4 * g_quad]) = ga;
         }
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -349,17 +327,14 @@ __global__ __launch_bounds__(512, 4) void k_mfma_backward(const float *__restric
     if (!TRANS_A) {
         // eight consecutive lanes share a row: add them in a fixed order
 #pragma unroll
-        for (int p = 0; p < 1; ++p) {
-#pragma unroll
-            for (int m = 1; m <= 4; m <<= 1) {
-                sr[p] += __shfl_xor(sr[p], m, 64);
-                sq[p] += __shfl_xor(sq[p], m, 64);
-            }
-            const int i = m0 + (tid >> 3);
-            if ((tid & 7) == 0 && i < I) {
-                sums[((size_t)split * 2 + 0) * I + i] = sr[p];
-                sums[((size_t)split * 2 + 1) * I + i] = sq[p];
-            }
+        for (int m = 1; m <= 4; m <<= 1) {
+            sr += __shfl_xor(sr, m, 64);
+            sq += __shfl_xor(sq, m, 64);
+        }
+        const int i = m0 + g_row;
+        if (g_quad == 0 && i < I) {
+            sums[((size_t)split * 2 + 0) * I + i] = sr;
+            sums[((size_t)split * 2 + 1) * I + i] = sq;
         }
     } else {
         // lanes q, q+16, q+32, q+48 of every wave hold the same four columns: add within the wave, then the waves
