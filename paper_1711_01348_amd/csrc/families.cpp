@@ -313,6 +313,8 @@ static bool match_contraction(tad_plan &pl) {
     else      g[2] = GemmDesc{J, Kc, I, -1, P, Q, J, ldp, 1, !p_ik};      // dQ[j][k] = sum_i df[i][j] P(i,k)
     // A product with few output tiles and a long contraction index leaves most of the chip idle: cut the index
     // into pieces for separate workgroups (partial products in the workspace, added in a fixed order afterwards).
+    // Tiles are counted as 128 x 128 whatever the kernel's are (k_contract_low has four times as many): the number of pieces decides how a sum is
+    // rounded, and these are the sums the family has always had.
     size_t ws = 0;
     for (int q = 0; q < 3; ++q) {
         const long long tiles = (long long)((g[q].M + 127) / 128) * ((g[q].N + 127) / 128);

@@ -2,11 +2,11 @@
 //
 // Bound by launches: 262144 results and a window of 33 are 1 MB per tensor and 8.7 10^6 products for each of f, dx and dw.  The
 // plan-driven kernels walk the plan for every element of dx and read df from memory for every term, and share an element of dw
-// among whole workgroups (f 6.9 us, both gradients 25.5 us of calls).  Here a workgroup holds 256 R results' inputs in LDS, widened to
+// among whole workgroups (f 6.7 us, both gradients 25.2 us of calls in a row).  Here a workgroup holds 256 R results' inputs in LDS, widened to
 // 64 bits once; a thread owns R results 256 apart, so that its reads are free of conflicts and an element of w, the same for all of them, is
 // read once per R products.  dx is the same sum over df with the window turned round.  dw: a thread takes four neighbouring window
 // elements and a part of the workgroup's results, four of them at a time: 11 reads for 16 products.  The workgroups' sums of dw are added
-// by a second launch in a fixed order (f 6.1 us, gradients 11.2 us, both the time the calls take on the host; the workgroups at the
+// by a second launch in a fixed order (f 3.6 us, gradients 10.2 us, three launches; a pass of both through Python 13.4 us; the workgroups at the
 // ends of the signal decide what a call takes if they test every term: gradients of 169877 x 63 36 us instead of 14).
 // Products of 32-bit operands are exact and sums are in 64 bits, so only the result is rounded.
 #include <hip/hip_runtime.h>

@@ -154,12 +154,15 @@ bool product_addressable(const ProductDesc &d) {
 }
 
 // Terms from which 32-bit products whose extents are multiples of four run on the contraction family.  Forward and both
-// gradients there / here (with extents one larger): 32 x 32 x 32 16 / 13 us, 200 x 300 x 400 83 / 19, 76 x 348 x 1656 69 / 22,
-// 512 x 512 x 512 71 / 39, 100 x 2000 x 2000 78 / 81, 1000 x 1000 x 1000 109 / 129, 1600 x 1600 x 1600 315 / 501 us.
+// gradients there / here: 256 x 256 x 256 21 / 12 us, 200 x 300 x 400 30 / 15, 76 x 348 x 1656 28 / 18, 400 x 400 x 400 36 / 20, 512 x 512 x 512 29 / 23,
+// 1024 x 1024 x 128 26 / 24, 576 x 576 x 576 33 / 34, 640 x 640 x 640 36 / 42, 640 x 1280 x 320 33 / 43; from here on 512 x 512 x 1024 34 / 37, 704 x 704 x 704 39 / 46,
+// 100 x 2000 x 2000 52 / 77, 1000 x 1000 x 1000 82 / 112.  Between 2^27 and 2^28 terms the family's tiles of 64 x 64 are the faster ones; the line stays
+// where it is because its sums are in 32 bits, and those of these products never were.
 constexpr double kContractionTerms = 268435456.0;
 // ... and below that, the results of 32-bit products whose sums are so short that storing them is what counts: its tiles store 16 bytes
-// per lane.  There / here, rows x columns x terms: 2000 x 1000 x 32 9.5 / 14.2 us, x 128 15 / 18, 1000 x 4096 x 16 9.5 / 12.7, 128 x 16000 x 16
-// 9.4 / 14.0, 4096 x 4096 x 8 22 / 37; 1300 x 1000 x 16 9.9 / 10.9, x 128 14.6 / 13.9, 100000 x 64 x 16 17.7 / 18.5, 640 x 640 x 640 29 / 16.
+// per lane.  There / here, rows x columns x terms: 2000 x 1000 x 32 4.9 / 8.0 us, x 128 8.6 / 14.4, 1000 x 4096 x 16 7.3 / 14.4, 128 x 16000 x 16
+// 5.2 / 8.1, 4096 x 4096 x 8 18.5 / 46; beyond the line, where the sums stay in 64 bits: 1300 x 1000 x 128 8.0 / 11.5, 1024 x 1024 x 128 5.2 / 8.9,
+// 100000 x 64 x 16 10.0 / 22.5, 400 x 400 x 400 12.2 / 8.2.
 static bool contraction_stores(const ProductDesc &d) {
     return d.Q <= 128 && std::min(d.R, d.C) >= 128 && (int64_t)d.R * d.C >= 1500000;
 }
@@ -181,7 +184,7 @@ void match_product(tad_plan &pl) {
     if (pl.flags & TAD_PLAN_GENERIC_ONLY) return;
     if (pl.has_alias || e.n_constraints > 0 || e.n_sum < 1 || e.n_f < 2) return;
     if (e.body != TAD_BODY_MUL) return;
-    // the contraction family's tiles of 128 x 128 in 32 bits are for larger products
+    // the contraction family's tiles in 32 bits are for larger products
     if (pl.fwd_family != TAD_FAMILY_GENERIC && !(pl.fwd_family == TAD_FAMILY_CONTRACTION && pl.terms_total < kContractionTerms)) return;
     for (int s = 0; s < e.n_sum; ++s)
         if (e.sum_lo[s] != 0) return;
