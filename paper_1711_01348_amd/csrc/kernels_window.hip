@@ -6,8 +6,11 @@
 // 64 bits once; a thread owns R results 256 apart, so that its reads are free of conflicts and an element of w, the same for all of them, is
 // read once per R products.  dx is the same sum over df with the window turned round.  dw: a thread takes four neighbouring window
 // elements and a part of the workgroup's results, four of them at a time: 11 reads for 16 products.  The workgroups' sums of dw are added
-// by a second launch in a fixed order (f 3.6 us, gradients 10.2 us, three launches; a pass of both through Python 13.4 us; the workgroups at the
-// ends of the signal decide what a call takes if they test every term: gradients of 169877 x 63 36 us instead of 14).
+// by a second launch in a fixed order.  262144 x 33: f 3.6 us, gradients 10.2, three launches; a pass of both through Python 13.3 us.  The workgroups at the
+// ends of the signal decide what a call takes if they test every term (gradients of 169877 x 63 36 us instead of 14), and where the signal is short they are
+// all there is: groups of 16 terms are taken or left as a whole where they can be (dw alone of 1100 x 256 21 -> 10 us, the plan-driven kernels 7;
+// 20000 x 256 16 -> 8.1).  Many parts of dw are added in two steps: one thread per window element would add up to 256 in a row (4000000 x 1,
+// both gradients 31.7 -> 25.7 us, dw alone 28 -> 21, the plan-driven kernels 117 and 12).
 // Products of 32-bit operands are exact and sums are in 64 bits, so only the result is rounded.
 #include <hip/hip_runtime.h>
 
@@ -100,25 +103,28 @@ __global__ __launch_bounds__(256) void k_window_forward(const WindowArgs A) {
 }
 
 // dx of the workgroup's elements of x and its part of dw, the sum over its results i
-template <typename T, int R>
+// DX = false: dw alone, without the elements of df that only dx reads
+template <typename T, int R, bool DX>
 __global__ __launch_bounds__(256) void k_window_backward(const WindowArgs A) {
     constexpr int C = 256 * R;
     constexpr int X = C + (int)kWindowSum + 2 * kWindowPad;
-    __shared__ double d[C + kWindowSum], x[X > 1024 ? X : 1024], w[kWindowSum];
+    constexpr int HALO = DX ? (int)kWindowSum : 0;
+    __shared__ double d[C + HALO], x[X > 1024 ? X : 1024], w[DX ? kWindowSum : 1];
     const int n0 = blockIdx.x * C, K = A.K, q = A.q, tid = threadIdx.x;
-    const int ahead = q > 0 ? K - 1 : 0;                     // elements of d in front of n0
+    const int ahead = DX && q > 0 ? K - 1 : 0;               // elements of d in front of n0
     const bool part = A.part && n0 < A.N;                    // the same for the whole workgroup
     const int x0 = n0 - (q > 0 ? 0 : K - 1);                 // element of x at x[kWindowPad]
     WindowSlice<T, 0> wv;
-    WindowSlice<T, R> dv, xv;
-    wv.load(static_cast<const T *>(A.w), 0, 0, K - 1);
+    WindowSlice<T, DX ? R : R - 2> dv;
+    WindowSlice<T, R> xv;
+    if constexpr (DX) wv.load(static_cast<const T *>(A.w), 0, 0, K - 1);
     dv.load(static_cast<const T *>(A.df), n0 - ahead, 0, A.N - 1);
     xv.load(static_cast<const T *>(A.x), x0 - kWindowPad, A.first, A.last);
-    wv.store(0, K, 0, K - 1, w);
-    dv.store(n0 - ahead, C + K - 1, 0, A.N - 1, d);
+    if constexpr (DX) wv.store(0, K, 0, K - 1, w);
+    dv.store(n0 - ahead, DX ? C + K - 1 : C, 0, A.N - 1, d);
     xv.store(x0 - kWindowPad, C + K - 1 + 2 * kWindowPad, A.first, A.last, x);
     __syncthreads();
-    if (A.dx) window_sums<T, R>(d, w, K, -q, n0, 0, A.N - 1, A.first, A.last, A.n_x, static_cast<T *>(A.dx));
+    if constexpr (DX) window_sums<T, R>(d, w, K, -q, n0, 0, A.N - 1, A.first, A.last, A.n_x, static_cast<T *>(A.dx));
     if (!part) return;
     const int groups = (K + 3) / 4, parts = 256 / groups;
     const int g = tid % groups, mine = tid / groups;
@@ -140,18 +146,27 @@ __global__ __launch_bounds__(256) void k_window_backward(const WindowArgs A) {
             }
         } else {
             for (int i = begin; i < end; i += 4) {
-                double dv[4], xv[7];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) dv[u] = dp[i + u];
-#pragma unroll
-                for (int u = 0; u < 7; ++u) xv[u] = xp[i + u];
                 const int m0 = n0 + i + (q > 0 ? 4 * g : -4 * g - 3);   // element of x at xv[0]
+                if (m0 + 6 < A.first || m0 > A.last || n0 + i >= A.N) continue;   // none of the 16 terms exists
+                double dv[4], xv[7];
+                bool in_d[4], in_x[7];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) { dv[u] = dp[i + u]; in_d[u] = n0 + i + u < A.N; }
+#pragma unroll
+                for (int u = 0; u < 7; ++u) { xv[u] = xp[i + u]; in_x[u] = m0 + u >= A.first && m0 + u <= A.last; }
+                if (__all(m0 >= A.first && m0 + 6 <= A.last && n0 + i + 3 < A.N)) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int a = 0; a < 4; ++a) acc[a] += dv[u] * xv[u + a];
+                    continue;
+                }
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
 #pragma unroll
                     for (int a = 0; a < 4; ++a) {
                         const double next = acc[a] + dv[u] * xv[u + a];
-                        acc[a] = n0 + i + u < A.N && m0 + u + a >= A.first && m0 + u + a <= A.last ? next : acc[a];
+                        acc[a] = in_d[u] && in_x[u + a] ? next : acc[a];
                     }
             }
         }
@@ -162,10 +177,26 @@ __global__ __launch_bounds__(256) void k_window_backward(const WindowArgs A) {
     for (int a = 0; a < 4; ++a)
         if (mine < parts) red[mine * 4 * groups + (q > 0 ? 4 * g + a : 4 * g + 3 - a)] = acc[a];
     __syncthreads();
+    const int cols = 4 * groups;
+    const double *sums = red;
+    int rows = parts;
+    if (parts > 64) {                                        // in two steps; the same for the whole workgroup
+        const int chunks = 256 / cols, each = (parts + chunks - 1) / chunks, c = tid % cols, chunk = tid / cols;
+        if (chunk < chunks) {
+            double s = 0.0;
+            const int to = min(parts, (chunk + 1) * each);
+#pragma unroll 4
+            for (int p = chunk * each; p < to; ++p) s += red[p * cols + c];
+            d[tid] = s;                                      // (nobody reads d any more)
+        }
+        __syncthreads();
+        sums = d;
+        rows = chunks;
+    }
     if (tid < K) {
         double s = 0.0;
 #pragma unroll 8
-        for (int p = 0; p < parts; ++p) s += red[p * 4 * groups + tid];
+        for (int p = 0; p < rows; ++p) s += sums[p * cols + tid];
         A.part[(size_t)tid * ((A.N + C - 1) / C) + blockIdx.x] = s;
     }
 }
@@ -215,7 +246,10 @@ static int backward_t(const WindowPlan &p, const void *const *args, const void *
     A.dx = dx[p.x];
     A.part = dx[p.w] ? static_cast<double *>(ws) : nullptr;
     const int C = 256 * R, blocks = (p.N + C - 1) / C, of_x = A.dx ? (p.n_x + C - 1) / C : 0;
-    TAD_LAUNCH("k_window_backward", (k_window_backward<T, R>), dim3(blocks > of_x ? blocks : of_x), dim3(256), 0, s, A);
+    if (!A.dx && !A.part) return TAD_OK;
+    const dim3 grid(blocks > of_x ? blocks : of_x), block(256);
+    if (A.dx) TAD_LAUNCH("k_window_backward", (k_window_backward<T, R, true>), grid, block, 0, s, A);
+    else TAD_LAUNCH("k_window_backward", (k_window_backward<T, R, false>), grid, block, 0, s, A);
     if (launched()) return TAD_EDEVICE;
     if (!A.part) return TAD_OK;
     TAD_LAUNCH("k_window_finish", (k_window_finish<T>), dim3((p.n_w + 3) / 4), dim3(256), 0, s, (const double *)A.part, blocks, p.K, p.n_w, static_cast<T *>(dx[p.w]));
