@@ -38,7 +38,7 @@ MIN_WINDOW_MS = 20.0            # the workloads beside the headline are timed fo
 MEASURED_TRAFFIC = {
     "cfg3": dict(source="kernels_worked.hip", sha256="c4542a3a73030316", fetch_bytes=521.5 * 2**20, write_bytes=9.5 * 2**20,
             summary="profiles/worked_8192x8192x5_f32.md"),
-    "cfg4": dict(source="kernels_mfma.hip", sha256="0d65477ef9a82f55", fetch_bytes=160.5 * 2**20, write_bytes=32.2 * 2**20,
+    "cfg4": dict(source="kernels_mfma.hip", sha256="0752fdee68d78bc8", fetch_bytes=160.5 * 2**20, write_bytes=32.2 * 2**20,
             summary="profiles/worked_mfma_4096x4096x256_f32.md"),
     "matmul": dict(source="kernels_split.hip", sha256="3979d7bbcfdbd32a", fetch_bytes=1001.8 * 2**20, write_bytes=64.0 * 2**20,
             summary="profiles/contraction_4096x4096x4096_f32.md"),
@@ -48,7 +48,7 @@ MEASURED_TRAFFIC = {
             summary="profiles/diagonal_8192_f32.md"),
     "cfg2_3": dict(source="kernels_patterns.hip", sha256="82a47a45178e317d", fetch_bytes=64.1 * 2**20, write_bytes=0.5 * 2**20,
             summary="profiles/antidiagonal_4096x4096_f32.md"),
-    "cfg5": dict(source="kernels_strided.hip", sha256="2467bb762145781f", fetch_bytes=13.7 * 2**20, write_bytes=8.1 * 2**20,
+    "cfg5": dict(source="kernels_strided.hip", sha256="b3bd407bbcbd2858", fetch_bytes=17.0 * 2**20, write_bytes=8.1 * 2**20,
             summary="profiles/strided_32x128x128_f32.md"),
 }
 

@@ -13,8 +13,8 @@
 // bytes without conflicts); there are two sets of tiles, so that a stage takes one barrier.
 // Instructions that are issued beside a matrix instruction cost nothing, in a row of their own they hold it back: every read, store and
 // load has its place between two matrix instructions, and the fragments are read one chunk ahead.  1000 x 1203 x 777 in 64 bits, forward:
-// 32 x 32 tiles 72 us, these tiles 55, fragments read ahead 47, everything in its place 42 (44 TFLOP/s; 247 of 256 compute units,
-// each of them 64000 cycles of matrix instructions in 97000); both gradients 104 -> 90; 512 x 1024 x 768 in 32 bits 24 -> 20,
+// 32 x 32 tiles 72 us, these tiles 55, fragments read ahead 47, everything in its place 41 (46 TFLOP/s; 247 of 256 compute units;
+// the matrix cores are busy for 61750 cycles, 63 % of that); both gradients 104 -> 90; 512 x 1024 x 768 in 32 bits 24 -> 20,
 // gradients 43 -> 36; 2000 x 2000 x 2000 311 -> 287.
 // Everything that depends on the tile's place is settled before the loop: a row beyond the edge repeats the last row (its
 // results are not stored), so that the loads are unconditional, from a uniform base plus a constant 32-bit offset per thread,
