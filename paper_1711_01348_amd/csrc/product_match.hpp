@@ -9,33 +9,49 @@
 
 namespace tad {
 
-// Time of a product in cycles of 2.2 GHz: tiles go to the 256 compute units in turn, whose matrix cores take 16 `rows` cycles per
-// value of q; a tile takes some time to begin and to end, which another one on the same unit covers (where there is none, storing a tall one takes
-// the longer: 3163 x 2693 x 98 in 32 bits, rows = 7 62 us, 4 with two tiles a unit 55).  kReduceCycles: the launch that adds pieces up.
-// Fitted to the forward passes of 197 products, half of them of 64-bit operands, 17 .. 6957 x 16 .. 5000 x 20 .. 5400, each with every height, both
-// orientations and several numbers of pieces: what is picked takes 0.8 % longer than the fastest in the mean, 14 % at most (1381 x 190 x 884 in 64 bits 22.4 /
-// 19.6 us); both gradients of 75 products in one launch of every height, or in two: 1.3 % in the mean, 24 % at most (2067 x 284 x 597 44.4 / 35.8).  Heights that
-// earn their place: 5 1000 x 1203 x 777 in 64 bits 41 us instead of 53; 7 1433 x 1190 x 306 24.6 / 26.7, 1665 x 1019 x 147 15.8 / 16.7; 6 where a program
-// follows, 3000 x 1500 x 64 44 / 48, 4710 x 315 x 76 17.9 / 21.8 (8 was the fastest nowhere).
-constexpr double kTileCycles = 7000, kAloneCycles = 300, kReduceCycles = 4000, kLaunchCycles = 7000;
-// A program that is applied to the results: per pass over a thread's results of every tile on a unit; and for sums in pieces its launch of its own.
-// Dense layers with tanh, 27 sizes: 0.5 % and 7 % from the fastest; without these costs 160 x 4296 x 83 13.3 us instead of 12.4, 1500 x 1024 x 200 28.6
-// instead of 24.1.
-constexpr double kOuterCycles = 3000, kOuterLaunch = 5000;
+// Time of a product in cycles of 2.2 GHz.  Tiles go to the 256 compute units in turn, and a unit works on as many at once as registers and LDS leave room
+// for; the next one starts when one of them is done.  A tile begins and ends (kEnds, longer where others do at the same time), and between them takes
+// stages of kProductStage values of q: the matrix instructions, 512 `rows` cycles, and what is not hidden behind them where it has the unit to itself
+// (`alone`), its share of the matrix cores where it has not (`shared`, longer for low tiles: more fragments to read per instruction).
+// Fitted to 197 forward passes, 17 .. 6957 x 16 .. 5000 x 20 .. 5400 with every height, both orientations and several numbers of pieces, and to both
+// gradients of 225 products in two launches and in one of every height: 4 % from the measured times in the mean.  What is picked takes 0.6 % longer than
+// the fastest in the mean and 11 % at most (forward), 0.7 % and 17 % (gradients; 385 x 902 x 1580 56.1 / 48.0 us); with a cost per tile and one per stage,
+// the same for all heights, and no account of the units' order 0.8 % and 14 %, 2.1 % and 36 % (1107 x 74 x 1411 26.4 / 20.0).  Heights that earn their
+// place: 5 1000 x 1203 x 777 in 64 bits 41 us instead of 53; 7 1433 x 1190 x 306 24.6 / 26.7, 1665 x 1019 x 147 15.8 / 16.7; 6 where a program follows,
+// 3000 x 1500 x 64 44 / 48, 4710 x 315 x 76 17.9 / 21.8 (8 was the fastest nowhere).
+constexpr int kUnits = 256;
+constexpr double kBegin = 3100, kEnds = 3150, kEndsRow = 1000, kEndsMore = 0.36;
+// The launch that adds pieces up, and a second launch for the other gradient; launches one after the other take at least 3.9 us each, 5 where the host is slow.
+constexpr double kReduceCycles = 4100, kReduceBytes = 2050, kLaunchCycles = 800, kLeastCycles = 10000;
+// A program that is applied to the results: where they are stored, in passes over a thread's results of every tile on a unit, which hide little of each other
+// (but low tiles: one pass, three on a unit); and for sums in pieces in the launch that adds them up.  Dense layers with tanh, 40 sizes with every height
+// and up to 13 pieces: 5 % from the measured times, what is picked takes 1.4 % longer than the fastest in the mean and 8 % at most; 2032 x 481 x 20 with
+// tiles of 32 rows, two rounds of them, 12.9 us, of 64 rows 10.4.
+constexpr double kOuterLaunch = 9000;
+static double outer_cycles(const ProductDesc &d, int rows, int64_t each) {
+    const int passes = (2 * rows + d.outer - 1) / d.outer;
+    if (d.outer <= 2) return (1500 + 5400.0 * passes) * (1.2 * (double)each - 0.2);
+    return rows == 1 && passes == 1 ? 4200 + 2000.0 * (double)each : (2000 + 4400.0 * passes) * (1.25 * (double)each - 0.25);
+}
 // Results that could be scaled where they are stored, of a sum in pieces: a launch over them (softplus 538 x 473 x 29, the gradient of one operand 25.0 us
 // whole, 29.2 in pieces).
 constexpr double kScaleLaunch = 10000;
-// Cycles of a stage for the matrix cores of a compute unit, per tile, and of the barrier, LDS and the loads behind a stage, which take as long where the
-// tiles of a unit leave the matrix cores idle (512 x 43 x 1832: one round of 58 stages 24 us).
-static double tile_cycles(int rows) { return (rows == 1 ? 20.0 : rows == 2 ? 18.0 : 17.0) * kProductStage * rows; }   // (low tiles: more fragments per instruction)
-constexpr double kStageCycles = 800;
 static int64_t stages_of(int64_t q) { return (q + kProductStage - 1) / kProductStage; }
-// Cycles of `each` tiles that a compute unit works on at once.
-static double sum_cycles(int rows, int64_t q, int64_t each) { return (double)stages_of(q) * std::max(kStageCycles, tile_cycles(rows) * (double)each); }
-// tiles that share a compute unit: what registers and LDS leave room for
-static int tiles_per_unit(const ProductDesc &d, int rows) {
-    if (d.a64 && d.b64) return rows == 1 ? 2 : 1;
-    return rows == 1 ? 3 : rows <= (d.a64 || d.b64 ? 3 : 4) ? 2 : 1;
+struct TileRate {
+    int at_once;
+    double alone, shared, ends;
+    double stage(int n) const { return std::max(alone, n * shared); }   // of each of n tiles
+    double begin_end(int n) const { return ends * (1 + kEndsMore * (n - 1)); }
+    double round(int n, int64_t stages) const { return begin_end(n) + (double)stages * stage(n); }
+};
+static TileRate tile_rate(const ProductDesc &d, int rows) {
+    const bool wide = d.a64 && d.b64;
+    TileRate r;
+    r.at_once = wide ? (rows == 1 ? 2 : 1) : rows == 1 ? 3 : rows <= (d.a64 || d.b64 ? 3 : 4) ? 2 : 1;
+    r.alone = 512.0 * rows + (wide ? 457 : 275);
+    r.shared = rows == 1 ? (wide ? 865 : 675) : rows == 2 ? 1115 : 497.0 * rows;
+    r.ends = kEnds + kEndsRow * rows;
+    return r;
 }
 static int64_t tile_count(const ProductDesc &d, int rows, bool flip) {
     const int64_t R = flip ? d.C : d.R, C = flip ? d.R : d.C;
@@ -44,14 +60,15 @@ static int64_t tile_count(const ProductDesc &d, int rows, bool flip) {
 // sums of 64-bit operands take three sets of registers: a tile of six does not fit
 static int rows_limit(const ProductDesc &d) { return d.a64 && d.b64 ? 5 : 7; }
 static double product_cycles(const ProductDesc &d, int rows, bool flip, int pieces, int chunk) {
-    const int64_t each = (tile_count(d, rows, flip) * pieces + 255) / 256, at_once = tiles_per_unit(d, rows);
-    const int64_t rounds = (each + at_once - 1) / at_once;
-    double t = (double)rounds * kTileCycles + (double)(rounds - 1) * sum_cycles(rows, chunk, at_once) +
-               sum_cycles(rows, chunk, each - (rounds - 1) * at_once);
-    if (at_once == 1) t += kAloneCycles * rows * (double)(rounds - 1);
+    const TileRate r = tile_rate(d, rows);
+    const int64_t each = (tile_count(d, rows, flip) * pieces + kUnits - 1) / kUnits, rounds = (each + r.at_once - 1) / r.at_once;
+    const int64_t stages = stages_of(chunk);
+    double t = kBegin + (double)(rounds - 1) * r.round(r.at_once, stages) + r.round((int)(each - (rounds - 1) * r.at_once), stages);
     if (d.scaled && pieces > 1) t += kScaleLaunch;
-    if (d.outer) t += pieces > 1 ? kOuterLaunch : kOuterCycles * (double)((2 * rows + d.outer - 1) / d.outer * each);
-    return pieces == 1 ? t : t + kReduceCycles + (double)pieces * d.R * d.C * 16.0 / 2000.0;   // written and read
+    if (d.outer) t += pieces > 1 ? kOuterLaunch : outer_cycles(d, rows, each);
+    if (pieces == 1) return t;
+    t += kReduceCycles + (double)pieces * d.R * d.C * 16.0 / kReduceBytes;   // written and read
+    return std::max(t, kLeastCycles * (2 + (d.scaled || d.outer)));
 }
 
 void product_shape(ProductDesc &d, size_t most_bytes) {
@@ -86,27 +103,87 @@ ProductDesc product_turned(const ProductDesc &d) {
     return t;
 }
 
-// n0 tiles of s0 stages, then n1 of s1 <= s0, on 256 compute units that take at_once tiles and the next one when one of them is done
-static double pair_cycles(int64_t n0, int64_t s0, int64_t n1, int64_t s1, int rows, int at_once) {
-    const double c = tile_cycles(rows);
-    if (at_once > 1 && n0 + n1 <= 256 * at_once) {   // all in their places from the start: the first unit has the most, and its long ones to itself in the end
-        const int64_t of0 = (n0 + 255) / 256, all = (n0 + n1 + 255) / 256;
-        return kTileCycles + (double)s1 * std::max(kStageCycles, (double)all * c) + (double)(s0 - s1) * std::max(kStageCycles, (double)of0 * c);
+// n0 tiles of s0 stages, then n1 of s1 <= s0, in one launch.  Units that have had the same tiles are followed together, from the end of one of their
+// tiles to the next; whole rounds of equal tiles are not followed.  Of units that have a place at about the same time the emptiest one gets the tile.
+constexpr double kSoon = 1500;
+static double pair_cycles(int64_t n0, int64_t s0, int64_t n1, int64_t s1, const TileRate &r) {
+    struct Tile { bool first; double ends, stages; };
+    struct Group { double at; int64_t units, ended; int n; Tile tile[3]; };   // the time of the state, tiles of the first kind that end then, what is left of the others
+    Group g[4], now[4];   // three at most: units part where either kind of tiles runs out
+    int groups = 0;
+    const int64_t round = (int64_t)kUnits * r.at_once, stages[2] = {s0, s1};
+    const int64_t whole = std::max<int64_t>(0, n0 / round - 1);
+    int64_t left[2] = {n0 - whole * round, n1}, longs = left[0];
+    double skipped = kBegin + (double)whole * r.round(r.at_once, s0), last = 0;
+    // gives the free places of a group's units their next tiles, one place of all of them after the other
+    auto start = [&](const Group &from) {
+        int count = 1;
+        now[0] = from;
+        now[0].ended = 0;
+        for (bool any = true; any && (left[0] || left[1]);) {
+            any = false;
+            for (int i = 0; i < count && (left[0] || left[1]); ++i) {
+                if (now[i].n == r.at_once) continue;
+                const int k = left[0] ? 0 : 1;
+                if (left[k] < now[i].units) {
+                    now[count] = now[i];
+                    now[count++].units -= left[k];
+                    now[i].units = left[k];
+                }
+                left[k] -= now[i].units;
+                now[i].tile[now[i].n++] = {k == 0, r.ends, (double)stages[k]};
+                any = true;
+            }
+        }
+        for (int i = 0; i < count; ++i) {
+            if (now[i].n) g[groups++] = now[i];
+            else last = std::max(last, now[i].at);
+        }
+    };
+    // to the end of one of its tiles
+    auto advance = [&](Group &p) {
+        for (bool done = false; !done;) {
+            int running = 0;
+            for (int i = 0; i < p.n; ++i) running += p.tile[i].ends <= 0;
+            const double step = r.stage(running), slow = r.begin_end(p.n) / r.ends;
+            double dt = 1e300;
+            for (int i = 0; i < p.n; ++i) dt = std::min(dt, p.tile[i].ends > 0 ? p.tile[i].ends * slow : p.tile[i].stages * step);
+            p.at += dt;
+            int kept = 0;
+            for (int i = 0; i < p.n; ++i) {
+                Tile t = p.tile[i];
+                if (t.ends > 0) t.ends = t.ends - dt / slow > 1e-3 ? t.ends - dt / slow : 0;
+                else t.stages -= dt / step;
+                if (t.ends <= 0 && t.stages < 1e-6) {
+                    done = true;
+                    if (t.first) p.ended += p.units;
+                } else p.tile[kept++] = t;
+            }
+            p.n = kept;
+        }
+    };
+    start({0, kUnits, 0, 0, {}});
+    for (int i = 0; i < groups; ++i) advance(g[i]);
+    while (groups) {
+        int next = 0;
+        for (int i = 1; i < groups; ++i)
+            if (g[i].at < g[next].at) next = i;
+        const double soon = g[next].at + kSoon;
+        for (int i = 0; i < groups; ++i)
+            if (g[i].at <= soon && g[i].n < g[next].n) next = i;
+        const Group p = g[next];
+        g[next] = g[--groups];
+        longs -= p.ended;
+        if (!longs && left[1] > 2 * round) {
+            const int64_t more = left[1] / round - 1;
+            left[1] -= more * round;
+            skipped += (double)more * r.round(r.at_once, s1);
+        }
+        const int behind = groups;
+        start(p);
+        for (int i = behind; i < groups; ++i) advance(g[i]);
     }
-    const double stage = std::max(kStageCycles / at_once, c);
-    const double t0 = (double)s0 * stage + kTileCycles / at_once, t1 = (double)s1 * stage + kTileCycles / at_once;
-    const int64_t late = n0 % 256;   // units that are free one tile after the others
-    const double from[2] = {(double)(n0 / 256) * t0, (double)(n0 / 256 + 1) * t0};
-    const int64_t units[2] = {256 - late, late};
-    const double even = ((double)n0 * t0 + (double)n1 * t1) / 256.0;   // no earlier than this
-    int64_t k[2];                    // tiles of the second kind that a unit has done
-    for (int i = 0; i < 2; ++i) k[i] = std::max<int64_t>(0, (int64_t)((even - from[i]) / t1));
-    while (units[0] * k[0] + units[1] * k[1] < n1) ++k[late && from[1] + (double)k[1] * t1 < from[0] + (double)k[0] * t1 ? 1 : 0];
-    const double t = std::max(from[0] + (double)k[0] * t1, late ? from[1] + (double)k[1] * t1 : 0.0);
-    // a long tile shares its unit as long as there are others, and has what is left of it to itself (321 x 2701 x 932, rows = 3: 90 us, 65 without this)
-    const double done = std::max(0.0, even - kTileCycles) / std::max(kStageCycles, (double)at_once * c);
-    const double alone = std::max(kStageCycles, c * (double)std::min<int64_t>(at_once, (n0 + 255) / 256));
-    return std::max(t, std::max(even, kTileCycles) + ((double)s0 - done) * alone);
+    return skipped + last;
 }
 
 void product_pair(ProductDesc &x, ProductDesc &y) {
@@ -119,8 +196,10 @@ void product_pair(ProductDesc &x, ProductDesc &y) {
         for (int rows = 1; rows <= rows_limit(x); ++rows) {
             const int64_t nx = tile_count(x, rows, fx), ny = tile_count(y, rows, fy);
             const int64_t sx = stages_of(x.Q), sy = stages_of(y.Q);
-            const int at_once = tiles_per_unit(x, rows);
-            const double t = sx >= sy ? pair_cycles(nx, sx, ny, sy, rows, at_once) : pair_cycles(ny, sy, nx, sx, rows, at_once);
+            const TileRate r = tile_rate(x, rows);
+            const double even = ((double)nx * (double)sx + (double)ny * (double)sy) / kUnits;   // stages of a unit, no fewer than this
+            if (kBegin + r.ends + std::max(even * r.stage(r.at_once) / r.at_once, (double)std::max(sx, sy) * r.alone) >= best) continue;
+            const double t = sx >= sy ? pair_cycles(nx, sx, ny, sy, r) : pair_cycles(ny, sy, nx, sx, r);
             if (t >= best) continue;
             best = t;
             x.pair_rows = y.pair_rows = rows;

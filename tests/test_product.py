@@ -186,7 +186,14 @@ def test_tiles_of_functions_and_with_an_outer_function(I, J, K):
 
 # every height of a tile: of plain products, with a program behind them, with column sums and scaled results beside them
 HEIGHTS = [("matmul", 1433, 1190, 306, "f32"), ("matmul", 719, 1729, 381, "f32"), ("dense", 4710, 315, 76, "f32"), ("dense", 160, 4296, 83, "f32"),
-           ("dense", 1500, 1024, 200, "f32"), ("dense", 2000, 300, 20, "f64"), ("matmul", 1077, 74, 14, "f32")]
+           ("dense", 1500, 1024, 200, "f32"), ("dense", 2000, 300, 20, "f64"), ("matmul", 1077, 74, 14, "f32"),
+           # ... where the model picks it for the sum, for sums in pieces, for one gradient and for both in a launch
+           ("matmul", 716, 349, 16, "f32"), ("matmul", 905, 558, 18, "f32"), ("matmul", 1648, 930, 16, "f32"), ("matmul", 1924, 545, 17, "f32"),
+           ("matmul", 879, 1729, 99, "f32"), ("matmul", 1129, 2765, 35, "f32"), ("matmul", 285, 345, 839, "f32"), ("matmul", 669, 593, 797, "f32"),
+           ("matmul", 1098, 477, 16, "f64"), ("matmul", 631, 1203, 16, "f64"), ("matmul", 509, 2069, 16, "f64"), ("matmul", 250, 1055, 676, "f64"),
+           ("matmul", 461, 524, 863, "f64"), ("matmul", 466, 429, 868, "f64"), ("matmul", 712, 529, 851, "f64"), ("dense", 420, 1832, 16, "f32"),
+           ("dense", 2934, 468, 16, "f32"), ("dense", 541, 2853, 16, "f32"), ("dense", 354, 397, 647, "f32"), ("dense", 790, 736, 698, "f32"),
+           ("dense", 457, 394, 875, "f64")]
 
 
 @pytest.mark.gpu
