@@ -6,11 +6,12 @@
 // 64 bits once; a thread owns R results 256 apart, so that its reads are free of conflicts and an element of w, the same for all of them, is
 // read once per R products.  dx is the same sum over df with the window turned round.  dw: a thread takes four neighbouring window
 // elements and a part of the workgroup's results, four of them at a time: 11 reads for 16 products.  The workgroups' sums of dw are added
-// by a second launch in a fixed order.  262144 x 33: f 3.6 us, gradients 10.2, three launches; a pass of both through Python 13.3 us.  The workgroups at the
+// by a second launch in a fixed order.  262144 x 33: f 3.6 us, gradients 9.1, three launches; a pass of both through Python 12.2 us.  The workgroups at the
 // ends of the signal decide what a call takes if they test every term (gradients of 169877 x 63 36 us instead of 14), and where the signal is short they are
 // all there is: groups of 16 terms are taken or left as a whole where they can be (dw alone of 1100 x 256 21 -> 10 us, the plan-driven kernels 7;
 // 20000 x 256 16 -> 8.1).  Many parts of dw are added in two steps: one thread per window element would add up to 256 in a row (4000000 x 1,
-// both gradients 31.7 -> 25.7 us, dw alone 28 -> 21, the plan-driven kernels 117 and 12).
+// both gradients 31.7 -> 25.7 us, dw alone 28 -> 21); with the second launch's sums shared by a workgroup 22.8 and 17.6 (the plan-driven kernels 117
+// and 12).
 // Products of 32-bit operands are exact and sums are in 64 bits, so only the result is rounded.
 #include <hip/hip_runtime.h>
 
@@ -201,25 +202,29 @@ __global__ __launch_bounds__(256) void k_window_backward(const WindowArgs A) {
     }
 }
 
-// a wavefront per element of dw; those behind the window are zero
-template <typename T>
+// a wavefront per element of dw, or a workgroup where there are many sums to add; those behind the window are zero
+template <typename T, int WAVES>
 __global__ __launch_bounds__(256) void k_window_finish(const double *__restrict__ part, int blocks, int K, int n_w, T *__restrict__ dw) {
-    const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (k >= n_w) return;   // the whole wavefront leaves together
+    __shared__ double sums[4];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int k = WAVES > 1 ? blockIdx.x : blockIdx.x * 4 + wave;
+    if (k >= n_w) return;   // the whole wavefront leaves together, the whole workgroup where it works on one element
     double mine = 0.0;
     if (k < K) {
         const double *at = part + (size_t)k * blocks;
-        constexpr int U = 4;
-        for (int b = lane; b < blocks; b += 64 * U) {
+        constexpr int U = 4, STEP = 64 * WAVES;
+        for (int b = WAVES > 1 ? threadIdx.x : lane; b < blocks; b += STEP * U) {
             double v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = b + 64 * u < blocks ? at[b + 64 * u] : 0.0;
+            for (int u = 0; u < U; ++u) v[u] = b + STEP * u < blocks ? at[b + STEP * u] : 0.0;
 #pragma unroll
             for (int u = 0; u < U; ++u) mine += v[u];
         }
     }
-    const double total = wave_sum_all(mine);
-    if (lane == 0) dw[k] = (T)total;
+    double total;
+    if constexpr (WAVES > 1) total = block_sum_256(mine, sums);
+    else total = wave_sum_all(mine);
+    if (lane == 0 && (WAVES == 1 || wave == 0)) dw[k] = (T)total;
 }
 
 static int launched() { return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE; }
@@ -252,7 +257,12 @@ static int backward_t(const WindowPlan &p, const void *const *args, const void *
     else TAD_LAUNCH("k_window_backward", (k_window_backward<T, R, false>), grid, block, 0, s, A);
     if (launched()) return TAD_EDEVICE;
     if (!A.part) return TAD_OK;
-    TAD_LAUNCH("k_window_finish", (k_window_finish<T>), dim3((p.n_w + 3) / 4), dim3(256), 0, s, (const double *)A.part, blocks, p.K, p.n_w, static_cast<T *>(dx[p.w]));
+    // Both gradients, sums added by a wavefront / a workgroup: 262144 x 33 (1024 sums) 10.2 / 9.1 us, 300000 x 1 (1172) 8.5 / 7.8, 4000000 x 1 (3907)
+    // 25.7 / 22.8; up to 256 are one round of loads for either (and a workgroup for each of many elements behind the window would only write zeros)
+    if (blocks > 256 && p.n_w <= 1024)
+        TAD_LAUNCH("k_window_finish", (k_window_finish<T, 4>), dim3(p.n_w), dim3(256), 0, s, (const double *)A.part, blocks, p.K, p.n_w, static_cast<T *>(dx[p.w]));
+    else
+        TAD_LAUNCH("k_window_finish", (k_window_finish<T, 1>), dim3((p.n_w + 3) / 4), dim3(256), 0, s, (const double *)A.part, blocks, p.K, p.n_w, static_cast<T *>(dx[p.w]));
     return launched();
 }
 

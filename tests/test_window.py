@@ -26,7 +26,8 @@ def window_expr(N, K, q, dtype, swap=False, more_x=0, more_w=0, limits=None):
 CASES = [(1025, 33, -1, {}), (1024, 2, -1, {}), (700, 128, -1, dict(swap=True)), (2047, 256, -1, dict(more_x=3, more_w=2)), (1000, 255, 1, {}),
          (1281, 7, 1, dict(more_x=5, more_w=1, swap=True)), (1500, 64, 1, dict(limits=(100, None))), (1500, 61, 1, dict(limits=(3, 1200))),
          (1500, 60, -1, dict(limits=(700, 1201))), (1030, 17, 1, dict(limits=(None, 40))), (131072, 5, -1, {}), (131077, 33, 1, dict(more_x=1)),
-         (133000, 130, -1, dict(limits=(1000, 131000))), (400100, 9, -1, {}), (750100, 24, 1, {})]
+         (133000, 130, -1, dict(limits=(1000, 131000))), (400100, 9, -1, {}), (750100, 24, 1, {}),
+         (70001, 5, 1, dict(more_w=1100))]
 
 
 def _run(plan, w, ws_bytes=None, skip=()):
