@@ -8,6 +8,7 @@
 #include "launch_geom.h"
 #include "product_match.hpp"
 #include "separable_match.hpp"
+#include "mfma_split.h"
 #include "split.h"
 #include "window_match.hpp"
 
@@ -441,6 +442,10 @@ void select_wide(tad_plan &plan) {
 }
 
 static void select_split(tad_plan &plan) {
+    if (plan.fwd_family == TAD_FAMILY_WORKED_MFMA && long_pays(plan.fast.I, plan.fast.J, plan.fast.K)) {
+        plan.mfma_split = true;
+        plan.ws_full = align256(plan.ws_bytes) + long_workspace_bytes(plan.fast.I, plan.fast.J, plan.fast.K);
+    }
     if (plan.fwd_family != TAD_FAMILY_CONTRACTION) return;
     for (const GemmDesc &g : plan.fast.gemm)
         if (split_pays(g.M, g.N, g.Kc)) {

@@ -21,6 +21,7 @@
 #include "plan_dev.h"
 #include "profile.h"
 #include "launch_geom.h"
+#include "mfma_split.h"
 
 namespace tad {
 
@@ -204,12 +205,14 @@ __device__ __forceinline__ void mfma_forward_tile(const float *__restrict__ a, c
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_mfma_forward(const float *__restrict__ a, const float *__restrict__ b,
                                                       const float *__restrict__ rowv, const float *__restrict__ nb,
-                                                      float *__restrict__ f, int I, int J, int K) {
+                                                      float *__restrict__ f, int I, int J, int K, const int *__restrict__ redo) {
+    if (redo && !*redo) return;   // done on the bf16 matrix cores
     mfma_forward_tile<1>(a, b, rowv, nb, f, I, J, K);
 }
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mfma_forward_large(const float *__restrict__ a, const float *__restrict__ b,
                                                       const float *__restrict__ rowv, const float *__restrict__ nb,
-                                                      float *__restrict__ f, int I, int J, int K) {
+                                                      float *__restrict__ f, int I, int J, int K, const int *__restrict__ redo) {
+    if (redo && !*redo) return;
     mfma_forward_tile<2>(a, b, rowv, nb, f, I, J, K);
 }
 
@@ -224,17 +227,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // (TRANS_A = true), so the plain sums over the collapsed index are accumulated on the side:
 //   TRANS_A = false:  sums[(split * 2 + 0) * I + i] = sum_j G_ij,  sums[(split * 2 + 1) * I + i] = sum_j G_ij |b_j|^2
 //   TRANS_A = true:   sums[split * J + j] = sum_i c_ii G_ij
+struct MfmaTiles {
+    float a[64 * MF_LD], b[32][256], red[8][64];
+};
 template <bool TRANS_A>
-__global__ __launch_bounds__(512, 4) void k_mfma_backward(const float *__restrict__ f, const float *__restrict__ df,
-                                                       const float *__restrict__ bmat, const float *__restrict__ rowv,
-                                                       const float *__restrict__ nb, float *__restrict__ out,
-                                                       float *__restrict__ sums, int I, int J, int K, int chunk) {
-    __shared__ float As[TRANS_A ? 32 : 64][TRANS_A ? 64 : MF_LD];
-    __shared__ float Bs[32][256];
-    __shared__ float tred[8][64];
+__device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int split, const float *__restrict__ f, const float *__restrict__ df,
+                                                 const float *__restrict__ bmat, const float *__restrict__ rowv, const float *__restrict__ nb,
+                                                 float *__restrict__ out, float *__restrict__ sums, int I, int J, int K, int chunk) {
+    float (*const As)[TRANS_A ? 64 : MF_LD] = reinterpret_cast<float (*)[TRANS_A ? 64 : MF_LD]>(S.a);
+    float (*const Bs)[256] = S.b, (*const tred)[64] = S.red;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave & 1, wn = wave >> 1;
     const int Mtot = TRANS_A ? J : I, Ctot = TRANS_A ? I : J;
-    const int m0 = blockIdx.x * 64, split = blockIdx.y, n0 = blockIdx.z * 256;
+    const int m0 = tile * 64, n0 = blockIdx.y * 256;
     const int cs = split * chunk, ce = min(Ctot, cs + chunk);
     float16v acc[2];
 #pragma unroll
@@ -323,7 +327,7 @@ __global__ __launch_bounds__(512, 4) void k_mfma_backward(const float *__restric
             if (m < Mtot && n < K) out[((size_t)split * Mtot + m) * K + n] = acc[tn][r];
         }
     }
-    if (blockIdx.z != 0) return;
+    if (blockIdx.y != 0) return;
     if (!TRANS_A) {
         // eight consecutive lanes share a row: add them in a fixed order
 #pragma unroll
@@ -354,117 +358,170 @@ __global__ __launch_bounds__(512, 4) void k_mfma_backward(const float *__restric
     }
 }
 
-__global__ __launch_bounds__(256) void k_mfma_fill_zero(float *__restrict__ p, long long n) {
-    const long long n4 = n >> 2;
-    const float4v z = {0.f, 0.f, 0.f, 0.f};
-    const long long stride = (long long)gridDim.x * 256;
-    for (long long q = (long long)blockIdx.x * 256 + threadIdx.x; q < n4; q += stride)
-        reinterpret_cast<float4v *>(p)[q] = z;
-    if (blockIdx.x == 0 && threadIdx.x < (int)(n & 3)) p[(n4 << 2) + threadIdx.x] = 0.f;
+// Both contractions in one launch, tiles of rows i, then tiles of rows j: small ones fill the chip together.
+struct MfmaSide {
+    const float *mat;
+    float *out, *sums;
+    int chunk;
+};
+__global__ __launch_bounds__(512, 4) void k_mfma_backward(const float *__restrict__ f, const float *__restrict__ df, const float *__restrict__ rowv,
+                                                          const float *__restrict__ nb, const MfmaSide P, const MfmaSide T, int I, int J, int K, int first,
+                                                          int n_j, int n_i, const int *__restrict__ redo) {
+    if (redo && !*redo) return;   // done on the bf16 matrix cores
+    __shared__ __attribute__((aligned(16))) MfmaTiles S;
+    const int id = blockIdx.x, second = id - first;   // (neighbours share a tile of rows)
+    if (id < first) mfma_contraction<false>(S, id / n_j, id % n_j, f, df, P.mat, rowv, nb, P.out, P.sums, I, J, K, P.chunk);
+    else mfma_contraction<true>(S, second / n_i, second % n_i, f, df, T.mat, rowv, nb, T.out, T.sums, I, J, K, T.chunk);
 }
 
 // ---------------------------------------------------------------------------------------------
-// finishing: one wave per output row, lane owns four consecutive k.
-// Blocks [0, blocks_rows): rows i (da, dc_ii, r_i); the rest: rows j (db).  Fixed summation order.
+// finishing, in one launch: rows i (da, dc_ii and the zeros of that row of dc), rows j (db), dd, rows of dc beyond I; one wavefront per output row, a
+// lane owns four consecutive k.  Fixed summation order.  The zeros (64 MB at 4096 x 4096) go out while the others wait for their partial sums.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_mfma_finish(const float *__restrict__ a, const float *__restrict__ b,
-                                                     const float *__restrict__ rowv, const float *__restrict__ Ppart,
-                                                     const float *__restrict__ Tpart, int n_split,
-                                                     const float *__restrict__ rowp, const float *__restrict__ colp,
-                                                     float *__restrict__ da, float *__restrict__ db,
-                                                     float *__restrict__ dc, float *__restrict__ rsum, int I, int J,
-                                                     int K, int c_ld, int blocks_rows) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if ((int)blockIdx.x < blocks_rows) {
-        const int i = blockIdx.x * 4 + wv;
+struct MfmaFinish {
+    const float *a, *b, *d, *rowv, *P, *T, *rowp, *colp;
+    float *da, *db, *dc, *dd;
+    long long n_c;             // elements of c
+    int I, J, K, c_ld, n_d;
+    int n_j, n_i;              // pieces of the sums over j and over i
+    int rows, cols, window;    // workgroups for rows i, for rows j, for dd; the rest: zeros beyond row I
+};
+// to[0 .. n) = 0, but to[at] = v; 16-byte stores whatever the alignment of the row
+__device__ __forceinline__ void mfma_zeros(float *to, int n, int at, float v, int lane) {
+    const int head = min(n, (int)((16 - (reinterpret_cast<uintptr_t>(to) & 15)) & 15) / 4), body = (n - head) / 4;
+    if (lane < head) to[lane] = lane == at ? v : 0.f;
+    for (int q = lane; q < body; q += 64) {
+        const int first = head + 4 * q;
+        float4v z;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = first + e == at ? v : 0.f;
+        __builtin_nontemporal_store(z, reinterpret_cast<float4v *>(to + first));
+    }
+    const int rest = head + 4 * body + lane;
+    if (rest < n) to[rest] = rest == at ? v : 0.f;
+}
+constexpr int kZeroPiece = 4096;   // floats of a wavefront
+__global__ __launch_bounds__(256) void k_mfma_finish(const MfmaFinish F, const FlatFeas feas, const FlatLevel win, int iy, int iz) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, I = F.I, J = F.J, K = F.K;
+    int block = blockIdx.x;
+    if (block < F.rows) {
+        const int i = block * 4 + wv;
         if (i >= I) return;
         double r = 0.0, Q = 0.0;
-        for (int s = 0; s < n_split; ++s) {
-            r += (double)rowp[((size_t)s * 2 + 0) * I + i];
-            Q += (double)rowp[((size_t)s * 2 + 1) * I + i];
+#pragma unroll 4
+        for (int s = 0; s < F.n_j; ++s) {
+            r += (double)F.rowp[((size_t)s * 2 + 0) * I + i];
+            Q += (double)F.rowp[((size_t)s * 2 + 1) * I + i];
         }
-        const double ci = (double)rowv[i * 4 + 3], na = (double)rowv[i * 4 + 0];
+        const double ci = (double)F.rowv[i * 4 + 3], na = (double)F.rowv[i * 4 + 0];
         float cross = 0.f;
-        if (da || dc)
+        if (F.da || F.dc)
             for (int k = lane * 4; k < K; k += 256) {
                 float4v P = {0.f, 0.f, 0.f, 0.f};
-                for (int s = 0; s < n_split; ++s)
-                    P += *reinterpret_cast<const float4v *>(Ppart + ((size_t)s * I + i) * K + k);
-                const float4v av = *reinterpret_cast<const float4v *>(a + (size_t)i * K + k);
-                if (da) {
+#pragma unroll 4
+                for (int s = 0; s < F.n_j; ++s) P += *reinterpret_cast<const float4v *>(F.P + ((size_t)s * I + i) * K + k);
+                const float4v av = *reinterpret_cast<const float4v *>(F.a + (size_t)i * K + k);
+                if (F.da) {
                     float4v o;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = (float)(-2.0 * ci * ((double)av[e] * r + (double)P[e]));
-                    *reinterpret_cast<float4v *>(da + (size_t)i * K + k) = o;
+                    *reinterpret_cast<float4v *>(F.da + (size_t)i * K + k) = o;
                 }
                 cross += (av[0] * P[0] + av[1] * P[1]) + (av[2] * P[2] + av[3] * P[3]);
             }
+        if (!F.dc) return;
         cross = wave_sum63m(cross);
-        if (lane == 63) {
-            if (dc) dc[(size_t)i * c_ld + i] = (float)(-(na * r + 2.0 * (double)cross + Q));
-            rsum[i] = (float)r;
+        const float total = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cross), 63));
+        mfma_zeros(F.dc + (size_t)i * F.c_ld, F.c_ld, i, (float)(-(na * r + 2.0 * (double)total + Q)), lane);
+        return;
+    }
+    block -= F.rows;
+    if (block < F.cols) {
+        const int j = block * 4 + wv;
+        if (j >= J) return;
+        double t = 0.0;
+#pragma unroll 4
+        for (int s = 0; s < F.n_i; ++s) t += (double)F.colp[(size_t)s * J + j];
+        for (int k = lane * 4; k < K; k += 256) {
+            float4v T = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+            for (int s = 0; s < F.n_i; ++s) T += *reinterpret_cast<const float4v *>(F.T + ((size_t)s * J + j) * K + k);
+            const float4v bv = *reinterpret_cast<const float4v *>(F.b + (size_t)j * K + k);
+            float4v o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (float)(-2.0 * ((double)T[e] + (double)bv[e] * t));
+            *reinterpret_cast<float4v *>(F.db + (size_t)j * K + k) = o;
         }
         return;
     }
-    const int j = ((int)blockIdx.x - blocks_rows) * 4 + wv;
-    if (j >= J || !db) return;
-    double t = 0.0;
-    for (int s = 0; s < n_split; ++s) t += (double)colp[(size_t)s * J + j];
-    for (int k = lane * 4; k < K; k += 256) {
-        float4v T = {0.f, 0.f, 0.f, 0.f};
-        for (int s = 0; s < n_split; ++s) T += *reinterpret_cast<const float4v *>(Tpart + ((size_t)s * J + j) * K + k);
-        const float4v bv = *reinterpret_cast<const float4v *>(b + (size_t)j * K + k);
-        float4v o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (float)(-2.0 * ((double)T[e] + (double)bv[e] * t));
-        *reinterpret_cast<float4v *>(db + (size_t)j * K + k) = o;
+    block -= F.cols;
+    if (block < F.window) {
+        // dd_m = -3 d_m^2 sum_{i in window(m)} r_i; window and masks from the plan of d
+        const int m = block * 4 + wv;
+        if (m >= F.n_d) return;
+        const int32_t y[3] = {m, 0, 0};
+        float s = 0.f;
+        const bool ok = flat_feasible(feas, y);
+        if (ok) {
+            int32_t lo, hi;
+            flat_bounds(win, y, lo, hi);
+            for (int32_t w = lo + lane; w <= hi; w += 64) {
+                double r = 0.0;
+#pragma unroll 4
+                for (int p = 0; p < F.n_j; ++p) r += (double)F.rowp[(size_t)p * 2 * I + iy * y[0] + iz * w];
+                s += (float)r;
+            }
+        }
+        s = wave_sum63m(s);
+        if (lane == 63) {
+            const float dm = F.d[m];
+            F.dd[m] = ok ? -3.f * dm * dm * s : 0.f;
+        }
+        return;
     }
-}
-
-// dd_m = -3 d_m^2 sum_{i in window(m)} r_i, one wave per m; window and masks from the plan of d
-__global__ __launch_bounds__(256) void k_mfma_dd(const FlatFeas feas, const FlatLevel win, int iy, int iz,
-                                                 const float *__restrict__ d, const float *__restrict__ rsum,
-                                                 float *__restrict__ dd, int n_d) {
-    const int lane = threadIdx.x & 63;
-    const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (m >= n_d) return;
-    const int32_t y[3] = {m, 0, 0};
-    float s = 0.f;
-    const bool ok = flat_feasible(feas, y);
-    if (ok) {
-        int32_t lo, hi;
-        flat_bounds(win, y, lo, hi);
-        for (int32_t w = lo + lane; w <= hi; w += 64) s += rsum[iy * y[0] + iz * w];
-    }
-    s = wave_sum63m(s);
-    if (lane == 63) {
-        const float dm = d[m];
-        dd[m] = ok ? -3.f * dm * dm * s : 0.f;
-    }
+    const long long from = (long long)I * F.c_ld + ((long long)(block - F.window) * 4 + wv) * kZeroPiece;
+    if (from < F.n_c) mfma_zeros(F.dc + from, (int)min((long long)kZeroPiece, F.n_c - from), -1, 0.f, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
-struct MfmaWs {
-    float *rowv, *nb, *Ppart, *Tpart, *rowp, *colp, *rsum;
-    int n_split, chunk_j, chunk_i;
+// The pieces that the sums over j and over i are cut into: every piece of a tile of rows is a workgroup of its own, and its partial results are
+// written and read again.
+struct MfmaPieces {
+    int n_j, n_i;              // pieces of the sum over j (results for rows i), of the sum over i (rows j; 0: not wanted)
+    int chunk_j, chunk_i;      // terms of a piece, a multiple of 32
 };
+// Time of a choice: rounds of the `slots` workgroups that run at once, a stage of 32 terms and what a workgroup takes besides its stages, and 5 TB/s for
+// the partial results.  No more pieces than the workspace holds: kMfmaSplit of either sum, and where one has fewer the other may have more.
+static MfmaPieces mfma_pieces(int64_t I, int64_t J, int64_t K, bool cols, int tile, int slots, double stage, double besides) {
+    MfmaPieces best{};
+    double least = -1;
+    const int64_t columns = (K + 255) / 256, ti = (I + tile - 1) / tile * columns, tj = cols ? (J + tile - 1) / tile * columns : 0;
+    const int64_t longest = (std::max(I, J) + 31) / 32;
+    for (int64_t n = 1; n <= longest; n += 1 + n / 16) {
+        const int64_t nj = ((J + 31) / 32 + n - 1) / n, ni = cols ? ((I + 31) / 32 + n - 1) / n : 0;
+        if (nj > kMfmaMostPieces || ni > kMfmaMostPieces || nj * I + ni * J > kMfmaSplit * (I + J) || 2 * nj * I + ni * J > kMfmaSplit * (2 * I + J)) continue;
+        const int64_t rounds = (ti * nj + tj * ni + slots - 1) / slots;
+        const double t = (double)rounds * ((double)n * stage + besides) + (double)(nj * I + ni * J) * (double)K * 8 / 5e6;
+        if (least >= 0 && t >= least) continue;
+        least = t;
+        best = {(int)nj, (int)ni, (int)(32 * n), (int)(32 * n)};
+    }
+    return best;
+}
 
+struct MfmaWs {
+    float *rowv, *nb, *partial, *sums;
+};
 static MfmaWs carve_mfma(void *ws, int64_t I, int64_t J, int64_t K) {
     MfmaWs w;
-    w.n_split = kMfmaSplit;
-    w.chunk_j = (int)(((J + kMfmaSplit - 1) / kMfmaSplit + 31) / 32 * 32);
-    w.chunk_i = (int)(((I + kMfmaSplit - 1) / kMfmaSplit + 31) / 32 * 32);
     char *p = static_cast<char *>(ws);
     auto take = [&](size_t bytes) { float *r = reinterpret_cast<float *>(p); p += align256(bytes); return r; };
     w.rowv = take((size_t)I * 16);
     w.nb = take((size_t)J * 4);
-    w.Ppart = take((size_t)kMfmaSplit * I * K * 4);
-    w.Tpart = take((size_t)kMfmaSplit * J * K * 4);
-    w.rowp = take((size_t)kMfmaSplit * 2 * I * 4);
-    w.colp = take((size_t)kMfmaSplit * J * 4);
-    w.rsum = take((size_t)I * 4);
+    w.partial = take((size_t)kMfmaSplit * (I + J) * K * 4);
+    w.sums = take((size_t)kMfmaSplit * (2 * I + J) * 4);
     return w;
 }
 
@@ -532,12 +589,28 @@ __global__ __launch_bounds__(256) void k_worked_forward_direct(const float *__re
     }
 }
 
-int mfma_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s) {
+static LongProducts long_products(const tad_plan &pl, const void *const *args, const MfmaWs &w, void *ws) {
+    int *const redo = reinterpret_cast<int *>(static_cast<char *>(ws) + align256(pl.ws_bytes));
+    return {(const float *)args[0], (const float *)args[1], (const float *)args[2], (const float *)args[3], w.rowv, w.nb, redo + 64, redo,
+            (int)pl.fast.I, (int)pl.fast.J, (int)pl.fast.K, (int)pl.fast.c_ld};
+}
+
+// full: the workspace holds the parts of a and b, the contractions run on the bf16 matrix cores and the kernels here do again what was not finite
+int mfma_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, bool full, hipStream_t s) {
     const int I = (int)pl.fast.I, J = (int)pl.fast.J, K = (int)pl.fast.K;
     MfmaWs w = carve_mfma(ws, I, J, K);
-    int rc = prep(pl, args, w, s);
+    const bool direct = pl.flags & TAD_PLAN_DIRECT_FORM;
+    const int *redo = nullptr;
+    int rc;
+    if (full && !direct && long_forward_pays(I, J, K)) {
+        const LongProducts L = long_products(pl, args, w, ws);
+        rc = long_forward(L, (float *)f, s);
+        redo = L.redo;
+    } else {
+        rc = prep(pl, args, w, s);
+    }
     if (rc) return rc;
-    if (pl.flags & TAD_PLAN_DIRECT_FORM) {
+    if (direct) {
         TAD_LAUNCH("k_worked_forward_direct", k_worked_forward_direct, dim3((J + 63) / 64, (I + 63) / 64), dim3(256), 0, s,
                    (const float *)args[0], (const float *)args[1], w.rowv, (float *)f, I, J, K);
         return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
@@ -545,48 +618,46 @@ int mfma_forward(const tad_plan &pl, const void *const *args, void *f, void *ws,
     // (c has at least I x I elements, fewer than 2^31 in all: the tiles along i fit the second axis of a grid)
     if (large_forward_tiles(I, J, K))
         TAD_LAUNCH("k_mfma_forward", k_mfma_forward_large, dim3((J + 127) / 128, (I + 127) / 128), dim3(256), 0, s,
-                   (const float *)args[0], (const float *)args[1], w.rowv, w.nb, (float *)f, I, J, K);
+                   (const float *)args[0], (const float *)args[1], w.rowv, w.nb, (float *)f, I, J, K, redo);
     else
         TAD_LAUNCH("k_mfma_forward", k_mfma_forward, dim3((J + 63) / 64, (I + 63) / 64), dim3(256), 0, s,
-                   (const float *)args[0], (const float *)args[1], w.rowv, w.nb, (float *)f, I, J, K);
+                   (const float *)args[0], (const float *)args[1], w.rowv, w.nb, (float *)f, I, J, K, redo);
     return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
 int mfma_backward(const tad_plan &pl, const void *const *args, const void *f_, const void *df_, void *const *dx,
-                  void *ws, hipStream_t s) {
+                  void *ws, bool full, hipStream_t s) {
     const int I = (int)pl.fast.I, J = (int)pl.fast.J, K = (int)pl.fast.K, c_ld = (int)pl.fast.c_ld;
     MfmaWs w = carve_mfma(ws, I, J, K);
     const float *a = (const float *)args[0], *b = (const float *)args[1], *d = (const float *)args[3];
     const float *f = (const float *)f_, *df = (const float *)df_;
-    int rc = prep(pl, args, w, s);
+    const int *redo = nullptr;
+    const bool cols = dx[1] != nullptr;
+    MfmaPieces n = full ? mfma_pieces(I, J, K, cols, 128, K <= 64 ? 512 : 256, K <= 64 ? 2.5 : K <= 128 ? 2.2 : 3.6, 6.0) : mfma_pieces(I, J, K, cols, 64, 512, 5.0, 5.0);
+    // partial results for rows i, then for rows j; sums of rows i, then of rows j
+    const MfmaSide P{b, w.partial, w.sums, n.chunk_j}, T{a, w.partial + (size_t)n.n_j * I * K, w.sums + (size_t)n.n_j * 2 * I, n.chunk_i};
+    int rc;
+    if (full) {
+        const LongProducts L = long_products(pl, args, w, ws);
+        rc = long_backward(L, f, df, P.out, P.sums, n.n_j, T.out, T.sums, n.n_i, n.chunk_j, s);
+        redo = L.redo;
+    } else {
+        rc = prep(pl, args, w, s);
+    }
     if (rc) return rc;
-    const int nz = (K + 255) / 256;
     // the row pass always runs: r_i feeds da, dc and dd; the column pass only for db
-    TAD_LAUNCH("k_mfma_backward", (k_mfma_backward<false>), dim3((I + 63) / 64, w.n_split, nz), dim3(512), 0, s, f, df,
-               b, w.rowv, w.nb, w.Ppart, w.rowp, I, J, K, w.chunk_j);
+    const int tiles = (I + 63) / 64, columns = (K + 255) / 256, first = tiles * n.n_j, blocks_both = first + (cols ? (J + 63) / 64 * n.n_i : 0);
+    TAD_LAUNCH("k_mfma_backward", k_mfma_backward, dim3(blocks_both, columns), dim3(512), 0, s, f, df, (const float *)w.rowv, (const float *)w.nb, P, T, I, J, K, first,
+               n.n_j, n.n_i, redo);
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    if (dx[1]) {
-        TAD_LAUNCH("k_mfma_backward", (k_mfma_backward<true>), dim3((J + 63) / 64, w.n_split, nz), dim3(512), 0, s, f,
-                   df, a, w.rowv, w.nb, w.Tpart, w.colp, I, J, K, w.chunk_i);
-        if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    }
-    if (dx[2]) {
-        const long long n = pl.arg_count[2];
-        const int g = (int)std::min<long long>(16384, (n / 4 + 255) / 256 + 1);
-        TAD_LAUNCH("k_fill_zero", k_mfma_fill_zero, dim3(g), dim3(256), 0, s, (float *)dx[2], n);
-        if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    }
-    const int br = (I + 3) / 4, bc = dx[1] ? (J + 3) / 4 : 0;
-    TAD_LAUNCH("k_mfma_finish", k_mfma_finish, dim3(br + bc), dim3(256), 0, s, a, b, w.rowv, w.Ppart, w.Tpart,
-               w.n_split, w.rowp, w.colp, (float *)dx[0], (float *)dx[1], (float *)dx[2], w.rsum, I, J, K, c_ld, br);
-    if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    if (dx[3]) {
-        const int n_d = (int)pl.arg_count[3];
-        TAD_LAUNCH("k_mfma_dd", k_mfma_dd, dim3((n_d + 3) / 4), dim3(256), 0, s, pl.fast.feas, pl.fast.flat[0],
-                   pl.fast.dd_iy, pl.fast.dd_iz, d, w.rsum, (float *)dx[3], n_d);
-        if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    }
-    return TAD_OK;
+    MfmaFinish F{a, b, d, w.rowv, P.out, T.out, P.sums, T.sums, (float *)dx[0], (float *)dx[1], (float *)dx[2], (float *)dx[3], (long long)pl.arg_count[2],
+                 I, J, K, c_ld, (int)pl.arg_count[3], n.n_j, n.n_i, (I + 3) / 4, cols ? (J + 3) / 4 : 0, 0};
+    if (dx[3]) F.window = (F.n_d + 3) / 4;
+    const long long beyond = dx[2] ? F.n_c - (long long)I * c_ld : 0;
+    if (!dx[0] && !dx[2]) F.rows = 0;
+    const unsigned blocks = (unsigned)(F.rows + F.cols + F.window + (beyond + 4 * kZeroPiece - 1) / (4 * kZeroPiece));
+    TAD_LAUNCH("k_mfma_finish", k_mfma_finish, dim3(blocks), dim3(256), 0, s, F, pl.fast.feas, pl.fast.flat[0], pl.fast.dd_iy, pl.fast.dd_iz);
+    return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
 }  // namespace tad

@@ -22,9 +22,9 @@ int worked_backward(const tad_plan &pl, const void *const *args, const void *f, 
 int worked_wide_forward(const tad_plan &pl, const void *const *args, void *f, hipStream_t s);
 int worked_wide_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx, void *ws, hipStream_t s);
 
-int mfma_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, hipStream_t s);
+int mfma_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, bool full, hipStream_t s);
 int mfma_backward(const tad_plan &pl, const void *const *args, const void *f, const void *df, void *const *dx,
-                  void *ws, hipStream_t s);
+                  void *ws, bool full, hipStream_t s);
 int pattern_forward(const tad_plan &pl, const void *const *args, void *f, hipStream_t s);
 int pattern_backward(const tad_plan &pl, const void *const *args, const void *df, void *const *dx, void *ws,
                      hipStream_t s);

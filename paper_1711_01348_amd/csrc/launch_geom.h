@@ -42,13 +42,11 @@ inline WideGeom worked_wide_geom(int64_t I, int64_t J, int64_t K) {
     return g;
 }
 
-// long summed index (MFMA family): number of chunks the collapsed contraction index is split in (4 leaves the
-// chip under-filled: 133 / 117 us per contraction instead of 98 / 94)
-constexpr int kMfmaSplit = 8;
+// long summed index (MFMA family): pieces that each of the two contractions of the gradients has room for; one may take what the other does not need
+constexpr int kMfmaSplit = 8, kMfmaMostPieces = 64;
 inline size_t mfma_workspace_bytes(int64_t I, int64_t J, int64_t K) {
-    return align256((size_t)I * 16) + align256((size_t)J * 4) + align256((size_t)kMfmaSplit * I * K * 4) +
-           align256((size_t)kMfmaSplit * J * K * 4) + align256((size_t)kMfmaSplit * 2 * I * 4) +
-           align256((size_t)kMfmaSplit * J * 4) + align256((size_t)I * 4);
+    return align256((size_t)I * 16) + align256((size_t)J * 4) + align256((size_t)kMfmaSplit * (I + J) * K * 4) +
+           align256((size_t)kMfmaSplit * (2 * I + J) * 4);
 }
 
 // Fallback (generic and program) kernels.  The cooperative form (one block per gradient element) pays off when

@@ -1,0 +1,113 @@
+"""Worked expression with a long sum: contractions on the bf16 matrix cores and on the 32-bit ones, in pieces of any number, against 64 bits."""
+import ctypes
+
+import pytest
+
+from paper_1711_01348_amd import check
+from paper_1711_01348_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def tensors(I, J, K, seed=3, c_extra=0):
+    import torch
+    expr = wl.worked_expr(I, J, K, "f32", c_shape=(I + c_extra, I + c_extra + 1) if c_extra else None)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed + I + J + K)
+    args = [(torch.rand(tuple(q.shape), generator=g, device="cuda") - 0.5) * s for q, s in zip(expr.args, (2.0, 2.0, 1.0 / K, 0.4))]
+    return expr, args, torch.rand((I, J), generator=g, device="cuda") * 2 - 1
+
+
+def evaluate(plan, args, df, ws_bytes, wanted=(0, 1, 2, 3), f=None):
+    """f and the wanted gradients with ws_bytes of workspace, everything behind it watched; gradients of a given f if there is one."""
+    import torch
+    from paper_1711_01348_amd import binding as B
+    out, grads = torch.full_like(df, float("nan")), [torch.full_like(a, float("nan")) for a in args]
+    ws = torch.full((ws_bytes + 4096,), 255, dtype=torch.uint8, device="cuda")
+    ptrs = (ctypes.c_void_p * 4)(*[t.data_ptr() for t in args])
+    outs = (ctypes.c_void_p * 4)(*[t.data_ptr() if q in wanted else None for q, t in enumerate(grads)])
+    assert B.lib.tad_eval_forward(plan._h, ptrs, out.data_ptr(), ws.data_ptr(), ws_bytes, None) == 0
+    f = out if f is None else f
+    assert B.lib.tad_eval_backward(plan._h, ptrs, f.data_ptr(), df.data_ptr(), outs, ws.data_ptr(), ws_bytes, None) == 0
+    torch.cuda.synchronize()
+    assert bool((ws[ws_bytes:] == 255).all()), "written beyond the workspace"
+    return [out] + [grads[q] for q in wanted]
+
+
+def exact(args, df, K):
+    import torch
+    a, b, c, d = [t.double() for t in args]
+    df, I = df.double(), df.shape[0]
+    ci, na, nb = c.diagonal()[:I], (a * a).sum(1), (b * b).sum(1)
+    f = torch.exp(-(ci[:, None] * (na[:, None] + nb[None, :] + 2 * (a @ b.t().contiguous())) + (d ** 3).unfold(0, K, 1)[:I].sum(1)[:, None]))
+    g = df * f
+    r, P = g.sum(1), g @ b
+    dc, dd = torch.zeros_like(c), torch.zeros_like(d)
+    dc.diagonal()[:I].copy_(-(na * r + 2 * (a * P).sum(1) + g @ nb))
+    for q in range(K):
+        dd[q:q + I] += r
+    db = -2 * ((ci[:, None] * g).t().contiguous() @ a + b * (ci[:, None] * g).sum(0)[:, None])
+    return [f, -2 * ci[:, None] * (a * r[:, None] + P), db, dc, -3 * d * d * dd]
+
+
+# 64, 128 and 256 columns of a tile, a part of them and more than one; rows and terms one beyond a tile, a stage, four of them short
+@pytest.mark.parametrize("I,J,K,c_extra", [(1025, 1024, 32, 3), (1150, 1028, 64, 0), (1537, 1284, 96, 0), (1409, 1412, 128, 1), (1409, 1540, 160, 0),
+                                           (1921, 1148, 256, 0), (4097, 516, 288, 0), (509, 4100, 512, 2), (2049, 4000, 160, 0)])
+def test_error_is_no_larger_than_that_of_the_32_bit_kernels(I, J, K, c_extra):
+    import torch
+    from paper_1711_01348_amd import binding as B
+    expr, args, df = tensors(I, J, K, c_extra=c_extra)
+    plan, want = B.Plan(expr), exact(args, df, K)
+    split, plain = (evaluate(plan, args, df, n) for n in (plan.workspace_bytes, plan.workspace_bytes - 16))
+    assert not torch.equal(split[1], plain[1])      # not the same kernels
+    for s, p, w in zip(split, plain, want):
+        e = [((t.double() - w).norm() / w.norm()).item() for t in (s, p)]
+        assert e[0] <= 1.1 * e[1] + 3e-8, e         # (sums of few pieces: dd, dc differ in the order of the pieces alone)
+        assert check.within(s.cpu().numpy(), w.cpu().numpy(), "f32"), check.errors(s.cpu().numpy(), w.cpu().numpy())
+    rest = split[3].clone()
+    rest.diagonal()[:I].zero_()
+    assert not rest.any()
+
+
+@pytest.mark.parametrize("wanted", [(0,), (1,), (2,), (3,), (0, 3), (1, 2)])
+def test_any_of_the_gradients(wanted):
+    import torch
+    from paper_1711_01348_amd import binding as B
+    expr, args, df = tensors(1409, 1412, 96)
+    plan = B.Plan(expr)
+    for ws_bytes in (plan.workspace_bytes, plan.workspace_bytes - 16):
+        both = evaluate(plan, args, df, ws_bytes)
+        some = evaluate(plan, args, df, ws_bytes, wanted)
+        for q, t in zip(wanted, some[1:]):
+            # (pieces of the sums depend on which of them are wanted)
+            assert ((t.double() - both[1 + q].double()).norm() <= 1e-6 * both[1 + q].double().norm()).item()
+
+
+# few rows on one side: up to 64 pieces of the other sum, in the room the first one leaves
+@pytest.mark.parametrize("I,J,K", [(4096, 64, 32), (64, 4096, 96), (70, 8200, 64), (3000, 132, 288), (33, 68, 32)])
+def test_pieces_of_long_sums_for_few_rows(I, J, K):
+    from paper_1711_01348_amd import binding as B
+    expr, args, df = tensors(I, J, K)
+    plan = B.Plan(expr)
+    assert plan.forward_family == "worked_mfma"
+    for g, w in zip(evaluate(plan, args, df, plan.workspace_bytes), exact(args, df, K)):
+        assert check.within(g.cpu().numpy(), w.cpu().numpy(), "f32"), check.errors(g.cpu().numpy(), w.cpu().numpy())
+
+
+@pytest.mark.parametrize("what", ["inf_df", "nan_df", "huge_df", "inf_a", "huge_b"])
+def test_what_is_not_finite_is_left_to_the_32_bit_kernels(what):
+    import torch
+    from paper_1711_01348_amd import binding as B
+    expr, args, df = tensors(2048, 3840, 128)
+    f = torch.rand_like(df)
+    if what.endswith("df"):
+        df[2047, 3839] = {"inf": float("inf"), "nan": float("nan"), "huge": 3.4e38}[what[:-3]]
+    else:
+        args[0 if what == "inf_a" else 1][5, 127] = float("inf") if what == "inf_a" else 3.4e38
+    plan = B.Plan(expr)
+    split, plain = (evaluate(plan, args, df, n, f=f) for n in (plan.workspace_bytes, plan.workspace_bytes - 16))
+    for s, p in zip(split, plain):
+        assert torch.equal(s.isnan(), p.isnan()) and torch.equal(s.isinf(), p.isinf())
+        both = s.isfinite()
+        # rows with 3.4e38 among their terms: the order of the pieces differs, the terms do not
+        assert bool(((s[both].double() - p[both].double()).abs() <= 1e-5 * p[both].double().abs() + 2e-5 * p[both].double().pow(2).mean().sqrt()).all())
