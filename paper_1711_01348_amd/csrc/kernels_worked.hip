@@ -20,6 +20,7 @@
 #include "plan_dev.h"
 #include "profile.h"
 #include "launch_geom.h"
+#include "zeros.h"
 
 namespace tad {
 
@@ -269,30 +270,16 @@ __global__ __launch_bounds__(256) void k_worked_backward(const float *__restrict
     }
 }
 
-// Dense zero fill of a gradient whose non-zero elements are written afterwards (cokernel mask: only the
-// diagonal of dc is non-zero).  A pure write stream runs faster than the same stores mixed into a read pass.
-constexpr int FILL_U = 1;   // 16-byte stores per thread
-__global__ __launch_bounds__(256) void k_fill_zero(float *__restrict__ p, long long n) {
-    // every block writes one contiguous 4 KiB piece: 41 us for 256 MiB against 45 / 47 us with 8 / 16 KiB pieces and
-    // more with grid-stride or tiled fills
-    const long long n4 = n >> 2;
-    const float4v z = {0.f, 0.f, 0.f, 0.f};
-    const long long lo = (long long)blockIdx.x * (256 * FILL_U) + threadIdx.x;
-#pragma unroll
-    for (int u = 0; u < FILL_U; ++u) {
-        const long long q = lo + 256 * u;
-        if (q < n4) __builtin_nontemporal_store(z, reinterpret_cast<float4v *>(p) + q);
-    }
-    if (blockIdx.x == 0 && threadIdx.x < (int)(n & 3)) p[(n4 << 2) + threadIdx.x] = 0.f;
-}
-
-// Finishing pass, one launch with three block roles, 64 outputs per block; the four waves of a block split
+// Finishing pass, one launch with four block roles, the first three of 64 outputs per block; the four waves of a block split
 // the tile partials (wave w takes tiles w, w+4, ...) and are combined in fixed order through LDS.
 //   rows:  da, diagonal of dc               (sum of the row partials over the column tiles)
 //   cols:  db                               (sum of the column partials over the row tiles)
 //   dd:    dd_m = -3 d_m^2 * sum over the window coordinate of r_i; masks and the window come from the
 //          plan of d (loop-free copy of its rows): one kernel coordinate is the window, the other one (j)
-//          is already summed in the row partials.
+//          is already summed in the row partials;
+//   zeros: dc off its diagonal (cokernel mask).  Behind the read pass: mixed into it they slow the reads down, and a write burst
+//          right before it does too.  In this launch they go out while the other blocks wait for their partial sums: 8192 x 8192 x 5
+//          40 us, in a launch of their own 41.6 + 6.8 and the gap between them.
 template <int K>
 __global__ __launch_bounds__(256) void k_worked_finish(const FlatFeas feas, const FlatLevel win, int iy, int iz,
                                                        const float *__restrict__ a, const float *__restrict__ b,
@@ -301,9 +288,9 @@ __global__ __launch_bounds__(256) void k_worked_finish(const FlatFeas feas, cons
                                                        const float *__restrict__ colp, int n_it,
                                                        float *__restrict__ da, float *__restrict__ db,
                                                        float *__restrict__ dc, float *__restrict__ dd, int I,
-                                                       int J, int c_ld, int n_d, int blocks_rows, int blocks_cols) {
+                                                       int J, int c_ld, int n_d, int blocks_rows, int blocks_cols, int blocks_dd, int n_c) {
     constexpr int RP = K + 2, CP = K + 1;
-    __shared__ double red[4][RP][64];
+    __shared__ double red[2][RP][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int blk = blockIdx.x;
     if (blk < blocks_rows) {
@@ -311,17 +298,15 @@ __global__ __launch_bounds__(256) void k_worked_finish(const FlatFeas feas, cons
         double acc[RP];
 #pragma unroll
         for (int q = 0; q < RP; ++q) acc[q] = 0.0;
+        const int own = min(i, I - 1);
+        const double ci = (double)c[(size_t)own * c_ld + own];
         if (i < I)
+#pragma unroll 2
             for (int jt = wave; jt < n_jt; jt += 4)
 #pragma unroll
                 for (int q = 0; q < RP; ++q) acc[q] += (double)rowp[((size_t)jt * RP + q) * I + i];
-#pragma unroll
-        for (int q = 0; q < RP; ++q) red[wave][q][lane] = acc[q];
-        __syncthreads();
+        add_wavefronts(acc, red, wave, lane);
         if (wave != 0 || i >= I) return;
-#pragma unroll
-        for (int q = 0; q < RP; ++q) acc[q] = (red[0][q][lane] + red[1][q][lane]) + (red[2][q][lane] + red[3][q][lane]);
-        const double ci = (double)c[(size_t)i * c_ld + i];
         double na = 0.0, cross = 0.0;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -340,15 +325,12 @@ __global__ __launch_bounds__(256) void k_worked_finish(const FlatFeas feas, cons
 #pragma unroll
         for (int q = 0; q < CP; ++q) acc[q] = 0.0;
         if (j < J && db)
+#pragma unroll 4
             for (int it = wave; it < n_it; it += 4)
 #pragma unroll
                 for (int q = 0; q < CP; ++q) acc[q] += (double)colp[((size_t)it * CP + q) * J + j];
-#pragma unroll
-        for (int q = 0; q < CP; ++q) red[wave][q][lane] = acc[q];
-        __syncthreads();
+        add_wavefronts(acc, red, wave, lane);
         if (wave != 0 || j >= J || !db) return;
-#pragma unroll
-        for (int q = 0; q < CP; ++q) acc[q] = (red[0][q][lane] + red[1][q][lane]) + (red[2][q][lane] + red[3][q][lane]);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             // the column partials carry c_ii a_ik and c_ii already:  db_jk = -2 (T_jk + b_jk t_j)
@@ -358,8 +340,12 @@ __global__ __launch_bounds__(256) void k_worked_finish(const FlatFeas feas, cons
         return;
     }
     blk -= blocks_cols;
+    if (blk >= blocks_dd) {
+        zeros_off_diagonal(dc, (unsigned)n_c, (unsigned)c_ld + 1u, (unsigned)I, (unsigned)(blk - blocks_dd));
+        return;
+    }
     const int m = blk * 64 + lane;
-    double s = 0.0;
+    double s[1] = {0.0};
     bool nonzero = false;
     if (m < n_d && dd) {
         const int32_t y[3] = {m, 0, 0};   // the transformed index is the gradient index (checked on the host)
@@ -367,20 +353,24 @@ __global__ __launch_bounds__(256) void k_worked_finish(const FlatFeas feas, cons
             nonzero = true;
             int32_t lo, hi;
             flat_bounds(win, y, lo, hi);
-            for (int32_t w = lo; w <= hi; ++w) {
-                const int i = iy * y[0] + iz * w;
-                for (int jt = wave; jt < n_jt; jt += 4) s += (double)rowp[((size_t)jt * RP) * I + i];
-            }
+            // the loads of a window go out together
+            constexpr int U = K;
+            for (int jt = wave; jt < n_jt; jt += 4)
+                for (int32_t w0 = lo; w0 <= hi; w0 += U) {
+                    float v[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[u] = rowp[(size_t)jt * RP * I + iy * y[0] + iz * min(w0 + u, hi)];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) s[0] += w0 + u <= hi ? (double)v[u] : 0.0;
+                }
         }
     }
-    red[wave][0][lane] = s;
-    __syncthreads();
+    add_wavefronts(s, red, wave, lane);
     if (wave != 0 || m >= n_d || !dd) return;
     float out = 0.f;
     if (nonzero) {
-        s = (red[0][0][lane] + red[1][0][lane]) + (red[2][0][lane] + red[3][0][lane]);
         const double dm = (double)d[m];
-        out = (float)(-3.0 * dm * dm * s);
+        out = (float)(-3.0 * dm * dm * s[0]);
     }
     dd[m] = out;
 }
@@ -426,22 +416,12 @@ static int bwd_k(const tad_plan &pl, const void *const *args, const void *f, con
     TAD_LAUNCH("k_worked_backward", (k_worked_backward<K>), grid, dim3(256), 0, s, a, b, c, (const float *)f,
                (const float *)df, w.rowp, w.colp, I, J, c_ld);
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    if (dc) {
-        // after the read pass: a write burst right before it slows the reads down
-        const long long n = pl.arg_count[2];
-        const int g = (int)((n / 4 + 256 * FILL_U - 1) / (256 * FILL_U) + 1);
-        TAD_LAUNCH("k_fill_zero", k_fill_zero, dim3(g), dim3(256), 0, s, dc, n);
-        if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    }
-    {
-        const int n_d = (int)pl.arg_count[3];
-        const int br = (I + 63) / 64, bc = (J + 63) / 64, bd = (n_d + 63) / 64;
-        TAD_LAUNCH("k_worked_finish", (k_worked_finish<K>), dim3(br + bc + bd), dim3(256), 0, s, pl.fast.feas,
-                   pl.fast.flat[0], pl.fast.dd_iy, pl.fast.dd_iz, a, b, c, d, w.rowp, w.n_jt, w.colp, w.n_it,
-                   (float *)dx[0], (float *)dx[1], dc, (float *)dx[3], I, J, c_ld, n_d, br, bc);
-        if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    }
-    return TAD_OK;
+    const int n_d = (int)pl.arg_count[3], n_c = (int)pl.arg_count[2];
+    const int br = (I + 63) / 64, bc = (J + 63) / 64, bd = (n_d + 63) / 64, bz = dc ? (int)(((long long)n_c * 4 + kZeroBytes - 1) / kZeroBytes) : 0;
+    TAD_LAUNCH("k_worked_finish", (k_worked_finish<K>), dim3(br + bc + bd + bz), dim3(256), 0, s, pl.fast.feas,
+               pl.fast.flat[0], pl.fast.dd_iy, pl.fast.dd_iz, a, b, c, d, w.rowp, w.n_jt, w.colp, w.n_it,
+               (float *)dx[0], (float *)dx[1], dc, (float *)dx[3], I, J, c_ld, n_d, br, bc, bd, n_c);
+    return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
 #define TAD_K_SWITCH(fn, ...)                       \

@@ -18,6 +18,7 @@
 #include "launch_geom.h"
 #include "plan_dev.h"
 #include "profile.h"
+#include "zeros.h"
 
 namespace tad {
 
@@ -235,34 +236,20 @@ __global__ __launch_bounds__(256) void k_worked_wide_finish(const FlatFeas feas,
                                                             const T *__restrict__ d, const double *__restrict__ rowp, int n_jt,
                                                             const double *__restrict__ colp, int n_it, T *__restrict__ da,
                                                             T *__restrict__ db, T *__restrict__ dc, T *__restrict__ dd, int I, int J,
-                                                            int c_ld, int n_d, int blocks_rows, int blocks_cols, int blocks_dd, int n_c) {
+                                                            int c_ld, int n_d, int blocks_rows, int blocks_cols, int cols, int blocks_dd, int n_c) {
     constexpr int RP = K + 2;
-    __shared__ double red[4][RP][64];
+    __shared__ double red[2][RP][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int blk = blockIdx.x;
     if (blk >= blocks_rows + blocks_cols + blocks_dd) {
         // dc is zero but for the first I elements of its diagonal, which the row blocks write
-        constexpr int V = 16 / (int)sizeof(T);
-        typedef T vec __attribute__((ext_vector_type(V)));
-        const unsigned at = ((unsigned)(blk - blocks_rows - blocks_cols - blocks_dd) * 256u + threadIdx.x) * V, step = (unsigned)c_ld + 1u;
-        if (at >= (unsigned)n_c) return;
-        const unsigned row = (at + step - 1) / step, diagonal = row < (unsigned)I ? row * step : 0xffffffffu;   // the first one from here on
-        if ((reinterpret_cast<uintptr_t>(dc) & 15) == 0 && at + V <= (unsigned)n_c && diagonal >= at + V) {
-            vec zero;
-#pragma unroll
-            for (int v = 0; v < V; ++v) zero[v] = T(0);
-            __builtin_nontemporal_store(zero, reinterpret_cast<vec *>(dc + at));
-        } else {
-            // (a row of one element: every element of c is on the diagonal's stride, step 2 -- more than one may be in here)
-#pragma unroll
-            for (int v = 0; v < V; ++v)
-                if (at + v < (unsigned)n_c && !((at + v) % step == 0 && (at + v) / step < (unsigned)I)) dc[at + v] = T(0);
-        }
+        zeros_off_diagonal(dc, (unsigned)n_c, (unsigned)c_ld + 1u, (unsigned)I, (unsigned)(blk - blocks_rows - blocks_cols - blocks_dd));
         return;
     }
     if (blk < blocks_rows) {
         const int i = blk * 64 + lane;
         double acc[RP] = {};
+        const double ci = (double)c[(size_t)min(i, I - 1) * c_ld + min(i, I - 1)];
         if (i < I) {
             // the loads of U tiles go out together: one after the other, the chain of them is longer than the pass over df and f
             constexpr int U = K <= 4 ? 4 : 2;
@@ -282,13 +269,8 @@ __global__ __launch_bounds__(256) void k_worked_wide_finish(const FlatFeas feas,
 #pragma unroll
                 for (int p = 0; p < RP; ++p) acc[p] += rowp[((size_t)jt * RP + p) * I + i];
         }
-#pragma unroll
-        for (int p = 0; p < RP; ++p) red[wave][p][lane] = acc[p];
-        __syncthreads();
+        add_wavefronts(acc, red, wave, lane);
         if (wave != 0 || i >= I) return;
-#pragma unroll
-        for (int p = 0; p < RP; ++p) acc[p] = (red[0][p][lane] + red[1][p][lane]) + (red[2][p][lane] + red[3][p][lane]);
-        const double ci = (double)c[(size_t)i * c_ld + i];
         if (da)
 #pragma unroll
             for (int k = 0; k < K; ++k) da[(size_t)i * K + k] = (T)(-2.0 * ci * acc[1 + k]);
@@ -297,38 +279,39 @@ __global__ __launch_bounds__(256) void k_worked_wide_finish(const FlatFeas feas,
     }
     blk -= blocks_rows;
     if (blk < blocks_cols) {
-        const int j = blk * 64 + lane;
+        // `cols` neighbouring columns, 256 / cols threads to each: a column is one sum per tile of rows, however few columns there are
+        const int j = blk * cols + lane % cols, parts = 256 / cols;
         double acc[K] = {};
         if (j < J && db) {
             constexpr int U = K <= 4 ? 8 : 4;   // as above
-            int it = wave;
-            for (; it + 4 * (U - 1) < n_it; it += 4 * U) {
+            int it = (int)threadIdx.x / cols;
+            for (; it + parts * (U - 1) < n_it; it += parts * U) {
                 double v[U][K];
 #pragma unroll
                 for (int u = 0; u < U; ++u)
 #pragma unroll
-                    for (int k = 0; k < K; ++k) v[u][k] = colp[((size_t)(it + 4 * u) * K + k) * J + j];
+                    for (int k = 0; k < K; ++k) v[u][k] = colp[((size_t)(it + parts * u) * K + k) * J + j];
 #pragma unroll
                 for (int u = 0; u < U; ++u)
 #pragma unroll
                     for (int k = 0; k < K; ++k) acc[k] += v[u][k];
             }
-            for (; it < n_it; it += 4)
+            for (; it < n_it; it += parts)
 #pragma unroll
                 for (int k = 0; k < K; ++k) acc[k] += colp[((size_t)it * K + k) * J + j];
         }
+        for (int m = cols; m < 64; m <<= 1)   // the same for the whole workgroup
 #pragma unroll
-        for (int k = 0; k < K; ++k) red[wave][k][lane] = acc[k];
-        __syncthreads();
-        if (wave != 0 || j >= J || !db) return;
+            for (int k = 0; k < K; ++k) acc[k] += __shfl_xor(acc[k], m, 64);
+        add_wavefronts(acc, red, wave, lane);
+        if (wave != 0 || lane >= cols || j >= J || !db) return;
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            db[(size_t)j * K + k] = (T)(-2.0 * ((red[0][k][lane] + red[1][k][lane]) + (red[2][k][lane] + red[3][k][lane])));
+        for (int k = 0; k < K; ++k) db[(size_t)j * K + k] = (T)(-2.0 * acc[k]);
         return;
     }
     blk -= blocks_cols;
     const int m = blk * 64 + lane;
-    double s = 0.0;
+    double s[1] = {0.0};
     bool nonzero = false;
     if (m < n_d && dd) {
         const int32_t y[3] = {m, 0, 0};   // the transformed index is the gradient index (checked on the host)
@@ -336,20 +319,24 @@ __global__ __launch_bounds__(256) void k_worked_wide_finish(const FlatFeas feas,
             nonzero = true;
             int32_t lo, hi;
             flat_bounds(win, y, lo, hi);
-            for (int32_t w = lo; w <= hi; ++w) {
-                const int i = iy * y[0] + iz * w;
-                for (int jt = wave; jt < n_jt; jt += 4) s += rowp[((size_t)jt * RP) * I + i];
-            }
+            // the loads of a window go out together
+            constexpr int U = K < 8 ? K : 8;
+            for (int jt = wave; jt < n_jt; jt += 4)
+                for (int32_t w0 = lo; w0 <= hi; w0 += U) {
+                    double v[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[u] = rowp[(size_t)jt * RP * I + iy * y[0] + iz * min(w0 + u, hi)];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) s[0] += w0 + u <= hi ? v[u] : 0.0;
+                }
         }
     }
-    red[wave][0][lane] = s;
-    __syncthreads();
+    add_wavefronts(s, red, wave, lane);
     if (wave != 0 || m >= n_d || !dd) return;
     T out = T(0);
     if (nonzero) {
-        s = (red[0][0][lane] + red[1][0][lane]) + (red[2][0][lane] + red[3][0][lane]);
         const double dm = (double)d[m];
-        out = (T)(-3.0 * dm * dm * s);
+        out = (T)(-3.0 * dm * dm * s[0]);
     }
     dd[m] = out;
 }
@@ -373,12 +360,16 @@ static int bwd_k(const tad_plan &pl, const void *const *args, const void *f, con
     TAD_LAUNCH("k_worked_wide_backward", (k_worked_wide_backward<T, K>), dim3(g.n_jt, g.n_it), dim3(256), 0, s, (const T *)args[0],
                (const T *)args[1], (const T *)args[2], (const T *)f, (const T *)df, rowp, colp, I, J, c_ld, g.tile_rows);
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
-    const int br = (I + 63) / 64, bc = (J + 63) / 64, bd = (n_d + 63) / 64;
+    // Columns of a workgroup that finishes them: as few as leave a thread about a dozen sums, whose loads go out four or eight at a time.  Gradients
+    // with 64 columns always / by this rule, I x J x K: 7663 x 60 x 6 (479 tiles of rows) 54 / 45 us, without dc 33 / 14; 5000 x 120 x 3 32 / 22.5, 333 x 6000 x 8 31 / 22,
+    // 4000 x 500 x 7 35 / 28, 2000 x 2000 x 4 20.0 / 17.7; 64 bits 1024 x 40 x 16 22.4 / 17.9.
+    const int cols = g.n_it <= 48 ? 64 : g.n_it <= 192 ? 16 : 4;
+    const int br = (I + 63) / 64, bc = dx[1] ? (J + cols - 1) / cols : 0, bd = (n_d + 63) / 64;
     // the zeros of dc in the same launch (behind the read pass: a write burst right before it slows the reads down)
-    const int n_c = (int)pl.arg_count[2], bz = dc ? (int)clear_blocks<T>(n_c) : 0;
+    const int n_c = (int)pl.arg_count[2], bz = dc ? (int)(((long long)n_c * (int)sizeof(T) + kZeroBytes - 1) / kZeroBytes) : 0;
     TAD_LAUNCH("k_worked_wide_finish", (k_worked_wide_finish<T, K>), dim3(br + bc + bd + bz), dim3(256), 0, s, pl.fast.feas, pl.fast.flat[0],
                pl.fast.dd_iy, pl.fast.dd_iz, (const T *)args[2], (const T *)args[3], (const double *)rowp, g.n_jt, (const double *)colp,
-               g.n_it, (T *)dx[0], (T *)dx[1], dc, (T *)dx[3], I, J, c_ld, n_d, br, bc, bd, n_c);
+               g.n_it, (T *)dx[0], (T *)dx[1], dc, (T *)dx[3], I, J, c_ld, n_d, br, bc, cols, bd, n_c);
     return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
