@@ -369,7 +369,7 @@ __device__ __forceinline__ void product_kernel(const ProductArgs &M, const Produ
         constexpr int U = ProgWidth<TO>::U;
 #pragma unroll 1
         for (int p0 = 0; p0 < RESULTS; p0 += U) {
-            TO s[U], w[kMaxArgs][U], o[U];
+            TO s[U], w[kMaxArgs][U], o[U], d[U];
             int at[U];
             bool inside[U];
 #pragma unroll
@@ -382,12 +382,13 @@ __device__ __forceinline__ void product_kernel(const ProductArgs &M, const Produ
 #pragma unroll
                 for (int q = 0; q < kMaxArgs; ++q)
                     w[q][u] = O->args.p[q] ? static_cast<const TO *>(O->args.p[q])[inside[u] ? O->off_r[q] * r + O->off_c[q] * c : 0] : TO(0);
+                d[u] = O->df ? static_cast<const TO *>(O->df)[at[u]] : TO(1);   // on its way while the program runs
             }
             prog_eval_block<TO, U, true>(O->prog, w, s, o);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (!inside[u]) continue;
-                reinterpret_cast<TO *>(out)[at[u]] = O->df ? static_cast<const TO *>(O->df)[at[u]] * o[u] : o[u];
+                reinterpret_cast<TO *>(out)[at[u]] = O->df ? d[u] * o[u] : o[u];
                 if (O->s_out) static_cast<TO *>(O->s_out)[at[u]] = s[u];
             }
         }
