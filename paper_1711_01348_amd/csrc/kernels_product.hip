@@ -105,6 +105,31 @@ __device__ __forceinline__ void column_sums(const ProductColumns &S, int block, 
     static_cast<T *>(S.out)[c] = (T)sum;
 }
 
+// What the program that is applied to a low tile's results reads besides the sums fits in registers and is sent for before the sum is begun: behind it, the
+// addresses and the wait took 1.4 us of a launch (dense 31 x 142 x 80 7.4 -> 6.5 us, softplus 512 x 384 x 200 17.3 -> 16.4).
+template <typename TO, int NR> struct OuterOperands {
+    static constexpr int ER = 16 * NR, EC = kProductCols, RESULTS = ER * EC / 512, U = RESULTS < ProgWidth<TO>::U ? RESULTS : ProgWidth<TO>::U;
+    static constexpr bool EARLY = RESULTS <= U;
+    TO w[kMaxArgs][U], d[U];
+    int at[U], place[U];   // element of the result (-1: none), place of the sum in LDS
+    __device__ __forceinline__ void fetch(const ProductTask &P, const ProductOuter *O, int tid, int r0, int c0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int n = tid + 512 * u, ir = P.turned ? n % ER : n / EC, ic = P.turned ? n / ER : n % EC, r = r0 + ir, c = c0 + ic;
+            const bool inside = r < P.R && c < P.C;
+            place[u] = ir * (EC + 1) + ic;
+            at[u] = !inside ? -1 : P.turned ? c * P.R + r : r * P.C + c;
+#pragma unroll
+            for (int q = 0; q < kMaxArgs; ++q)
+                w[q][u] = O->args.p[q] ? static_cast<const TO *>(O->args.p[q])[inside ? O->off_r[q] * r + O->off_c[q] * c : 0] : TO(0);
+            d[u] = O->df ? static_cast<const TO *>(O->df)[max(at[u], 0)] : TO(1);
+        }
+    }
+};
+template <int NR> struct OuterOperands<void, NR> {
+    static constexpr bool EARLY = false;
+};
+
 // EXTRA: scaled results or column sums (their code in every kernel: 1000 x 1203 x 777 in 64 bits 130 -> 134 us with its gradients)
 template <typename TA, typename TB, int NR, typename TO, bool EXTRA>
 __device__ __forceinline__ void product_kernel(const ProductArgs &M, const ProductOuter *O) {
@@ -145,6 +170,9 @@ __device__ __forceinline__ void product_kernel(const ProductArgs &M, const Produ
     auto a_dk = [&](int p) { return a_q ? 0 : p % PG * (NT / G); };
     auto b_dr = [&](int p) { return b_q ? p * (NT / KT) : 0; };
     auto b_dk = [&](int p) { return b_q ? 0 : p * (NT / EC); };
+    using Outer = OuterOperands<TO, NR>;
+    Outer outer;
+    if constexpr (Outer::EARLY) outer.fetch(P, O, tid, r0, c0);
     unsigned ao[PA], bo[PB];       // byte offsets within a stage
 #pragma unroll
     for (int p = 0; p < PA; ++p)
@@ -364,12 +392,24 @@ __device__ __forceinline__ void product_kernel(const ProductArgs &M, const Produ
             if (P.wide) reinterpret_cast<double *>(out)[at] = v;
             else reinterpret_cast<float *>(out)[at] = (float)v;
         }
+    } else if constexpr (Outer::EARLY) {
+        TO s[Outer::U], o[Outer::U];
+#pragma unroll
+        for (int u = 0; u < Outer::U; ++u) s[u] = (TO)sums[outer.place[u]];
+        prog_eval_block<TO, Outer::U, true>(O->prog, outer.w, s, o);
+#pragma unroll
+        for (int u = 0; u < Outer::U; ++u) {
+            if (outer.at[u] < 0) continue;
+            reinterpret_cast<TO *>(out)[outer.at[u]] = O->df ? outer.d[u] * o[u] : o[u];
+            if (O->s_out) static_cast<TO *>(O->s_out)[outer.at[u]] = s[u];
+        }
     } else {
-        // U results per pass of the interpreter: an operation costs more to fetch than to carry out
+        // U results per pass of the interpreter: an operation costs more to fetch than to carry out. df is read behind the program: before it, its registers
+        // cost the tall tiles more than the wait (dense 2000 x 1000 x 64: 22.4 us instead of 21.2).
         constexpr int U = ProgWidth<TO>::U;
 #pragma unroll 1
         for (int p0 = 0; p0 < RESULTS; p0 += U) {
-            TO s[U], w[kMaxArgs][U], o[U], d[U];
+            TO s[U], w[kMaxArgs][U], o[U];
             int at[U];
             bool inside[U];
 #pragma unroll
@@ -382,13 +422,12 @@ __device__ __forceinline__ void product_kernel(const ProductArgs &M, const Produ
 #pragma unroll
                 for (int q = 0; q < kMaxArgs; ++q)
                     w[q][u] = O->args.p[q] ? static_cast<const TO *>(O->args.p[q])[inside[u] ? O->off_r[q] * r + O->off_c[q] * c : 0] : TO(0);
-                d[u] = O->df ? static_cast<const TO *>(O->df)[at[u]] : TO(1);   // on its way while the program runs
             }
             prog_eval_block<TO, U, true>(O->prog, w, s, o);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (!inside[u]) continue;
-                reinterpret_cast<TO *>(out)[at[u]] = O->df ? d[u] * o[u] : o[u];
+                reinterpret_cast<TO *>(out)[at[u]] = O->df ? static_cast<const TO *>(O->df)[at[u]] * o[u] : o[u];
                 if (O->s_out) static_cast<TO *>(O->s_out)[at[u]] = s[u];
             }
         }
