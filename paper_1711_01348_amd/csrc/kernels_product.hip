@@ -235,6 +235,7 @@ __device__ __forceinline__ void product_kernel(const ProductArgs &M, const Produ
 #pragma unroll
         for (int n = 1; n <= AHEAD; ++n)
             if (q_begin + n * KT < q_end) load(q_begin + n * KT, regs[n % AHEAD]);
+        if constexpr (!std::is_same<TO, void>::value) fetch_program(O->prog);
         stage(0, begin);
     }
     __syncthreads();

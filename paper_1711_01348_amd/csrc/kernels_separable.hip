@@ -29,32 +29,64 @@ namespace tad {
 
 // Passes over the pairs of indices of a factor, several in one launch (a launch costs as much as such a pass): workgroup b works
 // on the task with first <= b < first of the next one.
+// The kernel's arguments are read from memory, 850 cycles for whatever is asked for at once: what a thread needs first stands at the front.  With a
+// plan that was walked index by index and a program read line by line, softplus 512 x 384 x 200 with its gradients took 52.9 us (a pass over
+// pairs 8.0 and 11.3), so 47.8; 16 x 16 x 8 34.0 -> 26.3, of it 3.5 for the programs of all launches.
 struct PairTask {
-    ForwardPlan plan;      // pairs of indices -> elements of the operands
-    DevProg prog;
-    ArgPtrs args;
+    int32_t n, n_ops;
+    // the index map as two indices with 32-bit steps, where it comes down to that (inner > 0: the extent of the inner one): operand p is at
+    // at[p][outer index * step[0][p] + inner index * step[1][p]], and what is not an operand is the first one's first element
+    int32_t inner, step[2][kMaxArgs];
+    const void *at[kMaxArgs];
     const double *d;       // null: out = prog, else out = d * prog
     double *out;           // 64-bit results, or null:
     void *dx;              // ... results of the operands' type
     double *results[3];    // a program of several results (all else null): where they go, null for those nobody wants
-    int32_t n_ops, n, first;
+    DevProg prog;
+    ForwardPlan plan;      // pairs of indices -> elements of the operands
+    ArgPtrs args;
 };
 template <int N> struct PairTasks {
-    int32_t count;
+    int32_t count, first[N];
     PairTask task[N];
 };
 // Everything in 64 bits: of 32-bit operands nothing can overflow on the way to a product of factors.
 template <typename T, int FORM, int N>
 __global__ __launch_bounds__(256) void k_sep_pairs(const PairTasks<N> M) {
-    int w = 0;
-    while (w + 1 < M.count && (int)blockIdx.x >= M.task[w + 1].first) ++w;   // the same for the whole workgroup
+    int w = 0, first = 0;
+#pragma unroll
+    for (int i = 1; i < N; ++i)
+        if (i < M.count && (int)blockIdx.x >= M.first[i]) { w = i; first = M.first[i]; }   // the same for the whole workgroup
     const PairTask &t = M.task[w];
-    const int lin = ((int)blockIdx.x - t.first) * 256 + threadIdx.x;
-    if (lin >= t.n) return;
+    const int lin = ((int)blockIdx.x - first) * 256 + threadIdx.x, n = t.n, inner = t.inner;
+    int32_t outer_step[kMaxArgs], inner_step[kMaxArgs];
+    const T *at[kMaxArgs];
+#pragma unroll
+    for (int p = 0; p < kMaxArgs; ++p) {
+        outer_step[p] = t.step[0][p];
+        inner_step[p] = t.step[1][p];
+        at[p] = static_cast<const T *>(t.at[p]);
+    }
+    // all of it in one go, and with it a word of every line of the program
+    static_assert(kMaxArgs == 6 && kMaxProgOps == 64, "fields held here");
+    asm volatile("" :: "s"(n), "s"(inner), "s"(outer_step[0]), "s"(outer_step[1]), "s"(outer_step[2]), "s"(outer_step[3]), "s"(outer_step[4]),
+                 "s"(outer_step[5]), "s"(inner_step[0]), "s"(inner_step[1]), "s"(inner_step[2]), "s"(inner_step[3]), "s"(inner_step[4]),
+                 "s"(inner_step[5]), "s"(at[0]), "s"(at[1]), "s"(at[2]), "s"(at[3]), "s"(at[4]), "s"(at[5]), "s"(t.prog.result),
+                 "s"(t.prog.cst[0]), "s"(t.prog.n_words), "s"(t.prog.word[0]), "s"(t.prog.word[16]), "s"(t.prog.word[32]), "s"(t.prog.word[48]));
+    if (lin >= n) return;
     double v[kMaxArgs];
-    element_values<T>(t.plan, t.n_ops, ~0u, t.args, lin, v);
-    const double o = prog_eval<double, FORM>(t.prog, v, 0.0, [&](int n, double value) {
-        double *const to = n == 0 ? t.results[0] : n == 1 ? t.results[1] : t.results[2];
+    if (inner > 0) {
+        const int32_t o = (int32_t)((uint32_t)lin / (uint32_t)inner), i = lin - o * inner;
+        T x[kMaxArgs];
+#pragma unroll
+        for (int p = 0; p < kMaxArgs; ++p) x[p] = at[p][o * outer_step[p] + i * inner_step[p]];
+#pragma unroll
+        for (int p = 0; p < kMaxArgs; ++p) v[p] = (double)x[p];
+    } else {
+        element_values<T>(t.plan, t.n_ops, ~0u, t.args, lin, v);
+    }
+    const double o = prog_eval<double, FORM>(t.prog, v, 0.0, [&](int result, double value) {
+        double *const to = result == 0 ? t.results[0] : result == 1 ? t.results[1] : t.results[2];
         if (to) to[lin] = value;
     });
     if (!t.out && !t.dx) return;
@@ -96,7 +128,14 @@ __device__ __forceinline__ bool sum_element(const GatherPlan &P, const TI *__res
 #pragma unroll
             for (int u = 0; u < U; ++u) acc += (double)v[u];
         }
-        for (; it < n; ++it) { acc += (double)*p; p += st; }
+        if (it < n) {   // the rest is sent for together too
+            TI v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = p[it + u < n ? u * st : 0];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (it + u < n) acc += (double)v[u];
+        }
     }, group, groups);
     *sum = acc;
     return true;
@@ -158,6 +197,7 @@ __global__ __launch_bounds__(256) void k_sep_outer_block(const DevProg prog, con
         x[u] = s[at];
         d[u] = df ? df[at] : T(1);
     }
+    fetch_program(prog);
     prog_eval_block<T, U, true>(prog, v, x, o);
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -170,6 +210,46 @@ static ArgPtrs operand_pointers(const SepSide &side, const void *const *args) {
     ArgPtrs A{};
     for (size_t p = 0; p < side.operands.size(); ++p) A.p[p] = args[side.operands[p]];
     return A;
+}
+
+// The index map of a pass as two indices: those of extent one fall away, and an index whose step is a whole turn of the one behind it, for every
+// operand, is one with it.  No 32-bit form (three indices or more, far operands, no operand): inner = 0.
+template <typename T>
+static void two_indices(const ForwardPlan &P, PairTask &t) {
+    int32_t count = 0, extent[kMaxExt];
+    int64_t step[kMaxExt][kMaxArgs];   // from the innermost one
+    t.inner = 0;
+    for (int p = 0; p < kMaxArgs; ++p) {
+        t.at[p] = nullptr;
+        t.step[0][p] = t.step[1][p] = 0;
+    }
+    for (int d = P.n_f - 1; d >= 0; --d) {
+        if (P.f_shape[d] == 1) continue;
+        bool joins = count > 0;
+        for (int p = 0; p < t.n_ops; ++p) joins = joins && P.off[p][d] == step[count - 1][p] * extent[count - 1];
+        if (joins) {
+            extent[count - 1] *= P.f_shape[d];   // (at most the pairs there are)
+            continue;
+        }
+        extent[count] = P.f_shape[d];
+        for (int p = 0; p < t.n_ops; ++p) step[count][p] = P.off[p][d];
+        ++count;
+    }
+    if (count > 2 || t.n_ops < 1) return;
+    for (int p = 0; p < t.n_ops; ++p) {
+        int64_t reach = 0;
+        for (int d = 0; d < count; ++d) {
+            if (step[d][p] > INT32_MAX || step[d][p] < -INT32_MAX) return;
+            reach += (step[d][p] < 0 ? -step[d][p] : step[d][p]) * (extent[d] - 1);
+        }
+        if (reach > INT32_MAX) return;
+    }
+    t.inner = count ? extent[0] : 1;
+    for (int p = 0; p < kMaxArgs; ++p) {
+        const int of = p < t.n_ops ? p : 0;
+        t.at[p] = static_cast<const T *>(t.args.p[of]) + P.base0[of];
+        for (int d = 0; d < count && p < t.n_ops; ++d) t.step[1 - d][p] = (int32_t)step[d][p];
+    }
 }
 
 // passes over pairs of indices collected for one launch
@@ -199,7 +279,8 @@ struct PairPass {
         for (int n = 0; n < 3; ++n) t.results[n] = results ? results[n] : nullptr;
         t.n_ops = (int)sub.args.size();
         t.n = (int)sub.f_count;
-        t.first = blocks;
+        two_indices<T>(sub.fwd, t);
+        tasks.first[tasks.count - 1] = blocks;
         blocks += (t.n + 255) / 256;
         registers = registers && has_register_form(prog);
         return TAD_OK;
@@ -207,6 +288,7 @@ struct PairPass {
     template <int N> int launch() {
         PairTasks<N> M;
         M.count = tasks.count;
+        std::copy(tasks.first, tasks.first + N, M.first);
         std::copy(tasks.task, tasks.task + N, M.task);
         if (registers) TAD_LAUNCH("k_sep_pairs", (k_sep_pairs<T, 1, N>), dim3(blocks), dim3(256), 0, stream, M);
         else TAD_LAUNCH("k_sep_pairs", (k_sep_pairs<T, 0, N>), dim3(blocks), dim3(256), 0, stream, M);

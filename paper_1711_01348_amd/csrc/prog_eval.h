@@ -9,6 +9,13 @@
 
 namespace tad {
 
+// A program is read from the kernel's arguments line by line as it runs, 850 cycles a line that the scalar cache does not hold: a kernel that has
+// something else to wait for first asks for a word of every line here.
+__device__ __forceinline__ void fetch_program(const DevProg &P) {
+    static_assert(kMaxProgOps == 64, "four lines of words");
+    asm volatile("" :: "s"(P.result), "s"(P.cst[0]), "s"(P.n_words), "s"(P.word[0]), "s"(P.word[16]), "s"(P.word[32]), "s"(P.word[48]));
+}
+
 template <typename T> struct Fn;
 template <> struct Fn<float> {
     static __device__ __forceinline__ float exp_(float x) { return expf(x); }
