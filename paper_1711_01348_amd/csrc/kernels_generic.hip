@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include "bodies.h"
+#include "fetch_args.h"
 #include "gather_loop.h"
 #include "launch.h"
 #include "plan_dev.h"
@@ -141,10 +142,14 @@ __device__ __forceinline__ double forward_sum(const ForwardPlan &P, const ArgPtr
     return acc;
 }
 
+// up to this many results the plan is asked for at once (8 x 6 x 5 in 64 bits 4.5 -> 3.5 us): a longer launch finds most of its lines in the
+// scalar cache
+constexpr int kFetchElements = 1 << 18;
 template <int BODY, typename T>
 __global__ __launch_bounds__(256) void k_generic_forward(const ForwardPlan P, const ArgPtrs A,
                                                          T *__restrict__ f, int nf) {
     const int lin = blockIdx.x * blockDim.x + threadIdx.x;
+    if (nf <= kFetchElements) fetch_lines<sizeof(ForwardPlan)>(&P);
     if (lin >= nf) return;
     f[lin] = body_outer<BODY, T>((T)forward_sum<BODY, T>(P, A, lin, 0, 1));
 }
@@ -413,25 +418,38 @@ __global__ __launch_bounds__(64) void k_generic_gather_multi(const MultiGather M
 struct ListedOut {
     void *dx[kMaxArgs];   // per gradient of the list; null: not wanted
 };
-template <int BODY, typename T>
-__global__ __launch_bounds__(64) void k_generic_gather_listed(const TermList L, const ListedOut O, const ArgPtrs A,
+template <int BODY, typename T, typename LIST>
+__global__ __launch_bounds__(64) void k_generic_gather_listed(const LIST L, const ListedOut O, const ArgPtrs A,
                                                               const T *__restrict__ f, const T *__restrict__ df) {
     constexpr int NA = BodyTraits<BODY>::NA;
     const int e = blockIdx.x;
-    int g = 0;
-    while (g + 1 < L.n_grad && e >= L.first_element[g + 1]) ++g;   // the same for the whole workgroup
-    T *const dx = static_cast<T *>(O.dx[g]);
+    const int first_term = L.first_term[e], end_term = L.first_term[e + 1];
+    int first[kMaxArgs], operand[kMaxArgs];
+    T *out[kMaxArgs];
+#pragma unroll
+    for (int i = 0; i < kMaxArgs; ++i) {
+        first[i] = L.first_element[i];
+        operand[i] = L.operand[i];
+        out[i] = static_cast<T *>(O.dx[i]);
+    }
+    static_assert(kMaxArgs == 6, "fields held here");
+    asm volatile("" :: "s"(first_term), "s"(end_term), "s"(first[1]), "s"(first[5]), "s"(operand[0]), "s"(operand[5]), "s"(out[0]), "s"(out[1]),
+                 "s"(out[2]), "s"(out[3]), "s"(out[4]), "s"(out[5]), "s"(A.p[0]), "s"(A.p[NA - 1]), "s"(f), "s"(df));
+    T *dx = out[0];
+    int p = operand[0], begin = first[0];
+#pragma unroll
+    for (int i = 1; i < kMaxArgs; ++i)
+        if (i < L.n_grad && e >= first[i]) { dx = out[i]; p = operand[i]; begin = first[i]; }   // the same for the whole workgroup
     if (!dx) return;
-    const int p = L.operand[g];
     double acc = 0.0;
-    for (int t = L.first_term[e] + (int)threadIdx.x; t < (int)L.first_term[e + 1]; t += 64) {
+    for (int t = first_term + (int)threadIdx.x; t < end_term; t += 64) {
         T v[NA];
         for (int q = 0; q < NA; ++q) v[q] = static_cast<const T *>(A.p[q])[L.off[t][q]];
         const int of = L.off[t][kListSlots - 1];
         acc += (double)(df[of] * body_douter<BODY, T>(f[of], v) * body_dinner<BODY, T>(p, v));
     }
     const double total = wave_sum_all(acc);
-    if (threadIdx.x == 0) dx[e - L.first_element[g]] = (T)total;
+    if (threadIdx.x == 0) dx[e - begin] = (T)total;
 }
 
 template <int BODY, typename T>
@@ -469,8 +487,13 @@ static int launch_body(const tad_plan &pl, const void *const *args, const void *
             any = any || O.dx[g];
         }
         if (!any) return TAD_OK;
-        TAD_LAUNCH("k_generic_gather_listed", (k_generic_gather_listed<BODY, T>), dim3((unsigned)L.first_element[L.n_grad]),
-                   dim3(64), 0, s, L, O, A, static_cast<const T *>(f), static_cast<const T *>(df));
+        const dim3 grid((unsigned)L.first_element[L.n_grad]);
+        if (!pl.short_term_list.empty())
+            TAD_LAUNCH("k_generic_gather_listed", (k_generic_gather_listed<BODY, T, ShortTermList>), grid, dim3(64), 0, s, pl.short_term_list[0], O, A,
+                       static_cast<const T *>(f), static_cast<const T *>(df));
+        else
+            TAD_LAUNCH("k_generic_gather_listed", (k_generic_gather_listed<BODY, T, TermList>), grid, dim3(64), 0, s, L, O, A,
+                       static_cast<const T *>(f), static_cast<const T *>(df));
         return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
     }
     // an expression without aliases whose gradients are all small tensors with short sums: one launch for all

@@ -621,6 +621,18 @@ static void list_terms(tad_plan &pl) {
     for (int g = L.n_grad; g <= kMaxArgs; ++g) L.first_element[g] = e;
     for (int x = e; x <= kListElements; ++x) L.first_term[x] = (uint16_t)t;
     pl.term_list.push_back(L);
+    ShortTermList S{};
+    if (e > ShortTermList::kElements) return;
+    for (int x = 0; x < t; ++x)
+        for (int s = 0; s < kListSlots; ++s) {
+            if (L.off[x][s] > UINT16_MAX) return;
+            S.off[x][s] = (uint16_t)L.off[x][s];
+        }
+    S.n_grad = L.n_grad;
+    std::copy(L.first_element, L.first_element + kMaxArgs + 1, S.first_element);
+    std::copy(L.operand, L.operand + kMaxArgs, S.operand);
+    std::copy(L.first_term, L.first_term + ShortTermList::kElements + 1, S.first_term);
+    pl.short_term_list.push_back(S);
 }
 
 // plan of occurrence `occ` of the tensor given as operand `arg` (0: the operand itself, k: its k-th alias)

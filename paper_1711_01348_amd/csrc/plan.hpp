@@ -73,6 +73,7 @@ struct tad_plan {
     tad::FastParams fast;
     tad::ProgramBody prog;                     // TAD_BODY_PROGRAM only
     std::vector<tad::TermList> term_list;      // one entry if the terms of every gradient element are listed (small expressions)
+    std::vector<tad::ShortTermList> short_term_list;   // the same, if it fits
     tad::ProductPlan prod;                     // products that separate over the function indices (on: some run as dense products)
     bool worked_wide = false;                  // worked expression on the kernels with 64-bit sums (workspace: ws_full)
     int pattern_wide = TAD_FAMILY_GENERIC;     // row reduce or antidiagonal pattern on the kernels with 64-bit sums (workspace: ws_full)

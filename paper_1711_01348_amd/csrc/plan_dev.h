@@ -142,13 +142,18 @@ inline GatherShape sum_shape(const GatherPlan &P, long long n_elements, double t
 constexpr int kListElements = 1024;   // gradient elements of all operands together
 constexpr int kListTerms = 1024;      // terms of all of them together
 constexpr int kListSlots = 5;         // offsets per term: up to four operands, then f (and df)
-struct TermList {
+template <typename OFFSET, int ELEMENTS, int TERMS> struct TermListOf {
+    static constexpr int kElements = ELEMENTS;
     int32_t n_grad;
     int32_t first_element[kMaxArgs + 1];   // gradient g owns the element numbers first_element[g] .. first_element[g + 1] - 1
     int32_t operand[kMaxArgs];             // whose gradient g is
-    uint16_t first_term[kListElements + 1];   // element e sums the terms first_term[e] .. first_term[e + 1] - 1
-    int32_t off[kListTerms][kListSlots];
+    uint16_t first_term[ELEMENTS + 1];   // element e sums the terms first_term[e] .. first_term[e + 1] - 1
+    OFFSET off[TERMS][kListSlots];
 };
+using TermList = TermListOf<int32_t, kListElements, kListTerms>;
+// The list is an argument of the launch, which the host copies each time, so a small one is passed in a smaller form.  8 x 6 x 5 in 64 bits,
+// forward and gradients, two launches that wait for the host: 9.3 -> 9.0 us.
+using ShortTermList = TermListOf<uint16_t, 256, kListTerms>;   // 10.8 instead of 22.6 KB
 
 struct ForwardPlan {
     int32_t n_f, n_sum;
