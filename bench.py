@@ -36,11 +36,11 @@ MIN_WINDOW_MS = 20.0            # the workloads beside the headline are timed fo
 # 256 MiB copy in the same run (summaries under profiles/).  Each entry carries the SHA-256 prefix of the kernel source
 # the counters were taken with; once that file changes the entry is stale and the bench line reports traffic = null.
 MEASURED_TRAFFIC = {
-    "cfg3": dict(source="kernels_worked.hip", sha256="c4542a3a73030316", fetch_bytes=521.5 * 2**20, write_bytes=9.5 * 2**20,
+    "cfg3": dict(source="kernels_worked.hip", sha256="1f4c63bc74be30ff", fetch_bytes=521.5 * 2**20, write_bytes=9.5 * 2**20,
             summary="profiles/worked_8192x8192x5_f32.md"),
-    "cfg4": dict(source="kernels_mfma.hip", sha256="0752fdee68d78bc8", fetch_bytes=160.5 * 2**20, write_bytes=32.2 * 2**20,
+    "cfg4": dict(source="kernels_mfma_split.hip", sha256="5951ad71d1822ffc", fetch_bytes=60.3 * 2**20, write_bytes=64.0 * 2**20,
             summary="profiles/worked_mfma_4096x4096x256_f32.md"),
-    "matmul": dict(source="kernels_split.hip", sha256="3979d7bbcfdbd32a", fetch_bytes=1001.8 * 2**20, write_bytes=64.0 * 2**20,
+    "matmul": dict(source="kernels_split.hip", sha256="70483809f6744806", fetch_bytes=1166.0 * 2**20, write_bytes=64.0 * 2**20,
             summary="profiles/contraction_4096x4096x4096_f32.md"),
     "cfg2_1": dict(source="kernels_patterns.hip", sha256="82a47a45178e317d", fetch_bytes=64.3 * 2**20, write_bytes=0.1 * 2**20,
             summary="profiles/row_reduce_4096x4096_f32.md"),
