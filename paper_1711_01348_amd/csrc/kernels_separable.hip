@@ -17,6 +17,7 @@
 #include <algorithm>
 
 #include "element.h"
+#include "fetch_args.h"
 #include "gather_loop.h"
 #include "launch.h"
 #include "plan_dev.h"
@@ -146,6 +147,7 @@ __global__ __launch_bounds__(LAYOUT == kSumColumns ? 1024 : 256) void k_sep_sum(
                                                                                T *__restrict__ dx, int n, int accumulate,
                                                                                double *__restrict__ partial, int32_t *__restrict__ flag) {
     const int tid = threadIdx.x;
+    fetch_gather(P, kSlotF);
     int lin = -1;
     bool live = false;
     double total = 0.0;
