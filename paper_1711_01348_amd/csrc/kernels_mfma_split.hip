@@ -16,14 +16,18 @@
 // kernels_split.hip) and, in the gradients, G, whose 134 MB are read twice and whose parts are formed on the vector ALU while both wavefronts of a
 // SIMD wait for them.  Tried: fragments read from LDS half a stage ahead (132 -> 146 us), wavefronts of a SIMD that form G in turn (125 -> 137).
 //
-// A part that is no finite number turns every result it takes part in into one that is not finite, so the results tell whether all of it stayed
-// in range: if they do not, a flag is set and the kernels of kernels_mfma.hip, launched behind these, do the work again.
+// Parts and their products have to stay normal numbers, as in kernels_split.hip: what is split is 2^24 times as large, so that the third part of the
+// smallest 32-bit number is one, and the results are scaled back.  (Unscaled, G of 2^-115 gave da that was off by 2e-6, of 2^-118 by 2e-5, and db,
+// whose G carries c, by more.)  A part that is no finite number turns every result it takes part in into one that is not finite, so the results tell
+// whether all of it stayed below the upper end: if they do not (some sum of products beyond 2^80), a flag is set and the kernels of kernels_mfma.hip,
+// launched behind these, do the work again.
 #include <hip/hip_runtime.h>
 
 #include "launch.h"
 #include "launch_geom.h"
 #include "mfma_split.h"
 #include "profile.h"
+#include "split.h"
 
 namespace tad {
 
@@ -36,15 +40,18 @@ typedef __attribute__((address_space(3))) void *lds_ptr;
 
 constexpr int kFragment = 3 * 64;       // pieces of a fragment of 32 rows and 16 terms
 constexpr float kLog2eL = 1.4426950408889634f;
+constexpr float kLongBack = 1.f / (kSplitScale * kSplitScale);   // of a sum of products
 
 __device__ __forceinline__ int long_acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
+// the parts of v[] times kSplitScale
 __device__ __forceinline__ void split_three(const float (&v)[8], piece (&out)[3]) {
     bf16x8 p1, p2, p3;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        p1[e] = (__bf16)v[e];
-        const float r = v[e] - (float)p1[e];
+        const float sv = v[e] * kSplitScale;
+        p1[e] = (__bf16)sv;
+        const float r = sv - (float)p1[e];
         p2[e] = (__bf16)r;
         p3[e] = (__bf16)(r - (float)p2[e]);
     }
@@ -247,7 +254,7 @@ __global__ __launch_bounds__(256, 3) void k_long_forward(const piece *__restrict
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 finite = finite && __builtin_isfinite(ab[e]);
-                v[e] = __builtin_amdgcn_exp2f(fmaf(rv[1], rv[0] + nbj[e] + 2.f * ab[e], rv[2]));
+                v[e] = __builtin_amdgcn_exp2f(fmaf(rv[1], rv[0] + nbj[e] + 2.f * kLongBack * ab[e], rv[2]));
             }
             if (i < I && j < J) *reinterpret_cast<float4l *>(f + (size_t)i * J + j) = v;   // (J % 4 == 0: the four columns exist together)
         }
@@ -403,7 +410,7 @@ __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *c
 #pragma unroll
         for (int y = 0; y < RY; ++y)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) own[(32 * x + long_acc_row(r, lane)) * LO + 32 * y + (lane & 31)] = big[x][y][r] + small[x][y][r];
+            for (int r = 0; r < 16; ++r) own[(32 * x + long_acc_row(r, lane)) * LO + 32 * y + (lane & 31)] = (big[x][y][r] + small[x][y][r]) * kLongBack;
     bool finite = true;
     const int col = lane % (W / 4) * 4, k = (GROUP * z + wn * RY) * 32 + col;
     if (k < K) {   // (K % 32 == 0: the four columns exist together)

@@ -34,13 +34,14 @@ def evaluate(plan, args, df, ws_bytes, wanted=(0, 1, 2, 3), f=None):
     return [out] + [grads[q] for q in wanted]
 
 
-def exact(args, df, K):
+def exact(args, df, K, given=None):
+    """f and the gradients in 64 bits, those of a given f if there is one."""
     import torch
     a, b, c, d = [t.double() for t in args]
     df, I = df.double(), df.shape[0]
     ci, na, nb = c.diagonal()[:I], (a * a).sum(1), (b * b).sum(1)
     f = torch.exp(-(ci[:, None] * (na[:, None] + nb[None, :] + 2 * (a @ b.t().contiguous())) + (d ** 3).unfold(0, K, 1)[:I].sum(1)[:, None]))
-    g = df * f
+    g = df * (f if given is None else given.double())
     r, P = g.sum(1), g @ b
     dc, dd = torch.zeros_like(c), torch.zeros_like(d)
     dc.diagonal()[:I].copy_(-(na * r + 2 * (a * P).sum(1) + g @ nb))
@@ -69,6 +70,34 @@ def test_error_is_no_larger_than_that_of_the_32_bit_kernels(I, J, K, c_extra):
     assert not rest.any()
 
 
+def errors(tensors, want):
+    return [((t.double() - w).norm() / w.norm()).item() for t, w in zip(tensors, want)]
+
+
+# small numbers: what they do to a, b, df and a given f
+SMALL = {"df": lambda a, b, df, f: (a, b, df * 2.0 ** -115, None), "decayed_f": lambda a, b, df, f: (a, b, df, f * 2.0 ** -118),
+         "a_and_b": lambda a, b, df, f: (a * 2.0 ** -118, b * 2.0 ** -118, df * 2.0 ** 60, None),
+         "denormals": lambda a, b, df, f: (a * 2.0 ** 24, b * 2.0 ** 24, df * 2.0 ** -130, f)}
+
+
+@pytest.mark.parametrize("I,J,K", [(1150, 1028, 64), (1409, 1540, 128), (1921, 1148, 256)])
+@pytest.mark.parametrize("small", SMALL)
+def test_small_numbers_are_not_less_exact_than_on_the_32_bit_kernels(I, J, K, small):
+    """da, db, dc, which take products, against 64 bits (dc of the third kind, 2^-176, is 0 in 32 bits)."""
+    import torch
+    from paper_1711_01348_amd import binding as B
+    expr, (a, b, c, d), df = tensors(I, J, K)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    a, b, df, f = SMALL[small](a, b, df, torch.rand((I, J), generator=g, device="cuda"))
+    args, plan = [a, b, c.abs(), d], B.Plan(expr)
+    split, plain = (evaluate(plan, args, df, n, f=f)[1:] for n in (plan.workspace_bytes, plan.workspace_bytes - 16))
+    assert not torch.equal(split[0], plain[0])
+    want = exact(args, df, K, f)[1:]
+    for s, p in list(zip(errors(split, want), errors(plain, want)))[:3]:
+        assert s <= 1.02 * p, (s, p)
+
+
 @pytest.mark.parametrize("wanted", [(0,), (1,), (2,), (3,), (0, 3), (1, 2)])
 def test_any_of_the_gradients(wanted):
     import torch
@@ -94,14 +123,14 @@ def test_pieces_of_long_sums_for_few_rows(I, J, K):
         assert check.within(g.cpu().numpy(), w.cpu().numpy(), "f32"), check.errors(g.cpu().numpy(), w.cpu().numpy())
 
 
-@pytest.mark.parametrize("what", ["inf_df", "nan_df", "huge_df", "inf_a", "huge_b"])
+@pytest.mark.parametrize("what", ["inf_df", "nan_df", "huge_df", "large_df", "inf_a", "huge_b"])
 def test_what_is_not_finite_is_left_to_the_32_bit_kernels(what):
     import torch
     from paper_1711_01348_amd import binding as B
     expr, args, df = tensors(2048, 3840, 128)
     f = torch.rand_like(df)
     if what.endswith("df"):
-        df[2047, 3839] = {"inf": float("inf"), "nan": float("nan"), "huge": 3.4e38}[what[:-3]]
+        df[2047, 3839] = {"inf": float("inf"), "nan": float("nan"), "huge": 3.4e38, "large": 2.0 ** 110}[what[:-3]]   # (large: times 2^24, not finite)
     else:
         args[0 if what == "inf_a" else 1][5, 127] = float("inf") if what == "inf_a" else 3.4e38
     plan = B.Plan(expr)
@@ -109,5 +138,5 @@ def test_what_is_not_finite_is_left_to_the_32_bit_kernels(what):
     for s, p in zip(split, plain):
         assert torch.equal(s.isnan(), p.isnan()) and torch.equal(s.isinf(), p.isinf())
         both = s.isfinite()
-        # rows with 3.4e38 among their terms: the order of the pieces differs, the terms do not
+        # rows with a large number among their terms: the order of the pieces differs, the terms do not
         assert bool(((s[both].double() - p[both].double()).abs() <= 1e-5 * p[both].double().abs() + 2e-5 * p[both].double().pow(2).mean().sqrt()).all())
