@@ -389,13 +389,20 @@ __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *c
         const bool work = have > 0 && c0 >= begin;   // the same for the wavefront
         load_b(set ^ 1, c0 + 32);
         if (work) products(set, 0);
+        // G has to be here now, and the other operand's copies to LDS, half a stage old, are waited for with it: the barrier below then needs no
+        // count of the loads of G that are issued in between and may still be on their way
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
         stage_g(c0 + 32, set ^ 1);
         load_g(c0 + 64);
         if (work) products(set, 1);
-        // the next stage is in LDS; the loads of G, issued behind those of the other operand, may still be on their way
+        // what this wavefront has written and read of LDS is done
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(TRANS ? 0x4071 : 0x0076);   // vmcnt(17), vmcnt(6); lgkmcnt(0)
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     }
