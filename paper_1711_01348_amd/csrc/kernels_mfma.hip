@@ -230,21 +230,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 struct MfmaTiles {
     float a[64 * MF_LD], b[32][256], red[8][64];
 };
-template <bool TRANS_A>
+// The matrix instructions add two terms at a time, and every addition rounds the chain's sum: an eighth of the sum, at most 256 terms, is added up by itself
+// and then to the total (TOTALS; not needed where the pieces are no longer than that).  Error of da against 64 bits with one chain to a piece of up to the
+// whole sum / with totals / with eight pieces of one chain, 4096 x 4096 x 640: 4.2e-7 / 2.3e-7 / 3.0e-7; a sum of 8192 terms of one sign 6.0e-7 / 7.0e-8 / 1.6e-7.
+// All four gradients 471 / 479 / 536 us (4096 x 4096 x 640), 256 x 1024 x 64 16.7 / 17.5 / 33.5.
+__host__ __device__ inline int mfma_chain(int terms) { return MF_KT * std::min(8, (terms + 255) / 256); }
+template <bool TRANS_A, bool TOTALS>
 __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int split, const float *__restrict__ f, const float *__restrict__ df,
                                                  const float *__restrict__ bmat, const float *__restrict__ rowv, const float *__restrict__ nb,
                                                  float *__restrict__ out, float *__restrict__ sums, int I, int J, int K, int chunk) {
     float (*const As)[TRANS_A ? 64 : MF_LD] = reinterpret_cast<float (*)[TRANS_A ? 64 : MF_LD]>(S.a);
     float (*const Bs)[256] = S.b, (*const tred)[64] = S.red;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave & 1, wn = wave >> 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
     const int Mtot = TRANS_A ? J : I, Ctot = TRANS_A ? I : J;
     const int m0 = tile * 64, n0 = blockIdx.y * 256;
     const int cs = split * chunk, ce = min(Ctot, cs + chunk);
-    float16v acc[2];
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[x][r] = 0.f;
+    const int chain = TOTALS ? mfma_chain(Ctot) : chunk;
+    const float16v zero16 = {};
+    float16v acc[2] = {zero16, zero16}, total[2] = {zero16, zero16};
     float4v ga, gb[4];
     // what the loads of G bring in; the products and the sums on the side are formed one tile later, when the
     // tile is staged, so that nothing waits for these loads before the matrix instructions of the current tile
@@ -267,8 +270,7 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
         }
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            const int idx = tid + 512 * p, kk = idx >> 6, q = idx & 63;
-            const int cc = c0 + kk, n = n0 + 4 * q;
+            const int cc = c0 + wave + 8 * p, n = n0 + 4 * lane;
             gb[p] = (cc < ce && n < K) ? *reinterpret_cast<const float4v *>(bmat + (size_t)cc * K + n) : zero4;
         }
     };
@@ -284,7 +286,7 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
     };
     gload(cs);
     const int mrow = lane & 31, kof = lane >> 5;
-    for (int c0 = cs; c0 < ce; c0 += MF_KT) {
+    auto stage = [&](int c0) {
         gprep();
         if (!TRANS_A) {
 #pragma unroll
@@ -293,10 +295,7 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
             *reinterpret_cast<float4v *>(&As[g_row][4 * g_quad]) = ga;
         }
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int idx = tid + 512 * p, kk = idx >> 6, q = idx & 63;
-            *reinterpret_cast<float4v *>(&Bs[kk][4 * q]) = gb[p];
-        }
+        for (int p = 0; p < 4; ++p) *reinterpret_cast<float4v *>(&Bs[wave + 8 * p][4 * lane]) = gb[p];
         __syncthreads();
         if (c0 + MF_KT < ce) gload(c0 + MF_KT);
         auto afrag = [&](int kk) -> float { return TRANS_A ? As[kk + kof][32 * wm + mrow] : As[32 * wm + mrow][kk + kof]; };
@@ -317,6 +316,16 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
             a0 = na0; b0 = nb0; b1 = nb1;
         }
         __syncthreads();
+    };
+#pragma unroll 1
+    for (int first = cs; first < ce; first += chain) {
+        acc[0] = acc[1] = zero16;
+        const int end = min(ce, first + chain);
+#pragma unroll 1
+        for (int c0 = first; c0 < end; c0 += MF_KT) stage(c0);
+        if constexpr (!TOTALS) break;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) total[x] += acc[x];
     }
 #pragma unroll
     for (int tn = 0; tn < 2; ++tn) {
@@ -324,7 +333,7 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int m = m0 + wm * 32 + acc_row(r, lane);
-            if (m < Mtot && n < K) out[((size_t)split * Mtot + m) * K + n] = acc[tn][r];
+            if (m < Mtot && n < K) out[((size_t)split * Mtot + m) * K + n] = (TOTALS ? total : acc)[tn][r];
         }
     }
     if (blockIdx.y != 0) return;
@@ -364,14 +373,15 @@ struct MfmaSide {
     float *out, *sums;
     int chunk;
 };
+template <bool TOTALS>
 __global__ __launch_bounds__(512, 4) void k_mfma_backward(const float *__restrict__ f, const float *__restrict__ df, const float *__restrict__ rowv,
                                                           const float *__restrict__ nb, const MfmaSide P, const MfmaSide T, int I, int J, int K, int first,
                                                           int n_j, int n_i, const int *__restrict__ redo) {
     if (redo && !*redo) return;   // done on the bf16 matrix cores
     __shared__ __attribute__((aligned(16))) MfmaTiles S;
     const int id = blockIdx.x, second = id - first;   // (neighbours share a tile of rows)
-    if (id < first) mfma_contraction<false>(S, id / n_j, id % n_j, f, df, P.mat, rowv, nb, P.out, P.sums, I, J, K, P.chunk);
-    else mfma_contraction<true>(S, second / n_i, second % n_i, f, df, T.mat, rowv, nb, T.out, T.sums, I, J, K, T.chunk);
+    if (id < first) mfma_contraction<false, TOTALS>(S, id / n_j, id % n_j, f, df, P.mat, rowv, nb, P.out, P.sums, I, J, K, P.chunk);
+    else mfma_contraction<true, TOTALS>(S, second / n_i, second % n_i, f, df, T.mat, rowv, nb, T.out, T.sums, I, J, K, T.chunk);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -647,8 +657,12 @@ int mfma_backward(const tad_plan &pl, const void *const *args, const void *f_, c
     if (rc) return rc;
     // the row pass always runs: r_i feeds da, dc and dd; the column pass only for db
     const int tiles = (I + 63) / 64, columns = (K + 255) / 256, first = tiles * n.n_j, blocks_both = first + (cols ? (J + 63) / 64 * n.n_i : 0);
-    TAD_LAUNCH("k_mfma_backward", k_mfma_backward, dim3(blocks_both, columns), dim3(512), 0, s, f, df, (const float *)w.rowv, (const float *)w.nb, P, T, I, J, K, first,
-               n.n_j, n.n_i, redo);
+#define TAD_CONTRACTIONS(TOTALS)                                                                                                                          \
+    TAD_LAUNCH("k_mfma_backward", k_mfma_backward<TOTALS>, dim3(blocks_both, columns), dim3(512), 0, s, f, df, (const float *)w.rowv, (const float *)w.nb, P, T, I, J, \
+               K, first, n.n_j, n.n_i, redo)
+    if (n.chunk_j > mfma_chain(J) || (cols && n.chunk_i > mfma_chain(I))) TAD_CONTRACTIONS(true);
+    else TAD_CONTRACTIONS(false);
+#undef TAD_CONTRACTIONS
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
     MfmaFinish F{a, b, d, w.rowv, P.out, T.out, P.sums, T.sums, (float *)dx[0], (float *)dx[1], (float *)dx[2], (float *)dx[3], (long long)pl.arg_count[2],
                  I, J, K, c_ld, (int)pl.arg_count[3], n.n_j, n.n_i, (I + 3) / 4, cols ? (J + 3) / 4 : 0, 0};
