@@ -271,15 +271,16 @@ __global__ __launch_bounds__(256, 3) void k_long_forward(const piece *__restrict
 struct LongSide {
     const piece *parts;
     float *out, *sums;
+    int chunk;                 // terms of a piece
 };
 struct LongBackward {
     const float *f, *df, *rowv, *nb;
     LongSide side[2];
     int *redo;
-    int I, J, K, chunk;
+    int I, J, K;
     int first, n_j, n_i;       // workgroups of the first sum, pieces of either
 };
-template <bool TRANS, int RX, int RY, int WN>
+template <bool TRANS, int RX, int RY, int WN, bool TOTALS>
 __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *const smem, const int tile, const int split) {
     constexpr int GROUP = RY * WN;                             // fragments of 32 columns
     static_assert(RX * (8 / WN) == 4, "128 rows");
@@ -287,7 +288,7 @@ __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *c
     const float *const __restrict__ f = L.f, *const __restrict__ df = L.df, *const __restrict__ rowv = L.rowv, *const __restrict__ nb = L.nb;
     const piece *const __restrict__ parts = L.side[TRANS].parts;
     float *const __restrict__ out = L.side[TRANS].out, *const __restrict__ sums = L.side[TRANS].sums;
-    const int I = L.I, J = L.J, K = L.K, chunk = L.chunk;
+    const int I = L.I, J = L.J, K = L.K, chunk = L.side[TRANS].chunk;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
     const int M = TRANS ? J : I, C = TRANS ? I : J, m0 = tile * 128, z = blockIdx.y;
     const int begin = split * chunk, end = min(C, begin + chunk), wide = min(GROUP, K / 32 - GROUP * z);
@@ -357,13 +358,15 @@ __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *c
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
     };
-    float16l big[RX][RY], small[RX][RY];
+    // TOTALS: an eighth of the sum, at most 256 terms, is added up by itself and then to the total.  Tall tiles have no registers for three sums: their
+    // smaller products start from zero for every fragment of terms and are added to the larger ones on the vector ALU.
+    constexpr bool JOINED = TOTALS && RX > 1;
+    const float16l zero = {};
+    float16l big[RX][RY], small[RX][RY], total[RX][RY];
 #pragma unroll
     for (int x = 0; x < RX; ++x)
 #pragma unroll
-        for (int y = 0; y < RY; ++y)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) big[x][y][r] = small[x][y][r] = 0.f;
+        for (int y = 0; y < RY; ++y) big[x][y] = small[x][y] = total[x][y] = zero;
     const int have = min(RY, wide - wn * RY);   // column fragments of this wavefront that exist (may be negative)
     auto products = [&](int set, int qb) {      // (columns that do not exist are computed from the last one and not stored)
         const piece *S = smem + set * STAGE;
@@ -378,8 +381,18 @@ __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *c
 #pragma unroll
         for (int y = 0; y < RY; ++y)
 #pragma unroll
-            for (int x = 0; x < RX; ++x) six_products(av[x], bv[y], big[x][y], small[x][y]);
+            for (int x = 0; x < RX; ++x) {
+                if constexpr (JOINED) {
+                    float16l rest = zero;
+                    six_products(av[x], bv[y], big[x][y], rest);
+                    big[x][y] += rest;
+                } else {
+                    six_products(av[x], bv[y], big[x][y], small[x][y]);
+                }
+            }
     };
+    const int chain = 32 * min(8, (C + 255) / 256);
+    int left = chain;
     load_g(begin);
     int set = 1;
     // The first pass only brings the first stage to LDS.  Nothing here depends on whether there is a next stage (it is then the last one again, and
@@ -399,6 +412,18 @@ __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *c
         stage_g(c0 + 32, set ^ 1);
         load_g(c0 + 64);
         if (work) products(set, 1);
+        if constexpr (TOTALS) {
+            if (work && (left -= 32) == 0) {
+                left = chain;
+#pragma unroll
+                for (int x = 0; x < RX; ++x)
+#pragma unroll
+                    for (int y = 0; y < RY; ++y) {
+                        total[x][y] += big[x][y];
+                        big[x][y] = zero;
+                    }
+            }
+        }
         // what this wavefront has written and read of LDS is done
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
@@ -417,7 +442,8 @@ __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *c
 #pragma unroll
         for (int y = 0; y < RY; ++y)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) own[(32 * x + long_acc_row(r, lane)) * LO + 32 * y + (lane & 31)] = (big[x][y][r] + small[x][y][r]) * kLongBack;
+            for (int r = 0; r < 16; ++r) own[(32 * x + long_acc_row(r, lane)) * LO + 32 * y + (lane & 31)] =
+                    ((TOTALS ? total[x][y][r] : 0.f) + (JOINED ? big[x][y][r] : big[x][y][r] + small[x][y][r])) * kLongBack;
     bool finite = true;
     const int col = lane % (W / 4) * 4, k = (GROUP * z + wn * RY) * 32 + col;
     if (k < K) {   // (K % 32 == 0: the four columns exist together)
@@ -449,14 +475,14 @@ __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *c
 }
 
 // Both contractions in one launch: tiles of rows i, then tiles of rows j.
-template <int RX, int RY, int WN>
+template <int RX, int RY, int WN, bool TOTALS>
 __global__ __launch_bounds__(512, 2) void k_long_backward(const LongBackward L) {
     __shared__ piece smem[2 * (4 + RY * WN) * 2 * kFragment];
     // the dies take workgroups in turn: each gets a contiguous range of them, of as few pieces of the tensors as can be
     const int total = gridDim.x, id = (int)blockIdx.x < total / 8 * 8 ? (int)blockIdx.x % 8 * (total / 8) + (int)blockIdx.x / 8 : (int)blockIdx.x, second = id - L.first;
     const int ti = L.first / L.n_j;
-    if (id < L.first) long_contraction<false, RX, RY, WN>(L, smem, id % ti, id / ti);
-    else long_contraction<true, RX, RY, WN>(L, smem, second % ((total - L.first) / L.n_i), second / ((total - L.first) / L.n_i));
+    if (id < L.first) long_contraction<false, RX, RY, WN, TOTALS>(L, smem, id % ti, id / ti);
+    else long_contraction<true, RX, RY, WN, TOTALS>(L, smem, second % ((total - L.first) / L.n_i), second / ((total - L.first) / L.n_i));
 }
 
 int long_forward(const LongProducts &L, float *f, hipStream_t s) {
@@ -470,20 +496,21 @@ int long_forward(const LongProducts &L, float *f, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }
 
-int long_backward(const LongProducts &L, const float *f, const float *df, float *P_out, float *rowp, int n_j, float *T_out, float *colp, int n_i, int chunk,
-                  hipStream_t s) {
+int long_backward(const LongProducts &L, const float *f, const float *df, float *P_out, float *rowp, int n_j, int chunk_j, float *T_out, float *colp, int n_i,
+                  int chunk_i, bool totals, hipStream_t s) {
     LongPrep P{L.a, L.b, L.c, L.d, L.rowv, L.nb, static_cast<piece *>(L.parts), nullptr, L.redo, L.I, L.J, L.K, L.c_ld, (L.I + 31) / 32, 0, 0};
     P.pb = P.pa + (size_t)(2 * P.blocks_a) * (L.K / 32) * kFragment;
     TAD_LAUNCH("k_long_prep", k_long_prep<true>, dim3(P.blocks_a + (L.J + 31) / 32), dim3(256), 0, s, P);
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
     const int first = (L.I + 127) / 128 * n_j, blocks = first + (L.J + 127) / 128 * n_i;
-    const LongBackward B{f, df, L.rowv, L.nb, {{P.pb, P_out, rowp}, {P.pa, T_out, colp}}, L.redo, L.I, L.J, L.K, chunk, first, n_j, n_i};
-#define TAD_LONG(RX, RY, WN)                                                                                                                     \
-    TAD_LAUNCH("k_long_backward", (k_long_backward<RX, RY, WN>), dim3(blocks, (L.K / 32 + RY * WN - 1) / (RY * WN)), dim3(512), 0, s, B)
+    const LongBackward B{f, df, L.rowv, L.nb, {{P.pb, P_out, rowp, chunk_j}, {P.pa, T_out, colp, chunk_i}}, L.redo, L.I, L.J, L.K, first, n_j, n_i};
+#define TAD_LONG(RX, RY, WN, TOTALS)                                                                                                             \
+    TAD_LAUNCH("k_long_backward", (k_long_backward<RX, RY, WN, TOTALS>), dim3(blocks, (L.K / 32 + RY * WN - 1) / (RY * WN)), dim3(512), 0, s, B)
     // no more columns than there are
-    if (L.K <= 64) TAD_LONG(1, 1, 2);
-    else if (L.K <= 128) TAD_LONG(1, 2, 2);
-    else TAD_LONG(2, 2, 4);
+    if (L.K <= 64) TAD_LONG(1, 1, 2, true);
+    else if (L.K <= 128) TAD_LONG(1, 2, 2, true);
+    else if (totals) TAD_LONG(2, 2, 4, true);
+    else TAD_LONG(2, 2, 4, false);
 #undef TAD_LONG
     return hipGetLastError() == hipSuccess ? TAD_OK : TAD_EDEVICE;
 }

@@ -98,24 +98,24 @@ def test_small_numbers_are_not_less_exact_than_on_the_32_bit_kernels(I, J, K, sm
         assert s <= 1.02 * p, (s, p)
 
 
-@pytest.mark.parametrize("side", ["a", "b"])
-def test_long_sums_of_one_sign(side):
+# tall tiles in short pieces, in long ones with totals in the kernel; low tiles
+@pytest.mark.parametrize("I,J,K,side", [(8192, 8192, 160, "a"), (8192, 8192, 160, "b"), (512, 8192, 160, "a"), (8192, 512, 256, "b"), (8192, 8192, 32, "a"), (8192, 8192, 96, "b")])
+def test_long_sums_of_one_sign(I, J, K, side):
     """da (P, a small) or db (T, b small) of 8192 terms of one sign, the longest sums and the fewest pieces of a size.  Eight chains of additions of two terms
     round their sums, of up to an eighth, C / 16 times each, and seven more times: independent roundings of at most 2^-24, 2^-24 / sqrt(3) on average, of partial
     sums that grow evenly, are 2^-24 / sqrt(3) sqrt(C / 384 + 8 / 3) of the result together."""
     import math
     import torch
     from paper_1711_01348_amd import binding as B
-    I = J = 8192
-    expr, args, df = tensors(I, J, 160)
+    expr, args, df = tensors(I, J, K)
     args, df = [t.abs() for t in args], df.abs()
     args[0 if side == "a" else 1] *= 1e-3
     plan, q = B.Plan(expr), 1 if side == "a" else 2
     g = torch.Generator(device="cuda")
     g.manual_seed(4)
     f = torch.rand((I, J), generator=g, device="cuda")
-    want = exact(args, df, 160, f)[q]
-    for ws_bytes in (plan.workspace_bytes - 16,):
+    want = exact(args, df, K, f)[q]
+    for ws_bytes in (plan.workspace_bytes, plan.workspace_bytes - 16):
         got = evaluate(plan, args, df, ws_bytes, f=f)[q]
         assert errors([got], [want])[0] <= 2.0 ** -24 / math.sqrt(3) * math.sqrt(8192 / 384 + 8 / 3)
 
