@@ -224,11 +224,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // out[(split * Mtot + m) * K + n]
 // ---------------------------------------------------------------------------------------------
 // While G is staged, the same thread keeps meeting the same rows (TRANS_A = false) or the same columns
-// (TRANS_A = true), so the plain sums over the collapsed index are accumulated on the side:
+// (TRANS_A = true), so the plain sums over the collapsed index are accumulated on the side, those of a chain in 32 bits, all of
+// them in 64 (in 32 bits they drift with the length of the pieces: dc of 8192 x 8192 x 256 1.6e-7, now 7.5e-8; eight pieces in 32 bits 1.1e-7):
 //   TRANS_A = false:  sums[(split * 2 + 0) * I + i] = sum_j G_ij,  sums[(split * 2 + 1) * I + i] = sum_j G_ij |b_j|^2
 //   TRANS_A = true:   sums[split * J + j] = sum_i c_ii G_ij
 struct MfmaTiles {
-    float a[64 * MF_LD], b[32][256], red[8][64];
+    float a[64 * MF_LD], b[32][256];
+    double red[8][64];
 };
 // The matrix instructions add two terms at a time, and every addition rounds the chain's sum: an eighth of the sum, at most 256 terms, is added up by itself
 // and then to the total (TOTALS; not needed where the pieces are no longer than that).  Error of da against 64 bits with one chain to a piece of up to the
@@ -240,7 +242,8 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
                                                  const float *__restrict__ bmat, const float *__restrict__ rowv, const float *__restrict__ nb,
                                                  float *__restrict__ out, float *__restrict__ sums, int I, int J, int K, int chunk) {
     float (*const As)[TRANS_A ? 64 : MF_LD] = reinterpret_cast<float (*)[TRANS_A ? 64 : MF_LD]>(S.a);
-    float (*const Bs)[256] = S.b, (*const tred)[64] = S.red;
+    float (*const Bs)[256] = S.b;
+    double (*const tred)[64] = S.red;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
     const int Mtot = TRANS_A ? J : I, Ctot = TRANS_A ? I : J;
     const int m0 = tile * 64, n0 = blockIdx.y * 256;
@@ -254,8 +257,9 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
     float4v rdf, rf, rnv;
     float rc;
     const float4v zero4 = {0.f, 0.f, 0.f, 0.f};
-    float sr = 0.f, sq = 0.f;   // TRANS_A = false: row sums of the thread's row
+    float sr = 0.f, sq = 0.f;   // TRANS_A = false: row sums of the thread's row, of one chain
     float4v st = zero4;         // TRANS_A = true: column sums of the thread's four columns
+    double tr = 0.0, tq = 0.0, tt[4] = {};   // ... and of those before
     // the four elements of G of the thread: i = m0 + g_row, j = c0 + 4 g_quad, or (TRANS_A) i = c0 + g_row, j = m0 + 4 g_quad
     const int g_row = TRANS_A ? tid >> 4 : tid >> 3, g_quad = TRANS_A ? tid & 15 : tid & 7;
     auto gload = [&](int c0) {
@@ -323,6 +327,15 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
         const int end = min(ce, first + chain);
 #pragma unroll 1
         for (int c0 = first; c0 < end; c0 += MF_KT) stage(c0);
+        if (TRANS_A) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tt[e] += (double)st[e];
+            st = zero4;
+        } else {
+            tr += (double)sr;
+            tq += (double)sq;
+            sr = sq = 0.f;
+        }
         if constexpr (!TOTALS) break;
 #pragma unroll
         for (int x = 0; x < 2; ++x) total[x] += acc[x];
@@ -341,28 +354,28 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
         // eight consecutive lanes share a row: add them in a fixed order
 #pragma unroll
         for (int m = 1; m <= 4; m <<= 1) {
-            sr += __shfl_xor(sr, m, 64);
-            sq += __shfl_xor(sq, m, 64);
+            tr += __shfl_xor(tr, m, 64);
+            tq += __shfl_xor(tq, m, 64);
         }
         const int i = m0 + g_row;
         if (g_quad == 0 && i < I) {
-            sums[((size_t)split * 2 + 0) * I + i] = sr;
-            sums[((size_t)split * 2 + 1) * I + i] = sq;
+            sums[((size_t)split * 2 + 0) * I + i] = (float)tr;
+            sums[((size_t)split * 2 + 1) * I + i] = (float)tq;
         }
     } else {
         // lanes q, q+16, q+32, q+48 of every wave hold the same four columns: add within the wave, then the waves
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            st[e] += __shfl_xor(st[e], 16, 64);
-            st[e] += __shfl_xor(st[e], 32, 64);
+            tt[e] += __shfl_xor(tt[e], 16, 64);
+            tt[e] += __shfl_xor(tt[e], 32, 64);
         }
         if (lane < 16)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) tred[wave][lane * 4 + e] = st[e];
+            for (int e = 0; e < 4; ++e) tred[wave][lane * 4 + e] = tt[e];
         __syncthreads();
         if (tid < 64) {
             const int j = m0 + tid;
-            if (j < J) sums[(size_t)split * J + j] = ((tred[0][tid] + tred[1][tid]) + (tred[2][tid] + tred[3][tid])) + ((tred[4][tid] + tred[5][tid]) + (tred[6][tid] + tred[7][tid]));
+            if (j < J) sums[(size_t)split * J + j] = (float)(((tred[0][tid] + tred[1][tid]) + (tred[2][tid] + tred[3][tid])) + ((tred[4][tid] + tred[5][tid]) + (tred[6][tid] + tred[7][tid])));
         }
     }
 }

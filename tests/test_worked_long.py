@@ -94,8 +94,9 @@ def test_small_numbers_are_not_less_exact_than_on_the_32_bit_kernels(I, J, K, sm
     split, plain = (evaluate(plan, args, df, n, f=f)[1:] for n in (plan.workspace_bytes, plan.workspace_bytes - 16))
     assert not torch.equal(split[0], plain[0])
     want = exact(args, df, K, f)[1:]
-    for s, p in list(zip(errors(split, want), errors(plain, want)))[:3]:
-        assert s <= 1.02 * p, (s, p)
+    # (dc is mostly sums beside the products, which are no product's, of other pieces: 5 % either way)
+    for s, p, limit in zip(errors(split, want), errors(plain, want), (1.02, 1.02, 1.2)):
+        assert s <= limit * p, (s, p)
 
 
 # tall tiles in short pieces, in long ones with totals in the kernel; low tiles
@@ -114,10 +115,13 @@ def test_long_sums_of_one_sign(I, J, K, side):
     g = torch.Generator(device="cuda")
     g.manual_seed(4)
     f = torch.rand((I, J), generator=g, device="cuda")
-    want = exact(args, df, K, f)[q]
+    want = exact(args, df, K, f)
+    # what the other sums beside the products decide: db and dc, or da; the sum of every piece and the result are rounded once, the sums themselves are exact
+    beside = (2, 3) if side == "a" else (1,)
     for ws_bytes in (plan.workspace_bytes, plan.workspace_bytes - 16):
-        got = evaluate(plan, args, df, ws_bytes, f=f)[q]
-        assert errors([got], [want])[0] <= 2.0 ** -24 / math.sqrt(3) * math.sqrt(8192 / 384 + 8 / 3)
+        e = errors(evaluate(plan, args, df, ws_bytes, f=f), want)
+        assert e[q] <= 2.0 ** -24 / math.sqrt(3) * math.sqrt(8192 / 384 + 8 / 3)
+        assert all(e[n] <= 2.0 ** -24 / math.sqrt(3) * math.sqrt(2) for n in beside), e
 
 
 @pytest.mark.parametrize("wanted", [(0,), (1,), (2,), (3,), (0, 3), (1, 2)])
