@@ -442,7 +442,8 @@ void select_wide(tad_plan &plan) {
 }
 
 static void select_split(tad_plan &plan) {
-    if (plan.fwd_family == TAD_FAMILY_WORKED_MFMA && long_pays(plan.fast.I, plan.fast.J, plan.fast.K)) {
+    if (plan.fwd_family == TAD_FAMILY_WORKED_MFMA &&
+        (long_pays(plan.fast.I, plan.fast.J, plan.fast.K) || long_forward_pays(plan.fast.I, plan.fast.J, plan.fast.K))) {
         plan.mfma_split = true;
         plan.ws_full = align256(plan.ws_bytes) + long_workspace_bytes(plan.fast.I, plan.fast.J, plan.fast.K);
     }

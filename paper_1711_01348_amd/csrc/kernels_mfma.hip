@@ -619,7 +619,7 @@ static LongProducts long_products(const tad_plan &pl, const void *const *args, c
             (int)pl.fast.I, (int)pl.fast.J, (int)pl.fast.K, (int)pl.fast.c_ld};
 }
 
-// full: the workspace holds the parts of a and b, the contractions run on the bf16 matrix cores and the kernels here do again what was not finite
+// full: the workspace holds the parts of a and b; the contractions run on the bf16 matrix cores where that pays, and the kernels here do again what was not finite
 int mfma_forward(const tad_plan &pl, const void *const *args, void *f, void *ws, bool full, hipStream_t s) {
     const int I = (int)pl.fast.I, J = (int)pl.fast.J, K = (int)pl.fast.K;
     MfmaWs w = carve_mfma(ws, I, J, K);
@@ -656,10 +656,10 @@ int mfma_backward(const tad_plan &pl, const void *const *args, const void *f_, c
     const float *a = (const float *)args[0], *b = (const float *)args[1], *d = (const float *)args[3];
     const float *f = (const float *)f_, *df = (const float *)df_;
     const int *redo = nullptr;
-    const bool cols = dx[1] != nullptr;
+    const bool cols = dx[1] != nullptr, split = full && long_pays(I, J, K);
     bool totals = true;
     MfmaPieces n;
-    if (!full) {
+    if (!split) {
         n = mfma_pieces(I, J, K, cols, 64, 512, 5.0, 5.0, 1, 1);
     } else if (K <= 128) {
         n = mfma_pieces(I, J, K, cols, 128, K <= 64 ? 512 : 256, K <= 64 ? 2.5 : 2.2, 6.0, 1, 1);
@@ -672,7 +672,7 @@ int mfma_backward(const tad_plan &pl, const void *const *args, const void *f_, c
     // partial results for rows i, then for rows j; sums of rows i, then of rows j
     const MfmaSide P{b, w.partial, w.sums, n.chunk_j}, T{a, w.partial + (size_t)n.n_j * I * K, w.sums + (size_t)n.n_j * 2 * I, n.chunk_i};
     int rc;
-    if (full) {
+    if (split) {
         const LongProducts L = long_products(pl, args, w, ws);
         rc = long_backward(L, f, df, P.out, P.sums, n.n_j, n.chunk_j, T.out, T.sums, n.n_i, n.chunk_i, totals, s);
         redo = L.redo;

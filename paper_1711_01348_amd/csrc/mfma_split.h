@@ -19,13 +19,23 @@ constexpr int kLongMaxK = 512;
 // where the tile takes the registers (4096 x 4096 x 256 128.6 us instead of 120).  There they are left out where the sums are cut short anyway: 1.2e-7 in four
 // pieces; fewer are enough for short sums.
 inline int64_t long_least_pieces(int64_t C) { return C <= 64 ? 1 : C <= 256 ? 2 : C <= 768 ? 3 : 4; }
-// Gradients on the bf16 matrix cores / on the 32-bit ones, both of them with all four gradients, I x J x K: 1024 x 1024 x 32 18.9 / 21.1 us, x 64 21.0 / 23.7,
-// x 128 26.3 / 25.9, x 256 35 / 31; 1400 x 1400 x 128 32.6 / 41.8, x 256 42.5 / 47.6; 4096 x 512 x 128 40.8 / 45.2, x 256 50 / 49; 4096 x 256 x 64 39 / 41, x 256 47 / 46;
-// 2048 x 2048 x 256 54 / 58, x 512 83 / 95; 4096 x 4096 x 32 76 / 161, x 256 140 / 172.  Below the line there are too few workgroups of 128 rows.
-inline bool long_pays(int64_t I, int64_t J, int64_t K) { return K <= kLongMaxK && I * J >= (K <= 64 ? 1 << 20 : 1900000); }
+// Gradients on the bf16 matrix cores / on the 32-bit ones, both of them with all four gradients, I x J x K: 1024 x 1024 x 32 19.0 / 21.8 us, x 64 20.9 / 22.8,
+// 4096 x 256 x 64 38.0 / 41.3, 16384 x 64 x 64 221 / 234; 1380 x 1380 x 96 28.8 / 40.3, x 256 39.8 / 45.7, x 512 52 / 65; 4096 x 512 x 128 39.5 / 45.6, x 256 48.0 / 50.3;
+// 2048 x 2048 x 256 48.5 / 58, 4096 x 4096 x 256 120 / 176.  Below 1 900 000 results there are too few workgroups of 128 rows (1024 x 1024 x 128 26.3 / 25.9, x 256 35 / 31).
+// Where one side is much longer than the other, its results leave few pieces to the other's and the short tiles stay empty: 256 x 16384 x 512 114 / 126, 180 x 11000 x 224 51 / 57,
+// but 128 x 16384 x 256 60 / 58, x 512 109 / 93, 256 x 32000 x 256 137 / 125; 128 x 16384 x 192 54.8 / 55.3, 64 x 32768 x 192 111 / 77; 192 x 32000 x 128 89.6 / 92.5,
+// 128 x 65536 x 128 169 / 142, 64 x 32768 x 96 80 / 71; not for narrow tiles, 64 x 65536 x 64 103 / 125.
+inline bool long_pays(int64_t I, int64_t J, int64_t K) {
+    if (K <= 64) return I * J >= 1 << 20;
+    const int64_t shorter = I < J ? I : J, longer = I < J ? J : I;
+    return K <= kLongMaxK && I * J >= 1900000 && longer <= shorter * (K <= 128 ? 160 : K <= 192 ? 128 : 64);
+}
 // ... and the forward pass: 4096 x 4096 x 64 32.2 / 33.5, x 128 43.8 / 51.1, x 256 63.8 / 82.1; 3000 x 3000 x 256 50 / 53; 4096 x 2048 x 64 21.6 / 20.5, x 128 28.1 / 29.7;
-// 2045 x 3836 x 224 (480 tiles) 39.9 / 44.9; 2048 x 2048 x 256 (256 tiles) 31.9 / 27.7.
-inline bool long_forward_pays(int64_t I, int64_t J, int64_t K) { return K >= 128 && ((I + 127) / 128) * ((J + 127) / 128) >= 480; }
+// 2045 x 3836 x 224 (480 tiles) 39.9 / 44.9; 2048 x 2048 x 256 (256 tiles) 31.9 / 27.7.  The parts of a and b are made for I J / (I + J) uses of each: 16384 x 512 x 128 31.7 / 32.2,
+// 256 x 32000 x 128 34.0 / 32.3, 128 x 65536 x 128 38.0 / 36.8; 160 x 32000 x 256 44.6 / 47.5, 128 x 65536 x 256 69 / 58.
+inline bool long_forward_pays(int64_t I, int64_t J, int64_t K) {
+    return K >= 128 && K <= kLongMaxK && I * J >= 1900000 && ((I + 127) / 128) * ((J + 127) / 128) >= 480 && I * J >= (K < 256 ? 480 : 150) * (I + J);
+}
 
 #if defined(__HIPCC__)
 struct LongProducts {

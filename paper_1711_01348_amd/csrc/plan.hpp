@@ -79,7 +79,7 @@ struct tad_plan {
     int pattern_wide = TAD_FAMILY_GENERIC;     // row reduce or antidiagonal pattern on the kernels with 64-bit sums (workspace: ws_full)
     bool pattern_wide_sums = false;            // ... its gradient as well (else the forward pass alone)
     bool split = false;                        // contraction family: some products run on the bf16 matrix cores (workspace: ws_full)
-    bool mfma_split = false;                   // worked expression with a long sum: its contractions run on the bf16 matrix cores (workspace: ws_full)
+    bool mfma_split = false;                   // worked expression with a long sum: contractions of its gradients or its forward pass run on the bf16 matrix cores (workspace: ws_full)
     tad::WindowPlan window;                    // sums over a moving window (workspace of the gradients: ws_full)
     tad::SepPlan sep;                          // sums of products of two functions (on: the whole expression runs on dense products)
     size_t ws_bytes = 0;                       // workspace of the family's kernels
