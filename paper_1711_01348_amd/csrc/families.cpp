@@ -441,11 +441,52 @@ void select_wide(tad_plan &plan) {
     select_pattern_wide(plan);
 }
 
+// Time of a choice: rounds of the `slots` workgroups that run at once, a stage of 32 terms and what a workgroup takes besides its stages, and 5 TB/s for
+// the partial results.  No more pieces than the workspace holds: kMfmaSplit of either sum, and where one has fewer the other may have more.
+// least_j, least_i: pieces that the sum over j, over i, has at least.
+static MfmaPieces pieces_of_long_sums(int64_t I, int64_t J, int64_t K, bool cols, int tile, int slots, double stage, double besides, int64_t least_j, int64_t least_i) {
+    MfmaPieces best{};
+    best.time = -1;
+    const int64_t columns = (K + 255) / 256, ti = (I + tile - 1) / tile * columns, tj = cols ? (J + tile - 1) / tile * columns : 0;
+    const int64_t stages_j = (J + 31) / 32, stages_i = (I + 31) / 32, most_j = (stages_j + least_j - 1) / least_j, most_i = (stages_i + least_i - 1) / least_i;
+    for (int64_t n = 1; n <= std::max(stages_i, stages_j); n += 1 + n / 16) {
+        const int64_t in_j = std::min(n, most_j), in_i = std::min(n, most_i), nj = (stages_j + in_j - 1) / in_j, ni = cols ? (stages_i + in_i - 1) / in_i : 0;
+        if (nj > kMfmaMostPieces || ni > kMfmaMostPieces || nj * I + ni * J > kMfmaSplit * (I + J) || 2 * nj * I + ni * J > kMfmaSplit * (2 * I + J)) continue;
+        const int64_t rounds = (ti * nj + tj * ni + slots - 1) / slots;
+        const double t = (double)rounds * ((double)std::max(in_j, cols ? in_i : 0) * stage + besides) + (double)(nj * I + ni * J) * (double)K * 8 / 5e6;
+        if (best.time >= 0 && t >= best.time) continue;
+        best = {(int)nj, (int)ni, (int)(32 * in_j), (int)(32 * in_i), false, t};
+    }
+    return best;
+}
+
+static void select_pieces(tad_plan &plan) {
+    const int64_t I = plan.fast.I, J = plan.fast.J, K = plan.fast.K;
+    for (int cols = 0; cols < 2; ++cols) {
+        auto short_pieces = [&](const MfmaPieces &n) { return n.chunk_j <= mfma_chain((int)J) && (!cols || n.chunk_i <= mfma_chain((int)I)); };
+        MfmaPieces &plain = plan.mfma_pieces[0][cols], &n = plan.mfma_pieces[1][cols];
+        plain = pieces_of_long_sums(I, J, K, cols, 64, 512, 5.0, 5.0, 1, 1);
+        plain.totals = !short_pieces(plain);
+        if (!long_pays(I, J, K)) continue;
+        if (K <= 128) {
+            n = pieces_of_long_sums(I, J, K, cols, 128, K <= 64 ? 512 : 256, K <= 64 ? 2.5 : 2.2, 6.0, 1, 1);
+            n.totals = !short_pieces(n);
+            continue;
+        }
+        n = pieces_of_long_sums(I, J, K, cols, 128, 256, 3.6, 6.0, long_least_pieces(J), long_least_pieces(I));
+        const MfmaPieces any = pieces_of_long_sums(I, J, K, cols, 128, 256, 3.9, 6.0, 1, 1);
+        if (any.time >= n.time) continue;
+        n = any;
+        n.totals = !short_pieces(n);
+    }
+}
+
 static void select_split(tad_plan &plan) {
-    if (plan.fwd_family == TAD_FAMILY_WORKED_MFMA &&
-        (long_pays(plan.fast.I, plan.fast.J, plan.fast.K) || long_forward_pays(plan.fast.I, plan.fast.J, plan.fast.K))) {
-        plan.mfma_split = true;
-        plan.ws_full = align256(plan.ws_bytes) + long_workspace_bytes(plan.fast.I, plan.fast.J, plan.fast.K);
+    if (plan.fwd_family == TAD_FAMILY_WORKED_MFMA) {
+        const int64_t I = plan.fast.I, J = plan.fast.J, K = plan.fast.K;
+        select_pieces(plan);
+        plan.mfma_split = long_pays(I, J, K) || long_forward_pays(I, J, K);
+        if (plan.mfma_split) plan.ws_full = align256(plan.ws_bytes) + long_workspace_bytes(I, J, K);
     }
     if (plan.fwd_family != TAD_FAMILY_CONTRACTION) return;
     for (const GemmDesc &g : plan.fast.gemm)

@@ -236,7 +236,6 @@ struct MfmaTiles {
 // and then to the total (TOTALS; not needed where the pieces are no longer than that).  Error of da against 64 bits with one chain to a piece of up to the
 // whole sum / with totals / with eight pieces of one chain, 4096 x 4096 x 640: 4.2e-7 / 2.3e-7 / 3.0e-7; a sum of 8192 terms of one sign 6.0e-7 / 7.0e-8 / 1.6e-7.
 // All four gradients 471 / 479 / 536 us (4096 x 4096 x 640), 256 x 1024 x 64 16.7 / 17.5 / 33.5.
-__host__ __device__ inline int mfma_chain(int terms) { return MF_KT * std::min(8, (terms + 255) / 256); }
 template <bool TRANS_A, bool TOTALS>
 __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int split, const float *__restrict__ f, const float *__restrict__ df,
                                                  const float *__restrict__ bmat, const float *__restrict__ rowv, const float *__restrict__ nb,
@@ -509,32 +508,6 @@ __global__ __launch_bounds__(256) void k_mfma_finish(const MfmaFinish F, const F
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
-// The pieces that the sums over j and over i are cut into: every piece of a tile of rows is a workgroup of its own, and its partial results are
-// written and read again.
-struct MfmaPieces {
-    int n_j, n_i;              // pieces of the sum over j (results for rows i), of the sum over i (rows j; 0: not wanted)
-    int chunk_j, chunk_i;      // terms of a piece, a multiple of 32
-    double time;               // us, by the model
-};
-// Time of a choice: rounds of the `slots` workgroups that run at once, a stage of 32 terms and what a workgroup takes besides its stages, and 5 TB/s for
-// the partial results.  No more pieces than the workspace holds: kMfmaSplit of either sum, and where one has fewer the other may have more.
-// least_j, least_i: pieces that the sum over j, over i, has at least.
-static MfmaPieces mfma_pieces(int64_t I, int64_t J, int64_t K, bool cols, int tile, int slots, double stage, double besides, int64_t least_j, int64_t least_i) {
-    MfmaPieces best{};
-    best.time = -1;
-    const int64_t columns = (K + 255) / 256, ti = (I + tile - 1) / tile * columns, tj = cols ? (J + tile - 1) / tile * columns : 0;
-    const int64_t stages_j = (J + 31) / 32, stages_i = (I + 31) / 32, most_j = (stages_j + least_j - 1) / least_j, most_i = (stages_i + least_i - 1) / least_i;
-    for (int64_t n = 1; n <= std::max(stages_i, stages_j); n += 1 + n / 16) {
-        const int64_t in_j = std::min(n, most_j), in_i = std::min(n, most_i), nj = (stages_j + in_j - 1) / in_j, ni = cols ? (stages_i + in_i - 1) / in_i : 0;
-        if (nj > kMfmaMostPieces || ni > kMfmaMostPieces || nj * I + ni * J > kMfmaSplit * (I + J) || 2 * nj * I + ni * J > kMfmaSplit * (2 * I + J)) continue;
-        const int64_t rounds = (ti * nj + tj * ni + slots - 1) / slots;
-        const double t = (double)rounds * ((double)std::max(in_j, cols ? in_i : 0) * stage + besides) + (double)(nj * I + ni * J) * (double)K * 8 / 5e6;
-        if (best.time >= 0 && t >= best.time) continue;
-        best = {(int)nj, (int)ni, (int)(32 * in_j), (int)(32 * in_i), t};
-    }
-    return best;
-}
-
 struct MfmaWs {
     float *rowv, *nb, *partial, *sums;
 };
@@ -657,24 +630,13 @@ int mfma_backward(const tad_plan &pl, const void *const *args, const void *f_, c
     const float *f = (const float *)f_, *df = (const float *)df_;
     const int *redo = nullptr;
     const bool cols = dx[1] != nullptr, split = full && long_pays(I, J, K);
-    bool totals = true;
-    MfmaPieces n;
-    if (!split) {
-        n = mfma_pieces(I, J, K, cols, 64, 512, 5.0, 5.0, 1, 1);
-    } else if (K <= 128) {
-        n = mfma_pieces(I, J, K, cols, 128, K <= 64 ? 512 : 256, K <= 64 ? 2.5 : 2.2, 6.0, 1, 1);
-    } else {
-        n = mfma_pieces(I, J, K, cols, 128, 256, 3.6, 6.0, long_least_pieces(J), long_least_pieces(I));
-        const MfmaPieces any = mfma_pieces(I, J, K, cols, 128, 256, 3.9, 6.0, 1, 1);
-        totals = any.time < n.time;
-        if (totals) n = any;
-    }
+    const MfmaPieces &n = pl.mfma_pieces[split][cols];
     // partial results for rows i, then for rows j; sums of rows i, then of rows j
     const MfmaSide P{b, w.partial, w.sums, n.chunk_j}, T{a, w.partial + (size_t)n.n_j * I * K, w.sums + (size_t)n.n_j * 2 * I, n.chunk_i};
     int rc;
     if (split) {
         const LongProducts L = long_products(pl, args, w, ws);
-        rc = long_backward(L, f, df, P.out, P.sums, n.n_j, n.chunk_j, T.out, T.sums, n.n_i, n.chunk_i, totals, s);
+        rc = long_backward(L, f, df, P.out, P.sums, n.n_j, n.chunk_j, T.out, T.sums, n.n_i, n.chunk_i, n.totals, s);
         redo = L.redo;
     } else {
         rc = prep(pl, args, w, s);
@@ -685,7 +647,7 @@ int mfma_backward(const tad_plan &pl, const void *const *args, const void *f_, c
 #define TAD_CONTRACTIONS(TOTALS)                                                                                                                          \
     TAD_LAUNCH("k_mfma_backward", k_mfma_backward<TOTALS>, dim3(blocks_both, columns), dim3(512), 0, s, f, df, (const float *)w.rowv, (const float *)w.nb, P, T, I, J, \
                K, first, n.n_j, n.n_i, redo)
-    if (n.chunk_j > mfma_chain(J) || (cols && n.chunk_i > mfma_chain(I))) TAD_CONTRACTIONS(true);
+    if (split || n.totals) TAD_CONTRACTIONS(true);   // (behind the bf16 kernels: pieces that are theirs)
     else TAD_CONTRACTIONS(false);
 #undef TAD_CONTRACTIONS
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;

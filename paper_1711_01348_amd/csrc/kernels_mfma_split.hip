@@ -411,7 +411,7 @@ __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *c
                 }
         }
     };
-    const int chain = 32 * min(8, (C + 255) / 256);
+    const int chain = mfma_chain(C);
     int left = chain;
     load_g(begin);
     int set = 1;
@@ -519,8 +519,10 @@ int long_backward(const LongProducts &L, const float *f, const float *df, float 
 #define TAD_LONG(RX, RY, WN, TOTALS)                                                                                                             \
     TAD_LAUNCH("k_long_backward", (k_long_backward<RX, RY, WN, TOTALS>), dim3(blocks, (L.K / 32 + RY * WN - 1) / (RY * WN)), dim3(512), 0, s, B)
     // no more columns than there are
-    if (L.K <= 64) TAD_LONG(1, 1, 2, true);
-    else if (L.K <= 128) TAD_LONG(1, 2, 2, true);
+    if (L.K <= 64 && totals) TAD_LONG(1, 1, 2, true);
+    else if (L.K <= 64) TAD_LONG(1, 1, 2, false);
+    else if (L.K <= 128 && totals) TAD_LONG(1, 2, 2, true);
+    else if (L.K <= 128) TAD_LONG(1, 2, 2, false);
     else if (totals) TAD_LONG(2, 2, 4, true);
     else TAD_LONG(2, 2, 4, false);
 #undef TAD_LONG

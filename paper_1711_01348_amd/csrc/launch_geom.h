@@ -49,6 +49,17 @@ inline size_t mfma_workspace_bytes(int64_t I, int64_t J, int64_t K) {
            align256((size_t)kMfmaSplit * (2 * I + J) * 4);
 }
 
+// Terms that go through one chain of matrix instructions where the pieces may be longer (see kernels_mfma.hip)
+constexpr int mfma_chain(int terms) { return 32 * ((terms + 255) / 256 < 8 ? (terms + 255) / 256 : 8); }
+// The pieces that the sums over j and over i are cut into: every piece of a tile of rows is a workgroup of its own, and its partial results are
+// written and read again.
+struct MfmaPieces {
+    int n_j, n_i;              // pieces of the sum over j (results for rows i), of the sum over i (rows j; 0: not wanted)
+    int chunk_j, chunk_i;      // terms of a piece, a multiple of 32
+    bool totals;               // chains of matrix instructions end within a piece
+    double time;               // us, by the model
+};
+
 // Fallback (generic and program) kernels.  The cooperative form (one block per gradient element) pays off when
 // an element sums many terms: measured on the worked expression at 8192 x 8192 x 5, the gradients with 8192 and
 // 40960 terms per element take 0.8 ms this way against 11 ms with one thread per element.

@@ -6,6 +6,7 @@
 
 #include "../../include/tad.h"
 #include "fm.hpp"
+#include "launch_geom.h"
 #include "plan_dev.h"
 #include "product.hpp"
 #include "program.hpp"
@@ -80,6 +81,7 @@ struct tad_plan {
     bool pattern_wide_sums = false;            // ... its gradient as well (else the forward pass alone)
     bool split = false;                        // contraction family: some products run on the bf16 matrix cores (workspace: ws_full)
     bool mfma_split = false;                   // worked expression with a long sum: contractions of its gradients or its forward pass run on the bf16 matrix cores (workspace: ws_full)
+    tad::MfmaPieces mfma_pieces[2][2] = {};    // worked expression with a long sum: [on the bf16 matrix cores][with the gradient of b]
     tad::WindowPlan window;                    // sums over a moving window (workspace of the gradients: ws_full)
     tad::SepPlan sep;                          // sums of products of two functions (on: the whole expression runs on dense products)
     size_t ws_bytes = 0;                       // workspace of the family's kernels
