@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 //   TRANS_A = true:   sums[split * J + j] = sum_i c_ii G_ij
 struct MfmaTiles {
     float a[64 * MF_LD], b[32][256];
-    double red[8][64];
+    double red[8][64], side[4][512];
 };
 // The matrix instructions add two terms at a time, and every addition rounds the chain's sum: an eighth of the sum, at most 256 terms, is added up by itself
 // and then to the total (TOTALS; not needed where the pieces are no longer than that).  Error of da against 64 bits with one chain to a piece of up to the
@@ -258,7 +258,8 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
     const float4v zero4 = {0.f, 0.f, 0.f, 0.f};
     float sr = 0.f, sq = 0.f;   // TRANS_A = false: row sums of the thread's row, of one chain
     float4v st = zero4;         // TRANS_A = true: column sums of the thread's four columns
-    double tr = 0.0, tq = 0.0, tt[4] = {};   // ... and of those before
+#pragma unroll
+    for (int e = 0; e < 4; ++e) S.side[e][tid] = 0.0;   // ... and of those before, in LDS: the registers are taken
     // the four elements of G of the thread: i = m0 + g_row, j = c0 + 4 g_quad, or (TRANS_A) i = c0 + g_row, j = m0 + 4 g_quad
     const int g_row = TRANS_A ? tid >> 4 : tid >> 3, g_quad = TRANS_A ? tid & 15 : tid & 7;
     auto gload = [&](int c0) {
@@ -328,27 +329,30 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
         for (int c0 = first; c0 < end; c0 += MF_KT) stage(c0);
         if (TRANS_A) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) tt[e] += (double)st[e];
+            for (int e = 0; e < 4; ++e) S.side[e][tid] += (double)st[e];
             st = zero4;
         } else {
-            tr += (double)sr;
-            tq += (double)sq;
+            S.side[0][tid] += (double)sr;
+            S.side[1][tid] += (double)sq;
             sr = sq = 0.f;
         }
         if constexpr (!TOTALS) break;
 #pragma unroll
         for (int x = 0; x < 2; ++x) total[x] += acc[x];
     }
+    int late = tid;   // places of the results from the thread's number again: kept through the loop they would not fit in registers
+    asm volatile("" : "+v"(late));
 #pragma unroll
     for (int tn = 0; tn < 2; ++tn) {
-        const int n = n0 + wn * 64 + tn * 32 + mrow;
+        const int n = n0 + wn * 64 + tn * 32 + (late & 31);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int m = m0 + wm * 32 + acc_row(r, lane);
+            const int m = m0 + wm * 32 + acc_row(r, late & 63);
             if (m < Mtot && n < K) out[((size_t)split * Mtot + m) * K + n] = (TOTALS ? total : acc)[tn][r];
         }
     }
     if (blockIdx.y != 0) return;
+    double tr = S.side[0][tid], tq = S.side[1][tid], tt[4];   // (its own)
     if (!TRANS_A) {
         // eight consecutive lanes share a row: add them in a fixed order
 #pragma unroll
@@ -365,6 +369,7 @@ __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int spl
         // lanes q, q+16, q+32, q+48 of every wave hold the same four columns: add within the wave, then the waves
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
+            tt[e] = S.side[e][tid];
             tt[e] += __shfl_xor(tt[e], 16, 64);
             tt[e] += __shfl_xor(tt[e], 32, 64);
         }

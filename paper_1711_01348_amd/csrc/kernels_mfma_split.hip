@@ -271,7 +271,7 @@ __global__ __launch_bounds__(256, 3) void k_long_forward(const piece *__restrict
 struct LongSide {
     const piece *parts;
     float *out, *sums;
-    int chunk;                 // terms of a piece
+    int chunk, chain;          // terms of a piece, of a chain of instructions
 };
 struct LongBackward {
     const float *f, *df, *rowv, *nb;
@@ -411,7 +411,7 @@ __device__ __forceinline__ void long_contraction(const LongBackward &L, piece *c
                 }
         }
     };
-    const int chain = mfma_chain(C);
+    const int chain = L.side[TRANS].chain;
     int left = chain;
     load_g(begin);
     int set = 1;
@@ -515,7 +515,7 @@ int long_backward(const LongProducts &L, const float *f, const float *df, float 
     TAD_LAUNCH("k_long_prep", k_long_prep<true>, dim3(P.blocks_a + (L.J + 31) / 32), dim3(256), 0, s, P);
     if (hipGetLastError() != hipSuccess) return TAD_EDEVICE;
     const int first = (L.I + 127) / 128 * n_j, blocks = first + (L.J + 127) / 128 * n_i;
-    const LongBackward B{f, df, L.rowv, L.nb, {{P.pb, P_out, rowp, chunk_j}, {P.pa, T_out, colp, chunk_i}}, L.redo, L.I, L.J, L.K, first, n_j, n_i};
+    const LongBackward B{f, df, L.rowv, L.nb, {{P.pb, P_out, rowp, chunk_j, mfma_chain(L.J)}, {P.pa, T_out, colp, chunk_i, mfma_chain(L.I)}}, L.redo, L.I, L.J, L.K, first, n_j, n_i};
 #define TAD_LONG(RX, RY, WN, TOTALS)                                                                                                             \
     TAD_LAUNCH("k_long_backward", (k_long_backward<RX, RY, WN, TOTALS>), dim3(blocks, (L.K / 32 + RY * WN - 1) / (RY * WN)), dim3(512), 0, s, B)
     // no more columns than there are
