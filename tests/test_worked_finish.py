@@ -9,8 +9,12 @@ from paper_1711_01348_amd import workloads as wl
 # tiles of rows up to 48, 192 and beyond, few columns; c as large as I x I, longer rows, more rows, rows a little longer than a workgroup's stores or shorter
 @pytest.mark.parametrize("I,J,K,dtype,c_shape", [(3100, 9, 3, "f32", None), (3121, 70, 8, "f32", (3121, 3130)), (800, 33, 16, "f64", None), (3080, 3, 2, "f64", (3081, 3080)),
                                                  (40, 20, 2, "f32", (40, 1500)), (40, 20, 2, "f32", (1600, 41)), (17, 300, 5, "f64", (1021, 511)), (300, 5, 1, "f32", (301, 1023)),
-                                                 (2900, 2900, 5, "f32", (2905, 2901)), (2897, 2900, 8, "f32", None)])
-def test_finished_gradients(I, J, K, dtype, c_shape):
+                                                 (2900, 2900, 5, "f32", (2905, 2901)), (2897, 2900, 8, "f32", None),
+                                                 # rows shorter than a workgroup's stores, than a store, of one element; many behind the diagonal's last one
+                                                 (64, 40, 5, "f32", (9001, 64)), (600, 40, 3, "f32", (601, 603)), (3, 300, 3, "f32", (30001, 3)), (1, 40, 3, "f32", (9001, 1)),
+                                                 (33, 20, 2, "f64", (4001, 33)), (2, 300, 3, "f64", (9001, 2)), (1, 300, 3, "f64", (3, 1))])
+@pytest.mark.parametrize("before", [1, 4])   # a gradient of c that starts four or eight bytes off the alignment of the widest store, or on it
+def test_finished_gradients(I, J, K, dtype, c_shape, before):
     import torch
     from paper_1711_01348_amd import binding as B
     expr = wl.worked_expr(I, J, K, dtype, c_shape=c_shape)
@@ -21,9 +25,9 @@ def test_finished_gradients(I, J, K, dtype, c_shape):
     df = torch.rand((I, J), generator=g, device="cuda", dtype=dt)
     plan = B.Plan(expr)
     f = plan.forward(args)
-    # a gradient of c that starts four or eight bytes off the alignment of the widest store, and watched on both sides
-    room = torch.full((c.numel() + 2,), float("nan"), device="cuda", dtype=dt)
-    out = [torch.full_like(a, float("nan")), torch.full_like(b, float("nan")), room[1:-1].view(c.shape), torch.full_like(d, float("nan"))]
+    # the gradient of c is watched on both sides
+    room = torch.full((c.numel() + before + 1,), float("nan"), device="cuda", dtype=dt)
+    out = [torch.full_like(a, float("nan")), torch.full_like(b, float("nan")), room[before:-1].view(c.shape), torch.full_like(d, float("nan"))]
     plan.backward(args, f, df, out=out)
     A, Bm, D3 = a.double(), b.double(), d.double() ** 3
     ci = c.diagonal()[:I].double()
@@ -41,4 +45,4 @@ def test_finished_gradients(I, J, K, dtype, c_shape):
         assert bool(((x.double() - w).abs() <= (2e-6 if dtype == "f32" else 1e-13) * w.abs() + 1e-30).all())
     rest = out[2].clone()
     rest.diagonal()[:I].zero_()
-    assert not rest.any() and bool(room[0].isnan()) and bool(room[-1].isnan())
+    assert not rest.any() and bool(room[:before].isnan().all()) and bool(room[-1].isnan())
