@@ -13,7 +13,7 @@ def matmul(I, J, K, dtype):
 CASES = [("separable", lambda: wl.softplus_ratio_expr(70, 65, 33, "f32")), ("separable_from_f", lambda: wl.dense_layer_expr(64, 16, 1100, "f64")),
          ("product_pieces", lambda: matmul(40, 23, 1100, "f32")), ("worked_wide", lambda: wl.worked_expr(130, 65, 3, "f32")),
          ("index_sum_wide", lambda: wl.index_sum_exp_expr(517, 999, "f32")), ("conditions", lambda: wl.causal_convolution_expr(70, 9, "f32")),
-         ("bf16_parts", lambda: matmul(4100, 2052, 1028, "f32"))]
+         ("bf16_parts", lambda: matmul(4100, 2052, 1028, "f32")), ("worked_long", lambda: wl.worked_expr(2049, 3900, 128, "f32"))]
 
 
 @pytest.mark.parametrize("name,make", CASES, ids=[c[0] for c in CASES])

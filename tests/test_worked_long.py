@@ -51,27 +51,30 @@ def exact(args, df, K, given=None):
     return [f, -2 * ci[:, None] * (a * r[:, None] + P), db, dc, -3 * d * d * dd]
 
 
-# 64, 128 and 256 columns of a tile, a part of them and more than one; rows and terms one beyond a tile, a stage, four of them short
-@pytest.mark.parametrize("I,J,K,c_extra", [(1025, 1024, 32, 3), (1150, 1028, 64, 0), (1537, 1284, 96, 0), (1409, 1412, 128, 1), (1409, 1540, 160, 0),
-                                           (1921, 1148, 256, 0), (4097, 516, 288, 0), (509, 4100, 512, 2), (2049, 4000, 160, 0)])
-def test_error_is_no_larger_than_that_of_the_32_bit_kernels(I, J, K, c_extra):
+def errors(tensors, want):
+    return [((t.double() - w).norm() / w.norm()).item() for t, w in zip(tensors, want)]
+
+
+# 64, 128 and 256 columns of a tile, a part of them and more than one; rows and terms one beyond a tile, a stage, four of them short; the forward pass on the bf16
+# matrix cores as well, with sums of 128 to 512 terms
+@pytest.mark.parametrize("I,J,K,c_extra,forward", [(1025, 1024, 32, 3, False), (1150, 1028, 64, 0, False), (1537, 1284, 96, 0, False), (1409, 1412, 128, 1, False),
+                                                   (1409, 1540, 160, 0, False), (1921, 1148, 256, 0, False), (4097, 516, 288, 0, False), (509, 4100, 512, 2, False),
+                                                   (2049, 4000, 160, 0, True), (2049, 4000, 128, 0, True), (2433, 3076, 256, 1, True), (2817, 2700, 512, 0, True)])
+def test_error_is_no_larger_than_that_of_the_32_bit_kernels(I, J, K, c_extra, forward):
+    """f, da and db are products.  dc and dd are mostly sums beside them, made alike in pieces of other lengths: dc within a tenth, dd, where a few roundings of
+    long windows decide, within a factor of two (0.8 to 1.5 over sizes and inputs)."""
     import torch
     from paper_1711_01348_amd import binding as B
     expr, args, df = tensors(I, J, K, c_extra=c_extra)
     plan, want = B.Plan(expr), exact(args, df, K)
     split, plain = (evaluate(plan, args, df, n) for n in (plan.workspace_bytes, plan.workspace_bytes - 16))
-    assert not torch.equal(split[1], plain[1])      # not the same kernels
-    for s, p, w in zip(split, plain, want):
-        e = [((t.double() - w).norm() / w.norm()).item() for t in (s, p)]
-        assert e[0] <= 1.1 * e[1] + 3e-8, e         # (sums of few pieces: dd, dc differ in the order of the pieces alone)
+    assert not torch.equal(split[1], plain[1]) and torch.equal(split[0], plain[0]) == (not forward)      # not the same kernels
+    for e, p, limit, s, w in zip(errors(split, want), errors(plain, want), (1.02, 1.02, 1.02, 1.1, 2), split, want):
+        assert e <= limit * p, (e, p)
         assert check.within(s.cpu().numpy(), w.cpu().numpy(), "f32"), check.errors(s.cpu().numpy(), w.cpu().numpy())
     rest = split[3].clone()
     rest.diagonal()[:I].zero_()
     assert not rest.any()
-
-
-def errors(tensors, want):
-    return [((t.double() - w).norm() / w.norm()).item() for t, w in zip(tensors, want)]
 
 
 # small numbers: what they do to a, b, df and a given f
