@@ -82,8 +82,8 @@ def accounting(name, w):
         elems = nf + nf + nf + cdense + small_rw      # write f; read df; read f; write dense dc
         if name == "cfg4":
             # expanded form on the matrix cores: a.b^T, G b and (cG)^T a, 2 I J K flops each
-            # one of the three contractions (the other two share a launch); six bf16 products per 32-bit product
-            dom = dict(kernel="k_long_forward", bound="mfma", per_launch=2.0 * I * J * K, launches=1,
+            # the two contractions of the gradients share a launch; six bf16 products per 32-bit product
+            dom = dict(kernel="k_long_backward", bound="mfma", per_launch=4.0 * I * J * K, launches=1,
                        step_flops=6.0 * I * J * K, peak_tflops=BF16_MFMA_TFLOPS / 6)
         elif name == "cfg3":
             dom = dict(kernel="k_worked_backward", bound="hbm", per_launch=2 * nf * es, launches=1)

@@ -2,17 +2,18 @@
 // 32-bit precision.
 //
 // A 32-bit number is the sum of three bf16 numbers x1 + x2 + x3 (8 + 8 + 8 bits, each the nearest to what the ones before leave).  Six of the
-// nine products of the parts are taken, each exact in 32 bits: what is left out is at most 2^-25 of |x y|, of either sign.  x1 y1 is added up
-// by itself and the five smaller products by themselves, so that the roundings of those do not count.  v_mfma_f32_32x32x16_bf16 does sixteen
-// times the work of v_mfma_f32_32x32x2f32 per cycle: six of them take 3 / 8 of its time.
+// nine products of the parts are taken, each exact in 32 bits: what is left out is at most 2^-24 of |x y| (x2 y3 and x3 y2, 2^-25 each), of either sign
+// and 2^-27.5 on average; sums of one term are as exact as the 32-bit instructions' (da 4.4e-8).  x1 y1 is added up by itself and the five smaller products
+// by themselves, so that the roundings of those do not count; where pieces of a sum are long its chain ends after 256 terms (see mfma_split.h).
+// v_mfma_f32_32x32x16_bf16 does sixteen times the work of v_mfma_f32_32x32x2f32 per cycle: six of them take 3 / 8 of its time.
 //
 // Operands that are tensors (a, b) are split once, by the launch that also forms the norms (k_long_prep), and written fragment by fragment in the
 // order in which a wavefront feeds them to the matrix cores ([16 terms][32 rows][part][lane][8 terms], zeros beyond the edges): they go
 // from there to LDS without passing through registers.  G = df f exists nowhere: it is formed, split and written to LDS by the
 // threads that load df and f, one stage ahead.
 //
-// 4096 x 4096 x 256: forward pass 82 us on the 32-bit matrix instructions, 64 here; all four gradients 192 (six launches), 172 (the 32-bit kernels in three),
-// 125 here; the error of da against 64 bits 3.0e-7, 1.6e-7 here, of f 3.2e-8, 3.1e-8.  What bounds them: the clock under load (1.8 GHz, as in
+// 4096 x 4096 x 256: forward pass 82 us on the 32-bit matrix instructions, 64 here; all four gradients 192 (six launches), 176 (the 32-bit kernels in three),
+// 120 here; errors against 64 bits, 32-bit instructions in eight pieces and here, f 3.2e-8, 3.1e-8, da 3.0e-7, 1.5e-7, dc 9.3e-8, 7.6e-8, dd 1.5e-7, 1.4e-7.  What bounds them: the clock under load (1.8 GHz, as in
 // kernels_split.hip) and, in the gradients, G, whose 134 MB are read twice and whose parts are formed on the vector ALU while both wavefronts of a
 // SIMD wait for them.  Tried: fragments read from LDS half a stage ahead (132 -> 146 us), wavefronts of a SIMD that form G in turn (125 -> 137).
 //

@@ -8,7 +8,7 @@
 // the sum, and after 128 terms both are added to the total on the vector ALU: the instruction does not round its sums to nearest, and long chains
 // of it drift (all 4096 terms in one: 4.1e-7 for uniform operands, 1.2e-6 for nearly equal ones; the same additions after every 16 terms, with a
 // vector instruction for every second matrix instruction, 4.1e-7 and 840 us).  Error against 64 bits, these and the 32-bit instructions, 4096 x 4096 x 4096:
-// operands uniform in -1 .. 1 1.6e-7 / 1.15e-6, in 0 .. 1 8.3e-8 / 8.4e-7, nearly equal ones 1.1e-7 / 8.5e-7, one term per sum 2.5e-8 / 2.5e-8 (at most 0.5025 / 0.5 units in
+// operands uniform in -1 .. 1 1.6e-7 / 1.15e-6, in 0 .. 1 1.1e-7 / 8.4e-7, nearly equal ones 1.1e-7 / 8.3e-7, normal times 2^(-20 .. 20) 1.7e-7 / 4.9e-7, one term per sum 2.5e-8 / 2.5e-8 (at most 0.5025 / 0.5 units in
 // the last place).  (With six products into one total, uniform operands 1.0e-6 and one term 3.1e-8, 1.3 units.  Two fp16 parts, three products: 375 us, but
 // one term is off by up to 8 units; three fp16 parts, six products: 650 us, and a range of 2^40 at most within a tensor.)
 //
