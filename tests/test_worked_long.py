@@ -153,13 +153,14 @@ def test_pieces_of_long_sums_for_few_rows(I, J, K):
 
 
 @pytest.mark.parametrize("what", ["inf_df", "nan_df", "huge_df", "large_df", "inf_a", "huge_b"])
-def test_what_is_not_finite_is_left_to_the_32_bit_kernels(what):
+@pytest.mark.parametrize("I,J,K", [(2048, 3840, 128), (1409, 1540, 160), (512, 8192, 160)])   # low tiles, tall ones without and with totals
+def test_what_is_not_finite_is_left_to_the_32_bit_kernels(I, J, K, what):
     import torch
     from paper_1711_01348_amd import binding as B
-    expr, args, df = tensors(2048, 3840, 128)
+    expr, args, df = tensors(I, J, K)
     f = torch.rand_like(df)
     if what.endswith("df"):
-        df[2047, 3839] = {"inf": float("inf"), "nan": float("nan"), "huge": 3.4e38, "large": 2.0 ** 110}[what[:-3]]   # (large: times 2^24, not finite)
+        df[I - 1, J - 1] = {"inf": float("inf"), "nan": float("nan"), "huge": 3.4e38, "large": 2.0 ** 110}[what[:-3]]   # (large: times 2^24, not finite)
     else:
         args[0 if what == "inf_a" else 1][5, 127] = float("inf") if what == "inf_a" else 3.4e38
     plan = B.Plan(expr)
