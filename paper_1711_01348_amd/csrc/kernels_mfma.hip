@@ -403,7 +403,8 @@ __global__ __launch_bounds__(512, 4) void k_mfma_backward(const float *__restric
 
 // ---------------------------------------------------------------------------------------------
 // finishing, in one launch: rows i (da, dc_ii and the zeros of that row of dc), rows j (db), dd, rows of dc beyond I; one wavefront per output row, a
-// lane owns four consecutive k.  Fixed summation order.  The zeros (64 MB at 4096 x 4096) go out while the others wait for their partial sums.
+// lane owns four consecutive k.  Fixed summation order, pieces added in 64 bits (up to 64 of them: in 32 bits da of 64 x 2048 x 32, terms of one sign, was off by
+// 1.1e-7, so by 2.5e-8; 4096 x 4096 x 256 120 -> 120.5 us).  The zeros (64 MB at 4096 x 4096) go out while the others wait for their partial sums.
 // ---------------------------------------------------------------------------------------------
 struct MfmaFinish {
     const float *a, *b, *d, *rowv, *P, *T, *rowp, *colp;
@@ -444,17 +445,21 @@ __global__ __launch_bounds__(256) void k_mfma_finish(const MfmaFinish F, const F
         float cross = 0.f;
         if (F.da || F.dc)
             for (int k = lane * 4; k < K; k += 256) {
-                float4v P = {0.f, 0.f, 0.f, 0.f};
+                double P[4] = {};
 #pragma unroll 4
-                for (int s = 0; s < F.n_j; ++s) P += *reinterpret_cast<const float4v *>(F.P + ((size_t)s * I + i) * K + k);
+                for (int s = 0; s < F.n_j; ++s) {
+                    const float4v v = *reinterpret_cast<const float4v *>(F.P + ((size_t)s * I + i) * K + k);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) P[e] += (double)v[e];
+                }
                 const float4v av = *reinterpret_cast<const float4v *>(F.a + (size_t)i * K + k);
                 if (F.da) {
                     float4v o;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = (float)(-2.0 * ci * ((double)av[e] * r + (double)P[e]));
+                    for (int e = 0; e < 4; ++e) o[e] = (float)(-2.0 * ci * ((double)av[e] * r + P[e]));
                     *reinterpret_cast<float4v *>(F.da + (size_t)i * K + k) = o;
                 }
-                cross += (av[0] * P[0] + av[1] * P[1]) + (av[2] * P[2] + av[3] * P[3]);
+                cross += (av[0] * (float)P[0] + av[1] * (float)P[1]) + (av[2] * (float)P[2] + av[3] * (float)P[3]);
             }
         if (!F.dc) return;
         cross = wave_sum63m(cross);
@@ -470,13 +475,17 @@ __global__ __launch_bounds__(256) void k_mfma_finish(const MfmaFinish F, const F
 #pragma unroll 4
         for (int s = 0; s < F.n_i; ++s) t += (double)F.colp[(size_t)s * J + j];
         for (int k = lane * 4; k < K; k += 256) {
-            float4v T = {0.f, 0.f, 0.f, 0.f};
+            double T[4] = {};
 #pragma unroll 4
-            for (int s = 0; s < F.n_i; ++s) T += *reinterpret_cast<const float4v *>(F.T + ((size_t)s * J + j) * K + k);
+            for (int s = 0; s < F.n_i; ++s) {
+                const float4v v = *reinterpret_cast<const float4v *>(F.T + ((size_t)s * J + j) * K + k);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) T[e] += (double)v[e];
+            }
             const float4v bv = *reinterpret_cast<const float4v *>(F.b + (size_t)j * K + k);
             float4v o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (float)(-2.0 * ((double)T[e] + (double)bv[e] * t));
+            for (int e = 0; e < 4; ++e) o[e] = (float)(-2.0 * (T[e] + (double)bv[e] * t));
             *reinterpret_cast<float4v *>(F.db + (size_t)j * K + k) = o;
         }
         return;

@@ -102,28 +102,28 @@ def test_small_numbers_are_not_less_exact_than_on_the_32_bit_kernels(I, J, K, sm
         assert s <= limit * p, (s, p)
 
 
-# tall tiles in short pieces, in long ones with totals in the kernel; low tiles
-@pytest.mark.parametrize("I,J,K,side", [(8192, 8192, 160, "a"), (8192, 8192, 160, "b"), (512, 8192, 160, "a"), (8192, 512, 256, "b"), (8192, 8192, 32, "a"), (8192, 8192, 96, "b")])
+# tall tiles in short pieces, in long ones with totals in the kernel; low tiles; the most pieces of a size, on the 32-bit kernels alone
+@pytest.mark.parametrize("I,J,K,side", [(64, 2048, 32, "a"), (1024, 64, 96, "b"), (8192, 8192, 160, "a"), (8192, 8192, 160, "b"), (512, 8192, 160, "a"), (8192, 512, 256, "b"), (8192, 8192, 32, "a"), (8192, 8192, 96, "b")])
 def test_long_sums_of_one_sign(I, J, K, side):
-    """da (P, a small) or db (T, b small) of 8192 terms of one sign, the longest sums and the fewest pieces of a size.  Eight chains of additions of two terms
-    round their sums, of up to an eighth, C / 16 times each, and seven more times: independent roundings of at most 2^-24, 2^-24 / sqrt(3) on average, of partial
-    sums that grow evenly, are 2^-24 / sqrt(3) sqrt(C / 384 + 8 / 3) of the result together."""
+    """da (P, a small) or db (T, b small) of terms of one sign, with the longest sums and the fewest pieces of a size, or with up to 64.  Eight chains of additions of
+    two terms round their sums, of up to an eighth of the C terms, C / 16 times each, and seven more times: independent roundings of at most 2^-24,
+    2^-24 / sqrt(3) on average, of partial sums that grow evenly, are 2^-24 / sqrt(3) sqrt(C / 384 + 8 / 3) of the result together."""
     import math
     import torch
     from paper_1711_01348_amd import binding as B
     expr, args, df = tensors(I, J, K)
     args, df = [t.abs() for t in args], df.abs()
     args[0 if side == "a" else 1] *= 1e-3
-    plan, q = B.Plan(expr), 1 if side == "a" else 2
+    plan, q, C = B.Plan(expr), 1 if side == "a" else 2, J if side == "a" else I
     g = torch.Generator(device="cuda")
     g.manual_seed(4)
     f = torch.rand((I, J), generator=g, device="cuda")
     want = exact(args, df, K, f)
     # what the other sums beside the products decide: db and dc, or da; the sum of every piece and the result are rounded once, the sums themselves are exact
     beside = (2, 3) if side == "a" else (1,)
-    for ws_bytes in (plan.workspace_bytes, plan.workspace_bytes - 16):
+    for ws_bytes in {plan.workspace_bytes, plan.workspace_bytes - 16 * (I * J >= 1 << 20)}:   # (small: the family's alone)
         e = errors(evaluate(plan, args, df, ws_bytes, f=f), want)
-        assert e[q] <= 2.0 ** -24 / math.sqrt(3) * math.sqrt(8192 / 384 + 8 / 3)
+        assert e[q] <= 2.0 ** -24 / math.sqrt(3) * math.sqrt(C / 384 + 8 / 3)
         assert all(e[n] <= 2.0 ** -24 / math.sqrt(3) * math.sqrt(2) for n in beside), e
 
 
