@@ -38,9 +38,9 @@ MIN_WINDOW_MS = 20.0            # the workloads beside the headline are timed fo
 MEASURED_TRAFFIC = {
     "cfg3": dict(source="kernels_worked.hip", sha256="1f4c63bc74be30ff", fetch_bytes=521.5 * 2**20, write_bytes=9.5 * 2**20,
             summary="profiles/worked_8192x8192x5_f32.md"),
-    "cfg4": dict(source="kernels_mfma_split.hip", sha256="d93c03593d6d399d", fetch_bytes=276.3 * 2**20, write_bytes=32.2 * 2**20,
+    "cfg4": dict(source="kernels_mfma_split.hip", sha256="111eb2a4d62cba1a", fetch_bytes=276.3 * 2**20, write_bytes=32.2 * 2**20,
             summary="profiles/worked_mfma_4096x4096x256_f32.md"),
-    "matmul": dict(source="kernels_split.hip", sha256="331eaf58e0ce9f00", fetch_bytes=1167.7 * 2**20, write_bytes=64.0 * 2**20,
+    "matmul": dict(source="kernels_split.hip", sha256="331eaf58e0ce9f00", fetch_bytes=1165.0 * 2**20, write_bytes=64.0 * 2**20,
             summary="profiles/contraction_4096x4096x4096_f32.md"),
     "cfg2_1": dict(source="kernels_patterns.hip", sha256="82a47a45178e317d", fetch_bytes=64.3 * 2**20, write_bytes=0.1 * 2**20,
             summary="profiles/row_reduce_4096x4096_f32.md"),

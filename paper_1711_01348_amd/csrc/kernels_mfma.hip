@@ -234,7 +234,7 @@ struct MfmaTiles {
 };
 // The matrix instructions add two terms at a time, and every addition rounds the chain's sum: an eighth of the sum, at most 256 terms, is added up by itself
 // and then to the total (TOTALS; not needed where the pieces are no longer than that).  Error of da against 64 bits with one chain to a piece of up to the
-// whole sum / with totals / with eight pieces of one chain, 4096 x 4096 x 640: 4.2e-7 / 2.3e-7 / 3.0e-7; a sum of 8192 terms of one sign 6.0e-7 / 7.0e-8 / 1.6e-7.
+// whole sum / with totals / with eight pieces of one chain, 4096 x 4096 x 640: 4.2e-7 / 2.2e-7 / 3.0e-7; a sum of 8192 terms of one sign 6.0e-7 / 6.4e-8 / 1.6e-7.
 // All four gradients 471 / 479 / 536 us (4096 x 4096 x 640), 256 x 1024 x 64 16.7 / 17.5 / 33.5.
 template <bool TRANS_A, bool TOTALS>
 __device__ __forceinline__ void mfma_contraction(MfmaTiles &S, int tile, int split, const float *__restrict__ f, const float *__restrict__ df,

@@ -13,7 +13,7 @@
 // threads that load df and f, one stage ahead.
 //
 // 4096 x 4096 x 256: forward pass 82 us on the 32-bit matrix instructions, 64 here; all four gradients 192 (six launches), 176 (the 32-bit kernels in three),
-// 120 here; errors against 64 bits, 32-bit instructions in eight pieces and here, f 3.2e-8, 3.1e-8, da 3.0e-7, 1.5e-7, dc 9.3e-8, 7.6e-8, dd 1.5e-7, 1.4e-7.  What bounds them: the clock under load (1.8 GHz, as in
+// 120 here; errors against 64 bits, 32-bit instructions in eight pieces and here, f 3.2e-8, 3.1e-8, da 3.0e-7, 1.4e-7, dc 9.3e-8, 7.6e-8, dd 1.5e-7, 1.4e-7.  What bounds them: the clock under load (1.8 GHz, as in
 // kernels_split.hip) and, in the gradients, G, whose 134 MB are read twice and whose parts are formed on the vector ALU while both wavefronts of a
 // SIMD wait for them.  Tried: fragments read from LDS half a stage ahead (132 -> 146 us), wavefronts of a SIMD that form G in turn (125 -> 137).
 //

@@ -15,7 +15,7 @@ inline size_t long_workspace_bytes(int64_t I, int64_t J, int64_t K) {
 // Longer sums of products would want their total apart from the sum that is being added up.
 constexpr int kLongMaxK = 512;
 // A chain of matrix instructions rounds its sum at every sixteen terms: the sum of 8192 terms of one sign was off by 2.2e-7 in two pieces of one chain each (the
-// 32-bit instructions in eight pieces: 1.6e-7).  Totals in the kernel end the chains after 256 terms: 6e-8, and they cost 0.5 % for K <= 128, but 6 % above,
+// 32-bit instructions in eight pieces: 1.6e-7).  Totals in the kernel end the chains after 256 terms: 4e-8 to 6e-8, and they cost 0.5 % for K <= 128, but 6 % above,
 // where the tile takes the registers (4096 x 4096 x 256 128.6 us instead of 120).  There they are left out where the sums are cut short anyway: 1.2e-7 in four
 // pieces; fewer are enough for short sums.
 inline int64_t long_least_pieces(int64_t C) { return C <= 64 ? 1 : C <= 256 ? 2 : C <= 768 ? 3 : 4; }
