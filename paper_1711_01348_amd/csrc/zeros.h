@@ -20,9 +20,23 @@ __device__ __forceinline__ void zeros_off_diagonal(T *dc, unsigned n, unsigned s
     typedef T vec __attribute__((ext_vector_type(V)));
     const unsigned from = piece * PIECE, row = __builtin_amdgcn_readfirstlane((from + step - 1) / step);
     const unsigned first = row < I ? row * step : NONE;   // the first diagonal element from here on
-    const bool several = step < PIECE && first != NONE;   // the same for the workgroup
+    const bool several = step < PIECE && first != NONE, aligned = (reinterpret_cast<uintptr_t>(dc) & 15) == 0;   // the same for the workgroup
+    const unsigned at = from + threadIdx.x * V;
+    vec zero;
+#pragma unroll
+    for (unsigned v = 0; v < V; ++v) zero[v] = T(0);
+    if (aligned && !several && from + PIECE <= n) {       // nearly all pieces: a short way through
+        if (first < at || first >= at + V) {
+            __builtin_nontemporal_store(zero, reinterpret_cast<vec *>(dc + at));
+        } else {
+#pragma unroll
+            for (unsigned v = 0; v < V; ++v)
+                if (at + v != first) dc[at + v] = T(0);
+        }
+        return;
+    }
     auto on_diagonal = [&](unsigned e) { return several ? e % step == 0 && e / step < I : e == first; };
-    if ((reinterpret_cast<uintptr_t>(dc) & 15) != 0) {    // the same for the workgroup
+    if (!aligned) {
 #pragma unroll
         for (unsigned v = 0; v < V; ++v) {
             const unsigned e = from + 256 * v + threadIdx.x;
@@ -30,7 +44,6 @@ __device__ __forceinline__ void zeros_off_diagonal(T *dc, unsigned n, unsigned s
         }
         return;
     }
-    const unsigned at = from + threadIdx.x * V;
     if (at >= n) return;
     unsigned own = first;
     if (several) {
@@ -38,9 +51,6 @@ __device__ __forceinline__ void zeros_off_diagonal(T *dc, unsigned n, unsigned s
         own = r < I ? r * step : NONE;
     }
     if (at + V <= n && (own < at || own >= at + V)) {
-        vec zero;
-#pragma unroll
-        for (unsigned v = 0; v < V; ++v) zero[v] = T(0);
         __builtin_nontemporal_store(zero, reinterpret_cast<vec *>(dc + at));
         return;
     }
